@@ -8,9 +8,10 @@
 // A matrix of padded order L is cut into nb = L / BS blocks of BS indices.  One
 // sweep has nb - 1 rounds; in a round the blocks are paired by the circle
 // method and every pair (p, q) is handled in two launches:
-//   phase A  one workgroup per pair applies one cyclic parallel-Jacobi sweep
-//            to the 2BS x 2BS sub-matrix B[p u q, p u q] in LDS and writes the
-//            accumulated rotation R_pq (2BS x 2BS);
+//   phase A  one workgroup per pair applies parallel-Jacobi rotations to the
+//            2BS x 2BS sub-matrix B[p u q, p u q] in LDS (every coupling between
+//            the two blocks once, those inside them in some of the rounds) and
+//            writes the accumulated rotation R_pq (2BS x 2BS);
 //   phase B  every tile pair (P, Q), P <= Q, of the round is replaced by
 //            R_P^T B[P, Q] R_Q (and its transpose), and the eigenvector
 //            accumulator gets W[:, P] <- W[:, P] R_P; the 2BS-square products
@@ -37,17 +38,28 @@ namespace {
 
 constexpr double kRelTol = 1e-15;
 constexpr double kAbsFloor = 1e-14;
-constexpr int kPairThreads = 512;  // the pair kernel's rounds are bound by the 2x2 and R updates:
-                                   // 512 threads measured 6% faster than 256, 1024 no faster
-constexpr int kInnerSweeps = 1;   // one cyclic sweep per pair and round (block-Jacobi
-                                  // converges with 1-2 more outer sweeps, each far cheaper)
+constexpr int kPairThreads = 512;  // half of them update S, half rotate R
 
-// symmetric 2x2 Schur rotation: [c s; -s c]^T [app apq; apq aqq] [c s; -s c] is diagonal
-// (t = s / c is returned too; c comes from one reciprocal square root)
-__device__ __forceinline__ void sym_schur2(double app, double aqq, double apq, double& c, double& s, double& t) {
-    const double theta = (aqq - app) / (2.0 * apq);
-    t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(1.0 + theta * theta));
-    c = rsqrt(1.0 + t * t);
+// Rotation [c s; -s c] with [c s; -s c]^T [app apq; apq aqq] [c s; -s c] nearly
+// diagonal.  t = tan of the angle comes from the hardware's approximate square
+// root and reciprocal (about 2^-23): an inexact angle only leaves about 1e-7 of
+// the rotated coupling behind, which the following sweep removes.  What has to
+// hold to full precision is c^2 + s^2 = 1: c = 1 / sqrt(1 + t^2) takes one
+// third-order step from the approximate value.  d and f are scaled by a power of
+// two first, so that their squares neither overflow nor vanish.  The chain of a
+// division, two square roots and another division it replaces took about 600 of
+// the 2000 cycles of an inner step.
+__device__ __forceinline__ void jacobi_rotation(double app, double aqq, double apq, double& c, double& s) {
+    double d = aqq - app, f = 2.0 * apq;
+    const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(d), fabs(f)));
+    d = __builtin_amdgcn_ldexp(d, e);
+    f = __builtin_amdgcn_ldexp(f, e);
+    const double h = __builtin_amdgcn_sqrt(fma(d, d, f * f));
+    const double t = (d < 0.0 ? -f : f) * __builtin_amdgcn_rcp(fabs(d) + h);
+    const double x = fma(t, t, 1.0);
+    const double y = __builtin_amdgcn_rsq(x);
+    const double r = fma(-(x * y), y, 1.0);
+    c = fma(y * r, fma(r, 0.375, 0.5), y);
     s = t * c;
 }
 
@@ -62,149 +74,196 @@ __device__ __forceinline__ void round_pair(const EigDesc& d, int nb, int round, 
     }
 }
 
-// LDS of one pair solve
+// LDS of one pair solve.  Row stride PB + 8: the four rows that a wave's 2 x 2
+// blocks touch start 8 bank pairs apart, and the diagonal entries fall into
+// different ones.
 template <int BS>
 struct PairLds {
-    static constexpr int PB = 2 * BS, NP = BS;
-    double S[PB][PB + 1];
+    static constexpr int PB = 2 * BS;
+    static constexpr int NBUF = BS == 16 ? 2 : 1;   // 32-wide blocks would not fit twice
+    double S[NBUF][PB][PB + 8];
     double R[PB][PB + 1];
-    double csc[NP], css[NP], cst[NP], csd[NP], cse[NP];
-    int any;
-    int LO[PB];
+    unsigned long long lo;   // bit i: index i lies below the cut
+    int any;                 // 1: a coupling between the two index blocks, 2: inside one
 };
 
+// Indices (a < b) of rotation k in step st of a pair solve: steps 0..BS-2 pair the
+// indices inside each of the two blocks (circle method, k < BS/2 in the first),
+// steps BS-1..2BS-2 pair index k of the first with one of the second.
+template <int BS>
+__device__ __forceinline__ void step_pair(int st, int k, int& a, int& b) {
+    if (st >= BS - 1) {
+        a = k;
+        b = BS + ((k + st - (BS - 1)) & (BS - 1));
+    } else {
+        const int o = k < BS / 2 ? 0 : BS;
+        rr_pair(BS, st, k & (BS / 2 - 1), a, b);
+        a += o;
+        b += o;
+    }
+}
+
 // Phase A for slot P of a round, by the NT threads of a workgroup: one cyclic
-// sweep of the 2BS x 2BS sub-matrix in LDS, the rotation written to R_P.
+// sweep over the couplings between the two index blocks (BS steps) and, in every
+// eighth round and in targeted rounds, first over those inside each block (BS - 1
+// steps), on the 2BS x 2BS sub-matrix in LDS; the rotation goes to R_P.  Rotating
+// inside the blocks in every round, as a full cyclic sweep of the sub-matrix
+// does, costs 31 steps instead of 16 and saves no outer sweep (12 from the
+// identity at order 512 either way; with it only once per sweep, up to 12 instead
+// of 10 at order 208).
+// A step is bound by its chain of dependent instructions, not by throughput:
+// every lane computes the rotation of pair lane % BS itself (no hand-over through
+// LDS), the 2 x 2 block's row rotation comes from another lane, and S alternates
+// between two buffers, so that a step has one barrier.  Together with the cheaper
+// rotation: 32.7 -> about 15 us a launch (64 pair solves, 4 matrices of order
+// 512); a solve with m = 500, n = 2000, t = 4 465 -> 354 ms, plain LRR of 200
+// points 352 -> 252 ms.
 // wslot spreads the operation counter over its slots.  Every thread returns
 // through the same path (the branches depend on LDS values only).
 template <int BS, int NT>
 __device__ void pair_solve(const EigDesc& d, int round, int P, int sched, int wslot, PairLds<BS>& sm) {
     constexpr int PB = 2 * BS;
-    constexpr int NP = PB / 2;   // rotations per inner round
+    constexpr int NP = PB / 2;   // rotations per step
+    constexpr int NBUF = PairLds<BS>::NBUF;
+    constexpr bool SPLIT = NT >= 2 * NP * NP;      // separate waves for S and R
+    constexpr int NS = SPLIT ? NP * NP : NT;       // threads on S
+    constexpr int NR = SPLIT ? NT - NS : NT;       // threads on R
+    static_assert(64 % NP == 0 && NS % 64 == 0 && (NP * NP) % NS == 0 && (PB * NP) % NR == 0, "thread layout");
+    constexpr int IS = NP * NP / NS, IR = PB * NP / NR;
     const int nb = d.L / BS;
     int p, q;
     round_pair(d, nb, round, P, sched, p, q);
 
-    auto& S = sm.S;
-    auto& R = sm.R;
-    auto& csc = sm.csc;
-    auto& css = sm.css;
-    auto& cst = sm.cst;
-    auto& csd = sm.csd;
-    auto& cse = sm.cse;
-    auto& any = sm.any;
-    auto& LO = sm.LO;
-
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     const long L = d.L;
-    for (int idx = tid; idx < PB * PB; idx += NT) {
+    // every global load is issued before the first use
+    constexpr int NV = PB * PB / NT;
+    double v[NV];
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        const int idx = tid + u * NT;
         const int i = idx % PB, j = idx / PB;
         const long gi = (i < BS) ? (long)p * BS + i : (long)q * BS + (i - BS);
         const long gj = (j < BS) ? (long)p * BS + j : (long)q * BS + (j - BS);
-        S[i][j] = d.B[gi + gj * L];
-        R[i][j] = (i == j) ? 1.0 : 0.0;
-        if (j == 0) LO[i] = d.lo[gi];
+        v[u] = d.B[gi + gj * L];
     }
+    const int lo_i = tid < PB ? d.lo[(tid < BS) ? p * BS + tid : q * BS + (tid - BS)] : 0;
     const double floor_abs = kAbsFloor * d.scale[0];
-    int rotated = 0;
-    __syncthreads();
-
-    for (int sweep = 0; sweep < kInnerSweeps; ++sweep) {
-        // parallel convergence test of the whole sub-matrix
-        if (tid == 0) any = 0;
-        __syncthreads();
-        for (int idx = tid; idx < PB * PB; idx += NT) {
-            const int i = idx % PB, j = idx / PB;
-            if (i < j && !(LO[i] && LO[j]) &&
-                fabs(S[i][j]) > fmax(kRelTol * sqrt(fabs(S[i][i] * S[j][j])), floor_abs))
-                any = 1;
-        }
-        __syncthreads();
-        if (!any) break;
-        rotated = 1;
-        for (int r = 0; r < PB - 1; ++r) {
-            if (tid < NP) {
-                int a, b;
-                rr_pair(PB, r, tid, a, b);
-                const double app = S[a][a], aqq = S[b][b], apq = S[a][b];
-                double c = 1.0, s = 0.0, t = 0.0;
-                if (!(LO[a] && LO[b]) && fabs(apq) > fmax(kRelTol * sqrt(fabs(app * aqq)), floor_abs)) {
-                    sym_schur2(app, aqq, apq, c, s, t);
-                }
-                csc[tid] = c;
-                css[tid] = s;
-                cst[tid] = t;
-                csd[tid] = app - t * apq;   // rotated diagonal, closed form
-                cse[tid] = aqq + t * apq;
-            }
-            __syncthreads();
-            // the sub-matrix: (P2, Q2) blocks of the round's 2 x 2 index pairs
-            auto s_item = [&](int idx) {
-                const int P2 = idx / NP, Q2 = idx % NP;
-                int aP, bP, aQ, bQ;
-                rr_pair(PB, r, P2, aP, bP);
-                if (P2 == Q2) {
-                    // the rotated pair itself: exact zero off the diagonal
-                    if (cst[P2] != 0.0) {
-                        S[aP][aP] = csd[P2];
-                        S[bP][bP] = cse[P2];
-                        S[aP][bP] = 0.0;
-                        S[bP][aP] = 0.0;
-                    }
-                    return;
-                }
-                rr_pair(PB, r, Q2, aQ, bQ);
-                const double cP = csc[P2], sP = css[P2], cQ = csc[Q2], sQ = css[Q2];
-                const double s_aa = S[aP][aQ], s_ab = S[aP][bQ];
-                const double s_ba = S[bP][aQ], s_bb = S[bP][bQ];
-                // columns: T = S G_Q
-                const double t_aa = cQ * s_aa - sQ * s_ab, t_ab = sQ * s_aa + cQ * s_ab;
-                const double t_ba = cQ * s_ba - sQ * s_bb, t_bb = sQ * s_ba + cQ * s_bb;
-                // rows: S' = G_P^T T
-                S[aP][aQ] = cP * t_aa - sP * t_ba;
-                S[aP][bQ] = cP * t_ab - sP * t_bb;
-                S[bP][aQ] = sP * t_aa + cP * t_ba;
-                S[bP][bQ] = sP * t_ab + cP * t_bb;
-            };
-            // the accumulated rotation: row i, columns of pair Q2
-            auto r_item = [&](int idx) {
-                const int i = idx / NP, Q2 = idx % NP;
-                int aQ, bQ;
-                rr_pair(PB, r, Q2, aQ, bQ);
-                const double cQ = csc[Q2], sQ = css[Q2];
-                const double ra = R[i][aQ], rb = R[i][bQ];
-                R[i][aQ] = cQ * ra - sQ * rb;
-                R[i][bQ] = sQ * ra + cQ * rb;
-            };
-            if constexpr (NT >= 2 * NP * NP) {
-                // the two updates touch disjoint arrays: the first NP^2 threads (whole
-                // waves) update S while the others rotate R, instead of every wave
-                // doing both in turn
-                if (tid < NP * NP) s_item(tid);
-                else
-                    for (int idx = tid - NP * NP; idx < PB * NP; idx += NT - NP * NP) r_item(idx);
-            } else {
-                for (int idx = tid; idx < NP * NP; idx += NT) s_item(idx);
-                for (int idx = tid; idx < PB * NP; idx += NT) r_item(idx);
-            }
-            __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        const int idx = tid + u * NT;
+        const int i = idx % PB, j = idx / PB;
+        sm.S[0][i][j] = v[u];
+        sm.R[i][j] = (i == j) ? 1.0 : 0.0;
+    }
+    if (tid < 64) {
+        const unsigned long long m = __ballot(lo_i != 0);
+        if (tid == 0) {
+            sm.lo = m;
+            sm.any = 0;
         }
     }
-    if (!rotated) {
+    __syncthreads();
+    const unsigned long long lo = sm.lo;
+    // parallel convergence test of the whole sub-matrix
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        const int idx = tid + u * NT;
+        const int i = idx % PB, j = idx / PB;
+        if (i < j && !((lo >> i) & (lo >> j) & 1ull) &&
+            fabs(v[u]) > fmax(kRelTol * sqrt(fabs(sm.S[0][i][i] * sm.S[0][j][j])), floor_abs))
+            atomicOr(&sm.any, (i < BS) == (j < BS) ? 2 : 1);
+    }
+    __syncthreads();
+    const int any = sm.any;
+    const bool inside = (any & 2) && (sched || (round & 7) == 0), cross = (any & 1) != 0;
+    if (!inside && !cross) {
         if (tid == 0) d.prot[P] = 0;
         return;
     }
+    const int st0 = inside ? 0 : BS - 1, st1 = cross ? 2 * BS - 1 : BS - 1;
+    const int k = lane % NP;
+    int cur = 0;
+    for (int st = st0; st < st1; ++st) {
+        auto& S = sm.S[cur];
+        auto& Sn = sm.S[NBUF == 2 ? cur ^ 1 : 0];
+        int aQ, bQ;
+        step_pair<BS>(st, k, aQ, bQ);
+        double c = 1.0, s = 0.0;
+        {
+            const double app = S[aQ][aQ], aqq = S[bQ][bQ], apq = S[aQ][bQ];
+            // a little below the check's threshold, so that what it marks is rotated
+            // in spite of the approximate square root
+            const double thr =
+                fmax(0.999 * kRelTol * __builtin_amdgcn_sqrt(fabs(app * aqq)), floor_abs);
+            double cr, sr;
+            jacobi_rotation(app, aqq, apq, cr, sr);
+            if (!((lo >> aQ) & (lo >> bQ) & 1ull) && fabs(apq) > thr) {
+                c = cr;
+                s = sr;
+            }
+        }
+        double w[IS][4];
+        // the sub-matrix: (P2, Q2) blocks of the step's 2 x 2 index pairs
+        if (!SPLIT || tid < NS) {
+#pragma unroll
+            for (int u = 0; u < IS; ++u) {
+                const int P2 = (tid + u * NS) / NP;
+                int aP, bP;
+                step_pair<BS>(st, P2, aP, bP);
+                const double cP = __shfl(c, P2, 64), sP = __shfl(s, P2, 64);
+                const double s_aa = S[aP][aQ], s_ab = S[aP][bQ];
+                const double s_ba = S[bP][aQ], s_bb = S[bP][bQ];
+                // columns: T = S G_Q
+                const double t_aa = c * s_aa - s * s_ab, t_ab = s * s_aa + c * s_ab;
+                const double t_ba = c * s_ba - s * s_bb, t_bb = s * s_ba + c * s_bb;
+                // rows: S' = G_P^T T
+                w[u][0] = cP * t_aa - sP * t_ba;
+                w[u][1] = cP * t_ab - sP * t_bb;
+                w[u][2] = sP * t_aa + cP * t_ba;
+                w[u][3] = sP * t_ab + cP * t_bb;
+            }
+        }
+        if (NBUF == 1) __syncthreads();   // one buffer: every read before the first write
+        if (!SPLIT || tid < NS) {
+#pragma unroll
+            for (int u = 0; u < IS; ++u) {
+                const int P2 = (tid + u * NS) / NP;
+                int aP, bP;
+                step_pair<BS>(st, P2, aP, bP);
+                Sn[aP][aQ] = w[u][0];
+                Sn[aP][bQ] = w[u][1];
+                Sn[bP][aQ] = w[u][2];
+                Sn[bP][bQ] = w[u][3];
+            }
+        }
+        // the accumulated rotation: row i, columns of pair Q2
+        if (!SPLIT || tid >= NS) {
+            const int t0 = SPLIT ? tid - NS : tid;
+#pragma unroll
+            for (int u = 0; u < IR; ++u) {
+                const int i = (t0 + u * NR) / NP;
+                const double ra = sm.R[i][aQ], rb = sm.R[i][bQ];
+                sm.R[i][aQ] = c * ra - s * rb;
+                sm.R[i][bQ] = s * ra + c * rb;
+            }
+        }
+        __syncthreads();
+        if (NBUF == 2) cur ^= 1;
+    }
     if (tid == 0 && d.work) {
-        // per round: NP angles (~30 operations), (NP^2 - NP) 2x2 updates (24), PB*NP rotations of R (6)
-        const unsigned long long per_round = 30ull * NP + 24ull * (NP * NP - NP) + 6ull * PB * NP;
-        atomicAdd(&d.work[work_slot(0, wslot)], per_round * (PB - 1));
+        // per step: NP angles (~30 operations), NP^2 2x2 updates (24), PB*NP rotations of R (6)
+        const unsigned long long per_step = 30ull * NP + 24ull * NP * NP + 6ull * PB * NP;
+        atomicAdd(&d.work[work_slot(0, wslot)], per_step * (st1 - st0));
     }
     double* Rg = d.R + (long)P * PB * PB;
-    for (int idx = tid; idx < PB * PB; idx += NT) {
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        const int idx = tid + u * NT;
         const int i = idx % PB, j = idx / PB;
-        Rg[i + (long)j * PB] = R[i][j];
+        Rg[i + (long)j * PB] = sm.R[i][j];
     }
-    if (tid == 0) d.prot[P] = rotated;
+    if (tid == 0) d.prot[P] = 1;
 }
 
 template <int BS, int NT>
