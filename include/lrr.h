@@ -67,7 +67,9 @@ typedef enum {
  * application, the eigen-decomposition and every residual norm stay FP64.  M Q
  * is carried as a running sum of products of the changes of Q, re-formed in
  * FP64 every 16 iterations, so that its rounding error shrinks as the
- * iteration converges and the FP64 stopping tolerance stays reachable. */
+ * iteration converges and the FP64 stopping tolerance stays reachable.  In
+ * reduced coordinates the dictionary is diagonal and the Z-step holds no such
+ * product: only the combine then differs between the forms. */
 typedef enum {
     LRR_FP64 = 0,            /* every product in FP64                              */
     LRR_FP32 = 1,            /* operands rounded to FP32, FP32 MFMA                */
@@ -100,11 +102,14 @@ typedef enum {
  * range(A^T) (every update is a product with A^T or a column operation), so with
  * an orthonormal basis Qm of that range (n x r, r = numerical rank of A <= m)
  * Z = Qm Zr exactly and the iteration can run on r-row coefficients: the Gram
- * matrix of the thresholding step and the dictionary products shrink from n to
- * r rows, and the n x n states are never formed.  The results agree with the
- * full coordinates to rounding; the coupling residual max|Z - J| is bounded by
- * the coefficient columns' 2-norms (times 1 and 1/sqrt(n)) and formed in full
- * only when the bounds do not decide the stop test.  Basis directions with
+ * matrix of the thresholding step shrinks from n to r rows, the n x n states are
+ * never formed, and with the matching orthonormal basis of range(A) on the
+ * observations' side A is diagonal, so that the dictionary products become row
+ * scalings.  The results agree with the full coordinates to rounding; both
+ * residuals are bounded by the coefficient columns' 2-norms (times 1 and
+ * 1/sqrt(rows)) and formed in full only when the bounds do not decide the stop
+ * test (the reported primal residual is always the exact one of the last
+ * iteration).  Basis directions with
  * sigma^2 <= 1e-14 sigma_max^2 are dropped. */
 typedef enum {
     LRR_COORDS_AUTO = 0,     /* reduced when n >= 2m (the basis costs an m x m      */

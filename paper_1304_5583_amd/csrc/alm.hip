@@ -292,17 +292,6 @@ __global__ __launch_bounds__(256) void k_colmax(const double* __restrict__ A, in
     if (threadIdx.x == 0) atomic_max_nonneg(&out[b], mx);
 }
 
-// Wk[:, j] = W[:, idx[j]] / sqrt(lam[idx[j]]) (m rows)
-__global__ __launch_bounds__(256) void k_gather_scaled(const double* __restrict__ W, long ldw,
-                                                        const double* __restrict__ lam,
-                                                        const int* __restrict__ idx, double* __restrict__ Wk,
-                                                        long ldk, int m) {
-    const int j = blockIdx.x;
-    const int src = idx[j];
-    const double sc = lam[src] > 0.0 ? 1.0 / sqrt(lam[src]) : 0.0;
-    for (int i = threadIdx.x; i < m; i += 256) Wk[i + j * ldk] = W[i + (long)src * ldw] * sc;
-}
-
 // T = (3 I - G) / 2 (r x r), the Newton-Schulz orthogonalisation factor
 __global__ __launch_bounds__(256) void k_ns_factor(const double* __restrict__ G, double* __restrict__ T, int r) {
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
@@ -620,10 +609,6 @@ void launch_r2_decide(BlockState bs, unsigned long long* r2nrm, int* expand, int
 void launch_colmax(const double* A, int n, long ld, int ncols, const int* colblk, const int* expand,
                    unsigned long long* out, hipStream_t s) {
     hipLaunchKernelGGL(k_colmax, dim3(ncols), dim3(256), 0, s, A, n, ld, colblk, expand, out);
-}
-void launch_gather_scaled(const double* W, long ldw, const double* lam, const int* idx, double* Wk, long ldk,
-                          int m, int r, hipStream_t s) {
-    hipLaunchKernelGGL(k_gather_scaled, dim3(r), dim3(256), 0, s, W, ldw, lam, idx, Wk, ldk, m);
 }
 void launch_ns_factor(const double* G, double* T, int r, hipStream_t s) {
     const long nn = (long)r * r;

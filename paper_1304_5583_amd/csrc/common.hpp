@@ -149,6 +149,21 @@ struct BwDesc {
     const int* run;     // thresholding step taken by this block in the recorded iteration
 };
 
+// Arrays of one column pass of the ALM in singular coordinates (svdstep.hip): r
+// rows per column; buffer 0 holds the state before the pass, buffer 1 takes the
+// state after it.
+struct SvdStep {
+    const double *X, *J;            // observations U^T X, thresholded J
+    const double *d, *dinv;         // singular values of the dictionary, 1 / (1 + d^2)
+    const double *q0, *Y20, *f0;    // q (E = f q, Y1 = mu (1 - f) q), Y2, per column (f, 1 - f)
+    double *q1, *Y21, *f1;
+    double *Y0, *Y1;                // thresholding input: of this iteration, and of the next (written)
+    double *colsq;                  // per column |Y'|^2
+    const int* colblk;
+    int r, ncols;
+    double lam;
+};
+
 // Thresholding weights of one block after its Gram eigensolve.
 struct SvtDesc {
     const double* B;    // L x L, diagonal = eigenvalues of the Gram matrix

@@ -116,8 +116,6 @@ void launch_r2_decide(BlockState bs, unsigned long long* r2nrm, int* expand, int
                       hipStream_t s);
 void launch_colmax(const double* A, int n, long ld, int ncols, const int* colblk, const int* expand,
                    unsigned long long* out, hipStream_t s);
-void launch_gather_scaled(const double* W, long ldw, const double* lam, const int* idx, double* Wk, long ldk,
-                          int m, int r, hipStream_t s);
 void launch_ns_factor(const double* G, double* T, int r, hipStream_t s);
 void launch_estep(double* E, const double* V, double* Y1, int m, long ld, int ncols, double lam,
                   const int* colblk, BlockState bs, const DevIter* it, hipStream_t s);
@@ -128,6 +126,30 @@ void launch_scale_cols(double* U, long ld, int rows, int ncols, const double* h,
 void launch_set_identity(double* W, int L, hipStream_t s);
 void launch_scatter_block_diag(const double* J, long ldj, int ncols, const int* colblk, const int* boff,
                                const int* perm, double* out, long ldo, hipStream_t s);
+
+// svdstep.hip: the iteration in singular coordinates
+void launch_rows_factor(const double* G, double* T, int r, hipStream_t s);
+// d = diag(A), dinv = 1 / (1 + d^2); stat[0], stat[1] = largest off-diagonal and diagonal magnitude
+void launch_take_diag(const double* A, int r, long ld, double* d, double* dinv, unsigned long long* stat, hipStream_t s);
+void launch_colnorm_max(const double* A, int m, long ld, int ncols, unsigned long long* out, hipStream_t s);
+void launch_zstep_fused(const SvdStep& a, const BlockState& bs, const DevIter* it, const double* sched,
+                        hipStream_t s);
+void launch_svd_decide(const int* boff, int t, const BlockState& bs, unsigned long long* x2max, int* expand1,
+                       int* expand2, double tol, double sqrt_m, double sqrt_n, int n_iter, const DevIter* it,
+                       hipStream_t s);
+void launch_svd_decide2(const BlockState& bs, const unsigned long long* x2max, const int* expand1, int* expand2, int t,
+                        double tol, double sqrt_n, int n_iter, const DevIter* it, hipStream_t s);
+void launch_svd_resid(const SvdStep& a, const int* boff, int t, int maxl, const int* expand, double* R, int which,
+                      const DevIter* it, const double* sched, hipStream_t s);
+void launch_svd_colmax(const double* A, int rows, long ld, const int* boff, int t, int maxl, const int* expand,
+                       unsigned long long* out, const double* D, const double* R, int r, hipStream_t s);
+void launch_svd_outside(const double* T, int m, int c, double* D, double* len, hipStream_t s);
+void launch_svd_set_row(double* X, int row, int ld, int c, const double* v, hipStream_t s);
+void launch_svd_add_outside(double* out, long ldo, int m, int c, const double* D, const double* R, int r,
+                            const int* map, hipStream_t s);
+// what = 0: the outlier coefficients E, 1: the iterate Z
+void launch_svd_result(const SvdStep& a, const int* iters, double* out, int what, const double* sched, hipStream_t s);
+void launch_svd_zero_J(double* J, int r, int ncols, const int* colblk, const int* rank, hipStream_t s);
 
 // adjoint.hip
 void launch_bw_estep(const double* E0, const double* V, double* cE, const double* cY1, double* Vb,

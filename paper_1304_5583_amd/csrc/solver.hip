@@ -138,6 +138,7 @@ using lrr::EigDesc;
 using lrr::GemmDesc;
 using lrr::SvtDesc;
 using lrr::RefDesc;
+using lrr::SvdStep;
 
 thread_local std::string g_last_error;
 
@@ -180,7 +181,11 @@ struct Plan {
     // coordinates of the n-row iterates (Z, J, Y2 and their temporaries): n rows,
     // or nr <= min(m, n) coefficients on an orthonormal basis Qm of range(M^T)
     bool reduced = false;
-    int nrb = 0;                 // rows the layout reserves (n, or min(m, n))
+    // reduced coordinates with the dictionary diagonalised (svdstep.hip); decided
+    // when the basis is built, on the accuracy it reached
+    bool svd = false;
+    bool extra = false;          // the last coordinate holds what lies outside range(U) (finish_basis)
+    int nrb = 0;                 // rows the layout reserves (n, or min(m, n) + 1)
     int nr = 0;                  // rows in use (n, or the numerical rank of M)
     int Lm = 0, bq = 16;         // padded order / Jacobi block of the M M^T eigensolve
     // every block its own dictionary (the observations C_b, Section 2.2 footnote):
@@ -202,6 +207,12 @@ struct Buffers {
     double *Qm, *Qtmp, *Mr, *R2r, *R2full, *Ur, *Gb, *Wq, *Rq, *lamq, *scaleq, *Gq, *Tq;
     int *protq, *loq, *stq, *runq, *idxq, *expand;
     unsigned long long* r2nrm;
+    // singular coordinates: left basis (m x r), U^T A (r x n), diagonal, per-column factors, and
+    // the two buffers of each alternating array (aliases of the general form's arrays)
+    double *Um, *Ut, *Cr, *dsig, *dinv, *fcol[2], *Yp[2], *Y2p[2], *qp[2], *Rr;
+    unsigned long long* stat;
+    int* expand1;
+    GemmDesc *g_sv, *g_exp1;
     EigDesc* eq;
     GemmDesc *g_red, *g_exp;
     int *colblk, *boff, *perm;
@@ -337,7 +348,7 @@ size_t layout(const Plan& p, char* base, Buffers& b, int with_combine, bool need
     b.ref_eprev = a.take<double>(t);
     b.ref_scale = a.take<double>(t);
     b.ref_emax = a.take<unsigned long long>(t);
-    b.g_gram = a.take<GemmDesc>(t);
+    b.g_gram = a.take<GemmDesc>(2 * t);   // singular coordinates: one set per buffer of Y
     b.g_refT = a.take<GemmDesc>(t);
     b.g_refSG = a.take<GemmDesc>(t);
     b.g_refXE = a.take<GemmDesc>(t);
@@ -345,7 +356,7 @@ size_t layout(const Plan& p, char* base, Buffers& b, int with_combine, bool need
     b.g_Bq = a.take<GemmDesc>(t);
     b.ref = a.take<RefDesc>(t);
     b.g_P = a.take<GemmDesc>(t);
-    b.g_J = a.take<GemmDesc>(t);
+    b.g_J = a.take<GemmDesc>(2 * t);
     b.g_MQ = a.take<GemmDesc>(t);
     b.g_MQa = a.take<GemmDesc>(t);
     b.g_KV = a.take<GemmDesc>(t);
@@ -391,8 +402,22 @@ size_t layout(const Plan& p, char* base, Buffers& b, int with_combine, bool need
         b.expand = a.take<int>(t);
         b.r2nrm = a.take<unsigned long long>(t);
         b.eq = a.take<EigDesc>(1);
-        b.g_red = a.take<GemmDesc>(5);
+        b.g_red = a.take<GemmDesc>(1);
         b.g_exp = a.take<GemmDesc>(t);
+        b.Um = a.take<double>(m * n);
+        b.Ut = a.take<double>(m * n);
+        b.Cr = a.take<double>(n * nfull);
+        b.dsig = a.take<double>(n);
+        b.dinv = a.take<double>(n);
+        for (double*& x : b.fcol) x = a.take<double>(2 * c);
+        b.stat = a.take<unsigned long long>(4);
+        b.expand1 = a.take<int>(t);
+        b.g_sv = a.take<GemmDesc>(10);
+        b.g_exp1 = a.take<GemmDesc>(t);
+        b.Yp[0] = b.Y; b.Yp[1] = b.Z;
+        b.Y2p[0] = b.Y2; b.Y2p[1] = b.Q;
+        b.qp[0] = b.E; b.qp[1] = b.Y1;      // m x c each, r x c used
+        b.Rr = b.MtV;
     } else {
         b.Qm = b.Qtmp = b.Mr = b.R2r = b.R2full = b.Ur = b.Gb = b.Wq = b.Rq = b.lamq = b.scaleq = nullptr;
         b.Gq = b.Tq = nullptr;
@@ -400,6 +425,10 @@ size_t layout(const Plan& p, char* base, Buffers& b, int with_combine, bool need
         b.r2nrm = nullptr;
         b.eq = nullptr;
         b.g_red = b.g_exp = nullptr;
+        b.Um = b.Ut = b.Cr = b.dsig = b.dinv = b.Rr = nullptr;
+        b.stat = nullptr;
+        b.expand1 = nullptr;
+        b.g_sv = b.g_exp1 = nullptr;
     }
     (void)need_X;
     return a.off + 256;
@@ -546,7 +575,7 @@ Plan make_plan(const Problem& pr) {
                 (coords == LRR_COORDS_AUTO && pr.n >= 2 * pr.m && !pr.o.save_for_backward &&
                  pr.o.solve_form != LRR_SOLVE_LITERAL);
     if (pr.o.save_for_backward) p.reduced = false;
-    p.nrb = p.reduced ? std::min(pr.m, pr.n) : pr.n;
+    p.nrb = p.reduced ? std::min(pr.m, pr.n) + 1 : pr.n;   // + 1: Plan::extra
     p.local = pr.local != 0;
     if (p.local) {
         // rows of a block's iterates index its own points: l_b <= maxl rows; rows
@@ -581,10 +610,104 @@ hipStream_t ctx_capture_stream(lrr_ctx* ctx) {
 // of that range (n x r, r = numerical rank of M), Z = Qm Zr exactly and the
 // whole iteration runs on r-row coefficients: the Gram matrix Y^T Y equals
 // Yr^T Yr, and the dictionary products use Mr = M Qm (m x r).
-// Qm = M^T W diag(1/sigma) from the eigen-decomposition M M^T = W diag(sigma^2)
-// W^T (kept: sigma^2 > 1e-14 sigma_max^2), then one Newton-Schulz step
-// Qm <- Qm (3 I - Qm^T Qm) / 2 restores orthonormality to rounding.
+// Qm spans the rows of W^T M for the kept eigenvectors of M M^T = W diag(sigma^2)
+// W^T (sigma^2 > 1e-14 sigma_max^2); with the matching left basis the dictionary
+// becomes diagonal (finish_basis).
 constexpr double kRankCut = 1e-14;
+
+// Accuracy asked of the singular coordinates: the off-diagonal part of U^T A Qm
+// against its largest entry (2e-15 and less in every dictionary measured, up to
+// m = 512 and singular values over three decades); a basis that misses it is used
+// in the dense form (Mr = A Qm).  kSvdOut: what U U^T may leave of the
+// observations against their largest column before it gets its own coordinate
+// (3e-15 and less where nothing of them lies outside).
+constexpr double kSvdOff = 1e-13, kSvdOut = 1e-13;
+
+// Bases of range(A^T) and range(A) from the eigen-decomposition A A^T = W
+// diag(lam) W^T (kept indices, by decreasing eigenvalue, in b.idxq):
+//   C = W_k^T A, Qm = its normalised rows after a Newton-Schulz step (they lie in
+//   range(A^T) to rounding whatever the error of W), Mr = A Qm, whose columns are
+//   orthogonal up to the error of W; Jacobi sweeps on Mr^T Mr, every entry of
+//   which is accurate relative to its two columns, to the relative tolerance
+//   (no absolute floor), rotate Qm and Mr; U = the normalised columns of Mr after
+//   a Newton-Schulz step, d = diag(U^T Mr).
+// The observations U^T X go to b.X.  p.svd tells whether the accuracy above was
+// reached; Qm and Mr serve the dense form otherwise.
+void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
+    const int m = p.m, n = p.n, r = p.nr, c = p.ncols;
+    const int Lr = round_up(r, 2 * p.bq);
+    auto gemm = [&](int slot, const GemmDesc& g, bool ta, bool tb) {
+        // pageable host source: staged before the call returns
+        LRR_HIP(hipMemcpyAsync(b.g_sv + slot, &g, sizeof(g), hipMemcpyHostToDevice, s));
+        lrr::launch_dgemm(b.g_sv + slot, 1, g.M, g.N, ta, tb, s);
+    };
+    lrr::launch_gather_cols(b.Wq, p.Lm, b.Um, m, m, r, b.idxq, s);
+    gemm(0, GemmDesc{b.Um, pr.A, b.Cr, r, n, m, m, (int)pr.lda, r, 1.0, 0.0, nullptr, nullptr}, true, false);
+    gemm(1, GemmDesc{b.Cr, b.Cr, b.Gq, r, r, n, r, r, r, 1.0, 0.0, nullptr, nullptr}, false, true);
+    lrr::launch_rows_factor(b.Gq, b.Tq, r, s);
+    gemm(2, GemmDesc{b.Cr, b.Tq, b.Qm, n, r, r, r, r, n, 1.0, 0.0, nullptr, nullptr}, true, false);
+    gemm(3, GemmDesc{pr.A, b.Qm, b.Mr, m, r, n, (int)pr.lda, n, m, 1.0, 0.0, nullptr, nullptr}, false, false);
+    std::vector<int> lo(Lr);
+    for (int i = 0; i < Lr; ++i) lo[i] = i >= r ? 1 : 0;
+    const EigDesc ed{b.Gb, b.Wq, b.Rq, b.lamq, Lr, r, b.runq, b.stq, b.scaleq, b.protq, b.loq, nullptr};
+    LRR_HIP(hipMemcpyAsync(b.loq, lo.data(), sizeof(int) * Lr, hipMemcpyHostToDevice, s));
+    LRR_HIP(hipMemcpyAsync(b.eq, &ed, sizeof(EigDesc), hipMemcpyHostToDevice, s));
+    LRR_HIP(hipMemsetAsync(b.scaleq, 0, sizeof(double), s));
+    LRR_HIP(hipMemsetAsync(b.stq, 0, 2 * sizeof(int), s));
+    double st[4] = {0.0, 0.0, 0.0, 0.0};
+    bool diagonal = false;
+    // two sweeps (close singular values rotate by large angles, which takes two);
+    // once more if the measured off-diagonal part is still too large
+    for (int attempt = 0; attempt < 2 && !diagonal; ++attempt) {
+        LRR_HIP(hipMemsetAsync(b.Gb, 0, sizeof(double) * (size_t)Lr * Lr, s));
+        gemm(4, GemmDesc{b.Mr, b.Mr, b.Gb, r, r, m, m, m, Lr, 1.0, 0.0, nullptr, nullptr}, true, false);
+        lrr::launch_set_identity(b.Wq, Lr, s);
+        for (int sw = 0; sw < 2; ++sw)
+            for (int rd = 0; rd < Lr / p.bq - 1; ++rd) lrr::launch_jacobi_round(b.eq, 1, Lr, p.bq, rd, s);
+        gemm(5, GemmDesc{b.Mr, b.Wq, b.Ut, m, r, r, m, Lr, m, 1.0, 0.0, nullptr, nullptr}, false, false);
+        gemm(6, GemmDesc{b.Qm, b.Wq, b.Qtmp, n, r, r, n, Lr, n, 1.0, 0.0, nullptr, nullptr}, false, false);
+        std::swap(b.Mr, b.Ut);
+        std::swap(b.Qm, b.Qtmp);
+        gemm(7, GemmDesc{b.Mr, b.Mr, b.Gq, r, r, m, m, m, r, 1.0, 0.0, nullptr, nullptr}, true, false);
+        lrr::launch_rows_factor(b.Gq, b.Tq, r, s);
+        gemm(8, GemmDesc{b.Mr, b.Tq, b.Um, m, r, r, m, r, m, 1.0, 0.0, nullptr, nullptr}, false, false);
+        gemm(9, GemmDesc{b.Um, b.Mr, b.Gq, r, r, m, m, m, r, 1.0, 0.0, nullptr, nullptr}, true, false);
+        LRR_HIP(hipMemsetAsync(b.stat, 0, 4 * sizeof(unsigned long long), s));
+        lrr::launch_take_diag(b.Gq, r, r, b.dsig, b.dinv, b.stat, s);
+        LRR_HIP(hipMemcpyAsync(st, b.stat, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+        LRR_HIP(hipStreamSynchronize(s));
+        diagonal = st[1] > 0.0 && st[0] <= kSvdOff * st[1];
+    }
+    if (!diagonal) return;
+    // observations in the left basis, and what lies outside it
+    if (pr.perm) lrr::launch_gather_cols(pr.A, pr.lda, b.T, m, m, c, b.perm, s);
+    else lrr::launch_copy_cols(pr.X, pr.ldx, b.T, m, m, c, s);
+    lrr::launch_colnorm_max(b.T, m, m, c, b.stat + 3, s);
+    gemm(0, GemmDesc{b.Um, b.T, b.X, r, c, m, m, m, r, 1.0, 0.0, nullptr, nullptr}, true, false);    // U^T X
+    gemm(1, GemmDesc{b.Um, b.X, b.T, m, c, r, m, r, m, -1.0, 1.0, nullptr, nullptr}, false, false);  // X - U U^T X
+    lrr::launch_colnorm_max(b.T, m, m, c, b.stat + 2, s);
+    LRR_HIP(hipMemcpyAsync(st, b.stat, sizeof(st), hipMemcpyDeviceToHost, s));
+    LRR_HIP(hipStreamSynchronize(s));
+    p.svd = true;
+    if (st[2] <= kSvdOut * st[3]) return;
+    // Observations partly outside range(U) (lrr_solve with any X, or directions of
+    // the data below the rank cut): only column operations act on that part, so it
+    // keeps its direction and one more coordinate carries its length, as a row with
+    // singular value 0 (and zero columns of the bases, for the products).
+    p.extra = true;
+    p.nr = r + 1;
+    LRR_HIP(hipMemsetAsync(b.Um + (size_t)m * r, 0, sizeof(double) * m, s));
+    LRR_HIP(hipMemsetAsync(b.Qm + (size_t)n * r, 0, sizeof(double) * n, s));
+    LRR_HIP(hipMemsetAsync(b.dsig + r, 0, sizeof(double), s));
+    const double one = 1.0;
+    LRR_HIP(hipMemcpyAsync(b.dinv + r, &one, sizeof(double), hipMemcpyHostToDevice, s));
+    lrr::launch_svd_outside(b.T, m, c, b.V, b.Rr, s);              // b.V = its directions, b.Rr = lengths
+    if (pr.perm) lrr::launch_gather_cols(pr.A, pr.lda, b.T, m, m, c, b.perm, s);
+    else lrr::launch_copy_cols(pr.X, pr.ldx, b.T, m, m, c, s);
+    gemm(0, GemmDesc{b.Um, b.T, b.X, r, c, m, m, m, r + 1, 1.0, 0.0, nullptr, nullptr}, true, false);
+    lrr::launch_svd_set_row(b.X, r, r + 1, c, b.Rr, s);
+    LRR_HIP(hipStreamSynchronize(s));   // host value goes out of scope
+}
 
 void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     const int m = p.m, n = p.n, Lm = p.Lm, bq = p.bq;
@@ -622,26 +745,12 @@ void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     for (int i = 0; i < m; ++i)
         if (lam[i] > kRankCut * lmax) idx.push_back(i);
     std::stable_sort(idx.begin(), idx.end(), [&](int x, int y) { return lam[x] > lam[y]; });
-    if ((int)idx.size() > p.nrb) idx.resize(p.nrb);   // rank(M) <= min(m, n)
+    if ((int)idx.size() > std::min(m, n)) idx.resize(std::min(m, n));   // rank(M) <= min(m, n)
     if (idx.empty()) idx.push_back(0);     // M = 0: a single zero column (scaled by 0 below)
     const int r = (int)idx.size();
     p.nr = r;
     LRR_HIP(hipMemcpyAsync(b.idxq, idx.data(), sizeof(int) * r, hipMemcpyHostToDevice, s));
-    // Wk = W_kept diag(1/sigma) (m x r, in the Gram buffer), Qm = M^T Wk, NS step, Mr = M Qm
-    GemmDesc g[4] = {
-        GemmDesc{pr.A, b.Gb, b.Qm, n, r, m, (int)pr.lda, m, n, 1.0, 0.0, nullptr, nullptr},
-        GemmDesc{b.Qm, b.Qm, b.Gq, r, r, n, n, n, r, 1.0, 0.0, nullptr, nullptr},
-        GemmDesc{b.Qm, b.Tq, b.Qtmp, n, r, r, n, r, n, 1.0, 0.0, nullptr, nullptr},
-        GemmDesc{pr.A, b.Qtmp, b.Mr, m, r, n, (int)pr.lda, n, m, 1.0, 0.0, nullptr, nullptr}};
-    LRR_HIP(hipMemcpyAsync(b.g_red + 1, g, sizeof(g), hipMemcpyHostToDevice, s));
-    lrr::launch_gather_scaled(b.Wq, Lm, b.lamq, b.idxq, b.Gb, m, m, r, s);
-    lrr::launch_dgemm(b.g_red + 1, 1, n, r, true, false, s);
-    lrr::launch_dgemm(b.g_red + 2, 1, r, r, true, false, s);
-    lrr::launch_ns_factor(b.Gq, b.Tq, r, s);
-    lrr::launch_dgemm(b.g_red + 3, 1, n, r, false, false, s);
-    lrr::launch_dgemm(b.g_red + 4, 1, m, r, false, false, s);
-    std::swap(b.Qm, b.Qtmp);       // the orthonormalised basis
-    LRR_HIP(hipStreamSynchronize(s));   // host descriptors go out of scope
+    finish_basis(pr, p, b, s);
 }
 
 // Lay out the workspace, upload the descriptors, gather the observations,
@@ -655,6 +764,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
     LRR_HIP(hipMemsetAsync(ctx->dwork, 0, lrr::kWorkBytes, s));
     layout(p, static_cast<char*>(ctx->ws), b, with_combine, true);
     ensure_pinned(ctx, sizeof(int) * (4 * (size_t)t + 16) + sizeof(double) * 2 * t);
+    if (pr.perm) LRR_HIP(hipMemcpyAsync(b.perm, pr.perm, sizeof(int) * c, hipMemcpyHostToDevice, s));
     if (p.reduced) build_basis(pr, p, b, s);
     else if (!p.local) p.nr = n;
     const int nr = p.nr;
@@ -670,7 +780,8 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
     sched[0] = o.mu0;
     for (int k = 1; k < (int)sched.size(); ++k) sched[k] = std::min(o.rho * sched[k - 1], o.mu_max);
 
-    std::vector<GemmDesc> gram(t), gRT(t), gRSG(t), gRXE(t), gOG(t), gBq(t), gP(t), gJ(t);
+    const int ny = p.svd ? 2 : 1;   // buffers of Y
+    std::vector<GemmDesc> gram(ny * t), gRT(t), gRSG(t), gRXE(t), gOG(t), gBq(t), gP(t), gJ(ny * t), gExp1(t);
     std::vector<GemmDesc> gMQ(t), gMQa(t), gKV(t), gMtV(t), gExp(t), gF1T(t), gF2Q(t), gAZ(t);
     std::vector<EigDesc> eig(t);
     std::vector<size_t> need_off(t + 1, 0), sched_off(t + 1, 0);
@@ -684,14 +795,17 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
     for (int bb = 0; bb < t; ++bb) {
         const int l = p.boff[bb + 1] - p.boff[bb], L = p.L[bb];
         const size_t LL = (size_t)L * L;
-        double* Yb = b.Y + (size_t)p.boff[bb] * nr;
         double* Jb = b.J + (size_t)p.boff[bb] * nr;
         const int* run = b.svt_run + bb;    // thresholds this iteration
         const int* erun = b.eig_run + bb;   // needs an eigen-decomposition this iteration
         const int* rrun = b.ref_run + bb;
         double* X = b.Wm[bb];
         double* T = b.TX[bb];
-        gram[bb] = GemmDesc{Yb, Yb, b.Bm[bb], l, l, nr, nr, nr, L, 1.0, 0.0, erun, nullptr};
+        for (int y = 0; y < ny; ++y) {
+            double* Yb = (p.svd ? b.Yp[y] : b.Y) + (size_t)p.boff[bb] * nr;
+            gram[y * t + bb] = GemmDesc{Yb, Yb, b.Bm[bb], l, l, nr, nr, nr, L, 1.0, 0.0, erun, nullptr};
+            gJ[y * t + bb] = GemmDesc{Yb, b.Pm[bb], Jb, nr, l, l, nr, L, nr, 1.0, 0.0, run, nullptr};
+        }
         // refinement: T = B X, S = X^T T, G = X^T X (symmetric kernel), XE = X E
         gRT[bb] = GemmDesc{b.Bm[bb], X, T, L, L, L, L, L, L, 1.0, 0.0, rrun, nullptr};
         gRSG[bb] = GemmDesc{X, T, b.SG[bb], L, L, L, L, L, L, 1.0, 0.0, rrun, nullptr};
@@ -700,7 +814,6 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         gOG[bb] = GemmDesc{X, X, b.SG[bb] + LL, L, L, L, L, L, L, 1.0, 0.0, rrun, nullptr};
         gBq[bb] = GemmDesc{X, T, b.Bq[bb], L, L, L, L, L, L, 1.0, 0.0, rrun, nullptr};
         gP[bb] = GemmDesc{b.Wg[bb], X, b.Pm[bb], l, l, L, L, L, L, 1.0, 0.0, run, nullptr};
-        gJ[bb] = GemmDesc{Yb, b.Pm[bb], Jb, nr, l, l, nr, L, nr, 1.0, 0.0, run, nullptr};
         const int* act = b.active + bb;
         const size_t o_n = (size_t)p.boff[bb] * nr, o_m = (size_t)p.boff[bb] * m;
         // dictionary of this block: M (or Mr), or in local mode its own columns
@@ -725,8 +838,10 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         }
         gMtV[bb] = GemmDesc{Mb, b.V + o_m, b.MtV + o_n, kin, l, m, ldb_, m, nr, 1.0, 0.0, act, nullptr};
         if (p.reduced)   // expansion of the coupling residual: R2 = Qm R2r
-            gExp[bb] = GemmDesc{b.Qm, b.R2r + o_n, b.R2full + (size_t)p.boff[bb] * n, n, l, nr, n, nr, n, 1.0,
+            gExp[bb] = GemmDesc{b.Qm, (p.svd ? b.Rr : b.R2r) + o_n, b.R2full + (size_t)p.boff[bb] * n, n, l, nr, n, nr, n, 1.0,
                                 0.0, b.expand + bb, nullptr};
+        if (p.svd)       // and of the primal one: R1 = U R1r
+            gExp1[bb] = GemmDesc{b.Um, b.Rr + o_n, b.T + o_m, m, l, nr, m, nr, m, 1.0, 0.0, b.expand1 + bb, nullptr};
         eig[bb] = EigDesc{b.Bq[bb], X, b.Rm[bb], b.lam[bb], L, l, erun, b.eigst + 2 * bb,
                           b.eigscale + bb, b.prot[bb], b.lo[bb], ctx->dwork, b.locut + bb, b.passes + bb,
                           b.need_all + need_off[bb], b.sched_all + sched_off[bb], b.ref_clean + bb};
@@ -736,8 +851,9 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
                           b.ref_cont + bb, b.Bq[bb], b.locut + bb, L, l, bb, b.ref_rdev + bb,
                           b.ref_nsskip + bb, b.ref_clean + bb};
     }
-    std::vector<GemmDesc> gKK(p.local ? t : 1);
-    if (p.literal)
+    std::vector<GemmDesc> gKK(p.svd ? 0 : p.local ? t : 1);
+    if (p.svd) {}
+    else if (p.literal)
         gKK[0] = GemmDesc{pr.A, pr.A, b.K, n, n, m, (int)pr.lda, (int)pr.lda, n, 1.0, 0.0, nullptr, nullptr};
     else if (p.local)
         for (int bb = 0; bb < t; ++bb)
@@ -752,7 +868,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
     up(b.colblk, colblk.data(), sizeof(int) * c);
     up(b.boff, p.boff.data(), sizeof(int) * (t + 1));
     up(b.mu_sched, sched.data(), sizeof(double) * sched.size());
-    up(b.g_gram, gram.data(), sizeof(GemmDesc) * t);
+    up(b.g_gram, gram.data(), sizeof(GemmDesc) * ny * t);
     up(b.g_refT, gRT.data(), sizeof(GemmDesc) * t);
     up(b.g_refSG, gRSG.data(), sizeof(GemmDesc) * t);
     up(b.g_refXE, gRXE.data(), sizeof(GemmDesc) * t);
@@ -760,7 +876,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
     up(b.g_Bq, gBq.data(), sizeof(GemmDesc) * t);
     up(b.ref, ref.data(), sizeof(RefDesc) * t);
     up(b.g_P, gP.data(), sizeof(GemmDesc) * t);
-    up(b.g_J, gJ.data(), sizeof(GemmDesc) * t);
+    up(b.g_J, gJ.data(), sizeof(GemmDesc) * ny * t);
     up(b.g_MQ, gMQ.data(), sizeof(GemmDesc) * t);
     up(b.g_MQa, gMQa.data(), sizeof(GemmDesc) * t);
     up(b.g_KV, gKV.data(), sizeof(GemmDesc) * t);
@@ -773,8 +889,9 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         up(b.g_F1, &gF1, sizeof(GemmDesc));
     }
     if (p.reduced) up(b.g_exp, gExp.data(), sizeof(GemmDesc) * t);
+    if (p.svd) up(b.g_exp1, gExp1.data(), sizeof(GemmDesc) * t);
 
-    up(b.g_KK, gKK.data(), sizeof(GemmDesc) * gKK.size());
+    if (!gKK.empty()) up(b.g_KK, gKK.data(), sizeof(GemmDesc) * gKK.size());
     up(b.eig, eig.data(), sizeof(EigDesc) * t);
     {
         // item prefixes of the persistent eigensolve: rows, pair slots, apply items
@@ -789,10 +906,10 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         LRR_HIP(hipStreamSynchronize(s));   // the host table goes out of scope
     }
     up(b.svt, svt.data(), sizeof(SvtDesc) * t);
-    if (pr.perm) up(b.perm, pr.perm, sizeof(int) * c);
 
     // ---- setup: observations, state, factorisation (once per solve) -------
-    if (pr.perm) lrr::launch_gather_cols(pr.A, pr.lda, b.X, m, m, c, b.perm, s);
+    if (p.svd) {}   // U^T X is in place
+    else if (pr.perm) lrr::launch_gather_cols(pr.A, pr.lda, b.X, m, m, c, b.perm, s);
     else lrr::launch_copy_cols(pr.X, pr.ldx, b.X, m, m, c, s);
     const size_t nc = (size_t)nr * c, mc = (size_t)m * c;
     LRR_HIP(hipMemsetAsync(b.Z, 0, sizeof(double) * nc, s));
@@ -800,10 +917,15 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
     LRR_HIP(hipMemsetAsync(b.Y2, 0, sizeof(double) * nc, s));
     LRR_HIP(hipMemsetAsync(b.E, 0, sizeof(double) * mc, s));
     LRR_HIP(hipMemsetAsync(b.Y1, 0, sizeof(double) * mc, s));
+    if (p.svd) {   // first input Y = 0, q = 0
+        LRR_HIP(hipMemsetAsync(b.Yp[0], 0, sizeof(double) * nc, s));
+        LRR_HIP(hipMemsetAsync(b.fcol[0], 0, sizeof(double) * 2 * c, s));
+        LRR_HIP(hipMemsetAsync(b.colsq, 0, sizeof(double) * c, s));
+    }
     // local mode: the rows of M^T V beyond a block's width are never written
     if (p.local) LRR_HIP(hipMemsetAsync(b.MtV, 0, sizeof(double) * nc, s));
     // the carried product M Q starts from Q = 0
-    if (p.pm.dMQ) {
+    if (p.pm.dMQ && !p.svd) {
         LRR_HIP(hipMemsetAsync(b.Q, 0, sizeof(double) * nc, s));
         LRR_HIP(hipMemsetAsync(b.MQacc, 0, sizeof(double) * mc, s));
     }
@@ -831,6 +953,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
     if (p.reduced) LRR_HIP(hipMemsetAsync(b.r2nrm, 0, sizeof(unsigned long long) * t, s));
     lrr::launch_init_iter(b.it, b.mu_sched, 0, s);
 
+    if (p.svd) return;   // nothing to factor
     // literal form: K = I + A^T A (n x n), K^{-1} (FP64 Cholesky, once per
     // solve), F1 = K^{-1} A^T, then K^{-1} - I in place
     if (p.literal) {
@@ -849,6 +972,20 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         lrr::launch_add_identity(Kb, m, m, 1.0, s);
         lrr::spd_inverse(Kb, m, b.Lb, b.Linv, b.Dinv, b.Tb, b.g_spd, b.flag, s);
     }
+}
+
+// The column pass of an iteration that starts from buffer `par`.
+SvdStep svd_step(const Plan& p, const Buffers& b, int par, double lam) {
+    SvdStep a{};
+    if (!p.svd) return a;
+    a.X = b.X; a.J = b.J; a.d = b.dsig; a.dinv = b.dinv;
+    a.q0 = b.qp[par]; a.Y20 = b.Y2p[par]; a.f0 = b.fcol[par];
+    a.q1 = b.qp[par ^ 1]; a.Y21 = b.Y2p[par ^ 1]; a.f1 = b.fcol[par ^ 1];
+    a.Y0 = b.Yp[par]; a.Y1 = b.Yp[par ^ 1];
+    a.colsq = b.colsq; a.colblk = b.colblk;
+    a.r = p.nr; a.ncols = p.ncols;
+    a.lam = lam;
+    return a;
 }
 
 // Hooks of iterate_alm: called before iteration k starts and after it ends
@@ -882,7 +1019,7 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
     int* h_need = reinterpret_cast<int*>(reinterpret_cast<char*>(hp) + flag_bytes);
     int* h_sched = reinterpret_cast<int*>(reinterpret_cast<char*>(hp) + flag_bytes + need_bytes);
     BlockState bst{b.active, b.svt_run, b.iters, b.rank, b.res1, b.res2, b.r1max, b.r2max, b.colr1, b.colr2};
-    const ProductModes& pm = p.pm;
+    const ProductModes pm = p.svd ? ProductModes{} : p.pm;
     const int max_sweeps = o.max_sweeps > 0 ? o.max_sweeps : 30;
     const int check_every = o.check_every > 0 ? o.check_every : 1;
     const int fixed = o.fixed_iters > 0 ? 1 : 0;
@@ -924,7 +1061,46 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
     // device queries of the launch shapes, made before any stream capture
     (void)lrr::gemm_grid();
     if (device_loop) (void)lrr::jacobi_solve_grid(p.bs);
-    auto zstep = [&](hipStream_t st, bool anchor, auto&& tm, double cact) {
+    const SvdStep sv[2] = {svd_step(p, b, 0, pr.lam), svd_step(p, b, 1, pr.lam)};
+    auto zstep = [&](hipStream_t st, bool anchor, int par, auto&& tm, double cact) {
+        if (p.svd) {
+            // par: the buffer that holds the state before this iteration
+            const double rm = std::sqrt((double)m), rn = std::sqrt((double)nfull);
+            tm("k_zstep_fused", 0.0, 7.0 * n * cact * D, [&] {
+                lrr::launch_zstep_fused(sv[par], bst, b.it, b.mu_sched, st);
+            });
+            tm("k_svd_decide", 0.0, 0.0, [&] {
+                lrr::launch_svd_decide(b.boff, t, bst, b.r2nrm, b.expand1, b.expand, o.tol, rm, rn, p.n_iter, b.it,
+                                       st);
+            });
+            tm("k_svd_resid", 0.0, 0.0, [&] {
+                lrr::launch_svd_resid(sv[par], b.boff, t, p.maxl, b.expand1, b.Rr, 1, b.it, b.mu_sched, st);
+            });
+            tm("k_dgemm<false, false>", 0.0, 0.0, [&] {
+                lrr::launch_dgemm(b.g_exp1, t, m, p.maxl, false, false, st);
+            });
+            tm("k_svd_colmax", 0.0, 0.0, [&] {
+                lrr::launch_svd_colmax(b.T, m, m, b.boff, t, p.maxl, b.expand1, b.r1max, p.extra ? b.V : nullptr,
+                                       b.Rr, n, st);
+            });
+            tm("k_svd_decide2", 0.0, 0.0, [&] {
+                lrr::launch_svd_decide2(bst, b.r2nrm, b.expand1, b.expand, t, o.tol, rn, p.n_iter, b.it, st);
+            });
+            tm("k_svd_resid", 0.0, 0.0, [&] {
+                lrr::launch_svd_resid(sv[par], b.boff, t, p.maxl, b.expand, b.Rr, 2, b.it, b.mu_sched, st);
+            });
+            tm("k_dgemm<false, false>", 0.0, 0.0, [&] {
+                lrr::launch_dgemm(b.g_exp, t, nfull, p.maxl, false, false, st);
+            });
+            tm("k_svd_colmax", 0.0, 0.0, [&] {
+                lrr::launch_svd_colmax(b.R2full, nfull, nfull, b.boff, t, p.maxl, b.expand, b.r2max, nullptr, nullptr, n,
+                                       st);
+            });
+            tm("k_check", 0.0, 0.0, [&] {
+                lrr::launch_check(bst, t, b.it, b.mu_sched, o.tol, fixed, b.n_active, st);
+            });
+            return;
+        }
         tm("k_form_QT", 0.0, ((pm.dMQ ? 5.0 : 3.0) * n + 4.0 * m) * cact * D, [&] {
             lrr::launch_form_QT(b.J, b.Y2, b.Q, pm.dMQ ? b.Dn : nullptr, n, n, b.X, b.E, b.Y1, b.T, m, m, c,
                                 b.colblk, b.active, b.it, st);
@@ -1014,7 +1190,7 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
     // eigensolve proceeds), so the launches are the same in every iteration.
     // Only while profiling (`tm` times launches, prof.on) are the flags read back,
     // to price each launch with the flops of the blocks it actually covers.
-    auto jstep = [&](hipStream_t st, auto&& tm, double cact) {
+    auto jstep = [&](hipStream_t st, int par, auto&& tm, double cact) {
         const bool price = prof.on;
         auto read_flags = [&](int* dst, const int* src) {
             if (!price) return;
@@ -1022,11 +1198,14 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
             sync();
         };
         // J-step input and the exact zero test
-        tm("k_form_Y", 0.0, 3.0 * n * cact * D, [&] {
-            lrr::launch_form_Y(b.Z, b.Y2, b.Y, b.colsq, n, n, c, b.colblk, b.active, b.it, st);
-        });
+        // (in singular coordinates the previous column pass left Y and its column norms,
+        // and the next one takes J = 0 from the flags)
+        if (!p.svd)
+            tm("k_form_Y", 0.0, 3.0 * n * cact * D, [&] {
+                lrr::launch_form_Y(b.Z, b.Y2, b.Y, b.colsq, n, n, c, b.colblk, b.active, b.it, st);
+            });
         tm("k_block_fro", 0.0, cact * D, [&] { lrr::launch_block_fro(b.colsq, b.boff, t, bst, b.it, st); });
-        tm("k_zero_J", 0.0, 0.0, [&] { lrr::launch_zero_J(b.J, n, n, c, b.colblk, bst, st); });
+        if (!p.svd) tm("k_zero_J", 0.0, 0.0, [&] { lrr::launch_zero_J(b.J, n, n, c, b.colblk, bst, st); });
         tm("k_eig_select", 0.0, 0.0, [&] {
             lrr::launch_eig_select(b.colsq, b.boff, t, b.active, b.svt_run, b.warm, b.eig_run, b.it, prewarm, st);
         });
@@ -1046,7 +1225,7 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
         // the symmetric kernel computes the tiles on and above the diagonal
         const double hg = lrr::dgemm_sym_tiles(t, p.maxl) ? 0.5 : 1.0, hL = lrr::dgemm_sym_tiles(t, p.maxL) ? 0.5 : 1.0;
         // Gram matrix of each block that thresholds (FP64 in every precision form)
-        tm("k_dgemm_sym", hg * f_gram, 0.0, [&] { lrr::launch_dgemm_sym(b.g_gram, t, p.maxl, st); });
+        tm("k_dgemm_sym", hg * f_gram, 0.0, [&] { lrr::launch_dgemm_sym(b.g_gram + (p.svd ? par * t : 0), t, p.maxl, st); });
         // Newton refinement of the previous iteration's eigenvectors: a fixed
         // number of steps, each applied only where the per-block flags allow
         tm("k_ref_begin", 0.0, 0.0, [&] { lrr::launch_ref_begin(b.ref, t, p.maxL, b.eig_run, b.warm, st); });
@@ -1118,7 +1297,7 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
             lrr::launch_dgemm(b.g_P, t, p.maxl, p.maxl, false, true, st);
         });
         tm("k_dgemm<false, false>", f_J, 0.0, [&] {
-            lrr::launch_dgemm(b.g_J, t, n, p.maxl, false, false, st);
+            lrr::launch_dgemm(b.g_J + (p.svd ? par * t : 0), t, n, p.maxl, false, false, st);
         });
         tm("k_lo_mode", 0.0, 0.0, [&] { lrr::launch_lo_mode(b.eig_run, b.warm, b.passes, b.locut, t, st); });
         tm("k_mark_warm", 0.0, 0.0, [&] { lrr::launch_mark_warm(b.eig_run, b.warm, t, st); });
@@ -1128,13 +1307,16 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
     // read-back), each refinement step (a read-back of the continue flags), each
     // Jacobi pass (a read-back of the check marks, the round plan from the host).
     bool eig_seen = false;   // some block has been decomposed in this solve
-    auto host_jstep = [&](double cact) {
+    auto host_jstep = [&](int par, double cact) {
         // J-step input and the exact zero test
-        timed("k_form_Y", 0.0, 3.0 * n * cact * D, [&] {
-            lrr::launch_form_Y(b.Z, b.Y2, b.Y, b.colsq, n, n, c, b.colblk, b.active, b.it, s);
-        });
+        // (in singular coordinates the previous column pass left Y and its column norms,
+        // and the next one takes J = 0 from the flags)
+        if (!p.svd)
+            timed("k_form_Y", 0.0, 3.0 * n * cact * D, [&] {
+                lrr::launch_form_Y(b.Z, b.Y2, b.Y, b.colsq, n, n, c, b.colblk, b.active, b.it, s);
+            });
         timed("k_block_fro", 0.0, cact * D, [&] { lrr::launch_block_fro(b.colsq, b.boff, t, bst, b.it, s); });
-        timed("k_zero_J", 0.0, 0.0, [&] { lrr::launch_zero_J(b.J, n, n, c, b.colblk, bst, s); });
+        if (!p.svd) timed("k_zero_J", 0.0, 0.0, [&] { lrr::launch_zero_J(b.J, n, n, c, b.colblk, bst, s); });
         timed("k_eig_select", 0.0, 0.0, [&] {
             lrr::launch_eig_select(b.colsq, b.boff, t, b.active, b.svt_run, b.warm, b.eig_run, b.it, prewarm, s);
         });
@@ -1167,7 +1349,7 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
             // precision form)
             // the symmetric kernel computes the tiles on and above the diagonal
             const double hg = lrr::dgemm_sym_tiles(t, p.maxl) ? 0.5 : 1.0, hL = lrr::dgemm_sym_tiles(t, p.maxL) ? 0.5 : 1.0;
-            timed("k_dgemm_sym", hg * f_gram, 0.0, [&] { lrr::launch_dgemm_sym(b.g_gram, t, p.maxl, s); });
+            timed("k_dgemm_sym", hg * f_gram, 0.0, [&] { lrr::launch_dgemm_sym(b.g_gram + (p.svd ? par * t : 0), t, p.maxl, s); });
             // Newton refinement of the previous iteration's eigenvectors
             timed("k_ref_begin", 0.0, 0.0, [&] { lrr::launch_ref_begin(b.ref, t, p.maxL, b.eig_run, b.warm, s); });
             // the first kBlindSteps steps are launched without reading the flags back
@@ -1315,7 +1497,7 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
                 lrr::launch_dgemm(b.g_P, t, p.maxl, p.maxl, false, true, s);
             });
             timed("k_dgemm<false, false>", f_J, 0.0, [&] {
-                lrr::launch_dgemm(b.g_J, t, n, p.maxl, false, false, s);
+                lrr::launch_dgemm(b.g_J + (p.svd ? par * t : 0), t, n, p.maxl, false, false, s);
             });
             timed("k_lo_mode", 0.0, 0.0, [&] { lrr::launch_lo_mode(b.eig_run, b.warm, b.passes, b.locut, t, s); });
             timed("k_mark_warm", 0.0, 0.0, [&] { lrr::launch_mark_warm(b.eig_run, b.warm, t, s); });
@@ -1331,8 +1513,10 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
                              prof.wants("k_dgemm<false, false>") || prof.wants(lrr::xgemm_name(pm.MtV, true, false)) ||
                              prof.wants("k_sub_cols") || prof.wants("k_update_Z") || prof.wants("k_r2_decide") ||
                              prof.wants("k_colmax") || prof.wants("k_estep") || prof.wants("k_check") ||
-                             prof.wants("k_block_colmax");
+                             prof.wants("k_block_colmax") || prof.wants("k_zstep_fused") || prof.wants("k_svd_");
     const bool use_graph = device_loop ? (o.use_graph == 2 && !prof.on) : (o.use_graph == 1 && !chain_timed);
+    // two graphs: plain and re-anchoring iterations, or in singular coordinates the
+    // iterations that start from either buffer
     hipGraphExec_t g_plain = nullptr, g_anchor = nullptr;
     hipStream_t cs = use_graph ? ctx_capture_stream(ctx) : nullptr;
     struct GraphGuard {
@@ -1349,14 +1533,15 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
         double cact = 0.0;   // columns of blocks still iterating (as of the last read-back)
         for (int bb = 0; bb < t; ++bb) if (h_act[bb]) cact += p.boff[bb + 1] - p.boff[bb];
         const bool anchor = pm.dMQ && k > 0 && k % kAnchorEvery == 0;
-        if (!device_loop) host_jstep(cact);
+        const int par = k & 1;
+        if (!device_loop) host_jstep(par, cact);
         if (use_graph) {
-            hipGraphExec_t& ex = anchor ? g_anchor : g_plain;
+            hipGraphExec_t& ex = anchor || (p.svd && par) ? g_anchor : g_plain;
             if (!ex) {
                 hipGraph_t graph = nullptr;
                 LRR_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-                if (device_loop) jstep(cs, untimed, cact);
-                zstep(cs, anchor, untimed, cact);
+                if (device_loop) jstep(cs, par, untimed, cact);
+                zstep(cs, anchor, par, untimed, cact);
                 LRR_HIP(hipStreamEndCapture(cs, &graph));
                 const hipError_t e = hipGraphInstantiate(&ex, graph, nullptr, nullptr, 0);
                 (void)hipGraphDestroy(graph);
@@ -1364,8 +1549,8 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
             }
             LRR_HIP(hipGraphLaunch(ex, s));
         } else {
-            if (device_loop) jstep(s, timed, cact);
-            zstep(s, anchor, timed, cact);
+            if (device_loop) jstep(s, par, timed, cact);
+            zstep(s, anchor, par, timed, cact);
         }
         if (hooks && hooks->end) hooks->end(k);
         if (!fixed && ((k + 1) % check_every == 0 || k + 1 == p.n_iter)) {
@@ -1985,15 +2170,30 @@ static lrr_status lrr_solve_f64(lrr_ctx* ctx, int m, int n, int l, const void* A
         Plan p = make_plan(pr);
         Buffers b{};
         Result r = run_alm(ctx, pr, p, b, s, false);
+        const double* Zr = b.Z;
+        if (p.svd) {
+            lrr::launch_svd_result(svd_step(p, b, 0, lambda), b.iters, b.Rr, 1, b.mu_sched, s);
+            Zr = b.Rr;
+        }
         if (p.reduced) {
             // Z = Qm Zr
-            GemmDesc gz{b.Qm, b.Z, static_cast<double*>(Z), n, l, p.nr, n, p.nr, ldz, 1.0, 0.0, nullptr, nullptr};
+            GemmDesc gz{b.Qm, Zr, static_cast<double*>(Z), n, l, p.nr, n, p.nr, ldz, 1.0, 0.0, nullptr, nullptr};
             LRR_HIP(hipMemcpyAsync(b.g_U, &gz, sizeof(GemmDesc), hipMemcpyHostToDevice, s));
             lrr::launch_dgemm(b.g_U, 1, n, l, false, false, s);
         } else {
             lrr::launch_copy_cols(b.Z, n, static_cast<double*>(Z), ldz, n, l, s);
         }
-        if (E) lrr::launch_copy_cols(b.E, m, static_cast<double*>(E), lde, m, l, s);
+        if (E && p.svd) {
+            // E = U Er
+            lrr::launch_svd_result(svd_step(p, b, 0, lambda), b.iters, b.R2r, 0, b.mu_sched, s);
+            const GemmDesc ge{b.Um, b.R2r, static_cast<double*>(E), m, l, p.nr, m, p.nr, lde, 1.0, 0.0, nullptr,
+                              nullptr};
+            LRR_HIP(hipMemcpyAsync(b.g_H, &ge, sizeof(GemmDesc), hipMemcpyHostToDevice, s));
+            lrr::launch_dgemm(b.g_H, 1, m, l, false, false, s);
+            if (p.extra) lrr::launch_svd_add_outside(static_cast<double*>(E), lde, m, l, b.V, b.R2r, p.nr, nullptr, s);
+        } else if (E) {
+            lrr::launch_copy_cols(b.E, m, static_cast<double*>(E), lde, m, l, s);
+        }
         LRR_HIP(hipStreamSynchronize(s));
         fill_info(info, r, r.rank[0]);
         return r.converged ? LRR_OK : LRR_NOT_CONVERGED;
@@ -2048,7 +2248,10 @@ static lrr_status dfc_lrr_solve_f64(lrr_ctx* ctx, int m, int n, const void* M, i
             // U1^T [J_1 ... J_t] = Ur^T [Jr_1 ... Jr_t]
             const int nr = p.nr;
             double* Uc = p.reduced ? b.Ur : b.U;
-            GemmDesc gU{b.Y, b.Wm[0], Uc, nr, L0, l0, nr, L0, nr, 1.0, 0.0, nullptr, nullptr};
+            // the input of block 1's last thresholding step
+            const double* Y1 = p.svd ? b.Yp[(r.iters[0] + 1) & 1] : b.Y;
+            if (p.svd) lrr::launch_svd_zero_J(b.J, nr, n, b.colblk, b.rank, s);
+            GemmDesc gU{Y1, b.Wm[0], Uc, nr, L0, l0, nr, L0, nr, 1.0, 0.0, nullptr, nullptr};
             GemmDesc gH{Uc, b.J, b.H, L0, n, nr, nr, nr, L0, 1.0, 0.0, nullptr, nullptr};
             GemmDesc gZ{b.U, b.H, Zo, n, n, L0, n, L0, ldz, 1.0, 0.0, nullptr, b.perm};
             GemmDesc gQU{b.Qm, b.Ur, b.U, n, L0, nr, n, nr, n, 1.0, 0.0, nullptr, nullptr};
@@ -2071,7 +2274,18 @@ static lrr_status dfc_lrr_solve_f64(lrr_ctx* ctx, int m, int n, const void* M, i
             prof.run(s, lrr::xgemm_name(gm, false, false), 2.0 * n * n * L0, 0.0,
                      [&] { lrr::launch_xgemm(b.g_Z, 1, n, n, false, false, gm, s); });
         }
-        if (S) lrr::launch_scatter_cols(b.E, m, static_cast<double*>(S), lds, m, n, b.perm, s);
+        if (S && p.svd) {
+            // S = U [E_1 ... E_t], columns put back
+            lrr::launch_svd_result(svd_step(p, b, 0, lambda), b.iters, b.Rr, 0, b.mu_sched, s);
+            const GemmDesc ge{b.Um, b.Rr, static_cast<double*>(S), m, n, p.nr, m, p.nr, lds, 1.0, 0.0, nullptr,
+                              b.perm};
+            LRR_HIP(hipMemcpyAsync(b.g_exp1, &ge, sizeof(GemmDesc), hipMemcpyHostToDevice, s));
+            lrr::launch_dgemm(b.g_exp1, 1, m, n, false, false, s);
+            if (p.extra)
+                lrr::launch_svd_add_outside(static_cast<double*>(S), lds, m, n, b.V, b.Rr, p.nr, b.perm, s);
+        } else if (S) {
+            lrr::launch_scatter_cols(b.E, m, static_cast<double*>(S), lds, m, n, b.perm, s);
+        }
         if (o.save_for_backward) {
             Tape& tp = *ctx->tape;
             tp.b = b;

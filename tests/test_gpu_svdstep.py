@@ -1,0 +1,121 @@
+"""The iteration in singular coordinates (reduced coordinates with the dictionary
+diagonalised) against the FP64 oracle, at the edges of its column pass: a wave
+per column up to 512 rows in chunks of 128, a workgroup beyond, odd and even row
+counts, and the dictionaries and observations that have to take the dense form.
+
+Tolerances: the parity bar of the solver (1e-6) on Z and S; the primal residual
+after a fixed number of iterations, while it is far above the rounding of the
+O(1) quantities it is the difference of, to 1e-6 of its value.
+"""
+import numpy as np
+import pytest
+
+from gpu_util import need_gpu, one_thread, rel, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(p, **kw):
+    from paper_1304_5583_amd import binding as B
+    o = B.lrr_opts_default(coords=B.LRR_COORDS_REDUCED, **kw)
+    Zt, St, info = B.dfc_lrr_solve(B.to_device_colmajor(p.M), p.lam, p.perm, p.offsets, opts=o)
+    return B.from_device_colmajor(Zt), B.from_device_colmajor(St), info
+
+
+@pytest.mark.parametrize("m,ns,t", [(127, 48, 5), (128, 48, 5), (129, 48, 5), (257, 96, 9), (512, 180, 17),
+                                    (513, 180, 17)])
+def test_row_counts_vs_oracle(m, ns, t):
+    import oracle
+    from paper_1304_5583_amd.datagen import small_problem
+    need_gpu()
+    # noise on every column makes the rank min(m, n)
+    n = 3 * ns
+    p = small_problem(900 + m, m=m, k=3, r=4, ns=ns, n_replace=0, t=t, lam=0.2, uneven=(n // t - 3, n // t + 4),
+                      normalize=True)
+    rng = np.random.default_rng(m)
+    p.M[:] += 0.02 / np.sqrt(m) * rng.standard_normal(p.M.shape)
+    say(f"[svd rows] m={p.m} n={p.n} t={p.t}")
+    Z, S, info = _run(p, max_iter=400)
+    with one_thread():
+        ref = oracle.dfc_lrr(p.M, p.lam, p.perm, p.offsets)
+    assert info.status == 0
+    assert info.iters.tolist() == [b.iters for b in ref.blocks]
+    assert info.rank.tolist() == [b.rank for b in ref.blocks]
+    assert rel(Z, ref.Z) <= 1e-6
+    assert rel(S, ref.S) <= 1e-6 or np.linalg.norm(ref.S) == 0.0
+
+
+@pytest.mark.parametrize("iters", [1, 2, 61, 128])
+def test_fixed_iterations_report_the_last_residual(iters):
+    from oracle.lrr import ALMOptions, dfc_lrr
+    from paper_1304_5583_amd.datagen import small_problem
+    need_gpu()
+    p = small_problem(77, m=45, k=4, r=3, ns=33, n_replace=5, t=4, lam=0.25, uneven=(28, 40), normalize=True)
+    Z, S, info = _run(p, fixed_iters=iters)
+    with one_thread():
+        ref = dfc_lrr(p.M, p.lam, p.perm, p.offsets, ALMOptions(fixed_iters=iters))
+    assert info.iters.tolist() == [iters] * p.t
+    np.testing.assert_allclose(info.res_primal, [b.res1 for b in ref.blocks], rtol=1e-6)
+    assert np.linalg.norm(Z - ref.Z) <= 1e-6 * max(np.linalg.norm(ref.Z), 1e-300)
+    assert np.linalg.norm(S - ref.S) <= 1e-6 * max(np.linalg.norm(ref.S), 1e-300)
+
+
+def test_more_rows_than_a_wave_holds():
+    """1030 and 2050 rows (the workgroup-per-column pass): against full coordinates
+    of the same library, whose column kernels are separate."""
+    from paper_1304_5583_amd import binding as B
+    need_gpu()
+    for m in (1030, 2050):
+        rng = np.random.default_rng(m)
+        n = m + 46
+        M = rng.standard_normal((m, 12)) @ rng.standard_normal((12, n)) + 0.05 * rng.standard_normal((m, n))
+        M /= np.linalg.norm(M, axis=0)
+        offs = np.arange(0, n + 1, n // 12, dtype=np.int32)
+        offs[-1] = n
+        perm = rng.permutation(n).astype(np.int32)
+        Mt = B.to_device_colmajor(M)
+        out = {}
+        for coords in (B.LRR_COORDS_FULL, B.LRR_COORDS_REDUCED):
+            o = B.lrr_opts_default(coords=coords, fixed_iters=130)
+            Zt, St, info = B.dfc_lrr_solve(Mt, 0.15, perm, offs, opts=o)
+            out[coords] = (B.from_device_colmajor(Zt), B.from_device_colmajor(St), info)
+        a, b = out[B.LRR_COORDS_FULL], out[B.LRR_COORDS_REDUCED]
+        say(f"[svd rows] m={m} relZ={rel(b[0], a[0]):.2e}")
+        assert rel(b[0], a[0]) <= 1e-6 and rel(b[1], a[1]) <= 1e-6
+        assert b[2].rank.tolist() == a[2].rank.tolist()
+        np.testing.assert_allclose(b[2].res_primal, a[2].res_primal, rtol=1e-6)
+
+
+def test_observations_outside_the_dictionary_range():
+    """lrr_solve with X partly outside range(A): one more coordinate carries that part."""
+    from oracle.lrr import lrr_alm
+    from paper_1304_5583_amd import binding as B
+    need_gpu()
+    rng = np.random.default_rng(5)
+    A = rng.standard_normal((40, 6)) @ rng.standard_normal((6, 90))
+    A /= np.linalg.norm(A, axis=0)
+    X = A[:, :30] + 0.1 * rng.standard_normal((40, 30)) / np.sqrt(40)
+    Zt, Et, info = B.lrr_solve(B.to_device_colmajor(A), B.to_device_colmajor(X), 0.3)
+    with one_thread():
+        ref = lrr_alm(X, A, 0.3)
+    assert info.iters[0] == ref.iters
+    assert rel(B.from_device_colmajor(Zt), ref.Z) <= 1e-6
+    assert rel(B.from_device_colmajor(Et), ref.E) <= 1e-6
+
+
+def test_wide_singular_spread_vs_full_coordinates():
+    """Singular values over six decades, all above the rank cut."""
+    from paper_1304_5583_amd import binding as B
+    need_gpu()
+    rng = np.random.default_rng(9)
+    m, n = 48, 120
+    U, _ = np.linalg.qr(rng.standard_normal((m, m)))
+    V, _ = np.linalg.qr(rng.standard_normal((n, m)))
+    M = (U * np.logspace(0, -6, m)) @ V.T
+    offs, perm = np.array([0, 40, 80, 120], dtype=np.int32), rng.permutation(n).astype(np.int32)
+    out = []
+    for coords in (B.LRR_COORDS_FULL, B.LRR_COORDS_REDUCED):
+        o = B.lrr_opts_default(coords=coords, fixed_iters=110)
+        Zt, St, info = B.dfc_lrr_solve(B.to_device_colmajor(M), 0.5, perm, offs, opts=o)
+        out.append((B.from_device_colmajor(Zt), B.from_device_colmajor(St)))
+    assert rel(out[1][0], out[0][0]) <= 1e-6 and rel(out[1][1], out[0][1]) <= 1e-6
