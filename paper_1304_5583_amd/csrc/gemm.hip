@@ -63,8 +63,8 @@ __device__ __forceinline__ double buffer_ld(__amdgpu_buffer_rsrc_t r, unsigned o
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
 }
 
-// SYM (with TA, !TB, BM = BN, C square): C = A^T B for a product that is
-// symmetric in exact arithmetic (A^T A, or X^T (B X) with B symmetric); only the
+// SYM (with TA != TB, BM = BN, C square): C = A^T B or A B^T for a product that is
+// symmetric in exact arithmetic (A^T A, A A^T, or X^T (B X) with B symmetric); only the
 // tiles with P <= Q run, and an off-diagonal tile also writes its transpose, so
 // the result is exactly symmetric.  For A^T A it is bitwise the full product:
 // tile (P, Q) and tile (Q, P) multiply the same pairs of numbers in the same
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256, 4) void k_dgemm(const GemmDesc* __restrict__ d
                                                   int total) {
     constexpr int WM = BM / 2, TX = WM / 16;
     constexpr int NA = BM * BK / 256, NB = BN * BK / 256;   // operand elements per thread and K-tile
-    static_assert(!SYM || (TA && !TB && BM == BN), "symmetric tiles need C = A^T B with square tiles");
+    static_assert(!SYM || (TA != TB && BM == BN), "symmetric tiles need C = A^T B or A B^T with square tiles");
     const int per = SYM ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
     // double-buffered operand tiles: As[buf][k][i] = op(A)(m0+i, k0+k)
     __shared__ double As[2][BK][BM + PAD];
@@ -316,19 +316,22 @@ bool dgemm_sym_tiles(int count, int maxN) {
 
 int gemm_grid(void) { return gemm_grid_cap(); }
 
-void launch_dgemm_sym(const GemmDesc* d_descs, int count, int maxN, hipStream_t stream, bool always) {
+void launch_dgemm_sym(const GemmDesc* d_descs, int count, int maxN, hipStream_t stream, bool always, bool nt) {
     if (count <= 0 || maxN <= 0) return;
     const int tm = (maxN + BN - 1) / BN;
     // small batches keep every tile (32-row tiles give every CU two workgroups);
     // the result is the same either way
     if (!always && !dgemm_sym_tiles(count, maxN)) {
-        launch_dgemm(d_descs, count, maxN, maxN, true, false, stream);
+        launch_dgemm(d_descs, count, maxN, maxN, !nt, nt, stream);
         return;
     }
     const long total = (long)tm * (tm + 1) / 2 * count;
     if (total > 0x7fffffffL) throw HipError("GEMM grid too large");
-    hipLaunchKernelGGL((k_dgemm<BN, true, false, true>), dim3((unsigned)std::min<long>(total, gemm_grid_cap())),
-                       dim3(256), 0, stream, d_descs, tm, tm, (int)total);
+    const dim3 grid((unsigned)std::min<long>(total, gemm_grid_cap()));
+    if (nt)
+        hipLaunchKernelGGL((k_dgemm<BN, false, true, true>), grid, dim3(256), 0, stream, d_descs, tm, tm, (int)total);
+    else
+        hipLaunchKernelGGL((k_dgemm<BN, true, false, true>), grid, dim3(256), 0, stream, d_descs, tm, tm, (int)total);
 }
 
 void launch_dgemm(const GemmDesc* d_descs, int count, int maxM, int maxN, bool ta, bool tb,

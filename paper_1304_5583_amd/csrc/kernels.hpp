@@ -11,8 +11,9 @@ void launch_dgemm(const GemmDesc* d_descs, int count, int maxM, int maxN, bool t
 // C = A^T B for square C (descriptors with M = N) known to be symmetric (A^T A,
 // X^T (B X)): only the tiles on and above the diagonal are computed, the others
 // mirrored (for A^T A bitwise the full product); batches of fewer than 512 full
-// tiles take the full kernel unless `always`
-void launch_dgemm_sym(const GemmDesc* d_descs, int count, int maxN, hipStream_t stream, bool always = false);
+// tiles take the full kernel unless `always`.  nt: C = A B^T instead (B = A).
+void launch_dgemm_sym(const GemmDesc* d_descs, int count, int maxN, hipStream_t stream, bool always = false,
+                      bool nt = false);
 // whether launch_dgemm_sym runs the triangle of tiles for this batch
 bool dgemm_sym_tiles(int count, int maxN);
 // workgroups of a GEMM launch (looked up once; call before a stream capture)
@@ -149,6 +150,7 @@ void launch_svd_add_outside(double* out, long ldo, int m, int c, const double* D
                             const int* map, hipStream_t s);
 // what = 0: the outlier coefficients E, 1: the iterate Z
 void launch_svd_result(const SvdStep& a, const int* iters, double* out, int what, const double* sched, hipStream_t s);
+void launch_svd_left_basis(const double* W, int L, const double* h, double* U, int rows, hipStream_t s);
 void launch_svd_zero_J(double* J, int r, int ncols, const int* colblk, const int* rank, hipStream_t s);
 
 // adjoint.hip

@@ -174,8 +174,12 @@ struct Plan {
     int m = 0, n = 0, ncols = 0, t = 0;
     int bs = 16;                 // Jacobi block width
     std::vector<int> boff;       // t + 1 column offsets
+    std::vector<int> ord;        // Gram order per block: its width l, or nr when left
     std::vector<int> L;          // padded Gram order per block
-    int maxL = 0, maxl = 0;
+    int maxL = 0, maxl = 0, maxo = 0;
+    // singular coordinates: the thresholding step takes the eigen-decomposition of
+    // Y Y^T (r x r) instead of Y^T Y (l x l)
+    bool left = false;
     int n_iter = 0;
     ProductModes pm;             // arithmetic of each large product
     // coordinates of the n-row iterates (Z, J, Y2 and their temporaries): n rows,
@@ -559,12 +563,15 @@ Plan make_plan(const Problem& pr) {
     p.maxl = 0;
     for (int b = 0; b < pr.t; ++b) p.maxl = std::max(p.maxl, p.boff[b + 1] - p.boff[b]);
     p.bs = jacobi_bs(p.maxl, pr.o.eig_block);
+    p.ord.resize(pr.t);
     p.L.resize(pr.t);
     p.maxL = 0;
     for (int b = 0; b < pr.t; ++b) {
-        p.L[b] = round_up(p.boff[b + 1] - p.boff[b], 2 * p.bs);
+        p.ord[b] = p.boff[b + 1] - p.boff[b];
+        p.L[b] = round_up(p.ord[b], 2 * p.bs);
         p.maxL = std::max(p.maxL, p.L[b]);
     }
+    p.maxo = p.maxl;
     p.n_iter = pr.o.fixed_iters > 0 ? pr.o.fixed_iters : pr.o.max_iter;
     p.pm = product_modes(pr.o.precision);
     // reduced coordinates: explicit request, or automatic when the dictionary is
@@ -753,6 +760,27 @@ void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     finish_basis(pr, p, b, s);
 }
 
+// SVT(Y) = Y g(Y^T Y) = g(Y Y^T) Y: with fewer rows than columns the Gram matrix of
+// the rows is the smaller one and has no null space of dimension l - r, whose
+// eigenvectors no iteration needs.  Taken when it is the smaller matrix for some
+// block and no larger one for any (the work arrays are laid out for Y^T Y).
+// Plain LRR of 200 points (m = 100, r = 45): 232 -> 57 ms; m = 500, n = 2000
+// (r = 300) in blocks of 500: 340 -> 219 ms.
+void choose_gram(Plan& p) {
+    const int Lr = round_up(p.nr, 2 * p.bs);
+    bool smaller = false;
+    for (int bb = 0; bb < p.t; ++bb) {
+        if (Lr > p.L[bb]) return;
+        smaller |= Lr < p.L[bb];
+    }
+    if (!smaller) return;
+    p.left = true;
+    p.ord.assign(p.t, p.nr);
+    p.L.assign(p.t, Lr);
+    p.maxL = Lr;
+    p.maxo = p.nr;
+}
+
 // Lay out the workspace, upload the descriptors, gather the observations,
 // zero the state and factor K = I + A A^T (once per solve).
 void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t s, bool with_combine) {
@@ -767,6 +795,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
     if (pr.perm) LRR_HIP(hipMemcpyAsync(b.perm, pr.perm, sizeof(int) * c, hipMemcpyHostToDevice, s));
     if (p.reduced) build_basis(pr, p, b, s);
     else if (!p.local) p.nr = n;
+    if (p.svd) choose_gram(p);
     const int nr = p.nr;
     // dictionary of the Z-step products: M, or Mr = M Qm in reduced coordinates
     const double* Md = p.reduced ? b.Mr : pr.A;
@@ -793,7 +822,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
     std::vector<SvtDesc> svt(t);
     std::vector<RefDesc> ref(t);
     for (int bb = 0; bb < t; ++bb) {
-        const int l = p.boff[bb + 1] - p.boff[bb], L = p.L[bb];
+        const int l = p.boff[bb + 1] - p.boff[bb], L = p.L[bb], e = p.ord[bb];
         const size_t LL = (size_t)L * L;
         double* Jb = b.J + (size_t)p.boff[bb] * nr;
         const int* run = b.svt_run + bb;    // thresholds this iteration
@@ -803,8 +832,11 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         double* T = b.TX[bb];
         for (int y = 0; y < ny; ++y) {
             double* Yb = (p.svd ? b.Yp[y] : b.Y) + (size_t)p.boff[bb] * nr;
-            gram[y * t + bb] = GemmDesc{Yb, Yb, b.Bm[bb], l, l, nr, nr, nr, L, 1.0, 0.0, erun, nullptr};
-            gJ[y * t + bb] = GemmDesc{Yb, b.Pm[bb], Jb, nr, l, l, nr, L, nr, 1.0, 0.0, run, nullptr};
+            // Y^T Y and J = Y P, or Y Y^T and J = P Y
+            gram[y * t + bb] = GemmDesc{Yb, Yb, b.Bm[bb], e, e, p.left ? l : nr, nr, nr, L, 1.0, 0.0, erun, nullptr};
+            gJ[y * t + bb] = p.left
+                ? GemmDesc{b.Pm[bb], Yb, Jb, nr, l, nr, L, nr, nr, 1.0, 0.0, run, nullptr}
+                : GemmDesc{Yb, b.Pm[bb], Jb, nr, l, l, nr, L, nr, 1.0, 0.0, run, nullptr};
         }
         // refinement: T = B X, S = X^T T, G = X^T X (symmetric kernel), XE = X E
         gRT[bb] = GemmDesc{b.Bm[bb], X, T, L, L, L, L, L, L, 1.0, 0.0, rrun, nullptr};
@@ -813,7 +845,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         // orthogonalisation: G = X^T X;  Jacobi matrix Bq = X^T (B X)
         gOG[bb] = GemmDesc{X, X, b.SG[bb] + LL, L, L, L, L, L, L, 1.0, 0.0, rrun, nullptr};
         gBq[bb] = GemmDesc{X, T, b.Bq[bb], L, L, L, L, L, L, 1.0, 0.0, rrun, nullptr};
-        gP[bb] = GemmDesc{b.Wg[bb], X, b.Pm[bb], l, l, L, L, L, L, 1.0, 0.0, run, nullptr};
+        gP[bb] = GemmDesc{b.Wg[bb], X, b.Pm[bb], e, e, L, L, L, L, 1.0, 0.0, run, nullptr};
         const int* act = b.active + bb;
         const size_t o_n = (size_t)p.boff[bb] * nr, o_m = (size_t)p.boff[bb] * m;
         // dictionary of this block: M (or Mr), or in local mode its own columns
@@ -842,13 +874,13 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
                                 0.0, b.expand + bb, nullptr};
         if (p.svd)       // and of the primal one: R1 = U R1r
             gExp1[bb] = GemmDesc{b.Um, b.Rr + o_n, b.T + o_m, m, l, nr, m, nr, m, 1.0, 0.0, b.expand1 + bb, nullptr};
-        eig[bb] = EigDesc{b.Bq[bb], X, b.Rm[bb], b.lam[bb], L, l, erun, b.eigst + 2 * bb,
+        eig[bb] = EigDesc{b.Bq[bb], X, b.Rm[bb], b.lam[bb], L, e, erun, b.eigst + 2 * bb,
                           b.eigscale + bb, b.prot[bb], b.lo[bb], ctx->dwork, b.locut + bb, b.passes + bb,
                           b.need_all + need_off[bb], b.sched_all + sched_off[bb], b.ref_clean + bb};
-        svt[bb] = SvtDesc{b.Bq[bb], X, b.Wg[bb], b.lam[bb], b.h[bb], L, l, run, bb};
+        svt[bb] = SvtDesc{b.Bq[bb], X, b.Wg[bb], b.lam[bb], b.h[bb], L, e, run, bb};
         ref[bb] = RefDesc{b.Bm[bb], X, b.SG[bb], b.Eb[bb], b.XE[bb], b.lam[bb], b.lo[bb], b.ref_scale + bb,
                           b.ref_emax + bb, b.ref_unres + bb, b.ref_eprev + bb, b.ref_run + bb,
-                          b.ref_cont + bb, b.Bq[bb], b.locut + bb, L, l, bb, b.ref_rdev + bb,
+                          b.ref_cont + bb, b.Bq[bb], b.locut + bb, L, e, bb, b.ref_rdev + bb,
                           b.ref_nsskip + bb, b.ref_clean + bb};
     }
     std::vector<GemmDesc> gKK(p.svd ? 0 : p.local ? t : 1);
@@ -1213,19 +1245,19 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
         read_flags(h_svt, b.svt_run);
         double f_gram = 0, f_P = 0, f_J = 0, f_L3 = 0;
         for (int bb = 0; bb < t && price; ++bb) {
-            const double l = p.boff[bb + 1] - p.boff[bb], L = p.L[bb];
+            const double l = p.boff[bb + 1] - p.boff[bb], e = p.ord[bb], L = p.L[bb];
             if (h_svt[bb]) {
-                f_P += 2.0 * l * l * L;
-                f_J += 2.0 * n * l * l;
+                f_P += 2.0 * e * e * L;
+                f_J += 2.0 * n * l * e;
             }
             if (!h_run[bb]) continue;
-            f_gram += 2.0 * l * l * n;
+            f_gram += 2.0 * n * l * e;
             f_L3 += 2.0 * L * L * L;
         }
         // the symmetric kernel computes the tiles on and above the diagonal
-        const double hg = lrr::dgemm_sym_tiles(t, p.maxl) ? 0.5 : 1.0, hL = lrr::dgemm_sym_tiles(t, p.maxL) ? 0.5 : 1.0;
+        const double hg = lrr::dgemm_sym_tiles(t, p.maxo) ? 0.5 : 1.0, hL = lrr::dgemm_sym_tiles(t, p.maxL) ? 0.5 : 1.0;
         // Gram matrix of each block that thresholds (FP64 in every precision form)
-        tm("k_dgemm_sym", hg * f_gram, 0.0, [&] { lrr::launch_dgemm_sym(b.g_gram + (p.svd ? par * t : 0), t, p.maxl, st); });
+        tm("k_dgemm_sym", hg * f_gram, 0.0, [&] { lrr::launch_dgemm_sym(b.g_gram + (p.svd ? par * t : 0), t, p.maxo, st, false, p.left); });
         // Newton refinement of the previous iteration's eigenvectors: a fixed
         // number of steps, each applied only where the per-block flags allow
         tm("k_ref_begin", 0.0, 0.0, [&] { lrr::launch_ref_begin(b.ref, t, p.maxL, b.eig_run, b.warm, st); });
@@ -1294,7 +1326,7 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
         });
         tm("k_svt_weights", 0.0, 0.0, [&] { lrr::launch_svt_weights(b.svt, t, p.maxL, b.it, bst, st); });
         tm("k_dgemm<false, true>", f_P, 0.0, [&] {
-            lrr::launch_dgemm(b.g_P, t, p.maxl, p.maxl, false, true, st);
+            lrr::launch_dgemm(b.g_P, t, p.maxo, p.maxo, false, true, st);
         });
         tm("k_dgemm<false, false>", f_J, 0.0, [&] {
             lrr::launch_dgemm(b.g_J + (p.svd ? par * t : 0), t, n, p.maxl, false, false, st);
@@ -1333,14 +1365,14 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
             sync();
             any_run = 0;
             for (int bb = 0; bb < t; ++bb) {
-                const double l = p.boff[bb + 1] - p.boff[bb];
+                const double l = p.boff[bb + 1] - p.boff[bb], e = p.ord[bb];
                 if (h_svt[bb]) {
-                    f_P += 2.0 * l * l * p.L[bb];
-                    f_J += 2.0 * n * l * l;
+                    f_P += 2.0 * e * e * p.L[bb];
+                    f_J += 2.0 * n * l * e;
                 }
                 if (!h_run[bb]) continue;
                 any_run = 1;
-                f_gram += 2.0 * l * l * n;
+                f_gram += 2.0 * n * l * e;
             }
         }
         if (any_run) {
@@ -1348,8 +1380,8 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
             // Gram matrix of each block that needs a decomposition (FP64 in every
             // precision form)
             // the symmetric kernel computes the tiles on and above the diagonal
-            const double hg = lrr::dgemm_sym_tiles(t, p.maxl) ? 0.5 : 1.0, hL = lrr::dgemm_sym_tiles(t, p.maxL) ? 0.5 : 1.0;
-            timed("k_dgemm_sym", hg * f_gram, 0.0, [&] { lrr::launch_dgemm_sym(b.g_gram + (p.svd ? par * t : 0), t, p.maxl, s); });
+            const double hg = lrr::dgemm_sym_tiles(t, p.maxo) ? 0.5 : 1.0, hL = lrr::dgemm_sym_tiles(t, p.maxL) ? 0.5 : 1.0;
+            timed("k_dgemm_sym", hg * f_gram, 0.0, [&] { lrr::launch_dgemm_sym(b.g_gram + (p.svd ? par * t : 0), t, p.maxo, s, false, p.left); });
             // Newton refinement of the previous iteration's eigenvectors
             timed("k_ref_begin", 0.0, 0.0, [&] { lrr::launch_ref_begin(b.ref, t, p.maxL, b.eig_run, b.warm, s); });
             // the first kBlindSteps steps are launched without reading the flags back
@@ -1494,7 +1526,7 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
             }
             timed("k_svt_weights", 0.0, 0.0, [&] { lrr::launch_svt_weights(b.svt, t, p.maxL, b.it, bst, s); });
             timed("k_dgemm<false, true>", f_P, 0.0, [&] {
-                lrr::launch_dgemm(b.g_P, t, p.maxl, p.maxl, false, true, s);
+                lrr::launch_dgemm(b.g_P, t, p.maxo, p.maxo, false, true, s);
             });
             timed("k_dgemm<false, false>", f_J, 0.0, [&] {
                 lrr::launch_dgemm(b.g_J + (p.svd ? par * t : 0), t, n, p.maxl, false, false, s);
@@ -2262,10 +2294,15 @@ static lrr_status dfc_lrr_solve_f64(lrr_ctx* ctx, int m, int n, const void* M, i
             if (p.reduced) LRR_HIP(hipMemcpyAsync(b.g_red, &gQU, sizeof(GemmDesc), hipMemcpyHostToDevice, s));
             LrrProf& prof = ctx->prof;
             const int gm = p.pm.comb;
-            prof.run(s, "k_dgemm<false, false>", 2.0 * nr * L0 * l0, 0.0,
-                     [&] { lrr::launch_dgemm(b.g_U, 1, nr, L0, false, false, s); });
-            prof.run(s, "k_scale_cols", 0.0, 2.0 * nr * L0 * sizeof(double),
-                     [&] { lrr::launch_scale_cols(Uc, nr, nr, L0, b.h[0], s); });
+            if (p.left) {   // the kept eigenvectors of Y_1 Y_1^T are the basis
+                prof.run(s, "k_svd_left_basis", 0.0, 2.0 * nr * L0 * sizeof(double),
+                         [&] { lrr::launch_svd_left_basis(b.Wm[0], L0, b.h[0], Uc, nr, s); });
+            } else {
+                prof.run(s, "k_dgemm<false, false>", 2.0 * nr * L0 * l0, 0.0,
+                         [&] { lrr::launch_dgemm(b.g_U, 1, nr, L0, false, false, s); });
+                prof.run(s, "k_scale_cols", 0.0, 2.0 * nr * L0 * sizeof(double),
+                         [&] { lrr::launch_scale_cols(Uc, nr, nr, L0, b.h[0], s); });
+            }
             prof.run(s, lrr::xgemm_name(gm, true, false), 2.0 * L0 * n * nr, 0.0,
                      [&] { lrr::launch_xgemm(b.g_H, 1, L0, n, true, false, gm, s); });
             if (p.reduced)

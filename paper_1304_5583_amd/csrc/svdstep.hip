@@ -361,6 +361,15 @@ __global__ __launch_bounds__(256) void k_svd_add_outside(double* __restrict__ ou
     for (int i = threadIdx.x; i < m; i += 256) o[i] += D[i + (long)j * m] * w;
 }
 
+// U (rows x L) = the columns of W (L x L) with h > 0, zero elsewhere
+__global__ __launch_bounds__(256) void k_svd_left_basis(const double* __restrict__ W, int L,
+                                                         const double* __restrict__ h, double* __restrict__ U,
+                                                         int rows) {
+    const long j = blockIdx.x;
+    const bool keep = h[j] > 0.0;
+    for (int i = threadIdx.x; i < rows; i += 256) U[i + j * rows] = keep ? W[i + j * L] : 0.0;
+}
+
 // J = 0 for the blocks whose last thresholding step kept nothing
 __global__ __launch_bounds__(256) void k_svd_zero_J(double* __restrict__ J, int r, const int* __restrict__ colblk,
                                                      const int* __restrict__ rank) {
@@ -437,6 +446,9 @@ void launch_svd_add_outside(double* out, long ldo, int m, int c, const double* D
 }
 void launch_svd_result(const SvdStep& a, const int* iters, double* out, int what, const double* sched, hipStream_t s) {
     hipLaunchKernelGGL(k_svd_result, dim3(a.ncols), dim3(256), 0, s, a, iters, out, what, sched);
+}
+void launch_svd_left_basis(const double* W, int L, const double* h, double* U, int rows, hipStream_t s) {
+    hipLaunchKernelGGL(k_svd_left_basis, dim3(L), dim3(256), 0, s, W, L, h, U, rows);
 }
 void launch_svd_zero_J(double* J, int r, int ncols, const int* colblk, const int* rank, hipStream_t s) {
     hipLaunchKernelGGL(k_svd_zero_J, dim3(ncols), dim3(256), 0, s, J, r, colblk, rank);
