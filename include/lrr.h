@@ -113,8 +113,11 @@ typedef enum {
  * sigma^2 <= 1e-14 sigma_max^2 are dropped. */
 typedef enum {
     LRR_COORDS_AUTO = 0,     /* reduced when n >= 2m (the basis costs an m x m      */
-                             /* eigensolve), never for a recorded forward or an     */
-                             /* explicitly literal solve form                       */
+                             /* eigensolve), and in the FP64 form with solve_form   */
+                             /* AUTO when m < n < 2m and the basis holds the        */
+                             /* dictionary to rounding (1e-13 of its largest        */
+                             /* column, 1e-5 with FP32 buffers); never for a        */
+                             /* recorded forward or an explicitly literal solve form*/
     LRR_COORDS_FULL = 1,
     LRR_COORDS_REDUCED = 2
 } lrr_coords;

@@ -188,6 +188,9 @@ struct Plan {
     // reduced coordinates with the dictionary diagonalised (svdstep.hip); decided
     // when the basis is built, on the accuracy it reached
     bool svd = false;
+    // reduced coordinates taken by the rule for n < 2m: given up for full ones where
+    // they would drop more of the dictionary than its own rounding (build_basis)
+    bool ext = false, ext_ok = false;
     bool extra = false;          // the last coordinate holds what lies outside range(U) (finish_basis)
     int nrb = 0;                 // rows the layout reserves (n, or min(m, n) + 1)
     int nr = 0;                  // rows in use (n, or the numerical rank of M)
@@ -213,7 +216,7 @@ struct Buffers {
     unsigned long long* r2nrm;
     // singular coordinates: left basis (m x r), U^T A (r x n), diagonal, per-column factors, and
     // the two buffers of each alternating array (aliases of the general form's arrays)
-    double *Um, *Ut, *Cr, *dsig, *dinv, *fcol[2], *Yp[2], *Y2p[2], *qp[2], *Rr;
+    double *Um, *Ut, *Ares, *Cr, *dsig, *dinv, *fcol[2], *Yp[2], *Y2p[2], *qp[2], *Rr;
     unsigned long long* stat;
     int* expand1;
     GemmDesc *g_sv, *g_exp1;
@@ -410,6 +413,7 @@ size_t layout(const Plan& p, char* base, Buffers& b, int with_combine, bool need
         b.g_exp = a.take<GemmDesc>(t);
         b.Um = a.take<double>(m * n);
         b.Ut = a.take<double>(m * n);
+        b.Ares = p.ext ? a.take<double>(m * nfull) : nullptr;
         b.Cr = a.take<double>(n * nfull);
         b.dsig = a.take<double>(n);
         b.dinv = a.take<double>(n);
@@ -429,7 +433,7 @@ size_t layout(const Plan& p, char* base, Buffers& b, int with_combine, bool need
         b.r2nrm = nullptr;
         b.eq = nullptr;
         b.g_red = b.g_exp = nullptr;
-        b.Um = b.Ut = b.Cr = b.dsig = b.dinv = b.Rr = nullptr;
+        b.Um = b.Ut = b.Ares = b.Cr = b.dsig = b.dinv = b.Rr = nullptr;
         b.stat = nullptr;
         b.expand1 = nullptr;
         b.g_sv = b.g_exp1 = nullptr;
@@ -528,6 +532,7 @@ struct Problem {
     double lam;
     lrr_opts o;
     int local = 0;                // 1: block b uses its own observations as dictionary
+    int from32 = 0;               // 1: A and X were widened from FP32 buffers
 };
 
 struct Result {
@@ -581,13 +586,20 @@ Plan make_plan(const Problem& pr) {
     p.reduced = coords == LRR_COORDS_REDUCED ||
                 (coords == LRR_COORDS_AUTO && pr.n >= 2 * pr.m && !pr.o.save_for_backward &&
                  pr.o.solve_form != LRR_SOLVE_LITERAL);
-    if (pr.o.save_for_backward) p.reduced = false;
+    // a dictionary that is less than twice as wide as tall pays for its basis too:
+    // the iteration then has no dictionary product (m = 2016, n = 2432, 16 blocks of
+    // 100..200: 823 ms in full coordinates, 510 in reduced ones; m = 407, n = 456 in
+    // 4 blocks: 158 against 164); with n <= m AUTO stands for the literal form
+    p.ext = !p.reduced && pr.n > pr.m && coords == LRR_COORDS_AUTO && !pr.o.save_for_backward &&
+            pr.o.solve_form == LRR_SOLVE_AUTO && pr.o.precision == LRR_FP64 && !pr.local;
+    p.reduced |= p.ext;
+    if (pr.o.save_for_backward) p.reduced = p.ext = false;
     p.nrb = p.reduced ? std::min(pr.m, pr.n) + 1 : pr.n;   // + 1: Plan::extra
     p.local = pr.local != 0;
     if (p.local) {
         // rows of a block's iterates index its own points: l_b <= maxl rows; rows
         // beyond l_b meet zero dictionary columns and stay exactly zero
-        p.reduced = false;
+        p.reduced = p.ext = false;
         p.nrb = p.maxl;
     }
     // literal Z-step: on request, or automatically when the dictionary is at
@@ -600,8 +612,8 @@ Plan make_plan(const Problem& pr) {
     }
     p.ks = p.literal ? pr.n : pr.m;
     p.nr = p.nrb;
-    p.bq = pr.m > 512 ? 32 : 16;
-    p.Lm = round_up(pr.m, 2 * p.bq);
+    p.bq = 16;   // 32 above order 512 measured slower (order 2016: 180 against 110 ms for the basis)
+    p.Lm = round_up(std::min(pr.m, pr.n), 2 * p.bq);
     return p;
 }
 
@@ -628,11 +640,16 @@ constexpr double kRankCut = 1e-14;
 // in the dense form (Mr = A Qm).  kSvdOut: what U U^T may leave of the
 // observations against their largest column before it gets its own coordinate
 // (3e-15 and less where nothing of them lies outside).
-constexpr double kSvdOff = 1e-13, kSvdOut = 1e-13;
+// kSvdOrth: deviation of Qm^T Qm from the identity.  kTail32: what may be dropped
+// of a dictionary that came in FP32 (relative to its largest column): no solution
+// uses directions that small (m = 2016, n = 2432, image-like data that leaves
+// 2e-6: Z moves by 1e-7 to 3e-7, as it does between two orders of summation).
+constexpr double kSvdOff = 1e-13, kSvdOut = 1e-13, kSvdOrth = 1e-13, kTail32 = 1e-5;
 
 // Bases of range(A^T) and range(A) from the eigen-decomposition A A^T = W
 // diag(lam) W^T (kept indices, by decreasing eigenvalue, in b.idxq):
-//   C = W_k^T A, Qm = its normalised rows after a Newton-Schulz step (they lie in
+//   C = W_k^T A (with n < m, from A^T A = W diag(lam) W^T: C = (A W_k)^T A), Qm =
+//   its normalised rows, orthonormalised by Newton-Schulz steps (they lie in
 //   range(A^T) to rounding whatever the error of W), Mr = A Qm, whose columns are
 //   orthogonal up to the error of W; Jacobi sweeps on Mr^T Mr, every entry of
 //   which is accurate relative to its two columns, to the relative tolerance
@@ -648,11 +665,33 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
         LRR_HIP(hipMemcpyAsync(b.g_sv + slot, &g, sizeof(g), hipMemcpyHostToDevice, s));
         lrr::launch_dgemm(b.g_sv + slot, 1, g.M, g.N, ta, tb, s);
     };
-    lrr::launch_gather_cols(b.Wq, p.Lm, b.Um, m, m, r, b.idxq, s);
+    double st[4] = {0.0, 0.0, 0.0, 0.0};
+    auto read_stat = [&](int count) {
+        LRR_HIP(hipMemcpyAsync(st, b.stat, sizeof(double) * count, hipMemcpyDeviceToHost, s));
+        LRR_HIP(hipStreamSynchronize(s));
+    };
+    if (n < m) {
+        lrr::launch_gather_cols(b.Wq, p.Lm, b.Qtmp, n, n, r, b.idxq, s);
+        gemm(0, GemmDesc{pr.A, b.Qtmp, b.Um, m, r, n, (int)pr.lda, n, m, 1.0, 0.0, nullptr, nullptr}, false, false);
+    } else {
+        lrr::launch_gather_cols(b.Wq, p.Lm, b.Um, m, m, r, b.idxq, s);
+    }
     gemm(0, GemmDesc{b.Um, pr.A, b.Cr, r, n, m, m, (int)pr.lda, r, 1.0, 0.0, nullptr, nullptr}, true, false);
     gemm(1, GemmDesc{b.Cr, b.Cr, b.Gq, r, r, n, r, r, r, 1.0, 0.0, nullptr, nullptr}, false, true);
     lrr::launch_rows_factor(b.Gq, b.Tq, r, s);
     gemm(2, GemmDesc{b.Cr, b.Tq, b.Qm, n, r, r, r, r, n, 1.0, 0.0, nullptr, nullptr}, true, false);
+    // one step suffices unless the rows of C were far from orthogonal
+    for (int ns = 0; ns < 5; ++ns) {
+        gemm(3, GemmDesc{b.Qm, b.Qm, b.Gq, r, r, n, n, n, r, 1.0, 0.0, nullptr, nullptr}, true, false);
+        LRR_HIP(hipMemsetAsync(b.stat, 0, 4 * sizeof(unsigned long long), s));
+        lrr::launch_take_diag(b.Gq, r, r, b.dsig, b.dinv, b.stat, s);
+        read_stat(2);
+        if (st[0] <= kSvdOrth && std::fabs(st[1] - 1.0) <= kSvdOrth) break;
+        lrr::launch_ns_factor(b.Gq, b.Tq, r, s);
+        gemm(4, GemmDesc{b.Qm, b.Tq, b.Qtmp, n, r, r, n, r, n, 1.0, 0.0, nullptr, nullptr}, false, false);
+        std::swap(b.Qm, b.Qtmp);
+    }
+    const bool orth = st[0] <= kSvdOrth && std::fabs(st[1] - 1.0) <= kSvdOrth;
     gemm(3, GemmDesc{pr.A, b.Qm, b.Mr, m, r, n, (int)pr.lda, n, m, 1.0, 0.0, nullptr, nullptr}, false, false);
     std::vector<int> lo(Lr);
     for (int i = 0; i < Lr; ++i) lo[i] = i >= r ? 1 : 0;
@@ -661,11 +700,10 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     LRR_HIP(hipMemcpyAsync(b.eq, &ed, sizeof(EigDesc), hipMemcpyHostToDevice, s));
     LRR_HIP(hipMemsetAsync(b.scaleq, 0, sizeof(double), s));
     LRR_HIP(hipMemsetAsync(b.stq, 0, 2 * sizeof(int), s));
-    double st[4] = {0.0, 0.0, 0.0, 0.0};
     bool diagonal = false;
     // two sweeps (close singular values rotate by large angles, which takes two);
     // once more if the measured off-diagonal part is still too large
-    for (int attempt = 0; attempt < 2 && !diagonal; ++attempt) {
+    for (int attempt = 0; attempt < 2 && orth && !diagonal; ++attempt) {
         LRR_HIP(hipMemsetAsync(b.Gb, 0, sizeof(double) * (size_t)Lr * Lr, s));
         gemm(4, GemmDesc{b.Mr, b.Mr, b.Gb, r, r, m, m, m, Lr, 1.0, 0.0, nullptr, nullptr}, true, false);
         lrr::launch_set_identity(b.Wq, Lr, s);
@@ -681,8 +719,7 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
         gemm(9, GemmDesc{b.Um, b.Mr, b.Gq, r, r, m, m, m, r, 1.0, 0.0, nullptr, nullptr}, true, false);
         LRR_HIP(hipMemsetAsync(b.stat, 0, 4 * sizeof(unsigned long long), s));
         lrr::launch_take_diag(b.Gq, r, r, b.dsig, b.dinv, b.stat, s);
-        LRR_HIP(hipMemcpyAsync(st, b.stat, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-        LRR_HIP(hipStreamSynchronize(s));
+        read_stat(2);
         diagonal = st[1] > 0.0 && st[0] <= kSvdOff * st[1];
     }
     if (!diagonal) return;
@@ -693,9 +730,28 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     gemm(0, GemmDesc{b.Um, b.T, b.X, r, c, m, m, m, r, 1.0, 0.0, nullptr, nullptr}, true, false);    // U^T X
     gemm(1, GemmDesc{b.Um, b.X, b.T, m, c, r, m, r, m, -1.0, 1.0, nullptr, nullptr}, false, false);  // X - U U^T X
     lrr::launch_colnorm_max(b.T, m, m, c, b.stat + 2, s);
-    LRR_HIP(hipMemcpyAsync(st, b.stat, sizeof(st), hipMemcpyDeviceToHost, s));
-    LRR_HIP(hipStreamSynchronize(s));
+    read_stat(4);
     p.svd = true;
+    if (p.ext) {
+        // what the bases leave of the dictionary itself (for DFC-LRR the observations)
+        double left = st[2], all = st[3];
+        if (!pr.perm) {
+            LRR_HIP(hipMemsetAsync(b.stat, 0, 2 * sizeof(unsigned long long), s));
+            lrr::launch_copy_cols(pr.A, pr.lda, b.Ares, m, m, n, s);
+            lrr::launch_colnorm_max(b.Ares, m, m, n, b.stat + 1, s);
+            gemm(0, GemmDesc{b.Um, b.Ares, b.Cr, r, n, m, m, m, r, 1.0, 0.0, nullptr, nullptr}, true, false);
+            gemm(1, GemmDesc{b.Um, b.Cr, b.Ares, m, n, r, m, r, m, -1.0, 1.0, nullptr, nullptr}, false, false);
+            lrr::launch_colnorm_max(b.Ares, m, m, n, b.stat, s);
+            const double out = st[2], obs = st[3];
+            read_stat(2);
+            left = st[0];
+            all = st[1];
+            st[2] = out;
+            st[3] = obs;
+        }
+        p.ext_ok = left <= (pr.from32 ? kTail32 : kSvdOut) * all;
+        if (!p.ext_ok) return;
+    }
     if (st[2] <= kSvdOut * st[3]) return;
     // Observations partly outside range(U) (lrr_solve with any X, or directions of
     // the data below the rank cut): only column operations act on that part, so it
@@ -717,19 +773,20 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
 }
 
 void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
-    const int m = p.m, n = p.n, Lm = p.Lm, bq = p.bq;
-    // G = M M^T (padded to Lm), eigen-decomposition by block Jacobi from the identity
+    const int Lm = p.Lm, bq = p.bq, side = std::min(p.m, p.n);
+    const bool tall = p.n < p.m;
+    // the smaller of M M^T and M^T M (padded to Lm), eigen-decomposition by block Jacobi from the identity
     LRR_HIP(hipMemsetAsync(b.Gb, 0, sizeof(double) * (size_t)Lm * Lm, s));
-    GemmDesc gG{pr.A, pr.A, b.Gb, m, m, n, (int)pr.lda, (int)pr.lda, Lm, 1.0, 0.0, nullptr, nullptr};
+    GemmDesc gG{pr.A, pr.A, b.Gb, side, side, tall ? p.m : p.n, (int)pr.lda, (int)pr.lda, Lm, 1.0, 0.0, nullptr, nullptr};
     std::vector<int> lo(Lm);
-    for (int i = 0; i < Lm; ++i) lo[i] = i >= m ? 1 : 0;
+    for (int i = 0; i < Lm; ++i) lo[i] = i >= side ? 1 : 0;
     const int one = 1;
     LRR_HIP(hipMemcpyAsync(b.g_red, &gG, sizeof(GemmDesc), hipMemcpyHostToDevice, s));
     LRR_HIP(hipMemcpyAsync(b.loq, lo.data(), sizeof(int) * Lm, hipMemcpyHostToDevice, s));
     LRR_HIP(hipMemcpyAsync(b.runq, &one, sizeof(int), hipMemcpyHostToDevice, s));
-    EigDesc ed{b.Gb, b.Wq, b.Rq, b.lamq, Lm, m, b.runq, b.stq, b.scaleq, b.protq, b.loq, nullptr};
+    EigDesc ed{b.Gb, b.Wq, b.Rq, b.lamq, Lm, side, b.runq, b.stq, b.scaleq, b.protq, b.loq, nullptr};
     LRR_HIP(hipMemcpyAsync(b.eq, &ed, sizeof(EigDesc), hipMemcpyHostToDevice, s));
-    lrr::launch_dgemm(b.g_red, 1, m, m, false, true, s);
+    lrr::launch_dgemm(b.g_red, 1, side, side, tall, !tall, s);
     lrr::launch_set_identity(b.Wq, Lm, s);
     lrr::launch_jacobi_init(b.eq, 1, s);
     int* any = b.idxq;     // scratch flag until the index list is written
@@ -747,12 +804,11 @@ void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     LRR_HIP(hipMemcpyAsync(lam.data(), b.lamq, sizeof(double) * Lm, hipMemcpyDeviceToHost, s));
     LRR_HIP(hipStreamSynchronize(s));
     double lmax = 0.0;
-    for (int i = 0; i < m; ++i) lmax = std::max(lmax, lam[i]);
+    for (int i = 0; i < side; ++i) lmax = std::max(lmax, lam[i]);
     std::vector<int> idx;
-    for (int i = 0; i < m; ++i)
+    for (int i = 0; i < side; ++i)
         if (lam[i] > kRankCut * lmax) idx.push_back(i);
     std::stable_sort(idx.begin(), idx.end(), [&](int x, int y) { return lam[x] > lam[y]; });
-    if ((int)idx.size() > std::min(m, n)) idx.resize(std::min(m, n));   // rank(M) <= min(m, n)
     if (idx.empty()) idx.push_back(0);     // M = 0: a single zero column (scaled by 0 below)
     const int r = (int)idx.size();
     p.nr = r;
@@ -786,14 +842,23 @@ void choose_gram(Plan& p) {
 void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t s, bool with_combine) {
     const int m = p.m, n = p.n, c = p.ncols, t = p.t;
     const lrr_opts& o = pr.o;
-    const size_t need = layout(p, nullptr, b, with_combine, true);
-    ensure_ws(ctx, need);
     if (!ctx->dwork) LRR_HIP(hipMalloc((void**)&ctx->dwork, lrr::kWorkBytes));
     LRR_HIP(hipMemsetAsync(ctx->dwork, 0, lrr::kWorkBytes, s));
-    layout(p, static_cast<char*>(ctx->ws), b, with_combine, true);
     ensure_pinned(ctx, sizeof(int) * (4 * (size_t)t + 16) + sizeof(double) * 2 * t);
-    if (pr.perm) LRR_HIP(hipMemcpyAsync(b.perm, pr.perm, sizeof(int) * c, hipMemcpyHostToDevice, s));
+    auto lay_out = [&] {
+        ensure_ws(ctx, layout(p, nullptr, b, with_combine, true));
+        layout(p, static_cast<char*>(ctx->ws), b, with_combine, true);
+        if (pr.perm) LRR_HIP(hipMemcpyAsync(b.perm, pr.perm, sizeof(int) * c, hipMemcpyHostToDevice, s));
+    };
+    lay_out();
     if (p.reduced) build_basis(pr, p, b, s);
+    if (p.ext && !p.ext_ok) {
+        Problem full = pr;
+        full.o.coords = LRR_COORDS_FULL;
+        p = make_plan(full);
+        lay_out();
+    }
+    if (p.reduced) {}
     else if (!p.local) p.nr = n;
     if (p.svd) choose_gram(p);
     const int nr = p.nr;
@@ -2171,12 +2236,17 @@ lrr_status lrr_workspace_bytes(int m, int n, int t, const int* offsets, const lr
     Plan p = make_plan(pr);
     Buffers b{};
     *bytes = layout(p, nullptr, b, 1, true);
+    if (p.ext) {   // which of the two it runs in depends on the data
+        pr.o.coords = LRR_COORDS_FULL;
+        p = make_plan(pr);
+        *bytes = std::max(*bytes, layout(p, nullptr, b, 1, true));
+    }
     return LRR_OK;
 }
 
 static lrr_status lrr_solve_f64(lrr_ctx* ctx, int m, int n, int l, const void* A, int lda, const void* X, int ldx,
                      double lambda, const lrr_opts* opts, void* Z, int ldz, void* E, int lde,
-                     lrr_info* info, void* stream) {
+                     lrr_info* info, void* stream, int from32 = 0) {
     if (!ctx) return fail(nullptr, LRR_EINVAL, "ctx must not be NULL");
     if (m <= 0 || n <= 0 || l <= 0) return fail(ctx, LRR_EINVAL, "dimensions must be positive");
     if (!A || !X || !Z) return fail(ctx, LRR_EINVAL, "A, X and Z must not be NULL");
@@ -2198,7 +2268,7 @@ static lrr_status lrr_solve_f64(lrr_ctx* ctx, int m, int n, int l, const void* A
         int offs[2] = {0, l};
         apply_tune(ctx, o, m, n, 1, l);
         Problem pr{m, n, l, 1, static_cast<const double*>(A), lda, static_cast<const double*>(X), ldx,
-                   nullptr, offs, lambda, o};
+                   nullptr, offs, lambda, o, 0, from32};
         Plan p = make_plan(pr);
         Buffers b{};
         Result r = run_alm(ctx, pr, p, b, s, false);
@@ -2234,7 +2304,7 @@ static lrr_status lrr_solve_f64(lrr_ctx* ctx, int m, int n, int l, const void* A
 
 static lrr_status dfc_lrr_solve_f64(lrr_ctx* ctx, int m, int n, const void* M, int ldm, double lambda, int t,
                          const int* perm, const int* offsets, const lrr_opts* opts, void* Z, int ldz,
-                         void* S, int lds, lrr_info* info, void* stream) {
+                         void* S, int lds, lrr_info* info, void* stream, int from32 = 0) {
     if (!ctx) return fail(nullptr, LRR_EINVAL, "ctx must not be NULL");
     if (m <= 0 || n <= 0) return fail(ctx, LRR_EINVAL, "dimensions must be positive");
     if (!M || !Z) return fail(ctx, LRR_EINVAL, "M and Z must not be NULL");
@@ -2258,7 +2328,7 @@ static lrr_status dfc_lrr_solve_f64(lrr_ctx* ctx, int m, int n, const void* M, i
         int maxl = 0;
         for (int b = 0; b < t; ++b) maxl = std::max(maxl, offsets[b + 1] - offsets[b]);
         apply_tune(ctx, o, m, n, t, maxl);
-        Problem pr{m, n, n, t, static_cast<const double*>(M), ldm, nullptr, 0, perm, offsets, lambda, o};
+        Problem pr{m, n, n, t, static_cast<const double*>(M), ldm, nullptr, 0, perm, offsets, lambda, o, 0, from32};
         Plan p = make_plan(pr);
         Buffers b{};
         IterHooks hooks;
@@ -2474,7 +2544,7 @@ lrr_status lrr_solve(lrr_ctx* ctx, int m, int n, int l, const void* A, int lda, 
         lrr::launch_widen_cols(static_cast<const float*>(A), lda, A64, m, m, n, s);
         lrr::launch_widen_cols(static_cast<const float*>(X), ldx, X64, m, m, l, s);
         const lrr_status st = lrr_solve_f64(ctx, m, n, l, A64, m, X64, m, lambda, &o, Z64, n, E ? E64 : nullptr, m,
-                                            info, stream);
+                                            info, stream, 1);
         if (st != LRR_OK && st != LRR_NOT_CONVERGED) return st;
         lrr::launch_narrow_cols(Z64, n, static_cast<float*>(Z), ldz, n, l, s);
         if (E) lrr::launch_narrow_cols(E64, m, static_cast<float*>(E), lde, m, l, s);
@@ -2517,7 +2587,7 @@ lrr_status dfc_lrr_solve(lrr_ctx* ctx, int m, int n, const void* M, int ldm, dou
     return dfc_io32(ctx, m, n, M, ldm, Z, ldz, S, lds, opts, stream,
                     [&](const double* M64, const lrr_opts* o, double* Z64, double* S64) {
                         return dfc_lrr_solve_f64(ctx, m, n, M64, m, lambda, t, perm, offsets, o, Z64, n, S64, m,
-                                                 info, stream);
+                                                 info, stream, 1);
                     });
 }
 

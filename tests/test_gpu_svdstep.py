@@ -119,3 +119,26 @@ def test_wide_singular_spread_vs_full_coordinates():
         Zt, St, info = B.dfc_lrr_solve(B.to_device_colmajor(M), 0.5, perm, offs, opts=o)
         out.append((B.from_device_colmajor(Zt), B.from_device_colmajor(St)))
     assert rel(out[1][0], out[0][0]) <= 1e-6 and rel(out[1][1], out[0][1]) <= 1e-6
+
+
+@pytest.mark.parametrize("tail,reduced", [(0.0, True), (1e-9, False)])
+def test_auto_keeps_full_coordinates_where_reduced_ones_drop_data(tail, reduced):
+    """m < n < 2m: AUTO gives the reduced form's result bit for bit where the basis
+    holds the data to rounding, the full form's where directions of 1e-9 of the
+    data would be dropped."""
+    from paper_1304_5583_amd import binding as B
+    need_gpu()
+    rng = np.random.default_rng(21)
+    m, n = 60, 90
+    M = rng.standard_normal((m, 20)) @ rng.standard_normal((20, n))
+    M /= np.linalg.norm(M, axis=0)
+    M += tail * rng.standard_normal((m, n))
+    perm, offs = rng.permutation(n).astype(np.int32), np.array([0, 30, 60, 90], dtype=np.int32)
+    out = {}
+    for coords in (B.LRR_COORDS_AUTO, B.LRR_COORDS_FULL, B.LRR_COORDS_REDUCED):
+        Zt, St, _ = B.dfc_lrr_solve(B.to_device_colmajor(M), 0.3, perm, offs, opts=B.lrr_opts_default(coords=coords))
+        out[coords] = (B.from_device_colmajor(Zt), B.from_device_colmajor(St))
+    same = B.LRR_COORDS_REDUCED if reduced else B.LRR_COORDS_FULL
+    assert np.array_equal(out[B.LRR_COORDS_AUTO][0], out[same][0])
+    assert np.array_equal(out[B.LRR_COORDS_AUTO][1], out[same][1])
+    assert rel(out[B.LRR_COORDS_REDUCED][0], out[B.LRR_COORDS_FULL][0]) <= 1e-6
