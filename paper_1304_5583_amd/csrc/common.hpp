@@ -164,6 +164,17 @@ struct SvdStep {
     double lam;
 };
 
+// Thresholding step of one block of small order (smalleig.hip).
+struct SmallEig {
+    const double* G;    // Gram matrix, order e, ld L
+    double* X;          // eigenvectors, kept from one iteration to the next
+    double* P;          // X diag(g) X^T
+    double *lam, *h;    // L eigenvalues; 1 / sigma on the kept ones, 0 elsewhere
+    int L, e, block;
+    const int* run;
+    int* warm;          // X holds the previous iteration's eigenvectors
+};
+
 // Thresholding weights of one block after its Gram eigensolve.
 struct SvtDesc {
     const double* B;    // L x L, diagonal = eigenvalues of the Gram matrix

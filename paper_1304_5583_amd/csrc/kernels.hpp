@@ -128,6 +128,13 @@ void launch_set_identity(double* W, int L, hipStream_t s);
 void launch_scatter_block_diag(const double* J, long ldj, int ncols, const int* colblk, const int* boff,
                                const int* perm, double* out, long ldo, hipStream_t s);
 
+// smalleig.hip: orders up to kSmallEig, one workgroup per matrix
+constexpr int kSmallEig = 96;
+void small_eig_prepare(void);   // once per device use, before a stream capture
+void launch_small_svt(const SmallEig* d, int count, int maxe, BlockState bs, const DevIter* it, int max_sweeps,
+                      hipStream_t s);
+void launch_small_syev(const double* A, double* W, double* lam, int e, int L, int max_sweeps, hipStream_t s);
+
 // svdstep.hip: the iteration in singular coordinates
 void launch_rows_factor(const double* G, double* T, int r, hipStream_t s);
 // d = diag(A), dinv = 1 / (1 + d^2); stat[0], stat[1] = largest off-diagonal and diagonal magnitude
@@ -144,6 +151,10 @@ void launch_svd_resid(const SvdStep& a, const int* boff, int t, int maxl, const 
                       const DevIter* it, const double* sched, hipStream_t s);
 void launch_svd_colmax(const double* A, int rows, long ld, const int* boff, int t, int maxl, const int* expand,
                        unsigned long long* out, const double* D, const double* R, int r, hipStream_t s);
+// the expansions of a small problem, one launch each (which = 1: U R1, 2: Qm R2)
+void launch_svd_expand(const SvdStep& a, int which, const double* basis, int rows, const double* D, const int* boff,
+                       int t, int maxl, const BlockState& bs, const unsigned long long* x2max, const int* expand1,
+                       double tol, double sqrt_n, int n_iter, const DevIter* it, const double* sched, hipStream_t s);
 void launch_svd_outside(const double* T, int m, int c, double* D, double* len, hipStream_t s);
 void launch_svd_set_row(double* X, int row, int ld, int c, const double* v, hipStream_t s);
 void launch_svd_add_outside(double* out, long ldo, int m, int c, const double* D, const double* R, int r,

@@ -180,6 +180,9 @@ struct Plan {
     // singular coordinates: the thresholding step takes the eigen-decomposition of
     // Y Y^T (r x r) instead of Y^T Y (l x l)
     bool left = false;
+    // singular coordinates, Gram orders up to kSmallEig: a block's eigensolve is one
+    // workgroup's (smalleig.hip), and no decision of an iteration is the host's
+    bool small = false;
     int n_iter = 0;
     ProductModes pm;             // arithmetic of each large product
     // coordinates of the n-row iterates (Z, J, Y2 and their temporaries): n rows,
@@ -242,6 +245,7 @@ struct Buffers {
     GemmDesc *g_gram, *g_refT, *g_refSG, *g_refXE, *g_orthG, *g_Bq, *g_P, *g_J, *g_MQ, *g_MQa, *g_KV, *g_MtV, *g_U, *g_H,
         *g_Z, *g_spd, *g_KK, *g_F1T, *g_F2Q, *g_AZ, *g_F1;
     RefDesc* ref;
+    lrr::SmallEig* sme;
     EigDesc* eig;
     SvtDesc* svt;
     // combine
@@ -420,6 +424,7 @@ size_t layout(const Plan& p, char* base, Buffers& b, int with_combine, bool need
         for (double*& x : b.fcol) x = a.take<double>(2 * c);
         b.stat = a.take<unsigned long long>(4);
         b.expand1 = a.take<int>(t);
+        b.sme = a.take<lrr::SmallEig>(t);
         b.g_sv = a.take<GemmDesc>(10);
         b.g_exp1 = a.take<GemmDesc>(t);
         b.Yp[0] = b.Y; b.Yp[1] = b.Z;
@@ -825,6 +830,7 @@ void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
 void choose_gram(Plan& p) {
     const int Lr = round_up(p.nr, 2 * p.bs);
     bool smaller = false;
+    p.small = p.maxo <= lrr::kSmallEig;
     for (int bb = 0; bb < p.t; ++bb) {
         if (Lr > p.L[bb]) return;
         smaller |= Lr < p.L[bb];
@@ -835,6 +841,7 @@ void choose_gram(Plan& p) {
     p.L.assign(p.t, Lr);
     p.maxL = Lr;
     p.maxo = p.nr;
+    p.small = p.maxo <= lrr::kSmallEig;
 }
 
 // Lay out the workspace, upload the descriptors, gather the observations,
@@ -878,6 +885,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
     std::vector<GemmDesc> gram(ny * t), gRT(t), gRSG(t), gRXE(t), gOG(t), gBq(t), gP(t), gJ(ny * t), gExp1(t);
     std::vector<GemmDesc> gMQ(t), gMQa(t), gKV(t), gMtV(t), gExp(t), gF1T(t), gF2Q(t), gAZ(t);
     std::vector<EigDesc> eig(t);
+    std::vector<lrr::SmallEig> sme(t);
     std::vector<size_t> need_off(t + 1, 0), sched_off(t + 1, 0);
     for (int bb = 0; bb < t; ++bb) {
         const size_t nb = p.L[bb] / p.bs;
@@ -891,7 +899,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         const size_t LL = (size_t)L * L;
         double* Jb = b.J + (size_t)p.boff[bb] * nr;
         const int* run = b.svt_run + bb;    // thresholds this iteration
-        const int* erun = b.eig_run + bb;   // needs an eigen-decomposition this iteration
+        const int* erun = p.small ? run : b.eig_run + bb;   // needs an eigen-decomposition this iteration
         const int* rrun = b.ref_run + bb;
         double* X = b.Wm[bb];
         double* T = b.TX[bb];
@@ -942,6 +950,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         eig[bb] = EigDesc{b.Bq[bb], X, b.Rm[bb], b.lam[bb], L, e, erun, b.eigst + 2 * bb,
                           b.eigscale + bb, b.prot[bb], b.lo[bb], ctx->dwork, b.locut + bb, b.passes + bb,
                           b.need_all + need_off[bb], b.sched_all + sched_off[bb], b.ref_clean + bb};
+        sme[bb] = lrr::SmallEig{b.Bm[bb], X, b.Pm[bb], b.lam[bb], b.h[bb], L, e, bb, run, b.warm + bb};
         svt[bb] = SvtDesc{b.Bq[bb], X, b.Wg[bb], b.lam[bb], b.h[bb], L, e, run, bb};
         ref[bb] = RefDesc{b.Bm[bb], X, b.SG[bb], b.Eb[bb], b.XE[bb], b.lam[bb], b.lo[bb], b.ref_scale + bb,
                           b.ref_emax + bb, b.ref_unres + bb, b.ref_eprev + bb, b.ref_run + bb,
@@ -1003,6 +1012,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         LRR_HIP(hipStreamSynchronize(s));   // the host table goes out of scope
     }
     up(b.svt, svt.data(), sizeof(SvtDesc) * t);
+    if (p.small) up(b.sme, sme.data(), sizeof(lrr::SmallEig) * t);
 
     // ---- setup: observations, state, factorisation (once per solve) -------
     if (p.svd) {}   // U^T X is in place
@@ -1157,7 +1167,10 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
     const bool device_loop = o.use_graph >= 2;
     // device queries of the launch shapes, made before any stream capture
     (void)lrr::gemm_grid();
-    if (device_loop) (void)lrr::jacobi_solve_grid(p.bs);
+    if (device_loop && !p.small) (void)lrr::jacobi_solve_grid(p.bs);
+    if (p.small) lrr::small_eig_prepare();
+    // both bases within 2 MB: formed in one launch per residual instead of three
+    const bool small_expand = p.svd && (size_t)m * n <= 65536 && (size_t)nfull * n <= 262144;
     const SvdStep sv[2] = {svd_step(p, b, 0, pr.lam), svd_step(p, b, 1, pr.lam)};
     auto zstep = [&](hipStream_t st, bool anchor, int par, auto&& tm, double cact) {
         if (p.svd) {
@@ -1170,6 +1183,21 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
                 lrr::launch_svd_decide(b.boff, t, bst, b.r2nrm, b.expand1, b.expand, o.tol, rm, rn, p.n_iter, b.it,
                                        st);
             });
+            if (small_expand) {
+                const double* out = p.extra ? b.V : nullptr;
+                tm("k_svd_expand", 0.0, 0.0, [&] {
+                    lrr::launch_svd_expand(sv[par], 1, b.Um, m, out, b.boff, t, p.maxl, bst, b.r2nrm, b.expand1,
+                                           o.tol, rn, p.n_iter, b.it, b.mu_sched, st);
+                });
+                tm("k_svd_expand", 0.0, 0.0, [&] {
+                    lrr::launch_svd_expand(sv[par], 2, b.Qm, nfull, nullptr, b.boff, t, p.maxl, bst, b.r2nrm,
+                                           b.expand1, o.tol, rn, p.n_iter, b.it, b.mu_sched, st);
+                });
+                tm("k_check", 0.0, 0.0, [&] {
+                    lrr::launch_check(bst, t, b.it, b.mu_sched, o.tol, fixed, b.n_active, st);
+                });
+                return;
+            }
             tm("k_svd_resid", 0.0, 0.0, [&] {
                 lrr::launch_svd_resid(sv[par], b.boff, t, p.maxl, b.expand1, b.Rr, 1, b.it, b.mu_sched, st);
             });
@@ -1282,12 +1310,30 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
             lrr::launch_check(bst, t, b.it, b.mu_sched, o.tol, fixed, b.n_active, st);
         });
     };
+    // The J-step of small orders: Gram matrix, one workgroup per block for the
+    // eigensolve, the weights and P, reconstruction
+    auto small_jstep = [&](hipStream_t st, int par, auto&& tm, double cact) {
+        tm("k_block_fro", 0.0, cact * D, [&] { lrr::launch_block_fro(b.colsq, b.boff, t, bst, b.it, st); });
+        tm("k_dgemm_sym", 0.0, 0.0, [&] {
+            lrr::launch_dgemm_sym(b.g_gram + par * t, t, p.maxo, st, false, p.left);
+        });
+        tm("k_small_svt", 0.0, 0.0, [&] {
+            lrr::launch_small_svt(b.sme, t, p.maxo, bst, b.it, max_sweeps, st);
+        });
+        tm("k_dgemm<false, false>", 0.0, 0.0, [&] {
+            lrr::launch_dgemm(b.g_J + par * t, t, n, p.maxl, false, false, st);
+        });
+    };
     // One iteration's J-step: every decision is taken on the device from per-block
     // flags (which blocks threshold, which refinement steps apply, how the
     // eigensolve proceeds), so the launches are the same in every iteration.
     // Only while profiling (`tm` times launches, prof.on) are the flags read back,
     // to price each launch with the flops of the blocks it actually covers.
     auto jstep = [&](hipStream_t st, int par, auto&& tm, double cact) {
+        if (p.small) {
+            small_jstep(st, par, tm, cact);
+            return;
+        }
         const bool price = prof.on;
         auto read_flags = [&](int* dst, const int* src) {
             if (!price) return;
@@ -1611,7 +1657,13 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
                              prof.wants("k_sub_cols") || prof.wants("k_update_Z") || prof.wants("k_r2_decide") ||
                              prof.wants("k_colmax") || prof.wants("k_estep") || prof.wants("k_check") ||
                              prof.wants("k_block_colmax") || prof.wants("k_zstep_fused") || prof.wants("k_svd_");
-    const bool use_graph = device_loop ? (o.use_graph == 2 && !prof.on) : (o.use_graph == 1 && !chain_timed);
+    const bool whole = device_loop || p.small;   // an iteration without the host
+    const bool use_graph = device_loop ? (o.use_graph == 2 && !prof.on)
+                                       : (o.use_graph == 1 && !(p.small ? prof.on : chain_timed));
+    // Small orders: the flags are read every eighth iteration (iterations past the
+    // last block's convergence do nothing); the count reported is that of reads
+    // every check_every iterations.
+    const int read_every = p.small ? check_every * std::max(1, 8 / check_every) : check_every;
     // two graphs: plain and re-anchoring iterations, or in singular coordinates the
     // iterations that start from either buffer
     hipGraphExec_t g_plain = nullptr, g_anchor = nullptr;
@@ -1631,13 +1683,13 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
         for (int bb = 0; bb < t; ++bb) if (h_act[bb]) cact += p.boff[bb + 1] - p.boff[bb];
         const bool anchor = pm.dMQ && k > 0 && k % kAnchorEvery == 0;
         const int par = k & 1;
-        if (!device_loop) host_jstep(par, cact);
+        if (!whole) host_jstep(par, cact);
         if (use_graph) {
             hipGraphExec_t& ex = anchor || (p.svd && par) ? g_anchor : g_plain;
             if (!ex) {
                 hipGraph_t graph = nullptr;
                 LRR_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-                if (device_loop) jstep(cs, par, untimed, cact);
+                if (whole) jstep(cs, par, untimed, cact);
                 zstep(cs, anchor, par, untimed, cact);
                 LRR_HIP(hipStreamEndCapture(cs, &graph));
                 const hipError_t e = hipGraphInstantiate(&ex, graph, nullptr, nullptr, 0);
@@ -1646,11 +1698,11 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
             }
             LRR_HIP(hipGraphLaunch(ex, s));
         } else {
-            if (device_loop) jstep(s, par, timed, cact);
+            if (whole) jstep(s, par, timed, cact);
             zstep(s, anchor, par, timed, cact);
         }
         if (hooks && hooks->end) hooks->end(k);
-        if (!fixed && ((k + 1) % check_every == 0 || k + 1 == p.n_iter)) {
+        if (!fixed && ((k + 1) % read_every == 0 || k + 1 == p.n_iter)) {
             LRR_HIP(hipMemcpyAsync(h_misc + 1, b.n_active, sizeof(int), hipMemcpyDeviceToHost, s));
             LRR_HIP(hipMemcpyAsync(h_act, b.active, sizeof(int) * t, hipMemcpyDeviceToHost, s));
             LRR_HIP(hipMemcpyAsync(h_misc + 2, &b.jac_ctl->err, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -1689,6 +1741,10 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
     res.converged = true;
     if (!fixed)
         for (int bb = 0; bb < t; ++bb) if (act[bb]) res.converged = false;
+    if (p.small && !fixed && res.converged) {
+        const int last = *std::max_element(res.iters.begin(), res.iters.end()) - k0;
+        res.batch_iters = std::min(res.batch_iters, round_up(last, check_every));
+    }
     return res;
 }
 

@@ -314,6 +314,46 @@ __global__ __launch_bounds__(256) void k_svd_colmax(const double* __restrict__ A
     if ((threadIdx.x & 63) == 0 && mx > 0.0) atomic_max_nonneg(&out[b], mx);
 }
 
+// The expansions for small problems in one launch each, without the coefficient
+// and result matrices: max |basis R e_j| over a block's columns, R1 with the left
+// basis (which = 1) for the blocks flagged in expand1, then R2 with the right one
+// where its bounds leave the stop test open (the test of k_svd_decide2; the
+// recorded lower bound is not above the exact value, so the maximum replaces it).
+// One wave per column, a lane per row; the coefficients are formed on the way.
+template <int WHICH>
+__global__ __launch_bounds__(256) void k_svd_expand(SvdStep a, const double* __restrict__ basis, int rows,
+                                                     const double* __restrict__ D, const int* __restrict__ boff,
+                                                     BlockState bs, const unsigned long long* __restrict__ x2max,
+                                                     const int* __restrict__ expand1, double tol, double sqrt_n,
+                                                     int n_iter, const DevIter* __restrict__ it,
+                                                     const double* __restrict__ sched) {
+    const int b = blockIdx.y;
+    if (!expand1[b]) return;
+    const int k = it->k, r = a.r;
+    if (WHICH == 2) {
+        const double r1 = __longlong_as_double((long long)bs.r1max[b]);
+        const double x2 = __longlong_as_double((long long)x2max[b]);
+        if (!((r1 < tol || k + 1 >= n_iter) && x2 >= tol && x2 < sqrt_n * tol)) return;
+    }
+    const double imu = 1.0 / it->mu, ratio = k > 0 ? sched[k - 1] / it->mu : 1.0;
+    double mx = 0.0;
+    for (int j = boff[b] + blockIdx.x * 4 + (threadIdx.x >> 6); j < boff[b + 1]; j += gridDim.x * 4) {
+        const long o = (long)j * r;
+        const double g1 = a.f1[2 * j + 1], y1 = ratio * a.f0[2 * j + 1];
+        for (int i = threadIdx.x & 63; i < rows; i += 64) {
+            double acc = 0.0, v = 0.0;
+            for (int q = 0; q < r; ++q) {
+                v = WHICH == 1 ? g1 * a.q1[o + q] - y1 * a.q0[o + q] : a.Y21[o + q] * imu - a.Y20[o + q] * imu;
+                acc += basis[i + (long)q * rows] * v;
+            }
+            if (D) acc += D[i + (long)j * rows] * v;
+            mx = fmax(mx, fabs(acc));
+        }
+    }
+    mx = wave_max(mx);
+    if ((threadIdx.x & 63) == 0 && mx > 0.0) atomic_max_nonneg(WHICH == 1 ? &bs.r1max[b] : &bs.r2max[b], mx);
+}
+
 // Results of a finished solve, per block from the buffers its last pass wrote
 // (iters passes: buffer iters & 1):  what = 0: E = f q;  what = 1: Z = Y - Y2/mu'
 // (mu' the penalty after the last iteration).
@@ -433,6 +473,17 @@ void launch_svd_colmax(const double* A, int rows, long ld, const int* boff, int 
                        unsigned long long* out, const double* D, const double* R, int r, hipStream_t s) {
     hipLaunchKernelGGL(k_svd_colmax, block_cols_grid(t, maxl), dim3(256), 0, s, A, rows, ld, boff, expand, out, D, R,
                        r);
+}
+void launch_svd_expand(const SvdStep& a, int which, const double* basis, int rows, const double* D, const int* boff,
+                       int t, int maxl, const BlockState& bs, const unsigned long long* x2max, const int* expand1,
+                       double tol, double sqrt_n, int n_iter, const DevIter* it, const double* sched, hipStream_t s) {
+    const dim3 grid = block_cols_grid(t, maxl);
+    if (which == 1)
+        hipLaunchKernelGGL((k_svd_expand<1>), grid, dim3(256), 0, s, a, basis, rows, D, boff, bs, x2max, expand1, tol,
+                           sqrt_n, n_iter, it, sched);
+    else
+        hipLaunchKernelGGL((k_svd_expand<2>), grid, dim3(256), 0, s, a, basis, rows, D, boff, bs, x2max, expand1, tol,
+                           sqrt_n, n_iter, it, sched);
 }
 void launch_svd_outside(const double* T, int m, int c, double* D, double* len, hipStream_t s) {
     hipLaunchKernelGGL(k_svd_outside, dim3((c + 3) / 4), dim3(256), 0, s, T, m, c, D, len);

@@ -142,3 +142,51 @@ def test_auto_keeps_full_coordinates_where_reduced_ones_drop_data(tail, reduced)
     assert np.array_equal(out[B.LRR_COORDS_AUTO][0], out[same][0])
     assert np.array_equal(out[B.LRR_COORDS_AUTO][1], out[same][1])
     assert rel(out[B.LRR_COORDS_REDUCED][0], out[B.LRR_COORDS_FULL][0]) <= 1e-6
+
+
+@pytest.mark.parametrize("r", [1, 16, 17, 32, 33, 64, 65, 96, 97])
+@pytest.mark.parametrize("wide", [True, False])
+def test_small_gram_orders_vs_oracle(r, wide):
+    """Gram orders around the tile and workgroup sizes of the in-LDS eigensolver (up
+    to 96) and the first order beyond it, as Y Y^T (blocks wider than the rank) and
+    as Y^T Y (blocks of r columns)."""
+    import oracle
+    from paper_1304_5583_amd import binding as B
+    need_gpu()
+    rng = np.random.default_rng(300 + r)
+    rank, n = (r, 3 * r + 3) if wide else (2 * r + 1, 5 * r + 3)
+    M = rng.standard_normal((rank + 2, rank)) @ rng.standard_normal((rank, n))
+    M /= np.linalg.norm(M, axis=0)
+    width = (n + 1) // 2 if wide else r
+    offs = np.append(np.arange(0, n, width), n).astype(np.int32)
+    perm = rng.permutation(n).astype(np.int32)
+    o = B.lrr_opts_default(coords=B.LRR_COORDS_REDUCED)
+    Zt, St, info = B.dfc_lrr_solve(B.to_device_colmajor(M), 0.4, perm, offs, opts=o)
+    with one_thread():
+        ref = oracle.dfc_lrr(M, 0.4, perm, offs)
+    say(f"[gram order {r} wide={wide}] iters {info.iters.tolist()} oracle {[b.iters for b in ref.blocks]}")
+    assert info.iters.tolist() == [b.iters for b in ref.blocks]
+    assert info.rank.tolist() == [b.rank for b in ref.blocks]
+    assert info.batch_iters == max(b.iters for b in ref.blocks)
+    assert np.linalg.norm(B.from_device_colmajor(Zt) - ref.Z) <= 1e-6 * max(np.linalg.norm(ref.Z), 1e-300)
+    assert np.linalg.norm(B.from_device_colmajor(St) - ref.S) <= 1e-6 * max(np.linalg.norm(ref.S), 1e-300)
+
+
+def test_small_gram_orders_same_in_every_mode():
+    """The four ways of issuing an iteration, and reads of the flags every 1 or 5
+    iterations, give the same bits on blocks that the in-LDS eigensolver takes."""
+    from paper_1304_5583_amd import binding as B
+    from paper_1304_5583_amd.datagen import small_problem
+    need_gpu()
+    p = small_problem(31, m=50, k=3, r=4, ns=40, n_replace=9, t=3, lam=0.3, uneven=(36, 44))
+    Mt = B.to_device_colmajor(p.M)
+    first = None
+    for kw in (dict(use_graph=0), dict(use_graph=1), dict(use_graph=2), dict(use_graph=3),
+               dict(use_graph=1, check_every=5)):
+        Zt, St, info = B.dfc_lrr_solve(Mt, p.lam, p.perm, p.offsets, opts=B.lrr_opts_default(**kw))
+        got = (B.from_device_colmajor(Zt), B.from_device_colmajor(St), info.iters.tolist())
+        every = kw.get("check_every", 1)
+        assert info.batch_iters == -(-max(info.iters) // every) * every
+        if first is None:
+            first = got
+        assert np.array_equal(got[0], first[0]) and np.array_equal(got[1], first[1]) and got[2] == first[2]
