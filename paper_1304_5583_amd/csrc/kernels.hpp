@@ -133,7 +133,9 @@ constexpr int kSmallEig = 96;
 void small_eig_prepare(void);   // once per device use, before a stream capture
 void launch_small_svt(const SmallEig* d, int count, int maxe, BlockState bs, const DevIter* it, int max_sweeps,
                       hipStream_t s);
-void launch_small_syev(const double* A, double* W, double* lam, int e, int L, int max_sweeps, hipStream_t s);
+// cold eigen-decomposition; floor false: relative tolerance only
+void launch_small_syev(const double* A, double* W, double* lam, int e, int L, int max_sweeps, bool floor,
+                       hipStream_t s);
 
 // svdstep.hip: the iteration in singular coordinates
 void launch_rows_factor(const double* G, double* T, int r, hipStream_t s);

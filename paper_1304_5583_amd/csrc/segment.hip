@@ -473,10 +473,17 @@ struct Seg {
         LRR_HIP(hipMemcpyAsync(e.lo, lo.data(), sizeof(int) * L, hipMemcpyHostToDevice, s));
         LRR_HIP(hipMemcpyAsync(e.run, &one, sizeof(int), hipMemcpyHostToDevice, s));
         LRR_HIP(hipMemcpyAsync(e.d, &ed, sizeof(EigDesc), hipMemcpyHostToDevice, s));
-        lrr::launch_set_identity(e.W, L, s);
-        lrr::launch_jacobi_init(e.d, 1, s);
+        // small orders (the Rayleigh-Ritz problems of the embedding): one workgroup
+        const bool small = l <= lrr::kSmallEig;
+        if (small) {
+            lrr::small_eig_prepare();
+            timed("k_small_syev", 0.0, 0.0, [&] { lrr::launch_small_syev(e.A, e.W, e.lam, l, L, 80, true, s); });
+        } else {
+            lrr::launch_set_identity(e.W, L, s);
+            lrr::launch_jacobi_init(e.d, 1, s);
+        }
         int h_any = 1;
-        for (int sw = 0; sw < 80; ++sw) {
+        for (int sw = 0; sw < 80 && !small; ++sw) {
             LRR_HIP(hipMemsetAsync(e.any, 0, sizeof(int), s));
             timed("k_jacobi_offcheck", 0.0, 0.0, [&] { lrr::launch_jacobi_check(e.d, 1, L, e.any, s); });
             LRR_HIP(hipMemcpyAsync(&h_any, e.any, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -487,7 +494,7 @@ struct Seg {
                 timed("k_jacobi_apply<16>", 0.0, 0.0, [&] { lrr::launch_jacobi_apply(e.d, 1, L, kBs, r, s); });
             }
         }
-        lrr::launch_jacobi_eigvals(e.d, 1, s);
+        if (!small) lrr::launch_jacobi_eigvals(e.d, 1, s);
         hipLaunchKernelGGL(k_sort_desc, dim3(1), dim3(1024), 0, s, e.lam, l, e.idx, e.count, cut, use_sqrt);
         int cnt = 0;
         LRR_HIP(hipMemcpyAsync(&cnt, e.count, sizeof(int), hipMemcpyDeviceToHost, s));

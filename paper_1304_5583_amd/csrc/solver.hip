@@ -711,9 +711,14 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     for (int attempt = 0; attempt < 2 && orth && !diagonal; ++attempt) {
         LRR_HIP(hipMemsetAsync(b.Gb, 0, sizeof(double) * (size_t)Lr * Lr, s));
         gemm(4, GemmDesc{b.Mr, b.Mr, b.Gb, r, r, m, m, m, Lr, 1.0, 0.0, nullptr, nullptr}, true, false);
-        lrr::launch_set_identity(b.Wq, Lr, s);
-        for (int sw = 0; sw < 2; ++sw)
-            for (int rd = 0; rd < Lr / p.bq - 1; ++rd) lrr::launch_jacobi_round(b.eq, 1, Lr, p.bq, rd, s);
+        if (r <= lrr::kSmallEig) {
+            lrr::small_eig_prepare();
+            lrr::launch_small_syev(b.Gb, b.Wq, b.lamq, r, Lr, 2, false, s);
+        } else {
+            lrr::launch_set_identity(b.Wq, Lr, s);
+            for (int sw = 0; sw < 2; ++sw)
+                for (int rd = 0; rd < Lr / p.bq - 1; ++rd) lrr::launch_jacobi_round(b.eq, 1, Lr, p.bq, rd, s);
+        }
         gemm(5, GemmDesc{b.Mr, b.Wq, b.Ut, m, r, r, m, Lr, m, 1.0, 0.0, nullptr, nullptr}, false, false);
         gemm(6, GemmDesc{b.Qm, b.Wq, b.Qtmp, n, r, r, n, Lr, n, 1.0, 0.0, nullptr, nullptr}, false, false);
         std::swap(b.Mr, b.Ut);
@@ -792,11 +797,17 @@ void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     EigDesc ed{b.Gb, b.Wq, b.Rq, b.lamq, Lm, side, b.runq, b.stq, b.scaleq, b.protq, b.loq, nullptr};
     LRR_HIP(hipMemcpyAsync(b.eq, &ed, sizeof(EigDesc), hipMemcpyHostToDevice, s));
     lrr::launch_dgemm(b.g_red, 1, side, side, tall, !tall, s);
-    lrr::launch_set_identity(b.Wq, Lm, s);
-    lrr::launch_jacobi_init(b.eq, 1, s);
+    const bool small = side <= lrr::kSmallEig;
+    if (small) {
+        lrr::small_eig_prepare();
+        lrr::launch_small_syev(b.Gb, b.Wq, b.lamq, side, Lm, 80, true, s);
+    } else {
+        lrr::launch_set_identity(b.Wq, Lm, s);
+        lrr::launch_jacobi_init(b.eq, 1, s);
+    }
     int* any = b.idxq;     // scratch flag until the index list is written
     int h_any = 1;
-    for (int sw = 0; sw < 80; ++sw) {
+    for (int sw = 0; sw < 80 && !small; ++sw) {
         LRR_HIP(hipMemsetAsync(any, 0, sizeof(int), s));
         lrr::launch_jacobi_check(b.eq, 1, Lm, any, s);
         LRR_HIP(hipMemcpyAsync(&h_any, any, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -804,7 +815,7 @@ void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
         if (h_any == 0) break;
         for (int r = 0; r < Lm / bq - 1; ++r) lrr::launch_jacobi_round(b.eq, 1, Lm, bq, r, s);
     }
-    lrr::launch_jacobi_eigvals(b.eq, 1, s);
+    if (!small) lrr::launch_jacobi_eigvals(b.eq, 1, s);
     std::vector<double> lam(Lm);
     LRR_HIP(hipMemcpyAsync(lam.data(), b.lamq, sizeof(double) * Lm, hipMemcpyDeviceToHost, s));
     LRR_HIP(hipStreamSynchronize(s));
