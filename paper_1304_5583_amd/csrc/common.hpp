@@ -74,14 +74,14 @@ __host__ __device__ __forceinline__ size_t work_slot(int kind, int wg) {
 struct EigDesc {
     double* B;          // L x L symmetric, diagonalised in place
     double* W;          // L x L, accumulates the rotations (eigenvectors)
-    double* R;          // (L / (2 bs)) rotation blocks of (2 bs)^2 each
+    double* R;          // two sets of L / (2 bs) rotation blocks of (2 bs)^2 each (see k_jacobi_step)
     double* lam;        // L eigenvalues (diagonal of B on exit)
     int L;              // padded order, multiple of 2 bs
     int l;              // true order (rows/cols >= l are padding)
     const int* run;     // skip the matrix if run[0] == 0
     int* st;            // [0] converged, [1] pairs that rotated in the current sweep
     double* scale;      // max |diag| of B at the start, for the absolute floor
-    int* prot;          // per pair of the current round: 1 if it rotated
+    int* prot;          // two sets: per pair of a round, 1 if it rotated
     int* lo;            // per index: Gershgorin disc below the cut (pairs of two such are skipped)
     unsigned long long* work;  // FP64 operation counters (may be null): pair solves, then tile
                                // updates, each spread over kWorkSlots counters (work_slot)
@@ -91,6 +91,7 @@ struct EigDesc {
                         // at p * (L/bs) + q) holding an entry that still needs a rotation
     const int* sched;   // (may be null) explicit rounds: entry r * (L/bs/2) + P is the pair
                         // p | q << 16 of slot P in round r; every round pairs all L/bs blocks
+    double* B2;         // L x L scratch: B alternates with it between rounds (bs = 16 only)
     const int* done;    // (may be null) done[0] set: the refinement left nothing to rotate; B
                         // was not formed, its diagonal is taken from lam and the matrix is
                         // closed at the start of the eigensolve

@@ -142,12 +142,13 @@ lrr_status lrr_diag_syevj(lrr_ctx* ctx, int count, const int* l, const double* B
     return run(ctx, [&]() -> lrr_status {
         hipStream_t s = static_cast<hipStream_t>(stream);
         const size_t LL = (size_t)L * L;
-        double *Bp, *Wp, *Rp, *lamp, *scale;
+        double *Bp, *B2p, *Wp, *Rp, *lamp, *scale;
         int *st, *run_on, *ls, *any, *prot, *lo;
         lrr::EigDesc* dd;
         LRR_HIP(hipMalloc((void**)&Bp, sizeof(double) * LL * count));
         LRR_HIP(hipMalloc((void**)&Wp, sizeof(double) * LL * count));
-        LRR_HIP(hipMalloc((void**)&Rp, sizeof(double) * (size_t)L * 2 * bs * count));
+        LRR_HIP(hipMalloc((void**)&B2p, sizeof(double) * LL * count));
+        LRR_HIP(hipMalloc((void**)&Rp, sizeof(double) * (size_t)L * 4 * bs * count));
         LRR_HIP(hipMalloc((void**)&lamp, sizeof(double) * (size_t)L * count));
         LRR_HIP(hipMalloc((void**)&scale, sizeof(double) * count));
         LRR_HIP(hipMalloc((void**)&st, sizeof(int) * 2 * count));
@@ -155,7 +156,7 @@ lrr_status lrr_diag_syevj(lrr_ctx* ctx, int count, const int* l, const double* B
         LRR_HIP(hipMalloc((void**)&ls, sizeof(int) * count));
         LRR_HIP(hipMalloc((void**)&any, sizeof(int)));
         const int npair = L / (2 * bs);
-        LRR_HIP(hipMalloc((void**)&prot, sizeof(int) * npair * count));
+        LRR_HIP(hipMalloc((void**)&prot, sizeof(int) * 2 * npair * count));
         // no threshold here: every pair of indices is resolved
         LRR_HIP(hipMalloc((void**)&lo, sizeof(int) * (size_t)L * count));
         LRR_HIP(hipMemsetAsync(lo, 0, sizeof(int) * (size_t)L * count, s));
@@ -163,9 +164,9 @@ lrr_status lrr_diag_syevj(lrr_ctx* ctx, int count, const int* l, const double* B
         std::vector<lrr::EigDesc> hd(count);
         std::vector<int> ones(count, 1);
         for (int i = 0; i < count; ++i)
-            hd[i] = lrr::EigDesc{Bp + LL * i, Wp + LL * i, Rp + (size_t)L * 2 * bs * i, lamp + (size_t)L * i,
-                                 L, l[i], run_on + i, st + 2 * i, scale + i, prot + npair * i,
-                                 lo + (size_t)L * i, nullptr};
+            hd[i] = lrr::EigDesc{Bp + LL * i, Wp + LL * i, Rp + (size_t)L * 4 * bs * i, lamp + (size_t)L * i,
+                                 L, l[i], run_on + i, st + 2 * i, scale + i, prot + 2 * npair * i,
+                                 lo + (size_t)L * i, nullptr, nullptr, nullptr, nullptr, nullptr, B2p + LL * i};
         LRR_HIP(hipMemcpy(dd, hd.data(), sizeof(lrr::EigDesc) * count, hipMemcpyHostToDevice));
         LRR_HIP(hipMemcpy(run_on, ones.data(), sizeof(int) * count, hipMemcpyHostToDevice));
         LRR_HIP(hipMemcpy(ls, l, sizeof(int) * count, hipMemcpyHostToDevice));
@@ -181,14 +182,14 @@ lrr_status lrr_diag_syevj(lrr_ctx* ctx, int count, const int* l, const double* B
             LRR_HIP(hipMemcpyAsync(&h_any, any, sizeof(int), hipMemcpyDeviceToHost, s));
             LRR_HIP(hipStreamSynchronize(s));
             if (h_any == 0 || sw == 60) break;
-            for (int r = 0; r < nb - 1; ++r) lrr::launch_jacobi_round(dd, count, L, bs, r, s);
+            lrr::launch_jacobi_rounds(dd, count, L, bs, nb - 1, s);
         }
         lrr::launch_jacobi_eigvals(dd, count, s);
         hipLaunchKernelGGL(k_unpad, dim3((unsigned)((LL + 255) / 256), count), dim3(256), 0, s, Wp, L, W, ldb,
                            strideB, lamp, lam, ldlam, ls);
         LRR_HIP(hipStreamSynchronize(s));
         if (sweeps) *sweeps = sw;
-        (void)hipFree(Bp); (void)hipFree(Wp); (void)hipFree(Rp); (void)hipFree(lamp); (void)hipFree(scale);
+        (void)hipFree(Bp); (void)hipFree(B2p); (void)hipFree(Wp); (void)hipFree(Rp); (void)hipFree(lamp); (void)hipFree(scale);
         (void)hipFree(st); (void)hipFree(run_on); (void)hipFree(ls); (void)hipFree(any); (void)hipFree(dd);
         (void)hipFree(prot);
         (void)hipFree(lo);

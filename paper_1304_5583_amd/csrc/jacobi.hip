@@ -98,8 +98,11 @@ __device__ __forceinline__ void step_pair(int st, int k, int& a, int& b) {
 // points 352 -> 252 ms.
 // wslot spreads the operation counter over its slots.  Every thread returns
 // through the same path (the branches depend on LDS values only).
+// set: which set of rotation blocks and flags takes the result.  loaded: S is in
+// sm.S[0] already (k_jacobi_step); otherwise it is read from B.
 template <int BS, int NT>
-__device__ void pair_solve(const EigDesc& d, int round, int P, int sched, int wslot, PairLds<BS>& sm) {
+__device__ void pair_solve(const EigDesc& d, int round, int P, int sched, int wslot, PairLds<BS>& sm, int set = 0,
+                           bool loaded = false) {
     constexpr int PB = 2 * BS;
     constexpr int NP = PB / 2;   // rotations per step
     constexpr int NBUF = PairLds<BS>::NBUF;
@@ -123,7 +126,7 @@ __device__ void pair_solve(const EigDesc& d, int round, int P, int sched, int ws
         const int i = idx % PB, j = idx / PB;
         const long gi = (i < BS) ? (long)p * BS + i : (long)q * BS + (i - BS);
         const long gj = (j < BS) ? (long)p * BS + j : (long)q * BS + (j - BS);
-        v[u] = d.B[gi + gj * L];
+        v[u] = loaded ? sm.S[0][i][j] : d.B[gi + gj * L];
     }
     const int lo_i = tid < PB ? d.lo[(tid < BS) ? p * BS + tid : q * BS + (tid - BS)] : 0;
     const double floor_abs = kAbsFloor * d.scale[0];
@@ -131,7 +134,7 @@ __device__ void pair_solve(const EigDesc& d, int round, int P, int sched, int ws
     for (int u = 0; u < NV; ++u) {
         const int idx = tid + u * NT;
         const int i = idx % PB, j = idx / PB;
-        sm.S[0][i][j] = v[u];
+        if (!loaded) sm.S[0][i][j] = v[u];
         sm.R[i][j] = (i == j) ? 1.0 : 0.0;
     }
     if (tid < 64) {
@@ -155,8 +158,9 @@ __device__ void pair_solve(const EigDesc& d, int round, int P, int sched, int ws
     __syncthreads();
     const int any = sm.any;
     const bool inside = (any & 2) && (sched || (round & 7) == 0), cross = (any & 1) != 0;
+    int* const prot = d.prot + set * (nb / 2);
     if (!inside && !cross) {
-        if (tid == 0) d.prot[P] = 0;
+        if (tid == 0) prot[P] = 0;
         return;
     }
     const int st0 = inside ? 0 : BS - 1, st1 = cross ? 2 * BS - 1 : BS - 1;
@@ -234,14 +238,14 @@ __device__ void pair_solve(const EigDesc& d, int round, int P, int sched, int ws
         const unsigned long long per_step = 30ull * NP + 24ull * NP * NP + 6ull * PB * NP;
         atomicAdd(&d.work[work_slot(0, wslot)], per_step * (st1 - st0));
     }
-    double* Rg = d.R + (long)P * PB * PB;
+    double* Rg = d.R + (long)(set * (nb / 2) + P) * PB * PB;
 #pragma unroll
     for (int u = 0; u < NV; ++u) {
         const int idx = tid + u * NT;
         const int i = idx % PB, j = idx / PB;
         Rg[i + (long)j * PB] = sm.R[i][j];
     }
-    if (tid == 0) d.prot[P] = 1;
+    if (tid == 0) prot[P] = 1;
 }
 
 template <int BS, int NT>
@@ -298,10 +302,14 @@ __device__ __forceinline__ int apply_items(int L) {
     return npair * (npair + 1) / 2 + ((L + kApplyRows - 1) / kApplyRows) * npair;
 }
 
-// phase B, item `item` of a round (256 threads): a tile pair of B or a row
-// chunk of W
+// phase B, item `item` of a round (256 threads, tid): a tile pair of B, read from
+// src and written to dst (the same buffer, or the other one), or a row chunk of W.
+// set: the round's set of rotation blocks and flags.  Two groups of 256 threads of
+// one workgroup may each run an item of the same kind: every group meets the same
+// barriers, whatever its item needs.
 template <int BS>
-__device__ void apply_item(const EigDesc& d, int round, int item, int sched, int wslot, ApplyLds<BS>& sm) {
+__device__ void apply_item(const EigDesc& d, int round, int item, int sched, int wslot, ApplyLds<BS>& sm,
+                           const double* src, double* dst, int set, int tid, bool live) {
     constexpr int PB = 2 * BS;
     constexpr int RC = kApplyRows;
     const int nb = d.L / BS;
@@ -311,41 +319,45 @@ __device__ void apply_item(const EigDesc& d, int round, int item, int sched, int
     auto& RP = sm.RP;
     auto& RQ = sm.RQ;
     auto& T = sm.T;
-    const int tid = threadIdx.x;
     const long L = d.L;
+    const int* const prot = d.prot + set * npair;
+    const double* const Rset = d.R + (long)set * npair * PB * PB;
 
     if (item < ntri) {
         // decode upper-triangular index (P <= Q)
         int P = 0, rem = item;
         while (rem >= npair - P) { rem -= npair - P; ++P; }
         const int Q = P + rem;
-        if (!d.prot[P] && !d.prot[Q]) return;
-        if (tid == 0 && d.work)   // two PB^3 products
+        const bool rotP = prot[P] != 0, rotQ = prot[Q] != 0, any = rotP || rotQ;
+        live = live && (any || src != dst);
+        if (live && any && tid == 0 && d.work)   // two PB^3 products
             atomicAdd(&d.work[work_slot(1, wslot)], 4ull * PB * PB * PB);
         int p1, q1, p2, q2;
         round_pair(d, nb, round, P, sched, p1, q1);
         round_pair(d, nb, round, Q, sched, p2, q2);
-        const double* RgP = d.R + (long)P * PB * PB;
-        const double* RgQ = d.R + (long)Q * PB * PB;
+        const double* RgP = Rset + (long)P * PB * PB;
+        const double* RgQ = Rset + (long)Q * PB * PB;
+        if (live)
+            for (int idx = tid; idx < PB * PB; idx += 256) {
+                const int i = idx % PB, j = idx / PB;
+                const long gi = (i < BS) ? (long)p1 * BS + i : (long)q1 * BS + (i - BS);
+                const long gj = (j < BS) ? (long)p2 * BS + j : (long)q2 * BS + (j - BS);
+                X[i][j] = src[gi + gj * L];
+                // a pair that did not rotate has R = I (its R block was not written)
+                RP[i][j] = rotP ? RgP[i + (long)j * PB] : (i == j ? 1.0 : 0.0);
+                RQ[i][j] = rotQ ? RgQ[i + (long)j * PB] : (i == j ? 1.0 : 0.0);
+            }
+        __syncthreads();
+        if (live && any) mm_lds<PB, false>(X, RQ, T, tid);       // T = X R_Q
+        __syncthreads();
+        if (live && any) mm_lds<PB, true>(RP, T, X, tid);        // X = R_P^T T (X is free after the first product)
+        __syncthreads();
+        if (!live) return;
         for (int idx = tid; idx < PB * PB; idx += 256) {
             const int i = idx % PB, j = idx / PB;
             const long gi = (i < BS) ? (long)p1 * BS + i : (long)q1 * BS + (i - BS);
             const long gj = (j < BS) ? (long)p2 * BS + j : (long)q2 * BS + (j - BS);
-            X[i][j] = d.B[gi + gj * L];
-            // a pair that did not rotate has R = I (its R block was not written)
-            RP[i][j] = d.prot[P] ? RgP[i + (long)j * PB] : (i == j ? 1.0 : 0.0);
-            RQ[i][j] = d.prot[Q] ? RgQ[i + (long)j * PB] : (i == j ? 1.0 : 0.0);
-        }
-        __syncthreads();
-        mm_lds<PB, false>(X, RQ, T, tid);       // T = X R_Q
-        __syncthreads();
-        mm_lds<PB, true>(RP, T, X, tid);        // X = R_P^T T (X is free after the first product)
-        __syncthreads();
-        for (int idx = tid; idx < PB * PB; idx += 256) {
-            const int i = idx % PB, j = idx / PB;
-            const long gi = (i < BS) ? (long)p1 * BS + i : (long)q1 * BS + (i - BS);
-            const long gj = (j < BS) ? (long)p2 * BS + j : (long)q2 * BS + (j - BS);
-            d.B[gi + gj * L] = X[i][j];
+            dst[gi + gj * L] = X[i][j];
         }
         if (P != Q) {
             // the mirrored tile, with consecutive threads on consecutive rows of it
@@ -353,37 +365,39 @@ __device__ void apply_item(const EigDesc& d, int round, int item, int sched, int
                 const int j = idx % PB, i = idx / PB;
                 const long gi = (i < BS) ? (long)p1 * BS + i : (long)q1 * BS + (i - BS);
                 const long gj = (j < BS) ? (long)p2 * BS + j : (long)q2 * BS + (j - BS);
-                d.B[gj + gi * L] = X[i][j];
+                dst[gj + gi * L] = X[i][j];
             }
         }
     } else {
         const int w = item - ntri;
         const int P = w % npair, chunk = w / npair;
-        if (!d.prot[P]) return;
-        if (tid == 0 && d.work)   // RC x PB times PB x PB
+        live = live && prot[P] != 0;
+        if (live && tid == 0 && d.work)   // RC x PB times PB x PB
             atomicAdd(&d.work[work_slot(1, wslot)], 2ull * RC * PB * PB);
         int p1, q1;
         round_pair(d, nb, round, P, sched, p1, q1);
-        const double* RgP = d.R + (long)P * PB * PB;
+        const double* RgP = Rset + (long)P * PB * PB;
         const int r0 = chunk * RC;
         // reuse X as a RC x PB panel when RC <= PB, else loop in pieces of PB rows
         for (int rr = 0; rr < RC; rr += PB) {
-            for (int idx = tid; idx < PB * PB; idx += 256) {
-                const int i = idx % PB, j = idx / PB;
-                const long gi = r0 + rr + i;
-                const long gj = (j < BS) ? (long)p1 * BS + j : (long)q1 * BS + (j - BS);
-                X[i][j] = (gi < L) ? d.W[gi + gj * L] : 0.0;
-                if (rr == 0) RP[i][j] = RgP[i + (long)j * PB];
-            }
+            if (live)
+                for (int idx = tid; idx < PB * PB; idx += 256) {
+                    const int i = idx % PB, j = idx / PB;
+                    const long gi = r0 + rr + i;
+                    const long gj = (j < BS) ? (long)p1 * BS + j : (long)q1 * BS + (j - BS);
+                    X[i][j] = (gi < L) ? d.W[gi + gj * L] : 0.0;
+                    if (rr == 0) RP[i][j] = RgP[i + (long)j * PB];
+                }
             __syncthreads();
-            mm_lds<PB, false>(X, RP, T, tid);   // T = W panel R_P
+            if (live) mm_lds<PB, false>(X, RP, T, tid);   // T = W panel R_P
             __syncthreads();
-            for (int idx = tid; idx < PB * PB; idx += 256) {
-                const int i = idx % PB, j = idx / PB;
-                const long gi = r0 + rr + i;
-                const long gj = (j < BS) ? (long)p1 * BS + j : (long)q1 * BS + (j - BS);
-                if (gi < L) d.W[gi + gj * L] = T[i][j];
-            }
+            if (live)
+                for (int idx = tid; idx < PB * PB; idx += 256) {
+                    const int i = idx % PB, j = idx / PB;
+                    const long gi = r0 + rr + i;
+                    const long gj = (j < BS) ? (long)p1 * BS + j : (long)q1 * BS + (j - BS);
+                    if (gi < L) d.W[gi + gj * L] = T[i][j];
+                }
             __syncthreads();
         }
     }
@@ -397,7 +411,160 @@ __global__ __launch_bounds__(256) void k_jacobi_apply(const EigDesc* __restrict_
     const int item = blockIdx.x;
     if (item >= apply_items<BS>(d.L) || round >= nb - 1) return;
     __shared__ ApplyLds<BS> sm;
-    apply_item<BS>(d, round, item, sched, blockIdx.x + blockIdx.y * gridDim.x, sm);
+    apply_item<BS>(d, round, item, sched, blockIdx.x + blockIdx.y * gridDim.x, sm, d.B, d.B, 0, threadIdx.x, true);
+}
+
+// Pairs of round r and tile updates of round r - 1 in one launch (16-wide blocks).
+// A round's pair solves need only three 16 x 16 blocks of the matrix that the tile
+// updates of the round before are still writing, so each forms those itself from
+// the matrix before that round and its rotations (the same products in the same
+// order: the same bits), while the other workgroups run the updates into the
+// second buffer.  A round then takes the longer of the two phases instead of their
+// sum, and one launch instead of two (15.5 + 11 us and two gaps -> about 21 us and
+// one, 4 matrices of order 320).
+struct AheadLds {
+    double X[3][32][33];     // tiles [A, A], [A, C], [C, C] of the previous round, then T
+    double RA[32][17], RC[32][17];
+    int slot[2];
+};
+
+// slot of index block x in round r, for x = p (first) and q (second half of the
+// workgroup's search); every thread takes part
+__device__ __forceinline__ void find_slots(const EigDesc& d, int nb, int round, int sched, int p, int q, int* slot) {
+    for (int k = threadIdx.x; k < nb / 2; k += blockDim.x) {
+        int a, b;
+        round_pair(d, nb, round, k, sched, a, b);
+        if (a == p || b == p) slot[0] = k;
+        if (a == q || b == q) slot[1] = k;
+    }
+    __syncthreads();
+}
+
+// S (32 x 32, index blocks p and q of round r) after the updates of round r - 1,
+// from src, the matrix before them.  Loads by every thread of the workgroup, products
+// by its first four waves.
+__device__ void look_ahead(const EigDesc& d, int round, int p, int q, int sched, const double* src, AheadLds& sm,
+                           double (*S)[40]) {
+    constexpr int BS = 16, PB = 32;
+    const int nb = d.L / BS, tid = threadIdx.x, prev = round - 1, set = prev & 1;
+    const long L = d.L;
+    find_slots(d, nb, prev, sched, p, q, sm.slot);
+    const int A = sm.slot[0], C = sm.slot[1];
+    int a1, a2, c1, c2;
+    round_pair(d, nb, prev, A, sched, a1, a2);
+    round_pair(d, nb, prev, C, sched, c1, c2);
+    const int hp = p == a1 ? 0 : BS, hq = q == c1 ? 0 : BS;   // halves of p and q in their pairs
+    const int* prot = d.prot + set * (nb / 2);
+    const bool rotA = prot[A] != 0, rotC = prot[C] != 0;
+    const double* RgA = d.R + (long)(set * (nb / 2) + A) * PB * PB;
+    const double* RgC = d.R + (long)(set * (nb / 2) + C) * PB * PB;
+    // the off-diagonal tile as the update forms it: rows of the lower slot
+    const bool swap = A > C;
+    const int r1 = swap ? c1 : a1, r2 = swap ? c2 : a2, s1 = swap ? a1 : c1, s2 = swap ? a2 : c2;
+    for (int idx = tid; idx < PB * PB; idx += blockDim.x) {
+        const int i = idx % PB, j = idx / PB;
+        const long ai = (i < BS ? a1 * BS : a2 * BS - BS) + i, aj = (j < BS ? a1 * BS : a2 * BS - BS) + j;
+        const long ci = (i < BS ? c1 * BS : c2 * BS - BS) + i, cj = (j < BS ? c1 * BS : c2 * BS - BS) + j;
+        const long ri = (i < BS ? r1 * BS : r2 * BS - BS) + i, sj = (j < BS ? s1 * BS : s2 * BS - BS) + j;
+        sm.X[0][i][j] = src[ai + aj * L];
+        sm.X[1][i][j] = src[ri + sj * L];
+        sm.X[2][i][j] = src[ci + cj * L];
+        if (j < BS) {
+            sm.RA[i][j] = rotA ? RgA[i + (long)(hp + j) * PB] : (i == hp + j ? 1.0 : 0.0);
+            sm.RC[i][j] = rotC ? RgC[i + (long)(hq + j) * PB] : (i == hq + j ? 1.0 : 0.0);
+        }
+    }
+    __syncthreads();
+    // T = X R, the 16 columns wanted: wave w < 3 takes tile w (rows 0..31); then
+    // 16 x 16 results R^T T.  Where p and q were a pair already (A = C), wave 3 forms
+    // the other half of that tile, which is not the mirror image to the last bit.
+    const int w = tid >> 6, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+    dbl4 t0 = {0.0, 0.0, 0.0, 0.0}, t1 = t0, o = t0;
+    // tile 1 has rows of the lower slot and columns of the upper one
+    const double (*Rr)[17] = w == 0 ? sm.RA : w == 2 ? sm.RC : swap ? sm.RA : sm.RC;   // on the columns
+    const double (*Rl)[17] = w == 0 ? sm.RA : w == 2 ? sm.RC : swap ? sm.RC : sm.RA;   // on the rows
+    if (w < 3) {
+#pragma unroll
+        for (int kk = 0; kk < PB; kk += 4) {
+            const int k = kk + lk;
+            const double b = Rr[k][lr];
+            t0 = __builtin_amdgcn_mfma_f64_16x16x4f64(sm.X[w][lr][k], b, t0, 0, 0, 0);
+            t1 = __builtin_amdgcn_mfma_f64_16x16x4f64(sm.X[w][16 + lr][k], b, t1, 0, 0, 0);
+        }
+    }
+    __syncthreads();
+    if (w < 3) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            sm.X[w][lk + 4 * v][lr] = t0[v];
+            sm.X[w][16 + lk + 4 * v][lr] = t1[v];
+        }
+    }
+    __syncthreads();
+    const bool other = w == 3 && A == C;
+    if (w < 3 || other) {
+        const double (*Rw)[17] = other ? sm.RC : Rl;
+        const double (*Tw)[33] = other ? sm.X[0] : sm.X[w];
+#pragma unroll
+        for (int kk = 0; kk < PB; kk += 4) {
+            const int k = kk + lk;
+            o = __builtin_amdgcn_mfma_f64_16x16x4f64(Rw[k][lr], Tw[k][lr], o, 0, 0, 0);
+        }
+    }
+    __syncthreads();   // S may share the space of sm
+    if (w < 3 || other) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = lk + 4 * v, j = lr;
+            if (w == 0) S[i][j] = o[v];
+            else if (w == 2) S[BS + i][BS + j] = o[v];
+            else if (w == 3) S[BS + i][j] = o[v];
+            else if (!swap) {
+                S[i][BS + j] = o[v];
+                if (A != C) S[BS + j][i] = o[v];
+            } else {
+                S[j][BS + i] = o[v];
+                S[BS + i][j] = o[v];
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// Workgroups [0, npair_max) of a matrix: pair solves of round r; then the tile
+// updates of round r - 1 (r >= 1), two per workgroup: first the tiles of B, then the
+// chunks of W.  rounds: of this pass; the last update writes the matrix back into B.
+__global__ __launch_bounds__(kPairThreads) void k_jacobi_step(const EigDesc* __restrict__ descs, int r, int rounds,
+                                                               int sched, int npair_max) {
+    constexpr int BS = 16;
+    const EigDesc d = descs[blockIdx.y];
+    if (d.run[0] == 0 || d.st[0] != 0) return;
+    __shared__ union {
+        ApplyLds<BS> a[2];
+        PairLds<BS> p;
+        AheadLds h;
+    } sm;
+    const int nb = d.L / BS, npair = nb / 2;
+    const int mine = min(rounds, nb - 1);   // rounds this matrix takes
+    const double* src = (r & 1) ? d.B : d.B2;   // the matrix before round r - 1
+    if ((int)blockIdx.x < npair_max) {
+        const int P = blockIdx.x;
+        if (P >= npair || r >= mine) return;
+        int p, q;
+        round_pair(d, nb, r, P, sched, p, q);
+        look_ahead(d, r, p, q, sched, src, sm.h, sm.p.S[0]);
+        pair_solve<BS, kPairThreads>(d, r, P, sched, blockIdx.x + blockIdx.y * gridDim.x, sm.p, r & 1, true);
+    } else {
+        const int half = threadIdx.x >> 8;
+        const int ntri = npair * (npair + 1) / 2, ntri2 = (ntri + 1) / 2, all = apply_items<BS>(d.L);
+        const int g = blockIdx.x - npair_max;
+        const int item = g < ntri2 ? 2 * g + half : ntri + 2 * (g - ntri2) + half;
+        if (ntri + 2 * (g - ntri2) >= all || r - 1 >= mine) return;
+        const bool live = g < ntri2 ? item < ntri : item < all;
+        double* dst = (r == mine || !(r & 1)) ? d.B : d.B2;
+        apply_item<BS>(d, r - 1, live ? item : (g < ntri2 ? 0 : ntri), sched, blockIdx.x + blockIdx.y * gridDim.x,
+                       sm.a[half], src, dst, (r - 1) & 1, threadIdx.x & 255, live);
+    }
 }
 
 // start of an eigensolve: reset flags, scale = max |diag|
@@ -803,7 +970,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_jacobi_solve(const EigDesc* _
                 const int b = item_block(off_apply, t, item);
                 const EigDesc d = descs[b];
                 if (d.run[0] == 0 || d.st[0] != 0 || r >= d.L / BS - 1) continue;
-                apply_item<BS>(d, r, item - off_apply[b], sched, wg, sm.a);
+                apply_item<BS>(d, r, item - off_apply[b], sched, wg, sm.a, d.B, d.B, 0, tid, true);
                 __syncthreads();
             }
             if (!grid_sync(ctl, G, gen)) return;
@@ -851,9 +1018,27 @@ void launch_jacobi_apply(const EigDesc* d_descs, int count, int maxL, int bs, in
                            d_descs, round, (int)sched);
 }
 
-void launch_jacobi_round(const EigDesc* d_descs, int count, int maxL, int bs, int round, hipStream_t s) {
-    launch_jacobi_pairs(d_descs, count, maxL, bs, round, s);
-    launch_jacobi_apply(d_descs, count, maxL, bs, round, s);
+void launch_jacobi_rounds(const EigDesc* d_descs, int count, int maxL, int bs, int rounds, hipStream_t s,
+                          bool sched) {
+    // Both phases in one launch while the pair solves alone do not fill the chip (256
+    // CUs): m = 500, n = 2000, 4 matrices of order 320, 219 -> 201 ms per solve.  With
+    // 640 pairs (40 matrices of order 512) there is nothing to overlap and the tiles
+    // that did not rotate would be copied: 336 -> 341 ms.
+    if (bs != 16 || count * (maxL / bs / 2) >= 256) {
+        for (int r = 0; r < rounds; ++r) {
+            launch_jacobi_pairs(d_descs, count, maxL, bs, r, s, sched);
+            launch_jacobi_apply(d_descs, count, maxL, bs, r, s, sched);
+        }
+        return;
+    }
+    const int npair = maxL / bs / 2;
+    const int items = (npair * (npair + 1) / 2 + 1) / 2 + (((maxL + 63) / 64) * npair + 1) / 2;
+    launch_jacobi_pairs(d_descs, count, maxL, bs, 0, s, sched);
+    for (int r = 1; r <= rounds; ++r) {
+        const int np = r < rounds ? npair : 0;
+        hipLaunchKernelGGL(k_jacobi_step, dim3(np + items, count), dim3(kPairThreads), 0, s, d_descs, r, rounds,
+                           (int)sched, np);
+    }
 }
 
 void launch_jacobi_check(const EigDesc* d_descs, int count, int maxL, int* d_open, hipStream_t s, int bs) {

@@ -34,7 +34,9 @@ void launch_add_identity(double* A, int lda, int m, double s, hipStream_t st);
 
 // jacobi.hip
 void launch_jacobi_init(const EigDesc* d_descs, int count, hipStream_t s);
-void launch_jacobi_round(const EigDesc* d_descs, int count, int maxL, int bs, int round, hipStream_t s);
+// rounds 0..rounds - 1 of a pass over all matrices (sched as below)
+void launch_jacobi_rounds(const EigDesc* d_descs, int count, int maxL, int bs, int rounds, hipStream_t s,
+                          bool sched = false);
 // sched: take the round's pairs from EigDesc::sched instead of the circle method
 void launch_jacobi_pairs(const EigDesc* d_descs, int count, int maxL, int bs, int round, hipStream_t s,
                          bool sched = false);

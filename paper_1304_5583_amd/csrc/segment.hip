@@ -379,7 +379,7 @@ struct Slab {
 
 // Symmetric eigensolver state for orders up to Lmax (block Jacobi from I).
 struct Eig {
-    double *A, *W, *R, *lam, *scale;
+    double *A, *B2, *W, *R, *lam, *scale;
     int *st, *prot, *lo, *run, *any, *idx, *count;
     EigDesc* d;
     int Lmax;
@@ -428,11 +428,12 @@ size_t layout(Slab& a, Work& w, int n, int p, int nk, int k, int p2, int Lmax, b
     e.Lmax = Lmax;
     e.A = a.take<double>((size_t)Lmax * Lmax);
     e.W = a.take<double>((size_t)Lmax * Lmax);
-    e.R = a.take<double>((size_t)Lmax * 2 * kBs);
+    e.B2 = a.take<double>((size_t)Lmax * Lmax);
+    e.R = a.take<double>((size_t)Lmax * 4 * kBs);
     e.lam = a.take<double>(Lmax);
     e.scale = a.take<double>(1);
     e.st = a.take<int>(2);
-    e.prot = a.take<int>(Lmax / (2 * kBs) + 1);
+    e.prot = a.take<int>(Lmax / kBs + 2);
     e.lo = a.take<int>(Lmax);
     e.run = a.take<int>(1);
     e.any = a.take<int>(1);
@@ -469,7 +470,8 @@ struct Seg {
         std::vector<int> lo(L);
         for (int i = 0; i < L; ++i) lo[i] = i >= l ? 1 : 0;
         const int one = 1;
-        EigDesc ed{e.A, e.W, e.R, e.lam, L, l, e.run, e.st, e.scale, e.prot, e.lo, nullptr, nullptr, nullptr};
+        EigDesc ed{e.A, e.W, e.R, e.lam, L, l, e.run, e.st, e.scale, e.prot, e.lo, nullptr, nullptr, nullptr, nullptr,
+                   nullptr, e.B2};
         LRR_HIP(hipMemcpyAsync(e.lo, lo.data(), sizeof(int) * L, hipMemcpyHostToDevice, s));
         LRR_HIP(hipMemcpyAsync(e.run, &one, sizeof(int), hipMemcpyHostToDevice, s));
         LRR_HIP(hipMemcpyAsync(e.d, &ed, sizeof(EigDesc), hipMemcpyHostToDevice, s));
@@ -489,10 +491,7 @@ struct Seg {
             LRR_HIP(hipMemcpyAsync(&h_any, e.any, sizeof(int), hipMemcpyDeviceToHost, s));
             sync();
             if (h_any == 0) break;
-            for (int r = 0; r < L / kBs - 1; ++r) {
-                timed("k_jacobi_pairs<16, 512>", 0.0, 0.0, [&] { lrr::launch_jacobi_pairs(e.d, 1, L, kBs, r, s); });
-                timed("k_jacobi_apply<16>", 0.0, 0.0, [&] { lrr::launch_jacobi_apply(e.d, 1, L, kBs, r, s); });
-            }
+            timed("k_jacobi_step", 0.0, 0.0, [&] { lrr::launch_jacobi_rounds(e.d, 1, L, kBs, L / kBs - 1, s); });
         }
         if (!small) lrr::launch_jacobi_eigvals(e.d, 1, s);
         hipLaunchKernelGGL(k_sort_desc, dim3(1), dim3(1024), 0, s, e.lam, l, e.idx, e.count, cut, use_sqrt);

@@ -214,7 +214,7 @@ struct Buffers {
     double *colsq, *mu_sched;
     double *Dn, *MQacc;          // difference form of M Q only
     // reduced coordinates only
-    double *Qm, *Qtmp, *Mr, *R2r, *R2full, *Ur, *Gb, *Wq, *Rq, *lamq, *scaleq, *Gq, *Tq;
+    double *Qm, *Qtmp, *Mr, *R2r, *R2full, *Ur, *Gb, *B2q, *Wq, *Rq, *lamq, *scaleq, *Gq, *Tq;
     int *protq, *loq, *stq, *runq, *idxq, *expand;
     unsigned long long* r2nrm;
     // singular coordinates: left basis (m x r), U^T A (r x n), diagonal, per-column factors, and
@@ -328,11 +328,11 @@ size_t layout(const Plan& p, char* base, Buffers& b, int with_combine, bool need
         b.Bq[i] = a.take<double>(L * L);
         b.Wg[i] = a.take<double>(L * L);
         b.Pm[i] = a.take<double>(L * L);
-        b.Rm[i] = a.take<double>(L * 2 * p.bs);
+        b.Rm[i] = a.take<double>(L * 4 * p.bs);
         b.lam[i] = a.take<double>(L);
         b.h[i] = a.take<double>(L);
         b.lo[i] = a.take<int>(L);
-        b.prot[i] = a.take<int>(L / (2 * p.bs) + 1);
+        b.prot[i] = a.take<int>(L / p.bs + 2);
     }
     {
         size_t nneed = 0, nsched = 0;
@@ -400,12 +400,13 @@ size_t layout(const Plan& p, char* base, Buffers& b, int with_combine, bool need
         b.Ur = with_combine ? a.take<double>(n * p.L[0]) : nullptr;
         b.Gb = a.take<double>(Lm * Lm);
         b.Wq = a.take<double>(Lm * Lm);
-        b.Rq = a.take<double>(Lm * 2 * p.bq);
+        b.Rq = a.take<double>(Lm * 4 * p.bq);
+        b.B2q = a.take<double>(Lm * Lm);
         b.lamq = a.take<double>(Lm);
         b.scaleq = a.take<double>(1);
         b.Gq = a.take<double>(n * n);
         b.Tq = a.take<double>(n * n);
-        b.protq = a.take<int>(Lm / (2 * p.bq) + 1);
+        b.protq = a.take<int>(Lm / p.bq + 2);
         b.loq = a.take<int>(Lm);
         b.stq = a.take<int>(2);
         b.runq = a.take<int>(1);
@@ -432,7 +433,7 @@ size_t layout(const Plan& p, char* base, Buffers& b, int with_combine, bool need
         b.qp[0] = b.E; b.qp[1] = b.Y1;      // m x c each, r x c used
         b.Rr = b.MtV;
     } else {
-        b.Qm = b.Qtmp = b.Mr = b.R2r = b.R2full = b.Ur = b.Gb = b.Wq = b.Rq = b.lamq = b.scaleq = nullptr;
+        b.Qm = b.Qtmp = b.Mr = b.R2r = b.R2full = b.Ur = b.Gb = b.B2q = b.Wq = b.Rq = b.lamq = b.scaleq = nullptr;
         b.Gq = b.Tq = nullptr;
         b.protq = b.loq = b.stq = b.runq = b.idxq = b.expand = nullptr;
         b.r2nrm = nullptr;
@@ -700,7 +701,8 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     gemm(3, GemmDesc{pr.A, b.Qm, b.Mr, m, r, n, (int)pr.lda, n, m, 1.0, 0.0, nullptr, nullptr}, false, false);
     std::vector<int> lo(Lr);
     for (int i = 0; i < Lr; ++i) lo[i] = i >= r ? 1 : 0;
-    const EigDesc ed{b.Gb, b.Wq, b.Rq, b.lamq, Lr, r, b.runq, b.stq, b.scaleq, b.protq, b.loq, nullptr};
+    const EigDesc ed{b.Gb, b.Wq, b.Rq, b.lamq, Lr, r, b.runq, b.stq, b.scaleq, b.protq, b.loq, nullptr, nullptr, nullptr,
+                     nullptr, nullptr, b.B2q};
     LRR_HIP(hipMemcpyAsync(b.loq, lo.data(), sizeof(int) * Lr, hipMemcpyHostToDevice, s));
     LRR_HIP(hipMemcpyAsync(b.eq, &ed, sizeof(EigDesc), hipMemcpyHostToDevice, s));
     LRR_HIP(hipMemsetAsync(b.scaleq, 0, sizeof(double), s));
@@ -716,8 +718,7 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
             lrr::launch_small_syev(b.Gb, b.Wq, b.lamq, r, Lr, 2, false, s);
         } else {
             lrr::launch_set_identity(b.Wq, Lr, s);
-            for (int sw = 0; sw < 2; ++sw)
-                for (int rd = 0; rd < Lr / p.bq - 1; ++rd) lrr::launch_jacobi_round(b.eq, 1, Lr, p.bq, rd, s);
+            for (int sw = 0; sw < 2; ++sw) lrr::launch_jacobi_rounds(b.eq, 1, Lr, p.bq, Lr / p.bq - 1, s);
         }
         gemm(5, GemmDesc{b.Mr, b.Wq, b.Ut, m, r, r, m, Lr, m, 1.0, 0.0, nullptr, nullptr}, false, false);
         gemm(6, GemmDesc{b.Qm, b.Wq, b.Qtmp, n, r, r, n, Lr, n, 1.0, 0.0, nullptr, nullptr}, false, false);
@@ -794,7 +795,8 @@ void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     LRR_HIP(hipMemcpyAsync(b.g_red, &gG, sizeof(GemmDesc), hipMemcpyHostToDevice, s));
     LRR_HIP(hipMemcpyAsync(b.loq, lo.data(), sizeof(int) * Lm, hipMemcpyHostToDevice, s));
     LRR_HIP(hipMemcpyAsync(b.runq, &one, sizeof(int), hipMemcpyHostToDevice, s));
-    EigDesc ed{b.Gb, b.Wq, b.Rq, b.lamq, Lm, side, b.runq, b.stq, b.scaleq, b.protq, b.loq, nullptr};
+    EigDesc ed{b.Gb, b.Wq, b.Rq, b.lamq, Lm, side, b.runq, b.stq, b.scaleq, b.protq, b.loq, nullptr, nullptr, nullptr,
+                     nullptr, nullptr, b.B2q};
     LRR_HIP(hipMemcpyAsync(b.eq, &ed, sizeof(EigDesc), hipMemcpyHostToDevice, s));
     lrr::launch_dgemm(b.g_red, 1, side, side, tall, !tall, s);
     const bool small = side <= lrr::kSmallEig;
@@ -813,7 +815,7 @@ void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
         LRR_HIP(hipMemcpyAsync(&h_any, any, sizeof(int), hipMemcpyDeviceToHost, s));
         LRR_HIP(hipStreamSynchronize(s));
         if (h_any == 0) break;
-        for (int r = 0; r < Lm / bq - 1; ++r) lrr::launch_jacobi_round(b.eq, 1, Lm, bq, r, s);
+        lrr::launch_jacobi_rounds(b.eq, 1, Lm, bq, Lm / bq - 1, s);
     }
     if (!small) lrr::launch_jacobi_eigvals(b.eq, 1, s);
     std::vector<double> lam(Lm);
@@ -960,7 +962,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
             gExp1[bb] = GemmDesc{b.Um, b.Rr + o_n, b.T + o_m, m, l, nr, m, nr, m, 1.0, 0.0, b.expand1 + bb, nullptr};
         eig[bb] = EigDesc{b.Bq[bb], X, b.Rm[bb], b.lam[bb], L, e, erun, b.eigst + 2 * bb,
                           b.eigscale + bb, b.prot[bb], b.lo[bb], ctx->dwork, b.locut + bb, b.passes + bb,
-                          b.need_all + need_off[bb], b.sched_all + sched_off[bb], b.ref_clean + bb};
+                          b.need_all + need_off[bb], b.sched_all + sched_off[bb], b.XE[bb], b.ref_clean + bb};
         sme[bb] = lrr::SmallEig{b.Bm[bb], X, b.Pm[bb], b.lam[bb], b.h[bb], L, e, bb, run, b.warm + bb};
         svt[bb] = SvtDesc{b.Bq[bb], X, b.Wg[bb], b.lam[bb], b.h[bb], L, e, run, bb};
         ref[bb] = RefDesc{b.Bm[bb], X, b.SG[bb], b.Eb[bb], b.XE[bb], b.lam[bb], b.lo[bb], b.ref_scale + bb,
@@ -1637,14 +1639,9 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
                     counted = true;
                 }
                 const bool sched = !counted;
-                for (int r = 0; r < rounds; ++r) {
-                    timed(p.bs == 16 ? "k_jacobi_pairs<16, 512>" : "k_jacobi_pairs<32, 512>", 0.0, 0.0, [&] {
-                        lrr::launch_jacobi_pairs(b.eig, t, p.maxL, p.bs, r, s, sched);
-                    });
-                    timed(p.bs == 16 ? "k_jacobi_apply<16>" : "k_jacobi_apply<32>", 0.0, 0.0, [&] {
-                        lrr::launch_jacobi_apply(b.eig, t, p.maxL, p.bs, r, s, sched);
-                    });
-                }
+                timed(p.bs == 16 ? "k_jacobi_step<16>" : "k_jacobi_step<32>", 0.0, 0.0, [&] {
+                    lrr::launch_jacobi_rounds(b.eig, t, p.maxL, p.bs, rounds, s, sched);
+                });
             }
             timed("k_svt_weights", 0.0, 0.0, [&] { lrr::launch_svt_weights(b.svt, t, p.maxL, b.it, bst, s); });
             timed("k_dgemm<false, true>", f_P, 0.0, [&] {
@@ -1732,8 +1729,7 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
             for (int w = 0; w < lrr::kWorkSlots; ++w) hw[kind] += slots[lrr::work_slot(kind, w)];
         const std::string sfx = p.bs == 16 ? "<16" : "<32";
         for (auto& e : prof.entries) {
-            if (e.name.rfind("k_jacobi_pairs" + sfx, 0) == 0) e.flops += (double)hw[0];
-            if (e.name.rfind("k_jacobi_apply" + sfx, 0) == 0) e.flops += (double)hw[1];
+            if (e.name.rfind("k_jacobi_step" + sfx, 0) == 0) e.flops += (double)(hw[0] + hw[1]);
             if (e.name == "k_jacobi_solve") e.flops += (double)(hw[0] + hw[1]);
         }
     }
