@@ -37,7 +37,8 @@
  *              example a column flagged as an outlier), or NULL (keep all)
  *   rank_tol   relative singular-value cut of step 1, 0 < rank_tol < 1
  *   rank_bound 0: step 1 works on Z itself (an n x n symmetric eigenproblem,
- *              n <= 8192).  > 0: an upper bound on the rank of Z (for the
+ *              n <= 8192; a Z of rank below n / 4 is recognised by a
+ *              sketch of its range first).  > 0: an upper bound on the rank of Z (for the
  *              DFC-LRR output, the rank of the combine basis, at most the
  *              first block's width); step 1 then works on the range sketch
  *              Z * Omega with rank_bound + 16 columns.  A bound that is too
@@ -66,7 +67,7 @@ extern "C" {
 typedef struct lrr_seg_info {
     int rank;            /* r of step 1                                          */
     int range_rank;      /* columns of the orthonormal range basis of Z           */
-    int sketch;          /* columns of the range sketch (n when Z is used itself)  */
+    int sketch;          /* columns of the range sketch (n when rank_bound is 0)   */
     int embed_iters;     /* subspace iterations of step 3                          */
     double embed_resid;  /* largest residual |L x - theta x| of the k vectors      */
     double theta_k;      /* k-th eigenvalue of L                                   */

@@ -393,9 +393,10 @@ struct Work {
     Eig e;
 };
 
-size_t layout(Slab& a, Work& w, int n, int p, int nk, int k, int p2, int Lmax, bool sketch) {
-    w.Om = sketch ? a.take<double>((size_t)n * p) : nullptr;
-    w.Y = sketch ? a.take<double>((size_t)n * p) : nullptr;
+// ps: columns of the range sketch (0: none)
+size_t layout(Slab& a, Work& w, int n, int p, int ps, int nk, int k, int p2, int Lmax) {
+    w.Om = ps ? a.take<double>((size_t)n * ps) : nullptr;
+    w.Y = ps ? a.take<double>((size_t)n * ps) : nullptr;
     w.Q0 = a.take<double>((size_t)n * p);
     w.Q = a.take<double>((size_t)n * p);
     w.Gq = a.take<double>((size_t)p * p);
@@ -590,6 +591,12 @@ extern "C" lrr_status lrr_segment(lrr_ctx* ctx, int n, const void* Zv, int ldz, 
         const int nk = (int)keep.size();
         if (k > nk) return lrr::ctx_fail(ctx, LRR_EINVAL, "k exceeds the number of kept points");
         const int p = sketch ? rank_bound + kSketchExtra : n;
+        // Without a bound a sketch of n / 4 columns is tried first: a Z of lower rank
+        // (what LRR returns) leaves its Gram matrix rank deficient, and then the range is
+        // the same as from Z itself; otherwise the n x n problem follows.  n = 2000, rank
+        // 200: 74 -> 22 ms, and about 10 ms more where the sketch has full rank.  Only where
+        // the cut of the range (1e-7 of sigma_1) lies clearly below the caller's.
+        const int ps = sketch ? p : (n >= 512 && rank_tol >= 1e-6 ? n / 4 : 0);
         const int p2 = std::min(nk, k + std::max(16, k / 2));
         const int L1 = round_up(std::max(p, 2), 2 * kBs);
         const int L3 = round_up(std::max(p2, 2), 2 * kBs);
@@ -597,10 +604,10 @@ extern "C" lrr_status lrr_segment(lrr_ctx* ctx, int n, const void* Zv, int ldz, 
 
         Slab probe;
         Work w;
-        const size_t bytes = layout(probe, w, n, p, nk, k, p2, Lmax, sketch);
+        const size_t bytes = layout(probe, w, n, p, ps, nk, k, p2, Lmax);
         Slab a;
         a.base = static_cast<char*>(lrr::ctx_seg_workspace(ctx, bytes));
-        layout(a, w, n, p, nk, k, p2, Lmax, sketch);
+        layout(a, w, n, p, ps, nk, k, p2, Lmax);
         Seg g{ctx, s, w};
         Eig& e = g.w.e;
         LRR_HIP(hipMemcpyAsync(w.keep, keep.data(), sizeof(int) * nk, hipMemcpyHostToDevice, s));
@@ -609,21 +616,36 @@ extern "C" lrr_status lrr_segment(lrr_ctx* ctx, int n, const void* Zv, int ldz, 
         // ---- range basis Q of Z (n x q) -------------------------------------------
         const double* Y = Z;
         long ldy = ldz;
-        if (sketch) {
-            hipLaunchKernelGGL(k_fill_uniform, dim3(grid1((long)n * p)), dim3(256), 0, s, w.Om, (long)n, n, p,
+        int pc = p, Lc = L1, q = 0;   // columns of Y, padded order of its Gram matrix
+        auto gram_rank = [&] {
+            g.clear_eig(Lc);
+            g.gemm(1, true, false, pc, pc, n, 1.0, Y, ldy, Y, ldy, 0.0, e.A, Lc);
+            q = std::max(1, g.eig(pc, Lc, kRangeCut, 0));
+        };
+        bool direct = !sketch;
+        if (ps) {
+            hipLaunchKernelGGL(k_fill_uniform, dim3(grid1((long)n * ps)), dim3(256), 0, s, w.Om, (long)n, n, ps,
                                0x5EEDull);
-            g.gemm(0, false, false, n, p, n, 1.0, Z, ldz, w.Om, n, 0.0, w.Y, n);
+            g.gemm(0, false, false, n, ps, n, 1.0, Z, ldz, w.Om, n, 0.0, w.Y, n);
             Y = w.Y;
             ldy = n;
+            pc = ps;
+            Lc = round_up(std::max(ps, 2), 2 * kBs);
+            gram_rank();
+            if (sketch && q >= p)
+                return lrr::ctx_fail(ctx, LRR_EINVAL,
+                                     "rank_bound is below the rank of Z (the range sketch has full rank)");
+            direct = !sketch && q > ps - kSketchExtra;
         }
-        g.clear_eig(L1);
-        g.gemm(1, true, false, p, p, n, 1.0, Y, ldy, Y, ldy, 0.0, e.A, L1);
-        int q = g.eig(p, L1, kRangeCut, 0);
-        if (q < 1) q = 1;
-        if (sketch && q >= p)
-            return lrr::ctx_fail(ctx, LRR_EINVAL, "rank_bound is below the rank of Z (the range sketch has full rank)");
-        hipLaunchKernelGGL(k_pick_cols, dim3(q), dim3(256), 0, s, e.W, (long)L1, e.lam, e.idx, p, 1, w.Wk, (long)p);
-        g.gemm(2, false, false, n, q, p, 1.0, Y, ldy, w.Wk, p, 0.0, w.Q0, n);
+        if (direct) {
+            Y = Z;
+            ldy = ldz;
+            pc = n;
+            Lc = L1;
+            gram_rank();
+        }
+        hipLaunchKernelGGL(k_pick_cols, dim3(q), dim3(256), 0, s, e.W, (long)Lc, e.lam, e.idx, pc, 1, w.Wk, (long)pc);
+        g.gemm(2, false, false, n, q, pc, 1.0, Y, ldy, w.Wk, pc, 0.0, w.Q0, n);
         g.gemm(3, true, false, q, q, n, 1.0, w.Q0, n, w.Q0, n, 0.0, w.Gq, q);
         lrr::launch_ns_factor(w.Gq, w.Tq, q, s);
         g.gemm(4, false, false, n, q, q, 1.0, w.Q0, n, w.Tq, q, 0.0, w.Q, n);

@@ -240,3 +240,28 @@ def test_outlier_flags_vs_oracle():
         B.lrr_outlier_flags(Mt, Mt, -1.0)
     with pytest.raises(B.LRRError):
         B.lrr_outlier_flags(Mt, Mt, float("nan"))
+
+
+@pytest.mark.parametrize("rank", [12, 134, 135, 150, 600])
+def test_range_without_a_bound_at_the_sketch_limits(rank):
+    """rank_bound = 0 at n = 600: ranks that the sketch of 150 columns recognises
+    (up to 134), and those for which Z itself is decomposed."""
+    import oracle
+    from paper_1304_5583_amd import binding as B
+    need_gpu()
+    rng = np.random.default_rng(rank)
+    k, ns = 6, 100
+    V = np.zeros((k * ns, k * 2))
+    for i in range(k):   # the cluster part, rank 12
+        V[i * ns:(i + 1) * ns, 2 * i:2 * i + 2] = np.linalg.qr(rng.standard_normal((ns, 2)))[0]
+    Z = V @ V.T
+    if rank > 12:        # and a weak part below the clusters' singular values
+        extra = np.linalg.qr(rng.standard_normal((k * ns, rank)))[0][:, :rank - 12]
+        extra = np.linalg.qr(extra - V @ (V.T @ extra))[0]
+        Z = Z + 1e-4 * extra @ extra.T
+    labels, info = B.lrr_segment(B.to_device_colmajor(Z), k, rank_tol=1e-3)
+    say(f"[range] rank {rank}: range {info['range_rank']} rank {info['rank']}")
+    assert info["rank"] == 12 and info["sketch"] == k * ns
+    assert info["range_rank"] == rank
+    with one_thread():
+        assert np.array_equal(labels.cpu().numpy(), oracle.segment(Z, k, rank_tol=1e-3))
