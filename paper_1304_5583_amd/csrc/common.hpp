@@ -165,15 +165,30 @@ struct SvdStep {
     double lam;
 };
 
+// What the end of a small problem's iteration needs beyond SvdStep (k_svd_tail).
+struct SvdTail {
+    const double *U, *Q, *D;        // left and right basis, directions outside range(U) (may be null)
+    const int* boff;
+    int m, n, n_iter, fixed;
+    double tol, sqrt_m, sqrt_n;
+    int* tick;                      // workgroups done, blocks still active (zero between launches)
+    int* n_active;
+};
+
 // Thresholding step of one block of small order (smalleig.hip).
 struct SmallEig {
-    const double* G;    // Gram matrix, order e, ld L
+    double* G;          // Gram matrix, order e, ld L
     double* X;          // eigenvectors, kept from one iteration to the next
     double* P;          // X diag(g) X^T
     double *lam, *h;    // L eigenvalues; 1 / sigma on the kept ones, 0 elsewhere
     int L, e, block;
     const int* run;
     int* warm;          // X holds the previous iteration's eigenvectors
+    // small blocks only (Y null otherwise: G comes from, and P goes to, the batched
+    // products): the step's input Y (nr x l), its result J, and which Gram matrix
+    const double* Y;
+    double* J;
+    int nr, l, left;
 };
 
 // Thresholding weights of one block after its Gram eigensolve.

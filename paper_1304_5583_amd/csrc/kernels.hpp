@@ -159,6 +159,8 @@ void launch_svd_colmax(const double* A, int rows, long ld, const int* boff, int 
 void launch_svd_expand(const SvdStep& a, int which, const double* basis, int rows, const double* D, const int* boff,
                        int t, int maxl, const BlockState& bs, const unsigned long long* x2max, const int* expand1,
                        double tol, double sqrt_n, int n_iter, const DevIter* it, const double* sched, hipStream_t s);
+void launch_svd_tail(const SvdStep& a, const SvdTail& z, int t, const BlockState& bs, DevIter* it,
+                     const double* sched, hipStream_t s);
 void launch_svd_outside(const double* T, int m, int c, double* D, double* len, hipStream_t s);
 void launch_svd_set_row(double* X, int row, int ld, int c, const double* v, hipStream_t s);
 void launch_svd_add_outside(double* out, long ldo, int m, int c, const double* D, const double* R, int r,

@@ -37,6 +37,7 @@ __device__ __forceinline__ void mm_regs(const double* A, const double* B, int E,
         acc[u] = dbl4{0.0, 0.0, 0.0, 0.0};
         if (t >= nt * nt) continue;
         const int ti = (t % nt) * 16 + lr, tj = (t / nt) * 16 + lr;
+#pragma unroll 2
         for (int k0 = 0; k0 < E; k0 += 4) {
             const int k = k0 + lk;
             const double a = TA ? A[k * ES + ti] : A[ti * ES + k];
@@ -58,91 +59,264 @@ __device__ __forceinline__ void each(const dbl4 (&acc)[MT], int E, F&& f) {
     }
 }
 
-// Jacobi sweeps on the E x E matrix B in LDS (order e), rotations accumulated in X.
-// Returns after a check that finds no entry above the tolerance (relative to the
-// two diagonal entries, and floor_rel of the largest one), or max_sweeps.  A round
-// is two barriers and the latency between them: 0.4 us at order 45 (0.9 with the
-// pair indices recomputed by every thread).
+// What a check of B finds (per workgroup, in LDS)
+struct Found {
+    int above;      // some entry exceeds the tolerance
+    int steep;      // some such entry exceeds kLinear of its two eigenvalues' distance
+    double sum;     // sum of the squared first-order corrections
+};
+constexpr double kLinear = 0.1;     // largest correction the refinement takes
+constexpr double kSumMax = 0.02;    // and largest sum of their squares
+
+// LDS of a small solve: B, X, then these
 template <int NT>
-__device__ void sweeps(double* B, double* X, double* cs, double* sn, int* flag, int e, int E, int ES, int max_sweeps,
-                       double floor_rel = kAbsFloor) {
-    const int tid = threadIdx.x;
-    __shared__ double red[16];
+struct SmallLds {
+    double *B, *X, *cs, *sn;
+    int* pr;
+    Found* f;
+    double* red;
+    __device__ SmallLds(double* lds, int E) {
+        B = lds;
+        X = B + E * (E + 1);
+        cs = X + E * (E + 1);
+        sn = cs + 48;
+        red = sn + 48;
+        f = reinterpret_cast<Found*>(red + 16);
+        pr = reinterpret_cast<int*>(f + 1);
+    }
+};
+constexpr int kSmallTail = 96 + 16 + 4 + 24;   // doubles beyond B and X
+
+template <int NT>
+__device__ double diag_max(const SmallLds<NT>& m, int e, int ES) {
     double mx = 0.0;
-    for (int i = tid; i < e; i += NT) mx = fmax(mx, fabs(B[i * ES + i]));
+    for (int i = threadIdx.x; i < e; i += NT) mx = fmax(mx, fabs(m.B[i * ES + i]));
     mx = wave_max(mx);
-    if ((tid & 63) == 0) red[tid >> 6] = mx;
     __syncthreads();
-    for (int w = 0; w < NT / 64; ++w) mx = fmax(mx, red[w]);
-    const double floor_abs = floor_rel * mx;
-    const int N = (e + 1) & ~1, NP = N / 2;
-    // thread layout: QW >= NP lanes over Q, PSTEP rows of threads over P
-    constexpr int QW = NT == 256 ? 16 : NT == 512 ? 32 : 64, PSTEP = NT / QW, NQ = QW / PSTEP > 1 ? (NT == 1024 ? 3 : QW / PSTEP) : 1;
-    const int tq = tid % QW, tp = tid / QW;
-    int* pr = flag + 2;
-    for (int sw = 0; sw < max_sweeps; ++sw) {
-        if (tid == 0) *flag = 0;
-        __syncthreads();
-        int any = 0;
-        for (int idx = tid; idx < e * e; idx += NT) {
-            const int i = idx / e, j = idx - i * e;
-            if (i < j && fabs(B[i * ES + j]) > fmax(kRelTol * sqrt(fabs(B[i * ES + i] * B[j * ES + j])), floor_abs))
-                any = 1;
-        }
-        if (any) *flag = 1;   // every writer stores 1
-        __syncthreads();
-        if (*flag == 0) break;
-        for (int r = 0; r < N - 1; ++r) {
-            if (tid < NP) {
-                int a, b;
-                rr_pair(N, r, tid, a, b);
-                const double app = B[a * ES + a], aqq = B[b * ES + b], apq = B[a * ES + b];
-                const double thr = fmax(0.999 * kRelTol * __builtin_amdgcn_sqrt(fabs(app * aqq)), floor_abs);
-                double c = 1.0, s = 0.0;
-                if (b < e && fabs(apq) > thr) jacobi_rotation(app, aqq, apq, c, s);
-                cs[tid] = c;
-                sn[tid] = s;
-                pr[tid] = a | (b << 8);
-            }
-            __syncthreads();
-            // 2 x 2 blocks (P, Q) of the round's pairs: a thread keeps its Q, the rows
-            // of threads step through P
-            if (tq < NP) {
-                const double cQ = cs[tq], sQ = sn[tq];
-                const int vQ = pr[tq], aQ = vQ & 255, bQ = vQ >> 8;
-#pragma unroll
-                for (int u = 0; u < NQ; ++u) {
-                    const int P = tp + u * PSTEP;
-                    if (P < NP) {
-                        const double cP = cs[P], sP = sn[P];
-                        const int vP = pr[P], aP = (vP & 255) * ES, bP = (vP >> 8) * ES;
-                        const double s_aa = B[aP + aQ], s_ab = B[aP + bQ];
-                        const double s_ba = B[bP + aQ], s_bb = B[bP + bQ];
-                        const double t_aa = cQ * s_aa - sQ * s_ab, t_ab = sQ * s_aa + cQ * s_ab;
-                        const double t_ba = cQ * s_ba - sQ * s_bb, t_bb = sQ * s_ba + cQ * s_bb;
-                        B[aP + aQ] = cP * t_aa - sP * t_ba;
-                        B[aP + bQ] = cP * t_ab - sP * t_bb;
-                        B[bP + aQ] = sP * t_aa + cP * t_ba;
-                        B[bP + bQ] = sP * t_ab + cP * t_bb;
-                    }
-                }
-                // the eigenvectors: rows i, columns of pair Q
-                if (sQ != 0.0) {
-#pragma unroll
-                    for (int u = 0; u < 2 * NQ; ++u) {
-                        const int i = tp + u * PSTEP;
-                        if (i < e) {
-                            const double xa = X[i * ES + aQ], xb = X[i * ES + bQ];
-                            X[i * ES + aQ] = cQ * xa - sQ * xb;
-                            X[i * ES + bQ] = sQ * xa + cQ * xb;
-                        }
-                    }
-                }
-            }
-            __syncthreads();
-        }
+    if ((threadIdx.x & 63) == 0) m.red[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    for (int w = 0; w < NT / 64; ++w) mx = fmax(mx, m.red[w]);
+    return mx;
+}
+
+// entries above the tolerance (relative to the two diagonal entries, and floor_abs),
+// and whether first-order corrections would resolve them
+template <int NT>
+__device__ Found check(const SmallLds<NT>& m, int e, int ES, double floor_abs) {
+    const int tid = threadIdx.x;
+    __syncthreads();
+    if (tid == 0) {
+        m.f->above = 0;
+        m.f->steep = 0;
     }
     __syncthreads();
+    int above = 0, steep = 0;
+    double sum = 0.0;
+    for (int idx = tid; idx < e * e; idx += NT) {
+        const int i = idx / e, j = idx - i * e;
+        if (i >= j) continue;
+        const double s = fabs(m.B[i * ES + j]), di = m.B[i * ES + i], dj = m.B[j * ES + j];
+        const double gap = fabs(dj - di);
+        if (s > fmax(kRelTol * sqrt(fabs(di * dj)), floor_abs)) {
+            above = 1;
+            if (s > kLinear * gap) steep = 1;
+            else sum += 2.0 * (s / gap) * (s / gap);
+        }
+    }
+    if (above) m.f->above = 1;   // every writer stores 1
+    if (steep) m.f->steep = 1;
+    sum = wave_sum(sum);
+    if ((tid & 63) == 0) m.red[tid >> 6] = sum;
+    __syncthreads();
+    Found f = *m.f;
+    f.sum = 0.0;
+    for (int w = 0; w < NT / 64; ++w) f.sum += m.red[w];
+    __syncthreads();
+    return f;
+}
+
+// One cyclic Jacobi sweep on the E x E matrix B in LDS (order e), rotations
+// accumulated in X.  A round is two barriers and the latency between them: 0.4 us at
+// order 45 (0.9 with the pair indices recomputed by every thread).
+template <int NT>
+__device__ void sweep(const SmallLds<NT>& m, int e, int ES, double floor_abs) {
+    const int tid = threadIdx.x;
+    double* const B = m.B;
+    double* const X = m.X;
+    const int N = (e + 1) & ~1, NP = N / 2;
+    // thread layout: QW >= NP lanes over Q, PSTEP rows of threads over P
+    constexpr int QW = NT == 256 ? 16 : NT == 512 ? 32 : 64, PSTEP = NT / QW;
+    constexpr int NQ = NT == 256 ? 1 : NT == 512 ? 2 : 3;
+    const int tq = tid % QW, tp = tid / QW;
+    for (int r = 0; r < N - 1; ++r) {
+        if (tid < NP) {
+            int a, b;
+            rr_pair(N, r, tid, a, b);
+            const double app = B[a * ES + a], aqq = B[b * ES + b], apq = B[a * ES + b];
+            const double thr = fmax(0.999 * kRelTol * __builtin_amdgcn_sqrt(fabs(app * aqq)), floor_abs);
+            double c = 1.0, s = 0.0;
+            if (b < e && fabs(apq) > thr) jacobi_rotation(app, aqq, apq, c, s);
+            m.cs[tid] = c;
+            m.sn[tid] = s;
+            m.pr[tid] = a | (b << 8);
+        }
+        __syncthreads();
+        // 2 x 2 blocks (P, Q) of the round's pairs: a thread keeps its Q, the rows
+        // of threads step through P
+        if (tq < NP) {
+            const double cQ = m.cs[tq], sQ = m.sn[tq];
+            const int vQ = m.pr[tq], aQ = vQ & 255, bQ = vQ >> 8;
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) {
+                const int P = tp + u * PSTEP;
+                if (P < NP) {
+                    const double cP = m.cs[P], sP = m.sn[P];
+                    const int vP = m.pr[P], aP = (vP & 255) * ES, bP = (vP >> 8) * ES;
+                    const double s_aa = B[aP + aQ], s_ab = B[aP + bQ];
+                    const double s_ba = B[bP + aQ], s_bb = B[bP + bQ];
+                    const double t_aa = cQ * s_aa - sQ * s_ab, t_ab = sQ * s_aa + cQ * s_ab;
+                    const double t_ba = cQ * s_ba - sQ * s_bb, t_bb = sQ * s_ba + cQ * s_bb;
+                    B[aP + aQ] = cP * t_aa - sP * t_ba;
+                    B[aP + bQ] = cP * t_ab - sP * t_bb;
+                    B[bP + aQ] = sP * t_aa + cP * t_ba;
+                    B[bP + bQ] = sP * t_ab + cP * t_bb;
+                }
+            }
+            // the eigenvectors: rows i, columns of pair Q
+            if (sQ != 0.0) {
+#pragma unroll
+                for (int u = 0; u < 2 * NQ; ++u) {
+                    const int i = tp + u * PSTEP;
+                    if (i < e) {
+                        const double xa = X[i * ES + aQ], xb = X[i * ES + bQ];
+                        X[i * ES + aQ] = cQ * xa - sQ * xb;
+                        X[i * ES + bQ] = sQ * xa + cQ * xb;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// X <- X (3 I - X^T X) / 2 (B is scratch)
+template <int NT, int MT>
+__device__ void orthonormalise(const SmallLds<NT>& m, int E, int ES) {
+    dbl4 acc[MT];
+    mm_regs<NT, MT, true, false>(m.X, m.X, E, ES, acc);
+    each<NT, MT>(acc, E, [&](int i, int j, double v) { m.B[i * ES + j] = (i == j ? 1.5 : 0.0) - 0.5 * v; });
+    __syncthreads();
+    mm_regs<NT, MT, false, false>(m.X, m.B, E, ES, acc);
+    __syncthreads();
+    each<NT, MT>(acc, E, [&](int i, int j, double v) { m.X[i * ES + j] = v; });
+    __syncthreads();
+}
+
+// B <- X^T B X
+template <int NT, int MT>
+__device__ void transform(const SmallLds<NT>& m, int E, int ES) {
+    dbl4 acc[MT];
+    mm_regs<NT, MT, false, false>(m.B, m.X, E, ES, acc);
+    __syncthreads();
+    each<NT, MT>(acc, E, [&](int i, int j, double v) { m.B[i * ES + j] = v; });
+    __syncthreads();
+    mm_regs<NT, MT, true, false>(m.X, m.B, E, ES, acc);
+    __syncthreads();
+    each<NT, MT>(acc, E, [&](int i, int j, double v) { m.B[i * ES + j] = v; });
+    __syncthreads();
+}
+
+// First-order correction of the eigenvectors (X orthonormal to rounding, B = X^T G X):
+// X <- X (I + E), E_ij = b_ij / (b_jj - b_ii) where b_ij exceeds the tolerance (Ogita
+// and Aishima 2018 with X^T X = I; the caller has checked that |E_ij| <= kLinear),
+// orthonormalised.  B is left as scratch.
+template <int NT, int MT>
+__device__ void refine(const SmallLds<NT>& m, int e, int E, int ES, double floor_abs, double sum) {
+    double* const d = m.cs;   // cs and sn: 96 diagonal entries
+    for (int i = threadIdx.x; i < E; i += NT) d[i] = m.B[i * ES + i];
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < E * E; idx += NT) {
+        const int i = idx / E, j = idx - i * E;
+        const double s = m.B[i * ES + j], gap = d[j] - d[i];
+        // below the tolerance an entry is rounding, and so may the distance be
+        const bool on = i != j && fabs(s) > fmax(kRelTol * sqrt(fabs(d[i] * d[j])), floor_abs);
+        m.B[i * ES + j] = on ? s / gap : 0.0;
+    }
+    __syncthreads();
+    dbl4 acc[MT];
+    mm_regs<NT, MT, false, false>(m.X, m.B, E, ES, acc);
+    __syncthreads();
+    each<NT, MT>(acc, E, [&](int i, int j, double v) { m.X[i * ES + j] += v; });
+    __syncthreads();
+    // (I + E)^T (I + E) = I - E^2 deviates by at most sum = |E|_F^2; a step squares that
+    for (double dev = sum; dev > 1e-16; dev *= dev) orthonormalise<NT, MT>(m, E, ES);
+}
+
+// Gram matrix of the block Y (nr x l) into B: Y Y^T (left) or Y^T Y, operands from
+// global memory (16 rows of 8 bytes or strided columns, L2-resident)
+template <int NT, int MT>
+__device__ void gram(const SmallEig& d, int E, int ES, double* B) {
+    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4, nt = E >> 4;
+    const int K = d.left ? d.l : d.nr, e = d.e;
+    const long si = d.left ? 1 : d.nr, sk = d.left ? d.nr : 1;   // strides of the Gram index and of k
+#pragma nounroll
+    for (int u = 0; u < MT; ++u) {
+        const int t = (threadIdx.x >> 6) + u * (NT / 64);
+        if (t >= nt * nt) continue;
+        const int i = (t % nt) * 16 + lr, j = (t / nt) * 16 + lr;
+        const double* pi = d.Y + si * (i < e ? i : 0);
+        const double* pj = d.Y + si * (j < e ? j : 0);
+        const double mi = i < e ? 1.0 : 0.0, mj = j < e ? 1.0 : 0.0;
+        dbl4 acc = {0.0, 0.0, 0.0, 0.0};
+        int k0 = 0;   // the same in every lane: a matrix instruction needs the whole wave
+        for (; k0 + 16 <= K; k0 += 16) {   // four chunks of loads in flight
+            double a[4], b[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                a[c] = pi[sk * (k0 + lk + 4 * c)] * mi;
+                b[c] = pj[sk * (k0 + lk + 4 * c)] * mj;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[c], b[c], acc, 0, 0, 0);
+        }
+        for (; k0 < K; k0 += 4) {
+            const int k = k0 + lk;
+            const double a = k < K ? pi[sk * k] * mi : 0.0, b = k < K ? pj[sk * k] * mj : 0.0;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) B[((t % nt) * 16 + lk + 4 * v) * ES + (t / nt) * 16 + lr] = acc[v];
+    }
+    __syncthreads();
+}
+
+// J = P Y (left) or Y P, P in LDS
+template <int NT>
+__device__ void rebuild(const SmallEig& d, int E, int ES, const double* P) {
+    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4, e = d.e, nr = d.nr, l = d.l;
+    const int tr = (nr + 15) >> 4, tc = (l + 15) >> 4;
+    for (int t = threadIdx.x >> 6; t < tr * tc; t += NT / 64) {
+        const int i0 = (t % tr) * 16, j0 = (t / tr) * 16;
+        const int i = i0 + lr, j = j0 + lr;
+        dbl4 acc = {0.0, 0.0, 0.0, 0.0};
+        for (int k0 = 0; k0 < E; k0 += 4) {
+            const int k = k0 + lk;
+            double a, b;
+            if (d.left) {
+                a = P[i * ES + k];   // tr * 16 = E rows
+                b = k < e && j < l ? d.Y[k + (long)j * nr] : 0.0;
+            } else {
+                a = k < e && i < nr ? d.Y[i + (long)k * nr] : 0.0;
+                b = P[k * ES + j];   // tc * 16 = E columns
+            }
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int r = i0 + lk + 4 * v;
+            if (r < nr && j < l) d.J[r + (long)j * nr] = acc[v];
+        }
+    }
 }
 
 // One block's thresholding step from its Gram matrix (see the top of the file)
@@ -154,45 +328,56 @@ __global__ __launch_bounds__(NT) void k_small_svt(const SmallEig* __restrict__ d
     if (!d.run[0]) return;
     const int e = d.e, E = (e + 15) & ~15, ES = E + 1, tid = threadIdx.x;
     const long L = d.L;
-    double* B = lds;
-    double* X = lds + E * ES;
-    double* cs = X + E * ES;
-    double* sn = cs + 48;
-    int* flag = reinterpret_cast<int*>(sn + 48);
+    const SmallLds<NT> m(lds, E);
+    double* const B = m.B;
+    double* const X = m.X;
     const bool warm = d.warm[0] != 0;
     dbl4 acc[MT];
+    auto load_gram = [&] {
+        for (int idx = tid; idx < E * E; idx += NT) {
+            const int j = idx / E, i = idx - j * E;
+            B[i * ES + j] = (i < e && j < e) ? d.G[i + j * L] : 0.0;
+        }
+        __syncthreads();
+    };
     for (int idx = tid; idx < E * E; idx += NT) {
         const int j = idx / E, i = idx - j * E;
         X[i * ES + j] = (warm && i < e && j < e) ? d.X[i + j * L] : (i == j ? 1.0 : 0.0);
     }
     __syncthreads();
-    if (warm) {
-        mm_regs<NT, MT, true, false>(X, X, E, ES, acc);
-        each<NT, MT>(acc, E, [&](int i, int j, double v) { B[i * ES + j] = (i == j ? 1.5 : 0.0) - 0.5 * v; });
+    if (warm) orthonormalise<NT, MT>(m, E, ES);
+    if (d.Y) {
+        // the Gram matrix as well (short rows or columns), kept for the refinement
+        gram<NT, MT>(d, E, ES, B);
+        for (int idx = tid; idx < e * e; idx += NT) {
+            const int j = idx / e, i = idx - j * e;
+            d.G[i + j * L] = B[i * ES + j];
+        }
+        __threadfence_block();
         __syncthreads();
-        mm_regs<NT, MT, false, false>(X, B, E, ES, acc);
-        __syncthreads();
-        each<NT, MT>(acc, E, [&](int i, int j, double v) { X[i * ES + j] = v; });
+    } else {
+        load_gram();
     }
-    __syncthreads();
-    for (int idx = tid; idx < E * E; idx += NT) {
-        const int j = idx / E, i = idx - j * E;
-        B[i * ES + j] = (i < e && j < e) ? d.G[i + j * L] : 0.0;
+    if (warm) transform<NT, MT>(m, E, ES);
+    // Corrections where they resolve everything that is left (6 products, about a
+    // quarter of a sweep's time at order 45), a Jacobi sweep otherwise
+    const double floor_abs = kAbsFloor * diag_max(m, e, ES);
+    int left = max_sweeps;
+    for (int step = 0; step < 4 * max_sweeps && left > 0; ++step) {
+        const Found f = check(m, e, ES, floor_abs);
+        if (!f.above) break;
+        if (!f.steep && f.sum <= kSumMax && step < 2 * max_sweeps) {
+            refine<NT, MT>(m, e, E, ES, floor_abs, f.sum);
+            load_gram();
+            transform<NT, MT>(m, E, ES);
+        } else {
+            sweep(m, e, ES, floor_abs);
+            --left;
+        }
     }
-    __syncthreads();
-    if (warm) {
-        mm_regs<NT, MT, false, false>(B, X, E, ES, acc);
-        __syncthreads();
-        each<NT, MT>(acc, E, [&](int i, int j, double v) { B[i * ES + j] = v; });
-        __syncthreads();
-        mm_regs<NT, MT, true, false>(X, B, E, ES, acc);
-        __syncthreads();
-        each<NT, MT>(acc, E, [&](int i, int j, double v) { B[i * ES + j] = v; });
-        __syncthreads();
-    }
-    sweeps<NT>(B, X, cs, sn, flag, e, E, ES, max_sweeps);
     // weights g = (1 - tau / sigma)_+, eigenvectors back, then B = X diag(g)
     const double tau = it->tau;
+    int* const flag = m.pr;
     if (tid == 0) *flag = 0;
     __syncthreads();
     int kept = 0;
@@ -208,7 +393,7 @@ __global__ __launch_bounds__(NT) void k_small_svt(const SmallEig* __restrict__ d
         const int j = idx / e, i = idx - j * e;
         d.X[i + j * L] = X[i * ES + j];
     }
-    double* g = cs;   // cs and sn are free now: E <= 96 weights
+    double* g = m.cs;   // cs and sn are free now: E <= 96 weights
     for (int j = tid; j < E; j += NT) {
         const double sig = j < e ? sqrt(fmax(B[j * ES + j], 0.0)) : 0.0;
         g[j] = sig > tau ? 1.0 - tau / sig : 0.0;
@@ -220,9 +405,16 @@ __global__ __launch_bounds__(NT) void k_small_svt(const SmallEig* __restrict__ d
     }
     __syncthreads();
     mm_regs<NT, MT, false, true>(B, X, E, ES, acc);
-    each<NT, MT>(acc, E, [&](int i, int j, double v) {
-        if (i < e && j < e) d.P[i + j * L] = v;
-    });
+    if (d.Y) {
+        __syncthreads();
+        each<NT, MT>(acc, E, [&](int i, int j, double v) { B[i * ES + j] = v; });   // P
+        __syncthreads();
+        rebuild<NT>(d, E, ES, B);
+    } else {
+        each<NT, MT>(acc, E, [&](int i, int j, double v) {
+            if (i < e && j < e) d.P[i + j * L] = v;
+        });
+    }
     if (tid == 0) {
         bs.rank[d.block] = *flag;
         d.warm[0] = 1;
@@ -237,18 +429,18 @@ __global__ __launch_bounds__(NT) void k_small_syev(const double* __restrict__ A,
                                                     double floor_rel) {
     extern __shared__ double lds[];
     const int E = (e + 15) & ~15, ES = E + 1, tid = threadIdx.x;
-    double* B = lds;
-    double* X = lds + E * ES;
-    double* cs = X + E * ES;
-    double* sn = cs + 48;
-    int* flag = reinterpret_cast<int*>(sn + 48);
+    const SmallLds<NT> m(lds, E);
+    double* const B = m.B;
+    double* const X = m.X;
     for (int idx = tid; idx < E * E; idx += NT) {
         const int j = idx / E, i = idx - j * E;
         B[i * ES + j] = (i < e && j < e) ? A[i + (long)j * L] : 0.0;
         X[i * ES + j] = i == j ? 1.0 : 0.0;
     }
     __syncthreads();
-    sweeps<NT>(B, X, cs, sn, flag, e, E, ES, max_sweeps, floor_rel);
+    const double floor_abs = floor_rel * diag_max(m, e, ES);
+    for (int sw = 0; sw < max_sweeps && check(m, e, ES, floor_abs).above; ++sw) sweep(m, e, ES, floor_abs);
+    __syncthreads();
     for (int i = tid; i < L; i += NT) lam[i] = i < e ? B[i * ES + i] : 0.0;
     for (long idx = tid; idx < (long)L * L; idx += NT) {
         const int j = (int)(idx / L), i = (int)(idx - (long)j * L);
@@ -258,7 +450,7 @@ __global__ __launch_bounds__(NT) void k_small_syev(const double* __restrict__ A,
 
 size_t lds_bytes(int e) {
     const int E = (e + 15) & ~15;
-    return sizeof(double) * (2 * (size_t)E * (E + 1) + 96 + 2 + 24);
+    return sizeof(double) * (2 * (size_t)E * (E + 1) + kSmallTail);
 }
 
 template <class K>

@@ -221,7 +221,7 @@ struct Buffers {
     // the two buffers of each alternating array (aliases of the general form's arrays)
     double *Um, *Ut, *Ares, *Cr, *dsig, *dinv, *fcol[2], *Yp[2], *Y2p[2], *qp[2], *Rr;
     unsigned long long* stat;
-    int* expand1;
+    int *expand1, *tick;
     GemmDesc *g_sv, *g_exp1;
     EigDesc* eq;
     GemmDesc *g_red, *g_exp;
@@ -425,7 +425,8 @@ size_t layout(const Plan& p, char* base, Buffers& b, int with_combine, bool need
         for (double*& x : b.fcol) x = a.take<double>(2 * c);
         b.stat = a.take<unsigned long long>(4);
         b.expand1 = a.take<int>(t);
-        b.sme = a.take<lrr::SmallEig>(t);
+        b.tick = a.take<int>(2);
+        b.sme = a.take<lrr::SmallEig>(2 * t);
         b.g_sv = a.take<GemmDesc>(10);
         b.g_exp1 = a.take<GemmDesc>(t);
         b.Yp[0] = b.Y; b.Yp[1] = b.Z;
@@ -441,7 +442,7 @@ size_t layout(const Plan& p, char* base, Buffers& b, int with_combine, bool need
         b.g_red = b.g_exp = nullptr;
         b.Um = b.Ut = b.Ares = b.Cr = b.dsig = b.dinv = b.Rr = nullptr;
         b.stat = nullptr;
-        b.expand1 = nullptr;
+        b.expand1 = b.tick = nullptr;
         b.g_sv = b.g_exp1 = nullptr;
     }
     (void)need_X;
@@ -834,6 +835,8 @@ void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     finish_basis(pr, p, b, s);
 }
 
+bool small_products(const Plan& p);
+
 // SVT(Y) = Y g(Y^T Y) = g(Y Y^T) Y: with fewer rows than columns the Gram matrix of
 // the rows is the smaller one and has no null space of dimension l - r, whose
 // eigenvectors no iteration needs.  Taken when it is the smaller matrix for some
@@ -898,7 +901,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
     std::vector<GemmDesc> gram(ny * t), gRT(t), gRSG(t), gRXE(t), gOG(t), gBq(t), gP(t), gJ(ny * t), gExp1(t);
     std::vector<GemmDesc> gMQ(t), gMQa(t), gKV(t), gMtV(t), gExp(t), gF1T(t), gF2Q(t), gAZ(t);
     std::vector<EigDesc> eig(t);
-    std::vector<lrr::SmallEig> sme(t);
+    std::vector<lrr::SmallEig> sme(2 * t);
     std::vector<size_t> need_off(t + 1, 0), sched_off(t + 1, 0);
     for (int bb = 0; bb < t; ++bb) {
         const size_t nb = p.L[bb] / p.bs;
@@ -963,7 +966,12 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         eig[bb] = EigDesc{b.Bq[bb], X, b.Rm[bb], b.lam[bb], L, e, erun, b.eigst + 2 * bb,
                           b.eigscale + bb, b.prot[bb], b.lo[bb], ctx->dwork, b.locut + bb, b.passes + bb,
                           b.need_all + need_off[bb], b.sched_all + sched_off[bb], b.XE[bb], b.ref_clean + bb};
-        sme[bb] = lrr::SmallEig{b.Bm[bb], X, b.Pm[bb], b.lam[bb], b.h[bb], L, e, bb, run, b.warm + bb};
+        for (int y = 0; y < 2; ++y) {
+            const bool in = p.svd && small_products(p);
+            const double* Yb = in ? b.Yp[y] + (size_t)p.boff[bb] * nr : nullptr;
+            sme[y * t + bb] = lrr::SmallEig{b.Bm[bb], X, b.Pm[bb], b.lam[bb], b.h[bb], L, e, bb, run, b.warm + bb,
+                                            Yb, in ? Jb : nullptr, nr, l, p.left ? 1 : 0};
+        }
         svt[bb] = SvtDesc{b.Bq[bb], X, b.Wg[bb], b.lam[bb], b.h[bb], L, e, run, bb};
         ref[bb] = RefDesc{b.Bm[bb], X, b.SG[bb], b.Eb[bb], b.XE[bb], b.lam[bb], b.lo[bb], b.ref_scale + bb,
                           b.ref_emax + bb, b.ref_unres + bb, b.ref_eprev + bb, b.ref_run + bb,
@@ -1025,7 +1033,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         LRR_HIP(hipStreamSynchronize(s));   // the host table goes out of scope
     }
     up(b.svt, svt.data(), sizeof(SvtDesc) * t);
-    if (p.small) up(b.sme, sme.data(), sizeof(lrr::SmallEig) * t);
+    if (p.small) up(b.sme, sme.data(), sizeof(lrr::SmallEig) * 2 * t);
 
     // ---- setup: observations, state, factorisation (once per solve) -------
     if (p.svd) {}   // U^T X is in place
@@ -1041,6 +1049,8 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         LRR_HIP(hipMemsetAsync(b.Yp[0], 0, sizeof(double) * nc, s));
         LRR_HIP(hipMemsetAsync(b.fcol[0], 0, sizeof(double) * 2 * c, s));
         LRR_HIP(hipMemsetAsync(b.colsq, 0, sizeof(double) * c, s));
+        LRR_HIP(hipMemsetAsync(b.svt_run, 0, sizeof(int) * t, s));
+        LRR_HIP(hipMemsetAsync(b.tick, 0, sizeof(int) * 2, s));
     }
     // local mode: the rows of M^T V beyond a block's width are never written
     if (p.local) LRR_HIP(hipMemsetAsync(b.MtV, 0, sizeof(double) * nc, s));
@@ -1093,6 +1103,11 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         lrr::spd_inverse(Kb, m, b.Lb, b.Linv, b.Dinv, b.Tb, b.g_spd, b.flag, s);
     }
 }
+
+// The Gram matrix and the reconstruction inside the workgroup that decomposes the
+// block: while both products are at most about the work of a few Jacobi rounds (the
+// other dimension up to 256), two launches cost more than one CU computing them.
+bool small_products(const Plan& p) { return p.small && (p.left ? p.maxl : p.nr) <= 256; }
 
 // The column pass of an iteration that starts from buffer `par`.
 SvdStep svd_step(const Plan& p, const Buffers& b, int par, double lam) {
@@ -1184,6 +1199,11 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
     if (p.small) lrr::small_eig_prepare();
     // both bases within 2 MB: formed in one launch per residual instead of three
     const bool small_expand = p.svd && (size_t)m * n <= 65536 && (size_t)nfull * n <= 262144;
+    // the whole end of an iteration in one launch where a workgroup forms a block's
+    // residuals quickly (they are needed in the last iterations only): m = 48, n = 96,
+    // blocks of 32 points, 15 -> 7 us an iteration; m = 100, n = 200, one block of 200
+    // (2.7e6 products): 18 -> 44 us
+    const bool tail = p.small && small_expand && ((size_t)m + nfull) * n * p.maxl <= 400000;
     const SvdStep sv[2] = {svd_step(p, b, 0, pr.lam), svd_step(p, b, 1, pr.lam)};
     auto zstep = [&](hipStream_t st, bool anchor, int par, auto&& tm, double cact) {
         if (p.svd) {
@@ -1192,6 +1212,14 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
             tm("k_zstep_fused", 0.0, 7.0 * n * cact * D, [&] {
                 lrr::launch_zstep_fused(sv[par], bst, b.it, b.mu_sched, st);
             });
+            if (tail) {
+                tm("k_svd_tail", 0.0, 0.0, [&] {
+                    const lrr::SvdTail z{b.Um, b.Qm, p.extra ? b.V : nullptr, b.boff, m, nfull, p.n_iter, fixed,
+                                         o.tol, rm, rn, b.tick, b.n_active};
+                    lrr::launch_svd_tail(sv[par], z, t, bst, b.it, b.mu_sched, st);
+                });
+                return;
+            }
             tm("k_svd_decide", 0.0, 0.0, [&] {
                 lrr::launch_svd_decide(b.boff, t, bst, b.r2nrm, b.expand1, b.expand, o.tol, rm, rn, p.n_iter, b.it,
                                        st);
@@ -1326,13 +1354,17 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
     // The J-step of small orders: Gram matrix, one workgroup per block for the
     // eigensolve, the weights and P, reconstruction
     auto small_jstep = [&](hipStream_t st, int par, auto&& tm, double cact) {
-        tm("k_block_fro", 0.0, cact * D, [&] { lrr::launch_block_fro(b.colsq, b.boff, t, bst, b.it, st); });
-        tm("k_dgemm_sym", 0.0, 0.0, [&] {
-            lrr::launch_dgemm_sym(b.g_gram + par * t, t, p.maxo, st, false, p.left);
-        });
+        if (!tail)   // else the end of the previous iteration decided who thresholds
+            tm("k_block_fro", 0.0, cact * D, [&] { lrr::launch_block_fro(b.colsq, b.boff, t, bst, b.it, st); });
+        const bool in = small_products(p);
+        if (!in)
+            tm("k_dgemm_sym", 0.0, 0.0, [&] {
+                lrr::launch_dgemm_sym(b.g_gram + par * t, t, p.maxo, st, false, p.left);
+            });
         tm("k_small_svt", 0.0, 0.0, [&] {
-            lrr::launch_small_svt(b.sme, t, p.maxo, bst, b.it, max_sweeps, st);
+            lrr::launch_small_svt(b.sme + par * t, t, p.maxo, bst, b.it, max_sweeps, st);
         });
+        if (in) return;
         tm("k_dgemm<false, false>", 0.0, 0.0, [&] {
             lrr::launch_dgemm(b.g_J + par * t, t, n, p.maxl, false, false, st);
         });

@@ -354,6 +354,105 @@ __global__ __launch_bounds__(256) void k_svd_expand(SvdStep a, const double* __r
     if ((threadIdx.x & 63) == 0 && mx > 0.0) atomic_max_nonneg(WHICH == 1 ? &bs.r1max[b] : &bs.r2max[b], mx);
 }
 
+// The end of an iteration of a small problem in one launch, one workgroup per block:
+// the decision of k_svd_decide, the expansions it asks for, the stop test, and
+// ||Y||_F against the next threshold; the last workgroup to finish advances the
+// iteration.  Five launches of about 3 us otherwise.
+template <int WHICH>
+__device__ double expand_max(const SvdStep& a, const double* __restrict__ basis, int rows,
+                             const double* __restrict__ D, int c0, int c1, double imu, double ratio, double* red) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, r = a.r;
+    double mx = 0.0;
+    for (int j = c0 + w; j < c1; j += 16) {
+        const long o = (long)j * r;
+        const double g1 = a.f1[2 * j + 1], y1 = ratio * a.f0[2 * j + 1];
+        for (int i = lane; i < rows; i += 64) {
+            double acc = 0.0, v = 0.0;
+#pragma unroll 4
+            for (int q = 0; q < r; ++q) {
+                v = WHICH == 1 ? g1 * a.q1[o + q] - y1 * a.q0[o + q] : a.Y21[o + q] * imu - a.Y20[o + q] * imu;
+                acc += basis[i + (long)q * rows] * v;
+            }
+            if (D) acc += D[i + (long)j * rows] * v;
+            mx = fmax(mx, fabs(acc));
+        }
+    }
+    mx = wave_max(mx);
+    __syncthreads();
+    if (lane == 0) red[w] = mx;
+    __syncthreads();
+    for (int q = 0; q < 16; ++q) mx = fmax(mx, red[q]);
+    return mx;
+}
+
+__global__ __launch_bounds__(1024) void k_svd_tail(SvdStep a, SvdTail z, BlockState bs, DevIter* it,
+                                                    const double* __restrict__ sched) {
+    __shared__ double red[48];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int k = it->k;
+    const double mu = it->mu, imu = 1.0 / mu, ratio = k > 0 ? sched[k - 1] / mu : 1.0;
+    const bool last = k + 1 >= z.n_iter, act = bs.active[b] != 0;
+    if (act) {
+        const int c0 = z.boff[b], c1 = z.boff[b + 1];
+        double x1 = 0.0, x2 = 0.0, fro = 0.0;
+        for (int c = c0 + tid; c < c1; c += 1024) {
+            x1 = fmax(x1, bs.colr1[c]);
+            x2 = fmax(x2, bs.colr2[c]);
+            fro += a.colsq[c];
+        }
+        x1 = wave_max(x1);
+        x2 = wave_max(x2);
+        fro = wave_sum(fro);
+        if (lane == 0) {
+            red[w] = x1;
+            red[16 + w] = x2;
+            red[32 + w] = fro;
+        }
+        __syncthreads();
+        fro = 0.0;
+        for (int q = 0; q < 16; ++q) {
+            x1 = fmax(x1, red[q]);
+            x2 = fmax(x2, red[16 + q]);
+            fro += red[32 + q];
+        }
+        const double tol = z.tol;
+        const bool lo1 = x1 >= z.sqrt_m * tol, lo2 = x2 >= z.sqrt_n * tol;
+        // lower bounds that decide must not round below tol
+        double r1 = lo1 ? fmax(x1 / z.sqrt_m, tol) : x1 / z.sqrt_m;
+        double r2 = x2 < tol ? x2 : (lo2 ? fmax(x2 / z.sqrt_n, tol) : x2 / z.sqrt_n);
+        if (!(lo1 || lo2) || last) {
+            r1 = expand_max<1>(a, z.U, z.m, z.D, c0, c1, imu, ratio, red);
+            if ((r1 < tol || last) && x2 >= tol && !lo2)
+                r2 = expand_max<2>(a, z.Q, z.n, nullptr, c0, c1, imu, ratio, red);
+        }
+        if (tid == 0) {
+            bs.res1[b] = r1;
+            bs.res2[b] = r2;
+            bs.iters[b] = k + 1;
+            const bool stop = !z.fixed && r1 < tol && r2 < tol;
+            if (stop) bs.active[b] = 0;
+            else atomicAdd(&z.tick[1], 1);
+            // sigma_max <= ||Y||_F, so ||Y||_F <= tau gives J = 0 without a decomposition
+            const bool run = !stop && !last && sqrt(fro) > 1.0 / sched[k + 1];
+            if (!last) {
+                bs.svt_run[b] = run ? 1 : 0;
+                if (!stop && !run) bs.rank[b] = 0;
+            }
+        }
+    }
+    if (tid == 0) {
+        __threadfence();
+        if (atomicAdd(&z.tick[0], 1) == (int)gridDim.x - 1) {
+            __threadfence();
+            *z.n_active = atomicExch(&z.tick[1], 0);
+            z.tick[0] = 0;
+            it->k = k + 1;
+            it->mu = sched[k + 1];
+            it->tau = 1.0 / sched[k + 1];
+        }
+    }
+}
+
 // Results of a finished solve, per block from the buffers its last pass wrote
 // (iters passes: buffer iters & 1):  what = 0: E = f q;  what = 1: Z = Y - Y2/mu'
 // (mu' the penalty after the last iteration).
@@ -484,6 +583,10 @@ void launch_svd_expand(const SvdStep& a, int which, const double* basis, int row
     else
         hipLaunchKernelGGL((k_svd_expand<2>), grid, dim3(256), 0, s, a, basis, rows, D, boff, bs, x2max, expand1, tol,
                            sqrt_n, n_iter, it, sched);
+}
+void launch_svd_tail(const SvdStep& a, const SvdTail& z, int t, const BlockState& bs, DevIter* it,
+                     const double* sched, hipStream_t s) {
+    hipLaunchKernelGGL(k_svd_tail, dim3(t), dim3(1024), 0, s, a, z, bs, it, sched);
 }
 void launch_svd_outside(const double* T, int m, int c, double* D, double* len, hipStream_t s) {
     hipLaunchKernelGGL(k_svd_outside, dim3((c + 3) / 4), dim3(256), 0, s, T, m, c, D, len);
