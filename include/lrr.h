@@ -136,7 +136,9 @@ typedef struct {
     int check_every;         /* read device convergence flags every c iterations   */
     int max_sweeps;          /* Jacobi sweep cap of the eigensolver (default 30)    */
     int save_for_backward;   /* record what dfc_lrr_backward needs                  */
-    int checkpoint_every;    /* adjoint checkpoint spacing k (default 20)           */
+    int checkpoint_every;    /* adjoint checkpoint spacing k (default 20); not used */
+                             /* where every iteration's record fits into 16 GiB and */
+                             /* an eighth of the free memory: all are then kept     */
     int eig_block;           /* Jacobi block width: 0 auto, 16 or 32                */
     int use_graph;           /* how an iteration is issued:                         */
                              /*  0: the J-step's decisions (blocks to threshold,    */
