@@ -61,6 +61,7 @@ struct PairLds {
     static constexpr int NBUF = BS == 16 ? 2 : 1;   // 32-wide blocks would not fit twice
     double S[NBUF][PB][PB + 8];
     double R[PB][PB + 1];
+    double c[2][BS], s[2][BS];   // rotations of two consecutive steps (SPLIT)
     unsigned long long lo;   // bit i: index i lies below the cut
     int any;                 // 1: a coupling between the two index blocks, 2: inside one
 };
@@ -109,6 +110,7 @@ __device__ void pair_solve(const EigDesc& d, int round, int P, int sched, int ws
     constexpr bool SPLIT = NT >= 2 * NP * NP;      // separate waves for S and R
     constexpr int NS = SPLIT ? NP * NP : NT;       // threads on S
     constexpr int NR = SPLIT ? NT - NS : NT;       // threads on R
+    static_assert(!SPLIT || NBUF == 2, "the waves on R meet one barrier a step");
     static_assert(64 % NP == 0 && NS % 64 == 0 && (NP * NP) % NS == 0 && (PB * NP) % NR == 0, "thread layout");
     constexpr int IS = NP * NP / NS, IR = PB * NP / NR;
     const int nb = d.L / BS;
@@ -166,7 +168,28 @@ __device__ void pair_solve(const EigDesc& d, int round, int P, int sched, int ws
     const int st0 = inside ? 0 : BS - 1, st1 = cross ? 2 * BS - 1 : BS - 1;
     const int k = lane % NP;
     int cur = 0;
+    // With separate waves the rotations of R follow one step behind those of S, from
+    // LDS: the waves on R then compute no rotations of their own (the redundant ones
+    // of every wave on S already fill half of a SIMD's issue slots).
+    auto rotate_R = [&](int st) {
+        int aQ, bQ;
+        step_pair<BS>(st, k, aQ, bQ);
+        const double c = sm.c[st & 1][k], s = sm.s[st & 1][k];
+#pragma unroll
+        for (int u = 0; u < IR; ++u) {
+            const int i = (tid - NS + u * NR) / NP;
+            const double ra = sm.R[i][aQ], rb = sm.R[i][bQ];
+            sm.R[i][aQ] = c * ra - s * rb;
+            sm.R[i][bQ] = s * ra + c * rb;
+        }
+    };
     for (int st = st0; st < st1; ++st) {
+        if (SPLIT && tid >= NS) {
+            if (st > st0) rotate_R(st - 1);
+            __syncthreads();
+            if (NBUF == 2) cur ^= 1;
+            continue;
+        }
         auto& S = sm.S[cur];
         auto& Sn = sm.S[NBUF == 2 ? cur ^ 1 : 0];
         int aQ, bQ;
@@ -185,9 +208,13 @@ __device__ void pair_solve(const EigDesc& d, int round, int P, int sched, int ws
                 s = sr;
             }
         }
+        if (SPLIT && tid < NP) {
+            sm.c[st & 1][k] = c;
+            sm.s[st & 1][k] = s;
+        }
         double w[IS][4];
         // the sub-matrix: (P2, Q2) blocks of the step's 2 x 2 index pairs
-        if (!SPLIT || tid < NS) {
+        {
 #pragma unroll
             for (int u = 0; u < IS; ++u) {
                 const int P2 = (tid + u * NS) / NP;
@@ -207,7 +234,7 @@ __device__ void pair_solve(const EigDesc& d, int round, int P, int sched, int ws
             }
         }
         if (NBUF == 1) __syncthreads();   // one buffer: every read before the first write
-        if (!SPLIT || tid < NS) {
+        {
 #pragma unroll
             for (int u = 0; u < IS; ++u) {
                 const int P2 = (tid + u * NS) / NP;
@@ -220,11 +247,10 @@ __device__ void pair_solve(const EigDesc& d, int round, int P, int sched, int ws
             }
         }
         // the accumulated rotation: row i, columns of pair Q2
-        if (!SPLIT || tid >= NS) {
-            const int t0 = SPLIT ? tid - NS : tid;
+        if (!SPLIT) {
 #pragma unroll
             for (int u = 0; u < IR; ++u) {
-                const int i = (t0 + u * NR) / NP;
+                const int i = (tid + u * NR) / NP;
                 const double ra = sm.R[i][aQ], rb = sm.R[i][bQ];
                 sm.R[i][aQ] = c * ra - s * rb;
                 sm.R[i][bQ] = s * ra + c * rb;
@@ -232,6 +258,10 @@ __device__ void pair_solve(const EigDesc& d, int round, int P, int sched, int ws
         }
         __syncthreads();
         if (NBUF == 2) cur ^= 1;
+    }
+    if (SPLIT) {
+        if (tid >= NS) rotate_R(st1 - 1);
+        __syncthreads();
     }
     if (tid == 0 && d.work) {
         // per step: NP angles (~30 operations), NP^2 2x2 updates (24), PB*NP rotations of R (6)
