@@ -162,6 +162,7 @@ struct SvdStep {
     double *colsq;                  // per column |Y'|^2
     const int* colblk;
     int r, ncols;
+    int dstride;                    // 0: one dictionary; else block b's d and dinv start at b * dstride (even)
     double lam;
 };
 

@@ -162,6 +162,7 @@ void launch_svd_expand(const SvdStep& a, int which, const double* basis, int row
 void launch_svd_tail(const SvdStep& a, const SvdTail& z, int t, const BlockState& bs, DevIter* it,
                      const double* sched, hipStream_t s);
 void launch_svd_outside(const double* T, int m, int c, double* D, double* len, hipStream_t s);
+void launch_svd_pad_cols(const double* Xs, int rows, double* X, int ldx, int cols, hipStream_t s);
 void launch_svd_set_row(double* X, int row, int ld, int c, const double* v, hipStream_t s);
 void launch_svd_add_outside(double* out, long ldo, int m, int c, const double* D, const double* R, int r,
                             const int* map, hipStream_t s);

@@ -201,6 +201,11 @@ struct Plan {
     // every block its own dictionary (the observations C_b, Section 2.2 footnote):
     // the iterates of block b use rows [0, l_b) of maxl rows, K is per block
     bool local = false;
+    // ... in singular coordinates of each block's own dictionary (build_local_bases
+    // decides): rows of the iterates = the largest rank, d per block
+    bool lsvd = false;
+    std::vector<int> rb;         // rank of each block's dictionary
+    int dstride() const { return (maxl + 1) & ~1; }
     // Z-step in the literal form: the n x n inverse of I + A^T A (full
     // coordinates, FP64 products) instead of the m x m one of I + A A^T
     bool literal = false;
@@ -219,6 +224,7 @@ struct Buffers {
     unsigned long long* r2nrm;
     // singular coordinates: left basis (m x r), U^T A (r x n), diagonal, per-column factors, and
     // the two buffers of each alternating array (aliases of the general form's arrays)
+    double *LU, *LQ, *Ld, *Ldinv;   // per block: left and right bases, d, 1 / (1 + d^2)
     double *Um, *Ut, *Ares, *Cr, *dsig, *dinv, *fcol[2], *Yp[2], *Y2p[2], *qp[2], *Rr;
     unsigned long long* stat;
     int *expand1, *tick;
@@ -390,8 +396,16 @@ size_t layout(const Plan& p, char* base, Buffers& b, int with_combine, bool need
     } else {
         b.U = b.H = nullptr;
     }
-    if (p.reduced) {
+    if (p.reduced || p.lsvd) {
         const size_t Lm = p.Lm;
+        // bases of one dictionary: the common one, or the largest of the blocks' own
+        const size_t n = p.lsvd ? std::min(p.m, p.maxl) + 1 : p.nrb, nfull = p.lsvd ? p.maxl : p.n;
+        if (p.lsvd) {
+            b.LU = a.take<double>(m * c);
+            b.LQ = a.take<double>(nfull * c);
+            b.Ld = a.take<double>(t * p.dstride());
+            b.Ldinv = a.take<double>(t * p.dstride());
+        }
         b.Qm = a.take<double>(nfull * n);
         b.Qtmp = a.take<double>(nfull * n);
         b.Mr = a.take<double>(m * n);
@@ -609,6 +623,14 @@ Plan make_plan(const Problem& pr) {
         // beyond l_b meet zero dictionary columns and stay exactly zero
         p.reduced = p.ext = false;
         p.nrb = p.maxl;
+        // each block's own singular coordinates: its Gram matrix is r_b x r_b and its
+        // Z-step has no products.  m = 500, 4 blocks of 500 points: 265 -> 102 ms where
+        // the rank is 225, 293 -> 293 at full rank; 8 of 250: 165 -> 156.  Many large
+        // blocks at full rank don't earn their bases back (40 of 100 points, m = 100:
+        // 141 -> 148, at rank 20 169 -> 36); up to kSmallEig a basis is a few launches
+        // (40 of 50 points: 199 -> 78).
+        p.lsvd = pr.o.precision == LRR_FP64 && coords == LRR_COORDS_AUTO && pr.o.solve_form == LRR_SOLVE_AUTO &&
+                 pr.t <= (std::min(pr.m, p.maxl) <= lrr::kSmallEig ? 64 : 8);
     }
     // literal Z-step: on request, or automatically when the dictionary is at
     // least as tall as wide (then n x n is the smaller factorisation); the
@@ -621,7 +643,7 @@ Plan make_plan(const Problem& pr) {
     p.ks = p.literal ? pr.n : pr.m;
     p.nr = p.nrb;
     p.bq = 16;   // 32 above order 512 measured slower (order 2016: 180 against 110 ms for the basis)
-    p.Lm = round_up(std::min(pr.m, pr.n), 2 * p.bq);
+    p.Lm = round_up(std::min(pr.m, p.local ? p.maxl : pr.n), 2 * p.bq);
     return p;
 }
 
@@ -705,6 +727,8 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     for (int i = 0; i < Lr; ++i) lo[i] = i >= r ? 1 : 0;
     const EigDesc ed{b.Gb, b.Wq, b.Rq, b.lamq, Lr, r, b.runq, b.stq, b.scaleq, b.protq, b.loq, nullptr, nullptr, nullptr,
                      nullptr, nullptr, b.B2q};
+    const int on = 1;
+    LRR_HIP(hipMemcpyAsync(b.runq, &on, sizeof(int), hipMemcpyHostToDevice, s));
     LRR_HIP(hipMemcpyAsync(b.loq, lo.data(), sizeof(int) * Lr, hipMemcpyHostToDevice, s));
     LRR_HIP(hipMemcpyAsync(b.eq, &ed, sizeof(EigDesc), hipMemcpyHostToDevice, s));
     LRR_HIP(hipMemsetAsync(b.scaleq, 0, sizeof(double), s));
@@ -785,6 +809,26 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     LRR_HIP(hipStreamSynchronize(s));   // host value goes out of scope
 }
 
+// Kept eigenpairs of the smaller Gram matrix (eigenvalues dlam, eigenvectors in b.Wq with
+// leading dimension p.Lm), then the bases.
+void pick_basis(const Problem& pr, Plan& p, Buffers& b, const double* dlam, hipStream_t s) {
+    const int side = std::min(p.m, p.n);
+    std::vector<double> lam(side);
+    LRR_HIP(hipMemcpyAsync(lam.data(), dlam, sizeof(double) * side, hipMemcpyDeviceToHost, s));
+    LRR_HIP(hipStreamSynchronize(s));
+    double lmax = 0.0;
+    for (int i = 0; i < side; ++i) lmax = std::max(lmax, lam[i]);
+    std::vector<int> idx;
+    for (int i = 0; i < side; ++i)
+        if (lam[i] > kRankCut * lmax) idx.push_back(i);
+    std::stable_sort(idx.begin(), idx.end(), [&](int x, int y) { return lam[x] > lam[y]; });
+    if (idx.empty()) idx.push_back(0);     // M = 0: a single zero column (scaled by 0 below)
+    const int r = (int)idx.size();
+    p.nr = r;
+    LRR_HIP(hipMemcpyAsync(b.idxq, idx.data(), sizeof(int) * r, hipMemcpyHostToDevice, s));
+    finish_basis(pr, p, b, s);
+}
+
 void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     const int Lm = p.Lm, bq = p.bq, side = std::min(p.m, p.n);
     const bool tall = p.n < p.m;
@@ -820,20 +864,105 @@ void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
         lrr::launch_jacobi_rounds(b.eq, 1, Lm, bq, Lm / bq - 1, s);
     }
     if (!small) lrr::launch_jacobi_eigvals(b.eq, 1, s);
-    std::vector<double> lam(Lm);
-    LRR_HIP(hipMemcpyAsync(lam.data(), b.lamq, sizeof(double) * Lm, hipMemcpyDeviceToHost, s));
-    LRR_HIP(hipStreamSynchronize(s));
-    double lmax = 0.0;
-    for (int i = 0; i < side; ++i) lmax = std::max(lmax, lam[i]);
-    std::vector<int> idx;
-    for (int i = 0; i < side; ++i)
-        if (lam[i] > kRankCut * lmax) idx.push_back(i);
-    std::stable_sort(idx.begin(), idx.end(), [&](int x, int y) { return lam[x] > lam[y]; });
-    if (idx.empty()) idx.push_back(0);     // M = 0: a single zero column (scaled by 0 below)
-    const int r = (int)idx.size();
-    p.nr = r;
-    LRR_HIP(hipMemcpyAsync(b.idxq, idx.data(), sizeof(int) * r, hipMemcpyHostToDevice, s));
-    finish_basis(pr, p, b, s);
+    pick_basis(pr, p, b, b.lamq, s);
+}
+
+// Bases of every block's own dictionary C_b (m x l_b, also its observations), kept in
+// b.LU, b.LQ, b.Ld; U_b^T C_b, padded to the largest rank, goes to b.X.  False when
+// some block misses the accuracy of singular coordinates: the general form runs.
+bool build_local_bases(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
+    const int m = p.m, c = p.ncols, t = p.t, ds = p.dstride();
+    lrr::launch_gather_cols(pr.A, pr.lda, b.V, m, m, c, b.perm, s);
+    LRR_HIP(hipMemsetAsync(b.Ld, 0, sizeof(double) * t * ds, s));
+    LRR_HIP(hipMemsetAsync(b.Ldinv, 0, sizeof(double) * t * ds, s));
+    p.rb.assign(t, 0);
+    // the eigen-decompositions of all blocks in the same launches, in the blocks' own
+    // arrays of the iteration (order min(m, l_b) <= l_b); up to kSmallEig one block is
+    // a single launch anyway (4 blocks of 500 points, the whole solve: 133 -> 102 ms)
+    const bool batch = std::min(m, p.maxl) > lrr::kSmallEig;
+    if (batch) {
+        std::vector<GemmDesc> gg(t);
+        std::vector<EigDesc> ed(t);
+        std::vector<int> ones(t, 1);
+        int maxL = 0;
+        for (int bb = 0; bb < t; ++bb) {
+            const int l = p.boff[bb + 1] - p.boff[bb], L = p.L[bb], side = std::min(m, l);
+            const double* C = b.V + (size_t)p.boff[bb] * m;
+            std::vector<int> lo(L);
+            for (int i = 0; i < L; ++i) lo[i] = i >= side ? 1 : 0;
+            LRR_HIP(hipMemcpyAsync(b.lo[bb], lo.data(), sizeof(int) * L, hipMemcpyHostToDevice, s));
+            gg[bb] = GemmDesc{C, C, b.Bq[bb], side, side, std::max(m, l), m, m, L, 1.0, 0.0, nullptr, nullptr};
+            ed[bb] = EigDesc{b.Bq[bb], b.Wm[bb], b.Rm[bb], b.lam[bb], L, side, b.svt_run + bb, b.eigst + 2 * bb,
+                             b.eigscale + bb, b.prot[bb], b.lo[bb], nullptr, nullptr, nullptr, nullptr, nullptr, b.XE[bb]};
+            LRR_HIP(hipMemsetAsync(b.Bq[bb], 0, sizeof(double) * L * L, s));
+            lrr::launch_set_identity(b.Wm[bb], L, s);
+            maxL = std::max(maxL, L);
+        }
+        LRR_HIP(hipMemcpyAsync(b.svt_run, ones.data(), sizeof(int) * t, hipMemcpyHostToDevice, s));
+        LRR_HIP(hipMemcpyAsync(b.g_gram, gg.data(), sizeof(GemmDesc) * t, hipMemcpyHostToDevice, s));
+        LRR_HIP(hipMemcpyAsync(b.eig, ed.data(), sizeof(EigDesc) * t, hipMemcpyHostToDevice, s));
+        for (int bb = 0; bb < t; ++bb)
+            lrr::launch_dgemm(b.g_gram + bb, 1, gg[bb].M, gg[bb].N, gg[bb].M < m, gg[bb].M == m, s);
+        lrr::launch_jacobi_init(b.eig, t, s);
+        for (int sw = 0, any = 1; sw < 80; ++sw) {
+            LRR_HIP(hipMemsetAsync(b.eig_any, 0, sizeof(int), s));
+            lrr::launch_jacobi_check(b.eig, t, maxL, b.eig_any, s);
+            LRR_HIP(hipMemcpyAsync(&any, b.eig_any, sizeof(int), hipMemcpyDeviceToHost, s));
+            LRR_HIP(hipStreamSynchronize(s));
+            if (any == 0) break;
+            lrr::launch_jacobi_rounds(b.eig, t, maxL, p.bs, maxL / p.bs - 1, s);
+        }
+        lrr::launch_jacobi_eigvals(b.eig, t, s);
+    }
+    int nr = 1;
+    for (int bb = 0; bb < t; ++bb) {
+        const int l = p.boff[bb + 1] - p.boff[bb];
+        const size_t om = (size_t)p.boff[bb] * m;
+        const int offs[2] = {0, l};
+        Problem one{m, l, l, 1, b.V + om, m, b.V + om, m, nullptr, offs, pr.lam, pr.o};
+        Plan po;
+        po.m = m; po.n = l; po.ncols = l; po.t = 1; po.bq = p.bq;
+        po.Lm = round_up(std::min(m, l), 2 * p.bq);
+        po.reduced = true;
+        Buffers bo = b;
+        bo.X = b.E + om;   // r x l, kept until the largest rank is known
+        if (batch) {
+            bo.Wq = b.Wm[bb];   // then scratch of an order <= l_b
+            po.Lm = p.L[bb];
+            pick_basis(one, po, bo, b.lam[bb], s);
+        } else {
+            build_basis(one, po, bo, s);
+        }
+        if (!po.svd || po.extra) return false;
+        const int r = po.nr;
+        p.rb[bb] = r;
+        nr = std::max(nr, r);
+        LRR_HIP(hipMemcpyAsync(b.LU + om, bo.Um, sizeof(double) * m * r, hipMemcpyDeviceToDevice, s));
+        LRR_HIP(hipMemcpyAsync(b.LQ + (size_t)p.boff[bb] * p.maxl, bo.Qm, sizeof(double) * l * r,
+                               hipMemcpyDeviceToDevice, s));
+        LRR_HIP(hipMemcpyAsync(b.Ld + (size_t)bb * ds, bo.dsig, sizeof(double) * r, hipMemcpyDeviceToDevice, s));
+        LRR_HIP(hipMemcpyAsync(b.Ldinv + (size_t)bb * ds, bo.dinv, sizeof(double) * r, hipMemcpyDeviceToDevice, s));
+    }
+    p.svd = true;
+    p.nr = nr;
+    for (int bb = 0; bb < t; ++bb) {
+        const int l = p.boff[bb + 1] - p.boff[bb], r = p.rb[bb];
+        lrr::launch_svd_pad_cols(b.E + (size_t)p.boff[bb] * m, r, b.X + (size_t)p.boff[bb] * nr, nr, l, s);
+        p.left |= r < l;
+    }
+    // Y_b Y_b^T (r_b x r_b) is never the larger one, r_b <= l_b
+    if (p.left) {
+        p.maxL = p.maxo = 0;
+        for (int bb = 0; bb < t; ++bb) {
+            p.ord[bb] = p.rb[bb];
+            p.L[bb] = round_up(p.rb[bb], 2 * p.bs);
+            p.maxL = std::max(p.maxL, p.L[bb]);
+            p.maxo = std::max(p.maxo, p.rb[bb]);
+        }
+    }
+    p.small = p.maxo <= lrr::kSmallEig;
+    LRR_HIP(hipMemsetAsync(b.R2full, 0, sizeof(double) * p.maxl * (size_t)c, s));   // rows beyond l_b
+    return true;
 }
 
 bool small_products(const Plan& p);
@@ -882,9 +1011,10 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         p = make_plan(full);
         lay_out();
     }
+    if (p.lsvd) build_local_bases(pr, p, b, s);
     if (p.reduced) {}
     else if (!p.local) p.nr = n;
-    if (p.svd) choose_gram(p);
+    if (p.svd && !p.local) choose_gram(p);
     const int nr = p.nr;
     // dictionary of the Z-step products: M, or Mr = M Qm in reduced coordinates
     const double* Md = p.reduced ? b.Mr : pr.A;
@@ -925,7 +1055,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
             // Y^T Y and J = Y P, or Y Y^T and J = P Y
             gram[y * t + bb] = GemmDesc{Yb, Yb, b.Bm[bb], e, e, p.left ? l : nr, nr, nr, L, 1.0, 0.0, erun, nullptr};
             gJ[y * t + bb] = p.left
-                ? GemmDesc{b.Pm[bb], Yb, Jb, nr, l, nr, L, nr, nr, 1.0, 0.0, run, nullptr}
+                ? GemmDesc{b.Pm[bb], Yb, Jb, e, l, e, L, nr, nr, 1.0, 0.0, run, nullptr}
                 : GemmDesc{Yb, b.Pm[bb], Jb, nr, l, l, nr, L, nr, 1.0, 0.0, run, nullptr};
         }
         // refinement: T = B X, S = X^T T, G = X^T X (symmetric kernel), XE = X E
@@ -962,7 +1092,12 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         if (p.reduced)   // expansion of the coupling residual: R2 = Qm R2r
             gExp[bb] = GemmDesc{b.Qm, (p.svd ? b.Rr : b.R2r) + o_n, b.R2full + (size_t)p.boff[bb] * n, n, l, nr, n, nr, n, 1.0,
                                 0.0, b.expand + bb, nullptr};
-        if (p.svd)       // and of the primal one: R1 = U R1r
+        if (p.svd && p.local) {
+            gExp[bb] = GemmDesc{b.LQ + (size_t)p.boff[bb] * p.maxl, b.Rr + o_n, b.R2full + (size_t)p.boff[bb] * p.maxl,
+                                l, l, p.rb[bb], l, nr, p.maxl, 1.0, 0.0, b.expand + bb, nullptr};
+            gExp1[bb] = GemmDesc{b.LU + o_m, b.Rr + o_n, b.T + o_m, m, l, p.rb[bb], m, nr, m, 1.0, 0.0,
+                                 b.expand1 + bb, nullptr};
+        } else if (p.svd)       // and of the primal one: R1 = U R1r
             gExp1[bb] = GemmDesc{b.Um, b.Rr + o_n, b.T + o_m, m, l, nr, m, nr, m, 1.0, 0.0, b.expand1 + bb, nullptr};
         eig[bb] = EigDesc{b.Bq[bb], X, b.Rm[bb], b.lam[bb], L, e, erun, b.eigst + 2 * bb,
                           b.eigscale + bb, b.prot[bb], b.lo[bb], ctx->dwork, b.locut + bb, b.passes + bb,
@@ -1016,7 +1151,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
         const GemmDesc gF1{b.K, pr.A, b.F1, n, m, n, n, (int)pr.lda, n, 1.0, 0.0, nullptr, nullptr};
         up(b.g_F1, &gF1, sizeof(GemmDesc));
     }
-    if (p.reduced) up(b.g_exp, gExp.data(), sizeof(GemmDesc) * t);
+    if (p.reduced || p.svd) up(b.g_exp, gExp.data(), sizeof(GemmDesc) * t);
     if (p.svd) up(b.g_exp1, gExp1.data(), sizeof(GemmDesc) * t);
 
     if (!gKK.empty()) up(b.g_KK, gKK.data(), sizeof(GemmDesc) * gKK.size());
@@ -1081,7 +1216,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
     LRR_HIP(hipMemsetAsync(b.r2max, 0, sizeof(unsigned long long) * t, s));
     LRR_HIP(hipMemsetAsync(b.res1, 0, sizeof(double) * t, s));
     LRR_HIP(hipMemsetAsync(b.res2, 0, sizeof(double) * t, s));
-    if (p.reduced) LRR_HIP(hipMemsetAsync(b.r2nrm, 0, sizeof(unsigned long long) * t, s));
+    if (p.reduced || p.svd) LRR_HIP(hipMemsetAsync(b.r2nrm, 0, sizeof(unsigned long long) * t, s));
     // a recorded forward resolves every eigenpair where it is not replayed
     lrr::launch_init_iter(b.it, b.mu_sched, 0, s, pr.record_all);
 
@@ -1115,7 +1250,10 @@ bool small_products(const Plan& p) { return p.small && (p.left ? p.maxl : p.nr) 
 SvdStep svd_step(const Plan& p, const Buffers& b, int par, double lam) {
     SvdStep a{};
     if (!p.svd) return a;
-    a.X = b.X; a.J = b.J; a.d = b.dsig; a.dinv = b.dinv;
+    a.X = b.X; a.J = b.J;
+    a.d = p.local ? b.Ld : b.dsig;
+    a.dinv = p.local ? b.Ldinv : b.dinv;
+    a.dstride = p.local ? p.dstride() : 0;
     a.q0 = b.qp[par]; a.Y20 = b.Y2p[par]; a.f0 = b.fcol[par];
     a.q1 = b.qp[par ^ 1]; a.Y21 = b.Y2p[par ^ 1]; a.f1 = b.fcol[par ^ 1];
     a.Y0 = b.Yp[par]; a.Y1 = b.Yp[par ^ 1];
@@ -1137,7 +1275,7 @@ struct IterHooks {
 Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t s, int k0, int k1,
                    const IterHooks* hooks = nullptr) {
     // n: rows of the iterates (the numerical rank of M in reduced coordinates)
-    const int m = p.m, n = p.nr, nfull = p.n, c = p.ncols, t = p.t;
+    const int m = p.m, n = p.nr, nfull = p.local ? p.maxl : p.n, c = p.ncols, t = p.t;
     const lrr_opts& o = pr.o;
     // targeted Jacobi rounds: per-block offsets of the check marks and schedules
     std::vector<size_t> need_off(t + 1, 0), sched_off(t + 1, 0);
@@ -1200,7 +1338,7 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
     if (device_loop && !p.small) (void)lrr::jacobi_solve_grid(p.bs);
     if (p.small) lrr::small_eig_prepare();
     // both bases within 2 MB: formed in one launch per residual instead of three
-    const bool small_expand = p.svd && (size_t)m * n <= 65536 && (size_t)nfull * n <= 262144;
+    const bool small_expand = p.svd && !p.local && (size_t)m * n <= 65536 && (size_t)nfull * n <= 262144;
     // the whole end of an iteration in one launch where a workgroup forms a block's
     // residuals quickly (they are needed in the last iterations only): m = 48, n = 96,
     // blocks of 32 points, 15 -> 7 us an iteration; m = 100, n = 200, one block of 200
@@ -1325,7 +1463,9 @@ Result iterate_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStre
             lrr::launch_xgemm(b.g_MtV, t, n, p.maxl, true, false, pm.MtV, st);
         });
         tm("k_update_Z", 0.0, (p.reduced ? 7.0 : 6.0) * n * cact * D, [&] {
-            lrr::launch_update_Z(b.Q, b.MtV, b.J, b.Z, b.Y2, b.R2r, b.r2nrm, n, n, c, b.colblk, bst, b.it, st);
+            // residual norms of the coefficients in reduced coordinates only
+            lrr::launch_update_Z(b.Q, b.MtV, b.J, b.Z, b.Y2, p.reduced ? b.R2r : nullptr,
+                                 p.reduced ? b.r2nrm : nullptr, n, n, c, b.colblk, bst, b.it, st);
         });
         if (p.reduced) {
             // max-norm of R2 = Qm R2r: decided by the column 2-norm bounds, else expanded
@@ -1825,8 +1965,7 @@ int combine_local(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, const Re
         if (r.rank[bb] == 0 || r.iters[bb] == 0) continue;   // J_b = 0 (exact zero test)
         rmax = std::max(rmax, r.rank[bb]);
         const double tau = 1.0 / sched[r.iters[bb] - 1];
-        const int l = p.boff[bb + 1] - p.boff[bb];
-        for (int i = 0; i < l; ++i)
+        for (int i = 0; i < p.ord[bb]; ++i)
             if (h[bb][i] > 0.0) pool.push_back(Cand{std::sqrt(std::max(lam[bb][i], 0.0)) - tau, bb, i});
     }
     const int total = (int)pool.size();
@@ -1834,24 +1973,41 @@ int combine_local(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, const Re
     std::stable_sort(pool.begin(), pool.end(), [](const Cand& x, const Cand& y) { return x.sv > y.sv; });
     std::vector<std::vector<double>> mask(t);
     for (int bb = 0; bb < t; ++bb) mask[bb].assign(p.L[bb], 0.0);
-    for (int q = 0; q < k; ++q) mask[pool[q].b][pool[q].i] = 1.0;
-    std::vector<GemmDesc> gP(t), gJ(t);
+    for (int q = 0; q < k; ++q) {
+        const Cand& x = pool[q];
+        // in singular coordinates the eigenvectors are scaled here, by g m
+        mask[x.b][x.i] = p.svd ? 1.0 - h[x.b][x.i] / sched[r.iters[x.b] - 1] : 1.0;
+    }
+    std::vector<GemmDesc> gP(t), gJ(t), gZ(t);
     for (int bb = 0; bb < t; ++bb) {
-        const int l = p.boff[bb + 1] - p.boff[bb], L = p.L[bb];
+        const int l = p.boff[bb + 1] - p.boff[bb], L = p.L[bb], e = p.ord[bb];
+        const size_t on = (size_t)p.boff[bb] * nr;
         // the mask goes into h (no longer needed), then Wg <- Wg diag(mask)
         LRR_HIP(hipMemcpyAsync(b.h[bb], mask[bb].data(), sizeof(double) * L, hipMemcpyHostToDevice, s));
+        if (p.svd) lrr::launch_copy_cols(b.Wm[bb], L, b.Wg[bb], L, L, L, s);
         lrr::launch_scale_cols(b.Wg[bb], L, L, L, b.h[bb], s);
-        gP[bb] = GemmDesc{b.Wg[bb], b.Wm[bb], b.Pm[bb], l, l, L, L, L, L, 1.0, 0.0, nullptr, nullptr};
-        gJ[bb] = GemmDesc{b.Y + (size_t)p.boff[bb] * nr, b.Pm[bb], b.J + (size_t)p.boff[bb] * nr, nr, l, l, nr, L,
-                          nr, 1.0, 0.0, nullptr, nullptr};
+        gP[bb] = GemmDesc{b.Wg[bb], b.Wm[bb], b.Pm[bb], e, e, L, L, L, L, 1.0, 0.0, nullptr, nullptr};
+        // the input of the block's last thresholding step
+        const double* Yb = (p.svd ? b.Yp[(r.iters[bb] + 1) & 1] : b.Y) + on;
+        gJ[bb] = p.left ? GemmDesc{b.Pm[bb], Yb, b.J + on, e, l, e, L, nr, nr, 1.0, 0.0, nullptr, nullptr}
+                        : GemmDesc{Yb, b.Pm[bb], b.J + on, nr, l, l, nr, L, nr, 1.0, 0.0, nullptr, nullptr};
+        if (p.svd)   // Z_b = Qm_b J_b
+            gZ[bb] = GemmDesc{b.LQ + (size_t)p.boff[bb] * p.maxl, b.J + on, b.R2full + (size_t)p.boff[bb] * p.maxl, l, l,
+                              p.rb[bb], l, nr, p.maxl, 1.0, 0.0, nullptr, nullptr};
     }
     LRR_HIP(hipMemcpyAsync(b.g_P, gP.data(), sizeof(GemmDesc) * t, hipMemcpyHostToDevice, s));
     LRR_HIP(hipMemcpyAsync(b.g_J, gJ.data(), sizeof(GemmDesc) * t, hipMemcpyHostToDevice, s));
     LrrProf& prof = ctx->prof;
-    prof.run(s, "k_dgemm<false, true>", 0.0, 0.0, [&] { lrr::launch_dgemm(b.g_P, t, p.maxl, p.maxl, false, true, s); });
+    prof.run(s, "k_dgemm<false, true>", 0.0, 0.0, [&] { lrr::launch_dgemm(b.g_P, t, p.maxo, p.maxo, false, true, s); });
     prof.run(s, "k_dgemm<false, false>", 0.0, 0.0, [&] { lrr::launch_dgemm(b.g_J, t, nr, p.maxl, false, false, s); });
-    for (int j = 0; j < n; ++j) LRR_HIP(hipMemsetAsync(Zo + (size_t)j * ldz, 0, sizeof(double) * n, s));
-    lrr::launch_scatter_block_diag(b.J, nr, c, b.colblk, b.boff, b.perm, Zo, ldz, s);
+    LRR_HIP(hipMemset2DAsync(Zo, sizeof(double) * (size_t)ldz, 0, sizeof(double) * n, n, s));
+    if (p.svd) {
+        LRR_HIP(hipMemcpyAsync(b.g_exp, gZ.data(), sizeof(GemmDesc) * t, hipMemcpyHostToDevice, s));
+        lrr::launch_dgemm(b.g_exp, t, p.maxl, p.maxl, false, false, s);
+        lrr::launch_scatter_block_diag(b.R2full, p.maxl, c, b.colblk, b.boff, b.perm, Zo, ldz, s);
+    } else {
+        lrr::launch_scatter_block_diag(b.J, nr, c, b.colblk, b.boff, b.perm, Zo, ldz, s);
+    }
     LRR_HIP(hipStreamSynchronize(s));   // host masks and descriptors go out of scope
     return k;
 }
@@ -2470,8 +2626,7 @@ static lrr_status dfc_lrr_solve_f64(lrr_ctx* ctx, int m, int n, const void* M, i
         const int r1 = r.rank[0];
         double* Zo = static_cast<double*>(Z);
         if (r1 == 0) {
-            for (int j = 0; j < n; ++j)
-                LRR_HIP(hipMemsetAsync(Zo + (size_t)j * ldz, 0, sizeof(double) * n, s));
+            LRR_HIP(hipMemset2DAsync(Zo, sizeof(double) * (size_t)ldz, 0, sizeof(double) * n, n, s));
         } else {
             // in reduced coordinates U1 = Qm Ur with Ur = Yr W diag(h) and
             // U1^T [J_1 ... J_t] = Ur^T [Jr_1 ... Jr_t]
@@ -2564,7 +2719,20 @@ static lrr_status dfc_lrr_solve_local_f64(lrr_ctx* ctx, int m, int n, const void
         Buffers b{};
         Result r = run_alm(ctx, pr, p, b, s, false, nullptr);
         const int k = combine_local(ctx, pr, p, b, r, combine_rank, static_cast<double*>(Z), ldz, s);
-        if (S) lrr::launch_scatter_cols(b.E, m, static_cast<double*>(S), lds, m, n, b.perm, s);
+        if (S && p.svd) {
+            // S_b = U_b E_b, columns put back
+            lrr::launch_svd_result(svd_step(p, b, 0, lambda), b.iters, b.Rr, 0, b.mu_sched, s);
+            std::vector<GemmDesc> gs(t);
+            for (int bb = 0; bb < t; ++bb)
+                gs[bb] = GemmDesc{b.LU + (size_t)p.boff[bb] * m, b.Rr + (size_t)p.boff[bb] * p.nr,
+                                  static_cast<double*>(S), m, p.boff[bb + 1] - p.boff[bb], p.rb[bb], m, p.nr, lds, 1.0,
+                                  0.0, nullptr, b.perm + p.boff[bb]};
+            LRR_HIP(hipMemcpyAsync(b.g_exp1, gs.data(), sizeof(GemmDesc) * t, hipMemcpyHostToDevice, s));
+            lrr::launch_dgemm(b.g_exp1, t, m, p.maxl, false, false, s);
+            LRR_HIP(hipStreamSynchronize(s));   // host descriptors go out of scope
+        } else if (S) {
+            lrr::launch_scatter_cols(b.E, m, static_cast<double*>(S), lds, m, n, b.perm, s);
+        }
         LRR_HIP(hipStreamSynchronize(s));
         if (ctx->prof.on) ctx->prof.flush();
         fill_info(info, r, k);

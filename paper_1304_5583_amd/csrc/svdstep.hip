@@ -146,7 +146,7 @@ __global__ __launch_bounds__(256) void k_zstep_fused(SvdStep a, BlockState bs, c
     const double fnext = mu / sched[k + 1];
     const double f = a.f0[2 * j], g = a.f0[2 * j + 1];      // E = f q, Y1 = mu g q, g = 1 - f
     const double y1 = ratio * g, ax = y1 - f;               // T = X + ax q, Y1/mu = y1 q
-    const long o = (long)j * r;
+    const long o = (long)j * r, od = (long)b * a.dstride;
     constexpr int N = NCH > 0 ? NCH : 1;
     double qn[N][2], qo[N][2];
     double sq = 0.0, s2 = 0.0, sy = 0.0;
@@ -156,8 +156,8 @@ __global__ __launch_bounds__(256) void k_zstep_fused(SvdStep a, BlockState bs, c
         load2<VEC>(a.q0 + o, i, r, qold[0], qold[1]);
         load2<VEC>(a.Y20 + o, i, r, y2[0], y2[1]);
         if (run) load2<VEC>(a.J + o, i, r, jj[0], jj[1]);   // J = 0 where nothing was thresholded
-        load2<true>(a.d, i, r, d[0], d[1]);
-        load2<true>(a.dinv, i, r, di[0], di[1]);
+        load2<true>(a.d + od, i, r, d[0], d[1]);
+        load2<true>(a.dinv + od, i, r, di[0], di[1]);
         double y2n[2], yn[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -483,6 +483,13 @@ __global__ __launch_bounds__(256) void k_svd_outside(const double* __restrict__ 
     if ((threadIdx.x & 63) == 0) len[j] = nrm;
 }
 
+// X[:, j] (ldx) = the rows values of Xs[:, j] (ld rows), zero beyond
+__global__ __launch_bounds__(256) void k_svd_pad_cols(const double* __restrict__ Xs, int rows, double* __restrict__ X,
+                                                       int ldx) {
+    const long j = blockIdx.x;
+    for (int i = threadIdx.x; i < ldx; i += 256) X[i + j * ldx] = i < rows ? Xs[i + j * rows] : 0.0;
+}
+
 __global__ __launch_bounds__(256) void k_svd_set_row(double* __restrict__ X, int row, int ld, int c,
                                                       const double* __restrict__ v) {
     const int j = blockIdx.x * 256 + threadIdx.x;
@@ -590,6 +597,9 @@ void launch_svd_tail(const SvdStep& a, const SvdTail& z, int t, const BlockState
 }
 void launch_svd_outside(const double* T, int m, int c, double* D, double* len, hipStream_t s) {
     hipLaunchKernelGGL(k_svd_outside, dim3((c + 3) / 4), dim3(256), 0, s, T, m, c, D, len);
+}
+void launch_svd_pad_cols(const double* Xs, int rows, double* X, int ldx, int cols, hipStream_t s) {
+    hipLaunchKernelGGL(k_svd_pad_cols, dim3(cols), dim3(256), 0, s, Xs, rows, X, ldx);
 }
 void launch_svd_set_row(double* X, int row, int ld, int c, const double* v, hipStream_t s) {
     hipLaunchKernelGGL(k_svd_set_row, dim3((c + 255) / 256), dim3(256), 0, s, X, row, ld, c, v);

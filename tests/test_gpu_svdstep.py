@@ -190,3 +190,39 @@ def test_small_gram_orders_same_in_every_mode():
         if first is None:
             first = got
         assert np.array_equal(got[0], first[0]) and np.array_equal(got[1], first[1]) and got[2] == first[2]
+
+
+@pytest.mark.parametrize("m,widths,ranks", [
+    (40, (17, 30, 1), (3, 5, 1)),            # rank below width, one single point
+    (24, (31, 60, 25), (4, 24, 9)),          # wider than tall; one block of full row rank
+    (150, (130, 97, 140), (130, 97, 140)),   # full column rank: the other Gram side, over 96 points
+    (150, (170, 97, 260), (131, 20, 101)),   # odd row count, over 96 rows
+])
+def test_local_dictionaries_vs_full_coordinates(m, widths, ranks):
+    """Every block in the singular coordinates of its own points (ranks of the blocks
+    differ, rows beyond a block's rank stay zero) against the same solve in full
+    coordinates, which factor I + C C^T instead."""
+    from paper_1304_5583_amd import binding as B
+    need_gpu()
+    rng = np.random.default_rng(m + len(widths) + widths[0])
+    M = np.concatenate([rng.standard_normal((m, r)) @ rng.standard_normal((r, w)) for w, r in zip(widths, ranks)], 1)
+    M /= np.linalg.norm(M, axis=0)
+    M[:, 0] *= 3.0
+    offs = np.concatenate([[0], np.cumsum(widths)]).astype(np.int32)
+    n = int(offs[-1])
+    perm = rng.permutation(n).astype(np.int32)
+    Mp = np.empty_like(M)
+    Mp[:, perm] = M
+    Mt = B.to_device_colmajor(Mp)
+    out = []
+    for coords in (B.LRR_COORDS_AUTO, B.LRR_COORDS_FULL):
+        Zt, St, info = B.dfc_lrr_solve_local(Mt, 0.3, perm, offs, combine_rank=-1,
+                                             opts=B.lrr_opts_default(coords=coords))
+        out.append((B.from_device_colmajor(Zt), B.from_device_colmajor(St), info))
+    (Z, S, a), (Zf, Sf, f) = out
+    say(f"[local svd] m={m} relZ={rel(Z, Zf):.2e} iters={a.iters.tolist()} {f.iters.tolist()} rank={a.rank.tolist()}")
+    assert a.status == 0 and f.status == 0
+    assert a.iters.tolist() == f.iters.tolist()
+    assert a.rank.tolist() == f.rank.tolist() and a.combine_rank == f.combine_rank
+    assert rel(Z, Zf) <= 1e-6
+    assert rel(S, Sf) <= 1e-6 or np.linalg.norm(Sf) <= 1e-6
