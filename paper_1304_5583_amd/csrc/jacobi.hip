@@ -390,12 +390,13 @@ __device__ void apply_item(const EigDesc& d, int round, int item, int sched, int
             dst[gi + gj * L] = X[i][j];
         }
         if (P != Q) {
-            // the mirrored tile, with consecutive threads on consecutive rows of it
+            // the mirrored tile, with consecutive threads on consecutive rows of it; a tile
+            // that did not rotate keeps its own (its halves can differ in the last bits)
             for (int idx = tid; idx < PB * PB; idx += 256) {
                 const int j = idx % PB, i = idx / PB;
                 const long gi = (i < BS) ? (long)p1 * BS + i : (long)q1 * BS + (i - BS);
                 const long gj = (j < BS) ? (long)p2 * BS + j : (long)q2 * BS + (j - BS);
-                dst[gj + gi * L] = X[i][j];
+                dst[gj + gi * L] = any ? X[i][j] : src[gj + gi * L];
             }
         }
     } else {
@@ -486,6 +487,7 @@ __device__ void look_ahead(const EigDesc& d, int round, int p, int q, int sched,
     const int hp = p == a1 ? 0 : BS, hq = q == c1 ? 0 : BS;   // halves of p and q in their pairs
     const int* prot = d.prot + set * (nb / 2);
     const bool rotA = prot[A] != 0, rotC = prot[C] != 0;
+    const bool still = !rotA && !rotC;   // the mirrored half then is the one in memory
     const double* RgA = d.R + (long)(set * (nb / 2) + A) * PB * PB;
     const double* RgC = d.R + (long)(set * (nb / 2) + C) * PB * PB;
     // the off-diagonal tile as the update forms it: rows of the lower slot
@@ -551,9 +553,9 @@ __device__ void look_ahead(const EigDesc& d, int round, int p, int q, int sched,
             else if (w == 3) S[BS + i][j] = o[v];
             else if (!swap) {
                 S[i][BS + j] = o[v];
-                if (A != C) S[BS + j][i] = o[v];
+                if (A != C) S[BS + j][i] = still ? src[(long)q * BS + j + ((long)p * BS + i) * L] : o[v];
             } else {
-                S[j][BS + i] = o[v];
+                S[j][BS + i] = still ? src[(long)p * BS + j + ((long)q * BS + i) * L] : o[v];
                 S[BS + i][j] = o[v];
             }
         }
@@ -656,17 +658,6 @@ __global__ void k_jacobi_close(const EigDesc* __restrict__ descs, int count, int
     if (d.run[0] == 0 || d.st[0] != 0) return;
     if (d.st[1] == 0) d.st[0] = 1;
     else atomicAdd(n_open, 1);
-    d.st[1] = 0;
-}
-
-// end of a sweep: a sweep without rotations means converged
-__global__ void k_jacobi_sweep_end(const EigDesc* __restrict__ descs, int count, int* any_active) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= count) return;
-    const EigDesc d = descs[b];
-    if (d.run[0] == 0 || d.st[0] != 0) return;
-    if (d.st[1] == 0) d.st[0] = 1;
-    else atomicAdd(any_active, 1);
     d.st[1] = 0;
 }
 
@@ -1075,10 +1066,6 @@ void launch_jacobi_check(const EigDesc* d_descs, int count, int maxL, int* d_ope
     const int blocks = (maxL * maxL + 255) / 256 < 64 ? (maxL * maxL + 255) / 256 : 64;
     hipLaunchKernelGGL(k_jacobi_offcheck, dim3(blocks, count), dim3(256), 0, s, d_descs, d_open, bs);
     hipLaunchKernelGGL(k_jacobi_close, dim3((count + 63) / 64), dim3(64), 0, s, d_descs, count, d_open);
-}
-
-void launch_jacobi_sweep_end(const EigDesc* d_descs, int count, int* d_any, hipStream_t s) {
-    hipLaunchKernelGGL(k_jacobi_sweep_end, dim3((count + 63) / 64), dim3(64), 0, s, d_descs, count, d_any);
 }
 
 int jacobi_solve_grid(int bs) {

@@ -226,3 +226,19 @@ def test_local_dictionaries_vs_full_coordinates(m, widths, ranks):
     assert a.rank.tolist() == f.rank.tolist() and a.combine_rank == f.combine_rank
     assert rel(Z, Zf) <= 1e-6
     assert rel(S, Sf) <= 1e-6 or np.linalg.norm(Sf) <= 1e-6
+
+
+@pytest.mark.parametrize("m,ns,t", [(140, 160, 2), (260, 150, 3)])
+def test_launch_forms_agree_above_the_small_orders(m, ns, t):
+    """Gram orders above 96, where the Jacobi rounds run pair solves and tile updates
+    in one launch: the same bits as the persistent eigensolve (use_graph 2), whose
+    rounds take the two phases one after the other."""
+    from paper_1304_5583_amd import binding as B
+    from paper_1304_5583_amd.datagen import small_problem
+    need_gpu()
+    p = small_problem(40 + m, m=m, k=3, r=4, ns=ns, n_replace=ns // 2, t=t, lam=0.25, normalize=True)
+    Mt = B.to_device_colmajor(p.M)
+    out = [B.dfc_lrr_solve(Mt, p.lam, p.perm, p.offsets, opts=B.lrr_opts_default(use_graph=g, check_every=4))
+           for g in (1, 2)]
+    assert out[0][2].iters.tolist() == out[1][2].iters.tolist()
+    assert (out[0][0] == out[1][0]).all() and (out[0][1] == out[1][1]).all()
