@@ -7,7 +7,8 @@
 // iteration from the device-resident DevIter, so that the same launches can
 // be replayed without host-side arguments changing.
 //
-// Per iteration (push-through form of the Z-step, see the solver):
+// Per iteration in full coordinates (push-through form of the Z-step, see the solver;
+// in singular coordinates svdstep.hip replaces all but k_block_fro and k_check):
 //   k_form_Y      Y = Z + Y2/mu, column sums of squares        (J-step input)
 //   k_block_fro   ||Y_b||_F per block; ||Y_b||_F <= tau => J_b = 0 exactly
 //   k_form_QT     Q = J - Y2/mu,  T = X - E + Y1/mu

@@ -44,7 +44,6 @@ void launch_jacobi_apply(const EigDesc* d_descs, int count, int maxL, int bs, in
                          bool sched = false);
 // bs > 0: also mark the index-block pairs that need rotations (EigDesc::need)
 void launch_jacobi_check(const EigDesc* d_descs, int count, int maxL, int* d_open, hipStream_t s, int bs = 0);
-void launch_jacobi_sweep_end(const EigDesc* d_descs, int count, int* d_any, hipStream_t s);
 void launch_jacobi_eigvals(const EigDesc* d_descs, int count, hipStream_t s);
 // The whole block-Jacobi pass loop of `count` matrices (bs = 16 or 32) in
 // one persistent launch (after a reset of ctl): d_offs holds the prefix counts
@@ -71,7 +70,6 @@ void launch_orth_guard(const RefDesc* d, int count, int maxL, const int* warm, h
 void launch_lo_rows(const EigDesc* d, int count, int maxL, const DevIter* it, hipStream_t s,
                     bool count_pass = true);
 void launch_orth_E(const RefDesc* d, int count, int maxL, hipStream_t s);
-void launch_ref_set_run(const RefDesc* d, int count, const int* svt_run, hipStream_t s);
 // the orthogonalisation steps run for the blocks that need a decomposition and did not measure
 // |I - X^T X| <= 1e-8 in their last refinement step
 void launch_ref_set_run_ns(const RefDesc* d, int count, const int* svt_run, hipStream_t s);

@@ -346,14 +346,6 @@ __global__ void k_orth_decide(const RefDesc* __restrict__ descs, int count, doub
     if (!(dev <= kCleanDev)) d.clean[0] = 0;
 }
 
-// the steps after the refinement run on every matrix that needs a decomposition
-__global__ void k_ref_set_run(const RefDesc* __restrict__ descs, int count, const int* __restrict__ svt_run) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= count) return;
-    const RefDesc d = descs[b];
-    d.run[0] = svt_run[d.block];
-}
-
 // the orthogonalisation steps run for the matrices that need a decomposition,
 // except those whose last refinement step measured |I - X^T X| <= kNSSecond
 __global__ void k_ref_set_run_ns(const RefDesc* __restrict__ descs, int count, const int* __restrict__ svt_run) {
@@ -395,9 +387,6 @@ void launch_ref_next(const RefDesc* d, int count, hipStream_t s) {
 }
 void launch_orth_decide(const RefDesc* d, int count, hipStream_t s) {
     hipLaunchKernelGGL(k_orth_decide, dim3((count + 63) / 64), dim3(64), 0, s, d, count, kNSSecond);
-}
-void launch_ref_set_run(const RefDesc* d, int count, const int* svt_run, hipStream_t s) {
-    hipLaunchKernelGGL(k_ref_set_run, dim3((count + 63) / 64), dim3(64), 0, s, d, count, svt_run);
 }
 void launch_ref_set_run_ns(const RefDesc* d, int count, const int* svt_run, hipStream_t s) {
     hipLaunchKernelGGL(k_ref_set_run_ns, dim3((count + 63) / 64), dim3(64), 0, s, d, count, svt_run);

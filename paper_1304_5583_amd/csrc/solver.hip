@@ -9,7 +9,10 @@
 //   E  = column l2 shrinkage of X - A Z + Y1/mu by lam/mu
 //   Y1 += mu (X - A Z - E),  Y2 += mu (Z - J),  mu = min(rho mu, mu_max)
 //   stop when both residual max-norms are below tol.
-// The Z-step is evaluated in push-through form: with P = X - E + Y1/mu and
+// In singular coordinates (bases of range(A^T) and range(A) that make A diagonal,
+// finish_basis) the Z-step is a division per entry and the whole iteration after the
+// thresholding is one column pass (svdstep.hip).  In full coordinates, and with bases
+// that miss the accuracy, it is evaluated in push-through form: with P = X - E + Y1/mu and
 // Q = J - Y2/mu,  V = (I + A A^T)^{-1} (P - A Q),  Z = Q + A^T V  and
 // X - A Z + Y1/mu = E + V, so the m x m inverse is the only factorisation and no
 // product A Z is needed.
