@@ -793,6 +793,12 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
         if (!p.ext_ok) return;
     }
     if (st[2] <= kSvdOut * st[3]) return;
+    // U already spans everything: what is left is the rounding of its columns of small
+    // singular value, and there is no room for another coordinate
+    if (r >= m) {
+        p.svd = p.ext_ok = false;
+        return;
+    }
     // Observations partly outside range(U) (lrr_solve with any X, or directions of
     // the data below the rank cut): only column operations act on that part, so it
     // keeps its direction and one more coordinate carries its length, as a row with

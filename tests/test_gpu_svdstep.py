@@ -242,3 +242,26 @@ def test_launch_forms_agree_above_the_small_orders(m, ns, t):
            for g in (1, 2)]
     assert out[0][2].iters.tolist() == out[1][2].iters.tolist()
     assert (out[0][0] == out[1][0]).all() and (out[0][1] == out[1][1]).all()
+
+
+@pytest.mark.parametrize("m,n,cond", [(40, 100, 5.0), (130, 300, 6.0), (130, 200, 6.0)])
+def test_full_row_rank_with_small_singular_values(m, n, cond):
+    """Full row rank with singular values over many decades: the left basis spans the
+    whole space, so observations have no part outside it and no coordinate may be
+    added for one; against full coordinates of the same solve."""
+    from paper_1304_5583_amd import binding as B
+    need_gpu()
+    rng = np.random.default_rng(m + n)
+    U, _ = np.linalg.qr(rng.standard_normal((m, m)))
+    V, _ = np.linalg.qr(rng.standard_normal((n, m)))
+    M = (U * np.logspace(0.0, -cond, m)) @ V.T * 10.0
+    perm = rng.permutation(n).astype(np.int32)
+    offs = np.array([0, n // 2, n], dtype=np.int32)
+    out = []
+    for coords in (B.LRR_COORDS_AUTO, B.LRR_COORDS_REDUCED, B.LRR_COORDS_FULL):
+        Zt, _, info = B.dfc_lrr_solve(B.to_device_colmajor(M), 0.5, perm, offs,
+                                      opts=B.lrr_opts_default(coords=coords, tol=1e-7))
+        assert info.status == 0
+        out.append(B.from_device_colmajor(Zt))
+    say(f"[full row rank] m={m} n={n} auto {rel(out[0], out[2]):.2e} reduced {rel(out[1], out[2]):.2e}")
+    assert rel(out[0], out[2]) <= 1e-6 and rel(out[1], out[2]) <= 1e-6
