@@ -65,6 +65,20 @@ lrr_status lrr_diag_syevj(lrr_ctx *ctx, int count, const int *l, const double *B
                           long strideB, double *lam, int ldlam, double *W, int eig_block,
                           int *sweeps, void *stream);
 
+/* One block's thresholding step by the single-workgroup eigensolver of the small
+ * Gram orders (1 <= e <= 96): J = SVT_tau(Y), column-major device arrays.
+ *   Y != NULL: Y and J are nr x l; the Gram matrix is Y Y^T of the first e <= nr
+ *     rows (left != 0; the rows of Y from e on hold zeros, those of J receive
+ *     zeros) or Y^T Y (left == 0, e == l).  G and P are not used.
+ *   Y == NULL: the Gram matrix G (e x e) is given as it is, P (e x e) receives
+ *     X diag(g) X^T with g = (1 - tau / sqrt(lam))_+.
+ * X0 (e x e, NULL: none) holds the eigenvectors of a previous step to start from.
+ * lam (e), X (e x e) receive the eigenpairs, *rank (host) the number of weights
+ * above zero.  max_sweeps as in lrr_opts.  LRR_EINVAL if the orders don't fit. */
+lrr_status lrr_diag_small_svt(lrr_ctx *ctx, int e, int nr, int l, int left, const double *Y,
+                              const double *G, const double *X0, double tau, int max_sweeps,
+                              double *J, double *P, double *lam, double *X, int *rank, void *stream);
+
 /* Round schedule of a targeted Jacobi pass (host only, no device work).  After
  * each check of the off-diagonal entries, the solver marks the pairs of
  * index blocks (bs indices each) that still hold an entry above the tolerance

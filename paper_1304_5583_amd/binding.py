@@ -116,6 +116,8 @@ def load_library(path: str = LIB_PATH):
     lib.lrr_diag_spd_inverse_noalloc.restype = i
     lib.lrr_diag_syevj.argtypes = [vp, i, ip, vp, i, C.c_long, vp, i, vp, i, ip, vp]
     lib.lrr_diag_syevj.restype = i
+    lib.lrr_diag_small_svt.argtypes = [vp, i, i, i, i, vp, vp, vp, d, i, vp, vp, vp, vp, ip, vp]
+    lib.lrr_diag_small_svt.restype = i
     lib.lrr_diag_plan_rounds.argtypes = [ip, i, i, ip, ip]
     lib.lrr_diag_plan_rounds.restype = i
     lib.dfc_lrr_solve_local.argtypes = [vp, i, i, vp, i, d, i, ip, ip, i, C.POINTER(lrr_opts), vp, i, vp, i,
@@ -422,6 +424,31 @@ def lrr_diag_syevj(Bs, ls, eig_block: int = 16, ctx: Context | None = None):
                                        _stream(torch, Bs.device))
     _check(st, ctx, allow_nc=False)
     return lam, W, sw.value
+
+
+def lrr_diag_small_svt(e: int, tau: float, Yt=None, Gt=None, left: bool = True, X0t=None, Jt=None,
+                       max_sweeps: int = 30, ctx: Context | None = None):
+    """One thresholding step of the single-workgroup eigensolver (include/lrr_diag.h).
+
+    Yt: (l, nr) tensor holding Y (nr x l), or Gt: (e, e) tensor holding the Gram
+    matrix; X0t: (e, e) tensor holding eigenvectors to start from; Jt: the tensor
+    that receives J (as Yt).  Returns (Jt or Pt, lam, Xt, rank)."""
+    import torch
+    dev = (Yt if Yt is not None else Gt).device
+    ctx = ctx or get_context(dev.index or 0)
+    l, nr = Yt.shape if Yt is not None else (e, e)
+    if Jt is None:
+        Jt = torch.empty((l, nr), dtype=torch.float64, device=dev)
+    lam = torch.empty(e, dtype=torch.float64, device=dev)
+    Xt = torch.empty((e, e), dtype=torch.float64, device=dev)
+    rank = C.c_int(0)
+    ptr = lambda x: C.c_void_p(x.data_ptr()) if x is not None else None
+    st = load_library().lrr_diag_small_svt(ctx.handle, e, nr, l, int(left), ptr(Yt), ptr(Gt), ptr(X0t), float(tau),
+                                           int(max_sweeps), ptr(Jt) if Yt is not None else None,
+                                           ptr(Jt) if Yt is None else None, ptr(lam), ptr(Xt), C.byref(rank),
+                                           _stream(torch, dev))
+    _check(st, ctx, allow_nc=False)
+    return Jt, lam, Xt, rank.value
 
 
 def lrr_segment(Zt, k: int, exclude=None, rank_tol: float = 1e-6, rank_bound: int = 0,

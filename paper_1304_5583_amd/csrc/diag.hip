@@ -197,4 +197,47 @@ lrr_status lrr_diag_syevj(lrr_ctx* ctx, int count, const int* l, const double* B
     });
 }
 
+lrr_status lrr_diag_small_svt(lrr_ctx* ctx, int e, int nr, int l, int left, const double* Y, const double* G,
+                              const double* X0, double tau, int max_sweeps, double* J, double* P, double* lam,
+                              double* X, int* rank, void* stream) {
+    if (!ctx) return lrr::ctx_fail(nullptr, LRR_EINVAL, "ctx must not be NULL");
+    if (e < 1 || e > lrr::kSmallEig) return lrr::ctx_fail(ctx, LRR_EINVAL, "e must lie in [1, 96]");
+    if (Y ? (!J || nr < 1 || l < 1 || (left ? e > nr : e != l)) : (!G || !P))
+        return lrr::ctx_fail(ctx, LRR_EINVAL, "Y / J or G / P arguments do not fit");
+    if (!lam || !X || !rank || !(tau > 0.0) || max_sweeps < 1)
+        return lrr::ctx_fail(ctx, LRR_EINVAL, "bad arguments");
+    return run(ctx, [&]() -> lrr_status {
+        hipStream_t s = static_cast<hipStream_t>(stream);
+        const size_t ee = sizeof(double) * e * e;
+        double *Gd, *Pd, *h;
+        int *flags;   // run, warm, rank
+        lrr::DevIter* it;
+        lrr::SmallEig* dd;
+        LRR_HIP(hipMalloc((void**)&Gd, ee));
+        LRR_HIP(hipMalloc((void**)&Pd, ee));
+        LRR_HIP(hipMalloc((void**)&h, sizeof(double) * e));
+        LRR_HIP(hipMalloc((void**)&flags, sizeof(int) * 3));
+        LRR_HIP(hipMalloc((void**)&it, sizeof(lrr::DevIter)));
+        LRR_HIP(hipMalloc((void**)&dd, sizeof(lrr::SmallEig)));
+        const int hf[3] = {1, X0 ? 1 : 0, 0};
+        const lrr::DevIter hi{0, 0, 1.0 / tau, tau};
+        const lrr::SmallEig hd{Gd, X, Pd, lam, h, e, e, 0, flags, flags + 1, Y, J, nr, l, left ? 1 : 0};
+        LRR_HIP(hipMemcpyAsync(flags, hf, sizeof(hf), hipMemcpyHostToDevice, s));
+        LRR_HIP(hipMemcpyAsync(it, &hi, sizeof(hi), hipMemcpyHostToDevice, s));
+        LRR_HIP(hipMemcpyAsync(dd, &hd, sizeof(hd), hipMemcpyHostToDevice, s));
+        if (G) LRR_HIP(hipMemcpyAsync(Gd, G, ee, hipMemcpyDeviceToDevice, s));
+        if (X0) LRR_HIP(hipMemcpyAsync(X, X0, ee, hipMemcpyDeviceToDevice, s));
+        lrr::BlockState bs{};
+        bs.rank = flags + 2;
+        lrr::small_eig_prepare();
+        lrr::launch_small_svt(dd, 1, e, bs, it, max_sweeps, s);
+        if (P && !Y) LRR_HIP(hipMemcpyAsync(P, Pd, ee, hipMemcpyDeviceToDevice, s));
+        LRR_HIP(hipMemcpyAsync(rank, flags + 2, sizeof(int), hipMemcpyDeviceToHost, s));
+        LRR_HIP(hipStreamSynchronize(s));
+        (void)hipFree(Gd); (void)hipFree(Pd); (void)hipFree(h); (void)hipFree(flags); (void)hipFree(it);
+        (void)hipFree(dd);
+        return LRR_OK;
+    });
+}
+
 }  // extern "C"

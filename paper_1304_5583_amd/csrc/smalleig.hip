@@ -290,7 +290,9 @@ __device__ void gram(const SmallEig& d, int E, int ES, double* B) {
     __syncthreads();
 }
 
-// J = P Y (left) or Y P, P in LDS
+// J = P Y (left) or Y P, P in LDS.  Left: Y and J have nr >= e rows (blocks with
+// dictionaries of their own share the largest rank as their row count), of which P
+// (E x E) covers the first e; the rows beyond are zero.
 template <int NT>
 __device__ void rebuild(const SmallEig& d, int E, int ES, const double* P) {
     const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4, e = d.e, nr = d.nr, l = d.l;
@@ -303,7 +305,7 @@ __device__ void rebuild(const SmallEig& d, int E, int ES, const double* P) {
             const int k = k0 + lk;
             double a, b;
             if (d.left) {
-                a = P[i * ES + k];   // tr * 16 = E rows
+                a = i < E ? P[i * ES + k] : 0.0;   // tr * 16 may exceed E
                 b = k < e && j < l ? d.Y[k + (long)j * nr] : 0.0;
             } else {
                 a = k < e && i < nr ? d.Y[i + (long)k * nr] : 0.0;

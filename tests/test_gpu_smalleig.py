@@ -1,0 +1,70 @@
+"""The single-workgroup thresholding step of small Gram orders (lrr_diag_small_svt)
+against numpy's eigen-decomposition, where it can go wrong: a block of lower rank
+beside one of higher rank.
+
+Tolerances: entries of J are differences of O(1) numbers formed from eigenpairs
+that are accurate to 1e-14 of the largest eigenvalue; with tau at a tenth of the
+largest singular value the weights 1 - tau / sigma amplify that by at most 100, so
+1e-11 of the largest entry.
+"""
+import numpy as np
+import pytest
+
+from gpu_util import need_gpu, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _svt(Y, tau):
+    U, s, Vt = np.linalg.svd(Y, full_matrices=False)
+    return (U * np.maximum(s - tau, 0.0)) @ Vt, int((s > tau).sum())
+
+
+@pytest.mark.parametrize("e,nr,l", [(12, 90, 40), (1, 96, 17), (16, 17, 16), (31, 48, 33), (48, 90, 256), (90, 90, 91),
+                                    (64, 65, 80)])
+def test_rows_beyond_a_blocks_rank_are_zero(e, nr, l):
+    """Blocks with dictionaries of their own share the largest rank as their row
+    count: J of a block of rank e has exact zeros in the rows from e on."""
+    torch = need_gpu()
+    from paper_1304_5583_amd import binding as B
+    rng = np.random.default_rng(e + nr + l)
+    Y = np.zeros((nr, l))
+    Y[:e] = rng.standard_normal((e, l))
+    tau = 0.1 * np.linalg.norm(Y, 2)
+    Jt = torch.full((l, nr), float("nan"), dtype=torch.float64, device="cuda")
+    Jt, lam, Xt, rank = B.lrr_diag_small_svt(e, tau, Yt=torch.from_numpy(np.ascontiguousarray(Y.T)).cuda(), Jt=Jt)
+    J = Jt.cpu().numpy().T
+    ref, k = _svt(Y, tau)
+    say(f"[small svt] e={e} nr={nr} l={l} err={np.abs(J - ref).max():.2e}")
+    assert np.all(J[e:] == 0.0)
+    assert np.abs(J - ref).max() <= 1e-11 * np.abs(ref).max()
+    assert rank == k
+
+
+def test_local_blocks_of_very_different_ranks():
+    """Ranks 12, 48 and 90 in one call: the outputs do not depend on what other
+    workgroups left in the LDS, so two calls with other work in between agree bit
+    for bit, and with full coordinates to the parity bar."""
+    need_gpu()
+    from paper_1304_5583_amd import binding as B
+    rng = np.random.default_rng(12)
+    m, widths, ranks = 100, (40, 60, 100), (12, 48, 90)
+    M = np.concatenate([rng.standard_normal((m, r)) @ rng.standard_normal((r, w)) for w, r in zip(widths, ranks)], 1)
+    M /= np.linalg.norm(M, axis=0)
+    offs = np.concatenate([[0], np.cumsum(widths)]).astype(np.int32)
+    perm = np.arange(M.shape[1], dtype=np.int32)
+    Mt = B.to_device_colmajor(M)
+
+    def solve(coords):
+        Zt, St, info = B.dfc_lrr_solve_local(Mt, 0.3, perm, offs, combine_rank=-1, opts=B.lrr_opts_default(coords=coords))
+        return B.from_device_colmajor(Zt), B.from_device_colmajor(St), info
+    Z, S, a = solve(B.LRR_COORDS_AUTO)
+    # other kernels that fill the LDS: a large eigenproblem and a solve of its own
+    G = rng.standard_normal((96, 96))
+    B.lrr_diag_small_svt(96, 1.0, Gt=B.to_device_colmajor(G @ G.T))
+    Z2, S2, _ = solve(B.LRR_COORDS_AUTO)
+    assert np.array_equal(Z, Z2) and np.array_equal(S, S2)
+    Zf, Sf, f = solve(B.LRR_COORDS_FULL)
+    assert a.iters.tolist() == f.iters.tolist() and a.rank.tolist() == f.rank.tolist()
+    assert np.linalg.norm(Z - Zf) <= 1e-6 * np.linalg.norm(Zf)
+    assert np.linalg.norm(S - Sf) <= 1e-6 * max(np.linalg.norm(Sf), 1.0)
