@@ -227,20 +227,27 @@ __device__ void transform(const SmallLds<NT>& m, int E, int ES) {
 }
 
 // First-order correction of the eigenvectors (X orthonormal to rounding, B = X^T G X):
-// X <- X (I + E), E_ij = b_ij / (b_jj - b_ii) where b_ij exceeds the tolerance (Ogita
-// and Aishima 2018 with X^T X = I; the caller has checked that |E_ij| <= kLinear),
+// X <- X (I + E), E_ij = -E_ji = b_ij / (b_jj - b_ii), i < j, where b_ij exceeds the
+// tolerance (Ogita and Aishima 2018 with X^T X = I; the caller's check of the same
+// entries found |E_ij| <= kLinear),
 // orthonormalised.  B is left as scratch.
 template <int NT, int MT>
 __device__ void refine(const SmallLds<NT>& m, int e, int E, int ES, double floor_abs, double sum) {
     double* const d = m.cs;   // cs and sn: 96 diagonal entries
     for (int i = threadIdx.x; i < E; i += NT) d[i] = m.B[i * ES + i];
     __syncthreads();
+    // One decision a pair, the check's (upper half): the halves of B differ in the last
+    // bits, and an entry that only the lower half puts above the tolerance would be
+    // divided by a distance nobody has looked at.  E is then skew-symmetric to the bit.
     for (int idx = threadIdx.x; idx < E * E; idx += NT) {
         const int i = idx / E, j = idx - i * E;
+        if (i > j) continue;
         const double s = m.B[i * ES + j], gap = d[j] - d[i];
         // below the tolerance an entry is rounding, and so may the distance be
         const bool on = i != j && fabs(s) > fmax(kRelTol * sqrt(fabs(d[i] * d[j])), floor_abs);
-        m.B[i * ES + j] = on ? s / gap : 0.0;
+        const double v = on ? s / gap : 0.0;
+        m.B[i * ES + j] = v;
+        if (i != j) m.B[j * ES + i] = -v;
     }
     __syncthreads();
     dbl4 acc[MT];

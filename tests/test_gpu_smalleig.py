@@ -68,3 +68,29 @@ def test_local_blocks_of_very_different_ranks():
     assert a.iters.tolist() == f.iters.tolist() and a.rank.tolist() == f.rank.tolist()
     assert np.linalg.norm(Z - Zf) <= 1e-6 * np.linalg.norm(Zf)
     assert np.linalg.norm(S - Sf) <= 1e-6 * max(np.linalg.norm(Sf), 1.0)
+
+
+@pytest.mark.parametrize("upper,lower", [(0.99e-14, 1.01e-14), (1.01e-14, 0.99e-14)])
+@pytest.mark.parametrize("e", [20, 50, 96])
+def test_halves_on_either_side_of_the_tolerance(e, upper, lower):
+    """The two halves of X^T G X differ in the last bits.  A pair of equal eigenvalues
+    whose coupling lies above the absolute floor (1e-14 of the largest eigenvalue) in
+    one half only, beside a coupling that a first-order correction resolves: the pair
+    must not be divided by its distance of zero."""
+    torch = need_gpu()
+    from paper_1304_5583_amd import binding as B
+    d = np.linspace(1.0, 0.3, e)
+    d[2] = d[3] = 1e-3
+    G = np.diag(d)
+    G[0, 5] = G[5, 0] = 1e-6
+    G[2, 3], G[3, 2] = upper, lower
+    tau = 0.01
+    # (e, e) tensor of the column-major G: G[i, j] at [j, i]
+    Pt, lam, Xt, rank = B.lrr_diag_small_svt(e, tau, Gt=B.to_device_colmajor(G),
+                                             X0t=torch.eye(e, dtype=torch.float64, device="cuda"))
+    w, V = np.linalg.eigh(0.5 * (G + G.T))
+    ref = (V * np.maximum(1.0 - tau / np.sqrt(w), 0.0)) @ V.T
+    X = Xt.cpu().numpy().T
+    assert rank == e
+    assert np.abs(Pt.cpu().numpy() - ref).max() <= 1e-11
+    assert np.abs(X.T @ X - np.eye(e)).max() <= 1e-13
