@@ -67,6 +67,8 @@ struct Found {
 };
 constexpr double kLinear = 0.1;     // largest correction the refinement takes
 constexpr double kSumMax = 0.02;    // and largest sum of their squares
+constexpr double kWarmMax = 1e-6;   // |X^T X - I| up to which earlier eigenvectors are used
+constexpr double kStepMax = 0.1;    // and above which a correction is given up
 
 // LDS of a small solve: B, X, then these
 template <int NT>
@@ -199,17 +201,32 @@ __device__ void sweep(const SmallLds<NT>& m, int e, int ES, double floor_abs) {
     }
 }
 
-// X <- X (3 I - X^T X) / 2 (B is scratch)
+// X <- X (3 I - X^T X) / 2 (B is scratch) if max |X^T X - I| is at most limit: a step
+// maps a deviation d to about 3 d^2 / 4, and moves away from large ones.  Returns the
+// deviation (infinity for a NaN), the same in every thread.
 template <int NT, int MT>
-__device__ void orthonormalise(const SmallLds<NT>& m, int E, int ES) {
+__device__ double orthonormalise(const SmallLds<NT>& m, int E, int ES, double limit) {
     dbl4 acc[MT];
     mm_regs<NT, MT, true, false>(m.X, m.X, E, ES, acc);
-    each<NT, MT>(acc, E, [&](int i, int j, double v) { m.B[i * ES + j] = (i == j ? 1.5 : 0.0) - 0.5 * v; });
+    double dev = 0.0;
+    each<NT, MT>(acc, E, [&](int i, int j, double v) {
+        const double x = fabs(v - (i == j ? 1.0 : 0.0));
+        dev = fmax(dev, x == x ? x : INFINITY);   // fmax would drop the NaN
+        m.B[i * ES + j] = (i == j ? 1.5 : 0.0) - 0.5 * v;
+    });
+    dev = wave_max(dev);
+    if ((threadIdx.x & 63) == 0) m.red[threadIdx.x >> 6] = dev;
     __syncthreads();
+    for (int w = 0; w < NT / 64; ++w) dev = fmax(dev, m.red[w]);
+    if (!(dev <= limit)) {
+        __syncthreads();
+        return dev;
+    }
     mm_regs<NT, MT, false, false>(m.X, m.B, E, ES, acc);
     __syncthreads();
     each<NT, MT>(acc, E, [&](int i, int j, double v) { m.X[i * ES + j] = v; });
     __syncthreads();
+    return dev;
 }
 
 // B <- X^T B X
@@ -230,9 +247,9 @@ __device__ void transform(const SmallLds<NT>& m, int E, int ES) {
 // X <- X (I + E), E_ij = -E_ji = b_ij / (b_jj - b_ii), i < j, where b_ij exceeds the
 // tolerance (Ogita and Aishima 2018 with X^T X = I; the caller's check of the same
 // entries found |E_ij| <= kLinear),
-// orthonormalised.  B is left as scratch.
+// orthonormalised.  B is left as scratch.  False if X was not orthonormal after all.
 template <int NT, int MT>
-__device__ void refine(const SmallLds<NT>& m, int e, int E, int ES, double floor_abs, double sum) {
+__device__ bool refine(const SmallLds<NT>& m, int e, int E, int ES, double floor_abs, double sum) {
     double* const d = m.cs;   // cs and sn: 96 diagonal entries
     for (int i = threadIdx.x; i < E; i += NT) d[i] = m.B[i * ES + i];
     __syncthreads();
@@ -256,7 +273,9 @@ __device__ void refine(const SmallLds<NT>& m, int e, int E, int ES, double floor
     each<NT, MT>(acc, E, [&](int i, int j, double v) { m.X[i * ES + j] += v; });
     __syncthreads();
     // (I + E)^T (I + E) = I - E^2 deviates by at most sum = |E|_F^2; a step squares that
-    for (double dev = sum; dev > 1e-16; dev *= dev) orthonormalise<NT, MT>(m, E, ES);
+    for (double dev = sum; dev > 1e-16; dev *= dev)
+        if (!(orthonormalise<NT, MT>(m, E, ES, kStepMax) <= kStepMax)) return false;
+    return true;
 }
 
 // Gram matrix of the block Y (nr x l) into B: Y Y^T (left) or Y^T Y, operands from
@@ -340,7 +359,7 @@ __global__ __launch_bounds__(NT) void k_small_svt(const SmallEig* __restrict__ d
     const SmallLds<NT> m(lds, E);
     double* const B = m.B;
     double* const X = m.X;
-    const bool warm = d.warm[0] != 0;
+    bool warm = d.warm[0] != 0;
     dbl4 acc[MT];
     auto load_gram = [&] {
         for (int idx = tid; idx < E * E; idx += NT) {
@@ -349,12 +368,24 @@ __global__ __launch_bounds__(NT) void k_small_svt(const SmallEig* __restrict__ d
         }
         __syncthreads();
     };
+    auto identity = [&] {
+        for (int idx = tid; idx < E * E; idx += NT) {
+            const int j = idx / E, i = idx - j * E;
+            X[i * ES + j] = i == j ? 1.0 : 0.0;
+        }
+        __syncthreads();
+    };
     for (int idx = tid; idx < E * E; idx += NT) {
         const int j = idx / E, i = idx - j * E;
         X[i * ES + j] = (warm && i < e && j < e) ? d.X[i + j * L] : (i == j ? 1.0 : 0.0);
     }
     __syncthreads();
-    if (warm) orthonormalise<NT, MT>(m, E, ES);
+    // earlier eigenvectors that are no longer orthonormal (of a step that met an overflow,
+    // say) would make X^T G X something else than a similarity: from the identity then
+    if (warm && !(orthonormalise<NT, MT>(m, E, ES, kWarmMax) <= kWarmMax)) {
+        identity();
+        warm = false;
+    }
     if (d.Y) {
         // the Gram matrix as well (short rows or columns), kept for the refinement
         gram<NT, MT>(d, E, ES, B);
@@ -372,13 +403,15 @@ __global__ __launch_bounds__(NT) void k_small_svt(const SmallEig* __restrict__ d
     // quarter of a sweep's time at order 45), a Jacobi sweep otherwise
     const double floor_abs = kAbsFloor * diag_max(m, e, ES);
     int left = max_sweeps;
+    bool linear = true;   // corrections are still tried
     for (int step = 0; step < 4 * max_sweeps && left > 0; ++step) {
         const Found f = check(m, e, ES, floor_abs);
         if (!f.above) break;
-        if (!f.steep && f.sum <= kSumMax && step < 2 * max_sweeps) {
-            refine<NT, MT>(m, e, E, ES, floor_abs, f.sum);
+        if (linear && !f.steep && f.sum <= kSumMax && step < 2 * max_sweeps) {
+            linear = refine<NT, MT>(m, e, E, ES, floor_abs, f.sum);
+            if (!linear) identity();
             load_gram();
-            transform<NT, MT>(m, E, ES);
+            if (linear) transform<NT, MT>(m, E, ES);
         } else {
             sweep(m, e, ES, floor_abs);
             --left;

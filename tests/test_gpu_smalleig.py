@@ -94,3 +94,26 @@ def test_halves_on_either_side_of_the_tolerance(e, upper, lower):
     assert rank == e
     assert np.abs(Pt.cpu().numpy() - ref).max() <= 1e-11
     assert np.abs(X.T @ X - np.eye(e)).max() <= 1e-13
+
+
+@pytest.mark.parametrize("kind", ["exact", "nan", "inf", "zero", "gaussian", "scaled", "one column lost"])
+@pytest.mark.parametrize("e", [7, 40, 96])
+def test_eigenvectors_of_an_earlier_step_that_are_not_orthonormal(e, kind):
+    """A step that starts from eigenvectors which have lost their orthonormality (or
+    are not finite) gives what one from the identity gives."""
+    need_gpu()
+    from paper_1304_5583_amd import binding as B
+    rng = np.random.default_rng(e)
+    Y = rng.standard_normal((e, 2 * e))
+    G = Y @ Y.T
+    w, V = np.linalg.eigh(G)
+    tau = 0.1 * np.sqrt(w[-1])
+    X0 = {"exact": V, "nan": np.full((e, e), np.nan), "inf": np.where(np.eye(e) > 0, np.inf, 0.0),
+          "zero": np.zeros((e, e)), "gaussian": rng.standard_normal((e, e)), "scaled": 2.0 * V,
+          "one column lost": np.where(np.arange(e) == 2, V[:, [0]], V)}[kind]
+    Pt, lam, Xt, rank = B.lrr_diag_small_svt(e, tau, Gt=B.to_device_colmajor(G), X0t=B.to_device_colmajor(X0))
+    ref = (V * np.maximum(1.0 - tau / np.sqrt(np.maximum(w, 1e-300)), 0.0)) @ V.T
+    X = Xt.cpu().numpy().T
+    assert rank == int((np.sqrt(np.maximum(w, 0.0)) > tau).sum())
+    assert np.abs(Pt.cpu().numpy() - ref).max() <= 1e-11
+    assert np.abs(X.T @ X - np.eye(e)).max() <= 1e-12
