@@ -213,8 +213,9 @@ __global__ __launch_bounds__(256) void k_zstep_fused(SvdStep a, BlockState bs, c
         a.f1[2 * j] = f1;
         a.f1[2 * j + 1] = g1;
         a.colsq[j] = sy;
-        bs.colr1[j] = sqrt(s1);
-        bs.colr2[j] = sqrt(s2);
+        // a NaN would lose every later comparison and meet the stop test
+        bs.colr1[j] = s1 == s1 ? sqrt(s1) : INFINITY;
+        bs.colr2[j] = s2 == s2 ? sqrt(s2) : INFINITY;
     }
 }
 
@@ -292,6 +293,9 @@ __global__ __launch_bounds__(256) void k_svd_resid(SvdStep a, const int* __restr
     }
 }
 
+// |x|, a NaN as infinity
+__device__ __forceinline__ double abs_or_inf(double x) { return x == x ? fabs(x) : INFINITY; }
+
 // max |A[:, j] + D[:, j] R[r - 1, j]| over the columns of the flagged blocks; D
 // (may be null): the directions outside range(U), whose coordinate is the last row
 // of the r-row coefficients R
@@ -307,7 +311,7 @@ __global__ __launch_bounds__(256) void k_svd_colmax(const double* __restrict__ A
         const double w = D ? R[r - 1 + (long)j * r] : 0.0;
         for (int i = threadIdx.x & 63; i < rows; i += 64) {
             const long k = i + (long)j * ld;
-            mx = fmax(mx, fabs(D ? A[k] + D[k] * w : A[k]));
+            mx = fmax(mx, abs_or_inf(D ? A[k] + D[k] * w : A[k]));
         }
     }
     mx = wave_max(mx);
@@ -347,7 +351,7 @@ __global__ __launch_bounds__(256) void k_svd_expand(SvdStep a, const double* __r
                 acc += basis[i + (long)q * rows] * v;
             }
             if (D) acc += D[i + (long)j * rows] * v;
-            mx = fmax(mx, fabs(acc));
+            mx = fmax(mx, abs_or_inf(acc));
         }
     }
     mx = wave_max(mx);
@@ -374,7 +378,7 @@ __device__ double expand_max(const SvdStep& a, const double* __restrict__ basis,
                 acc += basis[i + (long)q * rows] * v;
             }
             if (D) acc += D[i + (long)j * rows] * v;
-            mx = fmax(mx, fabs(acc));
+            mx = fmax(mx, abs_or_inf(acc));
         }
     }
     mx = wave_max(mx);

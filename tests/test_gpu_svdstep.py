@@ -265,3 +265,27 @@ def test_full_row_rank_with_small_singular_values(m, n, cond):
         out.append(B.from_device_colmajor(Zt))
     say(f"[full row rank] m={m} n={n} auto {rel(out[0], out[2]):.2e} reduced {rel(out[1], out[2]):.2e}")
     assert rel(out[0], out[2]) <= 1e-6 and rel(out[1], out[2]) <= 1e-6
+
+
+# 16: the whole end of an iteration in one launch; 60: one launch per expansion;
+# 300: expansions by products
+SMALLEST_PENALTY = [(16, 40, 20), (60, 130, 100), (300, 700, 400)]
+
+
+def _smallest_penalty(m, n, l, coords):
+    from paper_1304_5583_amd import binding as B
+    need_gpu()
+    A = np.random.default_rng(m).standard_normal((m, n))
+    A /= np.linalg.norm(A, axis=0)
+    Zt, Et, info = B.lrr_solve(B.to_device_colmajor(A), B.to_device_colmajor(A[:, :l]), 0.3,
+                               B.lrr_opts_default(coords=coords, mu0=1e-310, rho=10.0))
+    return B.from_device_colmajor(Zt), B.from_device_colmajor(Et), info
+
+
+@pytest.mark.parametrize("m,n,l", SMALLEST_PENALTY)
+def test_a_solve_that_meets_nan_does_not_converge(m, n, l):
+    """A penalty whose reciprocal overflows: whatever becomes of the iterates, LRR_OK is
+    not returned with anything but finite numbers."""
+    from paper_1304_5583_amd import binding as B
+    Z, E, info = _smallest_penalty(m, n, l, B.LRR_COORDS_REDUCED)
+    assert info.status != 0 or (np.isfinite(Z).all() and np.isfinite(E).all())
