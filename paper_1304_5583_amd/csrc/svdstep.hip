@@ -91,6 +91,9 @@ __global__ __launch_bounds__(256) void k_colnorm_max(const double* __restrict__ 
     if ((threadIdx.x & 63) == 0) atomic_max_nonneg(out, mx);
 }
 
+// 1 / mu, finite also for the smallest penalties: 0 / mu has to stay 0
+__device__ __forceinline__ double inv_mu(double mu) { return fmin(1.0 / mu, 1.7976931348623157e308); }
+
 // sum over the TPC threads (64 or 256) that share a column
 template <int TPC>
 __device__ __forceinline__ double col_sum(double v, double* red) {
@@ -141,7 +144,7 @@ __global__ __launch_bounds__(256) void k_zstep_fused(SvdStep a, BlockState bs, c
     if (!bs.active[b]) return;
     const bool run = bs.svt_run[b] != 0;
     const int lane = threadIdx.x % TPC, k = it->k, r = a.r;
-    const double mu = it->mu, imu = 1.0 / mu;
+    const double mu = it->mu, imu = inv_mu(mu);
     const double ratio = k > 0 ? sched[k - 1] / mu : 1.0;   // mu of the stored E, Y1 over mu
     const double fnext = mu / sched[k + 1];
     const double f = a.f0[2 * j], g = a.f0[2 * j + 1];      // E = f q, Y1 = mu g q, g = 1 - f
@@ -284,7 +287,7 @@ __global__ __launch_bounds__(256) void k_svd_resid(SvdStep a, const int* __restr
     const int b = blockIdx.y;
     if (!expand[b]) return;
     const int k = it->k, r = a.r;
-    const double imu = 1.0 / it->mu, ratio = k > 0 ? sched[k - 1] / it->mu : 1.0;
+    const double imu = inv_mu(it->mu), ratio = k > 0 ? sched[k - 1] / it->mu : 1.0;
     for (int j = boff[b] + blockIdx.x * 4 + (threadIdx.x >> 6); j < boff[b + 1]; j += gridDim.x * 4) {
         const long o = (long)j * r;
         const double g1 = a.f1[2 * j + 1], y1 = ratio * a.f0[2 * j + 1];
@@ -339,7 +342,7 @@ __global__ __launch_bounds__(256) void k_svd_expand(SvdStep a, const double* __r
         const double x2 = __longlong_as_double((long long)x2max[b]);
         if (!((r1 < tol || k + 1 >= n_iter) && x2 >= tol && x2 < sqrt_n * tol)) return;
     }
-    const double imu = 1.0 / it->mu, ratio = k > 0 ? sched[k - 1] / it->mu : 1.0;
+    const double imu = inv_mu(it->mu), ratio = k > 0 ? sched[k - 1] / it->mu : 1.0;
     double mx = 0.0;
     for (int j = boff[b] + blockIdx.x * 4 + (threadIdx.x >> 6); j < boff[b + 1]; j += gridDim.x * 4) {
         const long o = (long)j * r;
@@ -394,7 +397,7 @@ __global__ __launch_bounds__(1024) void k_svd_tail(SvdStep a, SvdTail z, BlockSt
     __shared__ double red[48];
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int k = it->k;
-    const double mu = it->mu, imu = 1.0 / mu, ratio = k > 0 ? sched[k - 1] / mu : 1.0;
+    const double mu = it->mu, imu = inv_mu(mu), ratio = k > 0 ? sched[k - 1] / mu : 1.0;
     const bool last = k + 1 >= z.n_iter, act = bs.active[b] != 0;
     if (act) {
         const int c0 = z.boff[b], c1 = z.boff[b + 1];
@@ -467,7 +470,7 @@ __global__ __launch_bounds__(256) void k_svd_result(SvdStep a, const int* __rest
     const int n = iters[a.colblk[j]];
     const bool odd = (n & 1) != 0;
     const long o = (long)j * a.r;
-    const double f = (odd ? a.f1 : a.f0)[2 * j], imu = 1.0 / sched[n];
+    const double f = (odd ? a.f1 : a.f0)[2 * j], imu = inv_mu(sched[n]);
     const double* q = odd ? a.q1 : a.q0;
     const double* Y = odd ? a.Y1 : a.Y0;
     const double* Y2 = odd ? a.Y21 : a.Y20;

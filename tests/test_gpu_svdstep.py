@@ -289,3 +289,14 @@ def test_a_solve_that_meets_nan_does_not_converge(m, n, l):
     from paper_1304_5583_amd import binding as B
     Z, E, info = _smallest_penalty(m, n, l, B.LRR_COORDS_REDUCED)
     assert info.status != 0 or (np.isfinite(Z).all() and np.isfinite(E).all())
+
+
+@pytest.mark.parametrize("m,n,l", SMALLEST_PENALTY)
+def test_smallest_penalties_vs_full_coordinates(m, n, l):
+    """... and the solve is that of full coordinates, which divide by the penalty."""
+    from paper_1304_5583_amd import binding as B
+    Z, E, info = _smallest_penalty(m, n, l, B.LRR_COORDS_REDUCED)
+    Zf, Ef, full = _smallest_penalty(m, n, l, B.LRR_COORDS_FULL)
+    assert info.status == 0 and full.status == 0
+    assert info.iters.tolist() == full.iters.tolist()
+    assert rel(Z, Zf) <= 1e-6 and np.linalg.norm(E - Ef) <= 1e-6 * max(np.linalg.norm(Ef), 1.0)
