@@ -556,7 +556,6 @@ struct Problem {
     double lam;
     lrr_opts o;
     int local = 0;                // 1: block b uses its own observations as dictionary
-    int from32 = 0;               // 1: A and X were widened from FP32 buffers
     int record_all = 0;           // 1: the forward records every iteration for the reverse sweep
 };
 
@@ -673,11 +672,10 @@ constexpr double kRankCut = 1e-14;
 // in the dense form (Mr = A Qm).  kSvdOut: what U U^T may leave of the
 // observations against their largest column before it gets its own coordinate
 // (3e-15 and less where nothing of them lies outside).
-// kSvdOrth: deviation of Qm^T Qm from the identity.  kTail32: what may be dropped
-// of a dictionary that came in FP32 (relative to its largest column): no solution
-// uses directions that small (m = 2016, n = 2432, image-like data that leaves
-// 2e-6: Z moves by 1e-7 to 3e-7, as it does between two orders of summation).
-constexpr double kSvdOff = 1e-13, kSvdOut = 1e-13, kSvdOrth = 1e-13, kTail32 = 1e-5;
+// The same bound holds for what may be left of the dictionary itself where reduced
+// coordinates are the rule's choice for m < n < 2m, whatever type the data came in: full
+// coordinates keep every direction.  kSvdOrth: deviation of Qm^T Qm from the identity.
+constexpr double kSvdOff = 1e-13, kSvdOut = 1e-13, kSvdOrth = 1e-13;
 
 // Bases of range(A^T) and range(A) from the eigen-decomposition A A^T = W
 // diag(lam) W^T (kept indices, by decreasing eigenvalue, in b.idxq):
@@ -789,7 +787,7 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
             st[2] = out;
             st[3] = obs;
         }
-        p.ext_ok = left <= (pr.from32 ? kTail32 : kSvdOut) * all;
+        p.ext_ok = left <= kSvdOut * all;
         if (!p.ext_ok) return;
     }
     if (st[2] <= kSvdOut * st[3]) return;
@@ -2537,7 +2535,7 @@ lrr_status lrr_workspace_bytes(int m, int n, int t, const int* offsets, const lr
 
 static lrr_status lrr_solve_f64(lrr_ctx* ctx, int m, int n, int l, const void* A, int lda, const void* X, int ldx,
                      double lambda, const lrr_opts* opts, void* Z, int ldz, void* E, int lde,
-                     lrr_info* info, void* stream, int from32 = 0) {
+                     lrr_info* info, void* stream) {
     if (!ctx) return fail(nullptr, LRR_EINVAL, "ctx must not be NULL");
     if (m <= 0 || n <= 0 || l <= 0) return fail(ctx, LRR_EINVAL, "dimensions must be positive");
     if (!A || !X || !Z) return fail(ctx, LRR_EINVAL, "A, X and Z must not be NULL");
@@ -2559,7 +2557,7 @@ static lrr_status lrr_solve_f64(lrr_ctx* ctx, int m, int n, int l, const void* A
         int offs[2] = {0, l};
         apply_tune(ctx, o, m, n, 1, l);
         Problem pr{m, n, l, 1, static_cast<const double*>(A), lda, static_cast<const double*>(X), ldx,
-                   nullptr, offs, lambda, o, 0, from32};
+                   nullptr, offs, lambda, o};
         Plan p = make_plan(pr);
         Buffers b{};
         Result r = run_alm(ctx, pr, p, b, s, false);
@@ -2595,7 +2593,7 @@ static lrr_status lrr_solve_f64(lrr_ctx* ctx, int m, int n, int l, const void* A
 
 static lrr_status dfc_lrr_solve_f64(lrr_ctx* ctx, int m, int n, const void* M, int ldm, double lambda, int t,
                          const int* perm, const int* offsets, const lrr_opts* opts, void* Z, int ldz,
-                         void* S, int lds, lrr_info* info, void* stream, int from32 = 0) {
+                         void* S, int lds, lrr_info* info, void* stream) {
     if (!ctx) return fail(nullptr, LRR_EINVAL, "ctx must not be NULL");
     if (m <= 0 || n <= 0) return fail(ctx, LRR_EINVAL, "dimensions must be positive");
     if (!M || !Z) return fail(ctx, LRR_EINVAL, "M and Z must not be NULL");
@@ -2619,7 +2617,7 @@ static lrr_status dfc_lrr_solve_f64(lrr_ctx* ctx, int m, int n, const void* M, i
         int maxl = 0;
         for (int b = 0; b < t; ++b) maxl = std::max(maxl, offsets[b + 1] - offsets[b]);
         apply_tune(ctx, o, m, n, t, maxl);
-        Problem pr{m, n, n, t, static_cast<const double*>(M), ldm, nullptr, 0, perm, offsets, lambda, o, 0, from32};
+        Problem pr{m, n, n, t, static_cast<const double*>(M), ldm, nullptr, 0, perm, offsets, lambda, o};
         Plan p = make_plan(pr);
         Buffers b{};
         IterHooks hooks;
@@ -2848,7 +2846,7 @@ lrr_status lrr_solve(lrr_ctx* ctx, int m, int n, int l, const void* A, int lda, 
         lrr::launch_widen_cols(static_cast<const float*>(A), lda, A64, m, m, n, s);
         lrr::launch_widen_cols(static_cast<const float*>(X), ldx, X64, m, m, l, s);
         const lrr_status st = lrr_solve_f64(ctx, m, n, l, A64, m, X64, m, lambda, &o, Z64, n, E ? E64 : nullptr, m,
-                                            info, stream, 1);
+                                            info, stream);
         if (st != LRR_OK && st != LRR_NOT_CONVERGED) return st;
         lrr::launch_narrow_cols(Z64, n, static_cast<float*>(Z), ldz, n, l, s);
         if (E) lrr::launch_narrow_cols(E64, m, static_cast<float*>(E), lde, m, l, s);
@@ -2891,7 +2889,7 @@ lrr_status dfc_lrr_solve(lrr_ctx* ctx, int m, int n, const void* M, int ldm, dou
     return dfc_io32(ctx, m, n, M, ldm, Z, ldz, S, lds, opts, stream,
                     [&](const double* M64, const lrr_opts* o, double* Z64, double* S64) {
                         return dfc_lrr_solve_f64(ctx, m, n, M64, m, lambda, t, perm, offsets, o, Z64, n, S64, m,
-                                                 info, stream, 1);
+                                                 info, stream);
                     });
 }
 

@@ -300,3 +300,21 @@ def test_smallest_penalties_vs_full_coordinates(m, n, l):
     assert info.status == 0 and full.status == 0
     assert info.iters.tolist() == full.iters.tolist()
     assert rel(Z, Zf) <= 1e-6 and np.linalg.norm(E - Ef) <= 1e-6 * max(np.linalg.norm(Ef), 1.0)
+
+
+def test_float32_buffers_drop_nothing_of_the_dictionary():
+    """m < n < 2m with float32 buffers: data rounded to float32 hold directions of 1e-8
+    of their size, below the rank cut of the bases; AUTO keeps them (full coordinates,
+    bit for bit), as it does for the same numbers in float64 buffers."""
+    from paper_1304_5583_amd import binding as B
+    need_gpu()
+    rng = np.random.default_rng(21)
+    m, n = 60, 90
+    M = rng.standard_normal((m, 20)) @ rng.standard_normal((20, n))
+    M /= np.linalg.norm(M, axis=0)
+    perm, offs = rng.permutation(n).astype(np.int32), np.array([0, 30, 60, 90], dtype=np.int32)
+    Mt = B.to_device_colmajor(M).float()
+    for X in (Mt, Mt.double()):
+        auto, full = (B.dfc_lrr_solve(X, 0.3, perm, offs, opts=B.lrr_opts_default(coords=c))
+                      for c in (B.LRR_COORDS_AUTO, B.LRR_COORDS_FULL))
+        assert (auto[0] == full[0]).all() and (auto[1] == full[1]).all()
