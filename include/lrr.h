@@ -116,7 +116,8 @@ typedef enum {
                              /* eigensolve), and in the FP64 form with solve_form   */
                              /* AUTO when m < n < 2m and the basis holds the        */
                              /* dictionary to rounding (1e-13 of its largest        */
-                             /* column); never for a recorded forward or an         */
+                             /* column) and the limits allow 128 iterations or more; */
+                             /* never for a recorded forward or an                  */
                              /* explicitly literal solve form                       */
     LRR_COORDS_FULL = 1,
     LRR_COORDS_REDUCED = 2

@@ -585,6 +585,22 @@ void* ensure_pinned(lrr_ctx* ctx, size_t bytes) {
     return p;
 }
 
+// Iterations a solve can be expected to take, at most: the iteration limit, or the
+// schedule's count up to a penalty of 100 (solves with a tolerance stop between 1e-1 and
+// 1e4; with the default schedule after 120 iterations or more, whatever the tolerance).
+int expected_iters(const lrr_opts& o, int n_iter) {
+    if (o.rho <= 1.0 || o.mu_max < 100.0) return n_iter;
+    return (int)std::min((double)n_iter, std::max(1.0, std::ceil(std::log(100.0 / o.mu0) / std::log(o.rho))));
+}
+
+// Fewer expected iterations than this don't earn back a basis that full coordinates do
+// without.  The first 100 or so of the default schedule threshold nothing, and cost next
+// to nothing.  Milliseconds in full coordinates and with bases: m = 2016, n = 2432, 16
+// blocks, 60 iterations 104 / 120, 100 167 / 123; m = 407, n = 456, 4 blocks, 60 7.7 /
+// 13.8, 120 32 / 35, 160 96 / 97; a dictionary per block, 4 of 500 points of rank 200, 50
+// 14 / 19, 100 35 / 22; 8 of 250 of rank 200, 100 14 / 18, 120 33 / 24.
+constexpr int kBasisIters = 128;
+
 Plan make_plan(const Problem& pr) {
     Plan p;
     p.m = pr.m; p.n = pr.n; p.ncols = pr.ncols; p.t = pr.t;
@@ -614,7 +630,8 @@ Plan make_plan(const Problem& pr) {
     // the iteration then has no dictionary product (m = 2016, n = 2432, 16 blocks of
     // 100..200: 823 ms in full coordinates, 510 in reduced ones; m = 407, n = 456 in
     // 4 blocks: 158 against 164); with n <= m AUTO stands for the literal form
-    p.ext = !p.reduced && pr.n > pr.m && coords == LRR_COORDS_AUTO && !pr.o.save_for_backward &&
+    const bool lasts = expected_iters(pr.o, p.n_iter) >= kBasisIters;
+    p.ext = lasts && !p.reduced && pr.n > pr.m && coords == LRR_COORDS_AUTO && !pr.o.save_for_backward &&
             pr.o.solve_form == LRR_SOLVE_AUTO && pr.o.precision == LRR_FP64 && !pr.local;
     p.reduced |= p.ext;
     if (pr.o.save_for_backward) p.reduced = p.ext = false;
@@ -631,7 +648,7 @@ Plan make_plan(const Problem& pr) {
         // blocks at full rank don't earn their bases back (40 of 100 points, m = 100:
         // 141 -> 148, at rank 20 169 -> 36); up to kSmallEig a basis is a few launches
         // (40 of 50 points: 199 -> 78).
-        p.lsvd = pr.o.precision == LRR_FP64 && coords == LRR_COORDS_AUTO && pr.o.solve_form == LRR_SOLVE_AUTO &&
+        p.lsvd = lasts && pr.o.precision == LRR_FP64 && coords == LRR_COORDS_AUTO && pr.o.solve_form == LRR_SOLVE_AUTO &&
                  pr.t <= (std::min(pr.m, p.maxl) <= lrr::kSmallEig ? 64 : 8);
     }
     // literal Z-step: on request, or automatically when the dictionary is at

@@ -318,3 +318,28 @@ def test_float32_buffers_drop_nothing_of_the_dictionary():
         auto, full = (B.dfc_lrr_solve(X, 0.3, perm, offs, opts=B.lrr_opts_default(coords=c))
                       for c in (B.LRR_COORDS_AUTO, B.LRR_COORDS_FULL))
         assert (auto[0] == full[0]).all() and (auto[1] == full[1]).all()
+
+
+@pytest.mark.parametrize("kw,reduced", [(dict(fixed_iters=60), False), (dict(fixed_iters=128), True), (dict(max_iter=127), False),
+                                        (dict(rho=1.5), False), (dict(), True)])
+def test_short_solves_do_without_a_basis(kw, reduced):
+    """m < n < 2m, and a dictionary per block: AUTO builds a basis only where the limits
+    and the penalty schedule leave enough iterations for it; the result then is the
+    explicit form's bit for bit."""
+    from paper_1304_5583_amd import binding as B
+    need_gpu()
+    rng = np.random.default_rng(22)
+    m, n = 60, 90
+    M = rng.standard_normal((m, 20)) @ rng.standard_normal((20, n))
+    M /= np.linalg.norm(M, axis=0)
+    perm, offs = rng.permutation(n).astype(np.int32), np.array([0, 30, 60, 90], dtype=np.int32)
+    Mt = B.to_device_colmajor(M)
+    same = B.LRR_COORDS_REDUCED if reduced else B.LRR_COORDS_FULL
+    auto, form = (B.dfc_lrr_solve(Mt, 0.3, perm, offs, opts=B.lrr_opts_default(coords=c, **kw))
+                  for c in (B.LRR_COORDS_AUTO, same))
+    assert (auto[0] == form[0]).all() and (auto[1] == form[1]).all()
+    auto, full = (B.dfc_lrr_solve_local(Mt, 0.3, perm, offs, combine_rank=-1, opts=B.lrr_opts_default(coords=c, **kw))
+                  for c in (B.LRR_COORDS_AUTO, B.LRR_COORDS_FULL))
+    assert bool((auto[0] == full[0]).all()) != reduced
+    # (the two forms stop in the same iteration, or a fixed one)
+    assert auto[2].iters.tolist() == full[2].iters.tolist()
