@@ -648,7 +648,7 @@ Plan make_plan(const Problem& pr) {
         // blocks at full rank don't earn their bases back (40 of 100 points, m = 100:
         // 141 -> 148, at rank 20 169 -> 36); up to kSmallEig a basis is a few launches
         // (40 of 50 points: 199 -> 78).
-        p.lsvd = lasts && pr.o.precision == LRR_FP64 && coords == LRR_COORDS_AUTO && pr.o.solve_form == LRR_SOLVE_AUTO &&
+        p.lsvd = lasts && pr.o.precision == LRR_FP64 && coords != LRR_COORDS_FULL && pr.o.solve_form == LRR_SOLVE_AUTO &&
                  pr.t <= (std::min(pr.m, p.maxl) <= lrr::kSmallEig ? 64 : 8);
     }
     // literal Z-step: on request, or automatically when the dictionary is at
@@ -2737,7 +2737,10 @@ static lrr_status dfc_lrr_solve_local_f64(lrr_ctx* ctx, int m, int n, const void
             return fail(ctx, LRR_ENUMERIC, "non-finite value in M");
         int maxl = 0;
         for (int b = 0; b < t; ++b) maxl = std::max(maxl, offsets[b + 1] - offsets[b]);
+        // the table's coordinates were measured with the common dictionary
+        const int coords = o.coords;
         apply_tune(ctx, o, m, n, t, maxl);
+        o.coords = coords;
         Problem pr{m, n, n, t, static_cast<const double*>(M), ldm, nullptr, 0, perm, offsets, lambda, o, 1};
         Plan p = make_plan(pr);
         Buffers b{};

@@ -127,3 +127,29 @@ def test_workload2_local_matches_stored_oracle():
     assert np.all(np.abs(info.iters - np.array(g["iters"])) <= 1)
     assert info.rank.tolist() == g["rank"]
     assert info.combine_rank == g["combine_rank"]
+
+
+def test_local_reduced_and_tuned_calls_take_the_automatic_form(tmp_path):
+    """coords REDUCED is AUTO where every block has its own dictionary, and the schedule
+    table, measured with the common dictionary, does not set coords: the same bits."""
+    torch = need_gpu()
+    from paper_1304_5583_amd import binding as B
+    p = _small(58, m=64, k=3, r=4, ns=40, n_replace=8, t=3, lam=0.3)
+    Mt = B.to_device_colmajor(p.M)
+    ctx = B.Context(0)
+
+    def solve(**kw):
+        return B.dfc_lrr_solve_local(Mt, p.lam, p.perm, p.offsets, combine_rank=-1, opts=B.lrr_opts_default(**kw),
+                                     ctx=ctx)
+    auto, full = solve(), solve(coords=B.LRR_COORDS_FULL)
+    assert not torch.equal(auto[0], full[0])     # two forms
+    assert rel(auto[0].cpu().numpy(), full[0].cpu().numpy()) <= 1e-6
+    red = solve(coords=B.LRR_COORDS_REDUCED)
+    assert torch.equal(red[0], auto[0]) and torch.equal(red[1], auto[1])
+    maxl = int(np.diff(p.offsets).max())
+    for co in (1, 2):
+        path = tmp_path / f"table{co}.txt"
+        path.write_text(f"{p.m} {p.n} {p.t} {maxl} 0 16 0 4 {co}\n")
+        B.lrr_tune_load(str(path), ctx=ctx)
+        tuned = solve(tune=1)
+        assert torch.equal(tuned[0], auto[0]) and torch.equal(tuned[1], auto[1])
