@@ -10,6 +10,8 @@
 #ifndef LRR_DIAG_H
 #define LRR_DIAG_H
 
+#include <stddef.h>
+
 #include "lrr.h"
 
 #ifdef __cplusplus
@@ -78,6 +80,13 @@ lrr_status lrr_diag_syevj(lrr_ctx *ctx, int count, const int *l, const double *B
 lrr_status lrr_diag_small_svt(lrr_ctx *ctx, int e, int nr, int l, int left, const double *Y,
                               const double *G, const double *X0, double tau, int max_sweeps,
                               double *J, double *P, double *lam, double *X, int *rank, void *stream);
+
+/* How recorded solves (save_for_backward) on this context keep their record.  bytes: up
+ * to this size of a record of every iteration the forward resolves every eigenpair and,
+ * if the record also takes at most `room`, keeps it; beyond, checkpoints are kept and the
+ * reverse sweep replays the iterations between them.  0 restores the defaults: 16 GiB,
+ * and an eighth of the device's free memory at the call. */
+lrr_status lrr_diag_record_limits(lrr_ctx *ctx, size_t bytes, size_t room);
 
 /* Round schedule of a targeted Jacobi pass (host only, no device work).  After
  * each check of the off-diagonal entries, the solver marks the pairs of

@@ -118,6 +118,8 @@ def load_library(path: str = LIB_PATH):
     lib.lrr_diag_syevj.restype = i
     lib.lrr_diag_small_svt.argtypes = [vp, i, i, i, i, vp, vp, vp, d, i, vp, vp, vp, vp, ip, vp]
     lib.lrr_diag_small_svt.restype = i
+    lib.lrr_diag_record_limits.argtypes = [vp, C.c_size_t, C.c_size_t]
+    lib.lrr_diag_record_limits.restype = i
     lib.lrr_diag_plan_rounds.argtypes = [ip, i, i, ip, ip]
     lib.lrr_diag_plan_rounds.restype = i
     lib.dfc_lrr_solve_local.argtypes = [vp, i, i, vp, i, d, i, ip, ip, i, C.POINTER(lrr_opts), vp, i, vp, i,
@@ -424,6 +426,12 @@ def lrr_diag_syevj(Bs, ls, eig_block: int = 16, ctx: Context | None = None):
                                        _stream(torch, Bs.device))
     _check(st, ctx, allow_nc=False)
     return lam, W, sw.value
+
+
+def lrr_diag_record_limits(bytes: int = 0, room: int = 0, ctx: Context | None = None):
+    """Limits of a recorded solve's record (include/lrr_diag.h; 0: the defaults)."""
+    ctx = ctx or get_context(0)
+    _check(load_library().lrr_diag_record_limits(ctx.handle, bytes, room), ctx, allow_nc=False)
 
 
 def lrr_diag_small_svt(e: int, tau: float, Yt=None, Gt=None, left: bool = True, X0t=None, Jt=None,

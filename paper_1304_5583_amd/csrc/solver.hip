@@ -125,6 +125,7 @@ struct lrr_ctx {
     int* dflag = nullptr;        // device flag for the input check
     unsigned long long* dwork = nullptr;   // operation counters of the Jacobi kernels
     Tape* tape = nullptr;
+    size_t record_limit = 0, record_room = 0;   // lrr_diag_record_limits (0: the defaults)
     hipStream_t capture = nullptr;         // private stream for graph capture
     void* seg_ws = nullptr;                // workspace of lrr_segment (kept apart from the solver's)
     void* io_ws = nullptr;                 // FP64 copies of FP32 arguments (opts.io_type)
@@ -556,7 +557,7 @@ struct Problem {
     double lam;
     lrr_opts o;
     int local = 0;                // 1: block b uses its own observations as dictionary
-    int record_all = 0;           // 1: the forward records every iteration for the reverse sweep
+    int record_all = 0;           // 1: a recorded forward resolves every eigenpair (tape_begin)
 };
 
 struct Result {
@@ -1241,7 +1242,7 @@ void setup_alm(lrr_ctx* ctx, const Problem& pr, Plan& p, Buffers& b, hipStream_t
     LRR_HIP(hipMemsetAsync(b.res1, 0, sizeof(double) * t, s));
     LRR_HIP(hipMemsetAsync(b.res2, 0, sizeof(double) * t, s));
     if (p.reduced || p.svd) LRR_HIP(hipMemsetAsync(b.r2nrm, 0, sizeof(unsigned long long) * t, s));
-    // a recorded forward resolves every eigenpair where it is not replayed
+    // (all eigenpairs or those above the threshold, see Problem::record_all)
     lrr::launch_init_iter(b.it, b.mu_sched, 0, s, pr.record_all);
 
     if (p.svd) return;   // nothing to factor
@@ -2159,8 +2160,9 @@ static size_t tape_layout(Tape& tp, char* base) {
     return a.off + 256;
 }
 
-// Prepare the tape before a recorded forward solve (allocates its memory).
-static void tape_begin(lrr_ctx* ctx, const Problem& pr, const Plan& p) {
+// Prepare the tape before a recorded forward solve (allocates its memory); sets
+// pr.record_all.
+static void tape_begin(lrr_ctx* ctx, Problem& pr, const Plan& p) {
     if (!ctx->tape) ctx->tape = new Tape();
     Tape& tp = *ctx->tape;
     tp.valid = false;
@@ -2187,16 +2189,23 @@ static void tape_begin(lrr_ctx* ctx, const Problem& pr, const Plan& p) {
     // Every iteration recorded by the forward itself (as one segment) while that takes
     // at most kDirectBytes and an eighth of the free memory: the reverse sweep then
     // replays nothing, which is the cost of a second forward (n = 600, 200 iterations:
-    // 1.7 GB; 396 -> 286 ms for both directions).
-    size_t free_b = 0, total_b = 0;
-    LRR_HIP(hipMemGetInfo(&free_b, &total_b));
+    // 1.7 GB; 396 -> 286 ms for both directions).  Which eigenpairs the forward resolves,
+    // and so its bits, follows from the sizes alone: all of them up to kDirectBytes, also
+    // where the memory only has room for checkpoints.
+    size_t room = ctx->record_room;
+    if (!room) {
+        size_t free_b = 0, total_b = 0;
+        LRR_HIP(hipMemGetInfo(&free_b, &total_b));
+        room = (free_b + tp.bytes) / 8;
+    }
     const int every = tp.every;
     tp.every = tp.K;
     tp.nck = 1;
-    tp.direct = true;
     size_t need = tape_layout(tp, nullptr);
-    if (need > kDirectBytes || need > (free_b + tp.bytes) / 8) {
-        tp.direct = false;
+    pr.record_all = need <= (ctx->record_limit ? ctx->record_limit : kDirectBytes) ? 1 : 0;
+    tp.pr.record_all = pr.record_all;
+    tp.direct = pr.record_all && need <= room;
+    if (!tp.direct) {
         tp.every = every;
         tp.nck = (tp.K + every - 1) / every;
         need = tape_layout(tp, nullptr);
@@ -2504,6 +2513,13 @@ lrr_status lrr_tune_load(lrr_ctx* ctx, const char* path) {
     return LRR_OK;
 }
 
+lrr_status lrr_diag_record_limits(lrr_ctx* ctx, size_t bytes, size_t room) {
+    if (!ctx) return fail(nullptr, LRR_EINVAL, "ctx must not be NULL");
+    ctx->record_limit = bytes;
+    ctx->record_room = room;
+    return LRR_OK;
+}
+
 void lrr_ctx_destroy(lrr_ctx* ctx) {
     if (!ctx) return;
     if (hipSetDevice(ctx->device) == hipSuccess) {
@@ -2640,7 +2656,6 @@ static lrr_status dfc_lrr_solve_f64(lrr_ctx* ctx, int m, int n, const void* M, i
         IterHooks hooks;
         if (o.save_for_backward) {
             tape_begin(ctx, pr, p);
-            pr.record_all = ctx->tape->direct ? 1 : 0;
             hooks = tape_forward_hooks(*ctx->tape, b, s);
         }
         Result r = run_alm(ctx, pr, p, b, s, true, o.save_for_backward ? &hooks : nullptr);

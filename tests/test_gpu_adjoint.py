@@ -208,3 +208,62 @@ def test_workload5_adjoint_vs_oracle_gradient_and_finite_differences():
             f"rel={abs(fdm - ad) / abs(fdm):.2e}")
         assert abs(fdm - ad) <= 1e-5 * abs(fdm)
         assert abs(fdm - gdir[k]) <= 1e-5 * abs(fdm)
+
+
+# ---- the record: every iteration, or checkpoints and a replay -------------------
+
+def _record_grad(p, W, opts, bytes=0, room=0):
+    """Z, dlambda and dM of one recorded solve with the given limits of the record."""
+    from paper_1304_5583_amd import binding as B
+    torch = need_gpu()
+    ctx = B.Context(0)
+    B.lrr_diag_record_limits(bytes, room, ctx=ctx)
+    Zt, _, _ = B.dfc_lrr_solve(B.to_device_colmajor(p.M), p.lam, p.perm, p.offsets, opts=opts, want_S=False, ctx=ctx)
+    Wt = torch.from_numpy(np.ascontiguousarray(W.T)).cuda()
+    dlam, dMt = B.dfc_lrr_backward(2.0 * Wt ** 2 * Zt, m=p.m, ctx=ctx)
+    return Zt, dlam, B.from_device_colmajor(dMt)
+
+
+@pytest.mark.parametrize("seed,t,iters,every", [(31, 3, 25, 7), (32, 1, 20, 20), (33, 4, 30, 8), (34, 2, 13, 1),
+                                                (35, 3, 30, 40)])
+def test_replayed_record_matches_oracle_gradient(seed, t, iters, every):
+    """Checkpoints and a replay of the segments between them (the last one not full in
+    the first and third case), which larger problems need, against the oracle's gradient
+    and the record of every iteration; the tolerances are those stated above."""
+    import oracle
+    from oracle import adjoint as adj
+    from paper_1304_5583_amd import binding as B
+    from paper_1304_5583_amd.datagen import small_problem
+    p = small_problem(seed, m=24, k=3, r=2, ns=12, n_replace=3, t=t, lam=0.4)
+    W = np.random.default_rng(seed).uniform(0.0, 1.0, (p.n, p.n))
+    fast = dict(mu0=0.05, rho=1.25)
+    Zt, dlam, dM = _record_grad(p, W, _opts(B, iters, every, **fast), bytes=1)
+    oo = oracle.ALMOptions(mu0=0.05, rho=1.25, fixed_iters=iters)
+    with one_thread():
+        tapes = []
+        for i in range(p.t):
+            cols = p.perm[p.offsets[i]:p.offsets[i + 1]]
+            tapes.append(adj.unrolled_forward(p.M[:, cols], p.M, p.lam, oo))
+        Zo = adj.dfc_combine(tapes, p.perm)[0]
+        _, dMo, dlo = adj.dfc_forward_backward(p.M, p.lam, p.perm, p.offsets, oo, 2.0 * W ** 2 * Zo)
+    assert rel(Zt.cpu().numpy().T, Zo) <= 1e-9
+    assert rel(dM, dMo) <= 1e-7 and abs(dlam - dlo) <= 1e-7 * abs(dlo)
+    Zd, dld, dMd = _record_grad(p, W, _opts(B, iters, every, **fast))
+    assert rel(dM, dMd) <= 1e-7 and abs(dlam - dld) <= 1e-7 * abs(dld)
+
+
+@pytest.mark.parametrize("prec,tol", [(0, 1e-7), (1, 1e-4)])
+def test_record_does_not_depend_on_the_free_memory(prec, tol):
+    """Where the memory has room for checkpoints only, the forward's bits stay the same
+    (default penalties: iterations that leave eigenpairs below the threshold), and the
+    gradient agrees; 1e-4 is the FP32 form's bound."""
+    from paper_1304_5583_amd import binding as B
+    from paper_1304_5583_amd.datagen import small_problem
+    torch = need_gpu()
+    p = small_problem(61, m=40, k=3, r=3, ns=40, n_replace=12, t=2, lam=0.4, normalize=True)
+    W = np.random.default_rng(61).uniform(0.0, 1.0, (p.n, p.n))
+    opts = _opts(B, 150, 40, prec=prec)
+    Zd, dld, dMd = _record_grad(p, W, opts)
+    Zr, dlr, dMr = _record_grad(p, W, opts, room=1)
+    assert torch.equal(Zd, Zr)
+    assert rel(dMr, dMd) <= tol and abs(dlr - dld) <= tol * abs(dld)
