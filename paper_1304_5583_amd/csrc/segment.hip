@@ -53,6 +53,7 @@ using lrr::GemmDesc;
 
 constexpr int kSketchExtra = 16;       // sketch columns beyond the rank bound
 constexpr double kRangeCut = 1e-14;    // eigenvalue cut of Y^T Y for the range basis
+constexpr int kProbes = 16;            // random columns that check the range basis
 constexpr double kEmbedTol = 2e-10;    // residual |L x - theta x| of the embedding
 constexpr int kEmbedMaxOuter = 400;    // filter + Rayleigh-Ritz rounds
 constexpr double kSpread = 1e5;        // largest amplification ratio of one filter
@@ -595,7 +596,8 @@ extern "C" lrr_status lrr_segment(lrr_ctx* ctx, int n, const void* Zv, int ldz, 
         // (what LRR returns) leaves its Gram matrix rank deficient, and then the range is
         // the same as from Z itself; otherwise the n x n problem follows.  n = 2000, rank
         // 200: 74 -> 22 ms, and about 10 ms more where the sketch has full rank.  Only where
-        // the cut of the range (1e-7 of sigma_1) lies clearly below the caller's.
+        // the cut of the range (1e-7 of sigma_1) lies clearly below the caller's, and if the
+        // basis leaves no more of Z than that cut does.
         const int ps = sketch ? p : (n >= 512 && rank_tol >= 1e-6 ? n / 4 : 0);
         const int p2 = std::min(nk, k + std::max(16, k / 2));
         const int L1 = round_up(std::max(p, 2), 2 * kBs);
@@ -637,18 +639,48 @@ extern "C" lrr_status lrr_segment(lrr_ctx* ctx, int n, const void* Zv, int ldz, 
                                      "rank_bound is below the rank of Z (the range sketch has full rank)");
             direct = !sketch && q > ps - kSketchExtra;
         }
+        auto basis = [&] {
+            hipLaunchKernelGGL(k_pick_cols, dim3(q), dim3(256), 0, s, e.W, (long)Lc, e.lam, e.idx, pc, 1, w.Wk,
+                               (long)pc);
+            g.gemm(2, false, false, n, q, pc, 1.0, Y, ldy, w.Wk, pc, 0.0, w.Q0, n);
+            g.gemm(3, true, false, q, q, n, 1.0, w.Q0, n, w.Q0, n, 0.0, w.Gq, q);
+            lrr::launch_ns_factor(w.Gq, w.Tq, q, s);
+            g.gemm(4, false, false, n, q, q, 1.0, w.Q0, n, w.Tq, q, 0.0, w.Q, n);
+        };
+        if (!direct) {
+            basis();
+            if (!sketch) {
+                // A direction of Z keeps sqrt((ps - q) / ps) of its weight in the sketch, less
+                // where the rank is close to ps: one between the caller's cut and the range's
+                // can fall below the latter and be missed.  D = Z - Q Q^T Z on kProbes new random
+                // columns (entries of variance 1/3) tells: |D|_F <= sqrt(3) max |D w| for a D
+                // of many directions, and with a probability above 1 - 1e-6 for one of few.
+                hipLaunchKernelGGL(k_fill_uniform, dim3(grid1((long)n * kProbes)), dim3(256), 0, s, w.Om, (long)n, n,
+                                   kProbes, 0x9B0BEull);
+                g.gemm(5, false, false, n, kProbes, n, 1.0, Z, ldz, w.Om, n, 0.0, w.Y, n);
+                g.gemm(6, true, false, q, kProbes, n, 1.0, w.Q, n, w.Y, n, 0.0, w.Gq, q);
+                g.gemm(7, false, false, n, kProbes, q, -1.0, w.Q, n, w.Gq, q, 1.0, w.Y, n);
+                LRR_HIP(hipMemsetAsync(e.scale, 0, sizeof(double), s));
+                lrr::launch_colnorm_max(w.Y, n, n, kProbes, reinterpret_cast<unsigned long long*>(e.scale), s);
+                double left = 0.0, lam1 = 0.0;
+                int i1 = 0;
+                LRR_HIP(hipMemcpyAsync(&i1, e.idx, sizeof(int), hipMemcpyDeviceToHost, s));
+                g.sync();
+                LRR_HIP(hipMemcpyAsync(&lam1, e.lam + i1, sizeof(double), hipMemcpyDeviceToHost, s));
+                LRR_HIP(hipMemcpyAsync(&left, e.scale, sizeof(double), hipMemcpyDeviceToHost, s));
+                g.sync();
+                // the sketch's largest eigenvalue is about ps / 3 sigma_1^2, or more
+                direct = !(left <= std::sqrt(kRangeCut * lam1 / ps));
+            }
+        }
         if (direct) {
             Y = Z;
             ldy = ldz;
             pc = n;
             Lc = L1;
             gram_rank();
+            basis();
         }
-        hipLaunchKernelGGL(k_pick_cols, dim3(q), dim3(256), 0, s, e.W, (long)Lc, e.lam, e.idx, pc, 1, w.Wk, (long)pc);
-        g.gemm(2, false, false, n, q, pc, 1.0, Y, ldy, w.Wk, pc, 0.0, w.Q0, n);
-        g.gemm(3, true, false, q, q, n, 1.0, w.Q0, n, w.Q0, n, 0.0, w.Gq, q);
-        lrr::launch_ns_factor(w.Gq, w.Tq, q, s);
-        g.gemm(4, false, false, n, q, q, 1.0, w.Q0, n, w.Tq, q, 0.0, w.Q, n);
 
         // ---- singular values of Z on the basis, left singular vectors U --------------
         const int L2 = round_up(std::max(q, 2), 2 * kBs);

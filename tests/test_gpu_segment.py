@@ -265,3 +265,18 @@ def test_range_without_a_bound_at_the_sketch_limits(rank):
     assert info["range_rank"] == rank
     with one_thread():
         assert np.array_equal(labels.cpu().numpy(), oracle.segment(Z, k, rank_tol=1e-3))
+
+
+@pytest.mark.parametrize("n,strong,weak,tail", [(1200, 200, 80, 1.2e-6), (1200, 200, 80, 1.5e-6), (1200, 200, 80, 2e-6),
+                                                (600, 100, 33, 1.2e-6), (600, 12, 122, 1.3e-6)])
+def test_weak_directions_above_the_cut_are_kept_without_a_bound(n, strong, weak, tail):
+    """Singular values a little above the default rank_tol (1e-6), ranks close to what
+    the sketch of n / 4 columns recognises: every one is found, as by the n x n problem."""
+    from paper_1304_5583_amd import binding as B
+    need_gpu()
+    rng = np.random.default_rng(n + weak)
+    U = np.linalg.qr(rng.standard_normal((n, strong + weak)))[0]
+    Z = (U * np.concatenate([np.linspace(1.0, 0.5, strong), np.full(weak, tail)])) @ U.T
+    labels, info = B.lrr_segment(B.to_device_colmajor(Z), 4)
+    say(f"[range] n={n} rank {info['rank']} of {strong + weak}, range {info['range_rank']}")
+    assert info["rank"] == strong + weak
