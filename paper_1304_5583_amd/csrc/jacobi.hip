@@ -7,7 +7,8 @@
 //
 // A matrix of padded order L is cut into nb = L / BS blocks of BS indices.  One
 // sweep has nb - 1 rounds; in a round the blocks are paired by the circle
-// method and every pair (p, q) is handled in two launches:
+// method and every pair (p, q) is handled in two phases, a launch each, or phase B
+// of a round and phase A of the next in one launch (k_jacobi_step):
 //   phase A  one workgroup per pair applies parallel-Jacobi rotations to the
 //            2BS x 2BS sub-matrix B[p u q, p u q] in LDS (every coupling between
 //            the two blocks once, those inside them in some of the rounds) and
@@ -1039,13 +1040,31 @@ void launch_jacobi_apply(const EigDesc* d_descs, int count, int maxL, int bs, in
                            d_descs, round, (int)sched);
 }
 
+constexpr double kLastLevelCache = 256.0 * 1048576.0;
+
+// compute units of the device (looked up once; outside any stream capture)
+static int cu_count() {
+    static int cus = 0;
+    if (cus == 0) {
+        int dev = 0, n = 0;
+        LRR_HIP(hipGetDevice(&dev));
+        LRR_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
+        cus = std::max(n, 1);
+    }
+    return cus;
+}
+
 void launch_jacobi_rounds(const EigDesc* d_descs, int count, int maxL, int bs, int rounds, hipStream_t s,
                           bool sched) {
-    // Both phases in one launch while the pair solves alone do not fill the chip (256
-    // CUs): m = 500, n = 2000, 4 matrices of order 320, 219 -> 201 ms per solve.  With
-    // 640 pairs (40 matrices of order 512) there is nothing to overlap and the tiles
-    // that did not rotate would be copied: 336 -> 341 ms.
-    if (bs != 16 || count * (maxL / bs / 2) >= 256) {
+    // Both phases in one launch while the pair solves alone do not fill the chip: m =
+    // 500, n = 2000, 4 matrices of order 320, 219 -> 201 ms per solve.  With 640 pairs (40
+    // matrices of order 512) there is nothing to overlap and the tiles that did not rotate
+    // would be copied: 336 -> 341 ms.  And while B, its second buffer and W stay in the
+    // last-level cache, as B and W alone do longer: whole eigensolves in two launches a
+    // round and in one, order 2016 93 / 79 ms, 3000 243 / 231, 3500 367 / 370, 4000 541 /
+    // 691, 5000 1362 / 1485; two matrices of order 2000 142 / 137, three 193 / 205.
+    const double bytes = 3.0 * count * (double)maxL * maxL * sizeof(double);
+    if (bs != 16 || count * (maxL / bs / 2) >= cu_count() || bytes > kLastLevelCache) {
         for (int r = 0; r < rounds; ++r) {
             launch_jacobi_pairs(d_descs, count, maxL, bs, r, s, sched);
             launch_jacobi_apply(d_descs, count, maxL, bs, r, s, sched);
@@ -1072,9 +1091,7 @@ int jacobi_solve_grid(int bs) {
     static int grid[2] = {0, 0};
     int& g = grid[bs == 32 ? 1 : 0];
     if (g == 0) {
-        int dev = 0, cus = 0, per = 0;
-        LRR_HIP(hipGetDevice(&dev));
-        LRR_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        int per = 0;
         if (bs == 32)
             LRR_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_jacobi_solve<32>, kSolveThreads, 0));
         else
@@ -1083,7 +1100,7 @@ int jacobi_solve_grid(int bs) {
         // one workgroup per CU: a grid barrier costs each workgroup an L2
         // write-back and invalidation at agent scope (measured 15-24 us with 256
         // workgroups, 67-93 us with 1024)
-        g = std::max(cus, 1);
+        g = cu_count();
     }
     return g;
 }

@@ -557,7 +557,7 @@ void launch_colnorm_max(const double* A, int m, long ld, int ncols, unsigned lon
 
 void launch_zstep_fused(const SvdStep& a, const BlockState& bs, const DevIter* it, const double* sched,
                         hipStream_t s) {
-    // a wave per column while it holds the column in at most 8 + 8 pairs; then a
+    // a wave per column while a lane holds it in at most 4 + 4 pairs; then a
     // workgroup per column up to 4096 rows, beyond that q is read again
     if (a.r <= 128) launch_fused<64, 1>(a, bs, it, sched, s);
     else if (a.r <= 256) launch_fused<64, 2>(a, bs, it, sched, s);

@@ -198,3 +198,20 @@ def test_reduced_precision_gemm_rejects_unknown_precision():
     with pytest.raises(B.LRRError) as e:
         B.lrr_diag_gemm(7, False, False, X, X, X, 4, 4, 4, 4, 4, 4)
     assert e.value.status == B.LRR_EINVAL
+
+
+def test_eigensolver_launch_forms_around_the_last_level_cache():
+    """Three matrices of order 1920 exceed the footprint above which the two phases of a
+    round take a launch each, one of them does not: the same bits."""
+    torch = need_gpu()
+    from paper_1304_5583_amd import binding as B
+    n = 1920
+    g = torch.Generator("cuda").manual_seed(n)
+    X = torch.randn(n, n // 8, dtype=torch.float64, device="cuda", generator=g)
+    A = (X @ X.T / n)[None]
+    lam, W, sweeps = B.lrr_diag_syevj(A.contiguous(), [n])
+    lam3, W3, sweeps3 = B.lrr_diag_syevj(A.repeat(3, 1, 1).contiguous(), [n] * 3)
+    say(f"[syevj] order {n}: {sweeps} sweeps")
+    assert sweeps3 == sweeps
+    for i in range(3):
+        assert torch.equal(lam3[i], lam[0]) and torch.equal(W3[i], W[0])
