@@ -109,8 +109,9 @@ typedef enum {
  * residuals are bounded by the coefficient columns' 2-norms (times 1 and
  * 1/sqrt(rows)) and formed in full only when the bounds do not decide the stop
  * test (the reported primal residual is always the exact one of the last
- * iteration).  Basis directions with
- * sigma^2 <= 1e-14 sigma_max^2 are dropped. */
+ * iteration).  Basis directions with sigma^2 <= 1e-14 sigma_max^2 are dropped, except
+ * where reduced coordinates are AUTO's choice for m < n < 2m: then they are kept (from
+ * 1000 rows on), or the solve runs in full coordinates. */
 typedef enum {
     LRR_COORDS_AUTO = 0,     /* reduced when n >= 2m (the basis costs an m x m      */
                              /* eigensolve), and in the FP64 form with solve_form   */

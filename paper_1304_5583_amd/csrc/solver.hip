@@ -694,6 +694,60 @@ constexpr double kRankCut = 1e-14;
 // coordinates are the rule's choice for m < n < 2m, whatever type the data came in: full
 // coordinates keep every direction.  kSvdOrth: deviation of Qm^T Qm from the identity.
 constexpr double kSvdOff = 1e-13, kSvdOut = 1e-13, kSvdOrth = 1e-13;
+// Further stages for what a basis leaves of the dictionary (finish_basis): eigenvalues
+// kept of a stage's largest, the smallest singular value kept (of the dictionary's largest
+// column), stages after the first, and the rows from which one earns its eigenproblem
+// back.  Milliseconds in full coordinates, and with a second stage: image-like data with
+// a tail across the rank cut, m = 700 576 / 576, 1000 467 / 439, 1400 559 / 464, 2016 (n =
+// 2432) 748 / 608; singular values over 13 decades (three stages), 700 130 / 166, 1000 336
+// / 326, 2016 852 / 769.
+constexpr double kStageCut = 1e-12, kStageLeast = 1e-14;
+constexpr int kStages = 3;
+constexpr int kStageRows = 1000;
+
+// Eigen-decomposition of the symmetric matrix of order `side` in b.Gb (ld p.Lm, zero
+// beyond): eigenvectors in b.Wq, eigenvalues in b.lamq; block Jacobi from the identity.
+void basis_eig(const Plan& p, Buffers& b, int side, hipStream_t s) {
+    const int Lm = p.Lm, bq = p.bq;
+    if (side <= lrr::kSmallEig) {
+        lrr::small_eig_prepare();
+        lrr::launch_small_syev(b.Gb, b.Wq, b.lamq, side, Lm, 80, true, s);
+        return;
+    }
+    std::vector<int> lo(Lm);
+    for (int i = 0; i < Lm; ++i) lo[i] = i >= side ? 1 : 0;
+    const int one = 1;
+    LRR_HIP(hipMemcpyAsync(b.loq, lo.data(), sizeof(int) * Lm, hipMemcpyHostToDevice, s));
+    LRR_HIP(hipMemcpyAsync(b.runq, &one, sizeof(int), hipMemcpyHostToDevice, s));
+    const EigDesc ed{b.Gb, b.Wq, b.Rq, b.lamq, Lm, side, b.runq, b.stq, b.scaleq, b.protq, b.loq, nullptr, nullptr,
+                     nullptr, nullptr, nullptr, b.B2q};
+    LRR_HIP(hipMemcpyAsync(b.eq, &ed, sizeof(EigDesc), hipMemcpyHostToDevice, s));
+    lrr::launch_set_identity(b.Wq, Lm, s);
+    lrr::launch_jacobi_init(b.eq, 1, s);
+    int* any = b.idxq;     // scratch flag until the index list is written
+    for (int sw = 0, h_any = 1; sw < 80; ++sw) {
+        LRR_HIP(hipMemsetAsync(any, 0, sizeof(int), s));
+        lrr::launch_jacobi_check(b.eq, 1, Lm, any, s);
+        LRR_HIP(hipMemcpyAsync(&h_any, any, sizeof(int), hipMemcpyDeviceToHost, s));
+        LRR_HIP(hipStreamSynchronize(s));
+        if (h_any == 0) break;
+        lrr::launch_jacobi_rounds(b.eq, 1, Lm, bq, Lm / bq - 1, s);
+    }
+    lrr::launch_jacobi_eigvals(b.eq, 1, s);
+}
+
+// Indices of the eigenvalues above `cut`, by decreasing eigenvalue, at most `most` of
+// them, into b.idxq; returns their number.
+int pick_eig(Buffers& b, const std::vector<double>& lam, double cut, int most, hipStream_t s) {
+    std::vector<int> idx;
+    for (int i = 0; i < (int)lam.size(); ++i)
+        if (lam[i] > cut) idx.push_back(i);
+    std::stable_sort(idx.begin(), idx.end(), [&](int x, int y) { return lam[x] > lam[y]; });
+    if (idx.empty()) idx.push_back(0);     // a zero matrix: a single zero column (scaled by 0 below)
+    if ((int)idx.size() > most) idx.resize(most);
+    LRR_HIP(hipMemcpyAsync(b.idxq, idx.data(), sizeof(int) * idx.size(), hipMemcpyHostToDevice, s));
+    return (int)idx.size();
+}
 
 // Bases of range(A^T) and range(A) from the eigen-decomposition A A^T = W
 // diag(lam) W^T (kept indices, by decreasing eigenvalue, in b.idxq):
@@ -707,8 +761,8 @@ constexpr double kSvdOff = 1e-13, kSvdOut = 1e-13, kSvdOrth = 1e-13;
 // The observations U^T X go to b.X.  p.svd tells whether the accuracy above was
 // reached; Qm and Mr serve the dense form otherwise.
 void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
-    const int m = p.m, n = p.n, r = p.nr, c = p.ncols;
-    const int Lr = round_up(r, 2 * p.bq);
+    const int m = p.m, n = p.n, c = p.ncols;
+    int r = p.nr;
     auto gemm = [&](int slot, const GemmDesc& g, bool ta, bool tb) {
         // pageable host source: staged before the call returns
         LRR_HIP(hipMemcpyAsync(b.g_sv + slot, &g, sizeof(g), hipMemcpyHostToDevice, s));
@@ -729,19 +783,60 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     gemm(1, GemmDesc{b.Cr, b.Cr, b.Gq, r, r, n, r, r, r, 1.0, 0.0, nullptr, nullptr}, false, true);
     lrr::launch_rows_factor(b.Gq, b.Tq, r, s);
     gemm(2, GemmDesc{b.Cr, b.Tq, b.Qm, n, r, r, r, r, n, 1.0, 0.0, nullptr, nullptr}, true, false);
-    // one step suffices unless the rows of C were far from orthogonal
-    for (int ns = 0; ns < 5; ++ns) {
-        gemm(3, GemmDesc{b.Qm, b.Qm, b.Gq, r, r, n, n, n, r, 1.0, 0.0, nullptr, nullptr}, true, false);
-        LRR_HIP(hipMemsetAsync(b.stat, 0, 4 * sizeof(unsigned long long), s));
-        lrr::launch_take_diag(b.Gq, r, r, b.dsig, b.dinv, b.stat, s);
-        read_stat(2);
-        if (st[0] <= kSvdOrth && std::fabs(st[1] - 1.0) <= kSvdOrth) break;
-        lrr::launch_ns_factor(b.Gq, b.Tq, r, s);
-        gemm(4, GemmDesc{b.Qm, b.Tq, b.Qtmp, n, r, r, n, r, n, 1.0, 0.0, nullptr, nullptr}, false, false);
-        std::swap(b.Qm, b.Qtmp);
-    }
-    const bool orth = st[0] <= kSvdOrth && std::fabs(st[1] - 1.0) <= kSvdOrth;
+    // X (rows x r) orthonormalised; scratch takes a step's result, the two are swapped.
+    // One step suffices unless the columns were far from orthogonal.
+    auto orthonormal = [&](double*& X, double*& scratch, int rows) -> bool {
+        for (int ns = 0;; ++ns) {
+            gemm(3, GemmDesc{X, X, b.Gq, r, r, rows, rows, rows, r, 1.0, 0.0, nullptr, nullptr}, true, false);
+            LRR_HIP(hipMemsetAsync(b.stat, 0, 2 * sizeof(unsigned long long), s));
+            lrr::launch_take_diag(b.Gq, r, r, b.dsig, b.dinv, b.stat, s);
+            read_stat(2);
+            if (st[0] <= kSvdOrth && std::fabs(st[1] - 1.0) <= kSvdOrth) return true;
+            if (ns == 5) return false;
+            lrr::launch_ns_factor(b.Gq, b.Tq, r, s);
+            gemm(4, GemmDesc{X, b.Tq, scratch, rows, r, r, rows, r, rows, 1.0, 0.0, nullptr, nullptr}, false, false);
+            std::swap(X, scratch);
+        }
+    };
+    bool orth = orthonormal(b.Qm, b.Qtmp, n);
     gemm(3, GemmDesc{pr.A, b.Qm, b.Mr, m, r, n, (int)pr.lda, n, m, 1.0, 0.0, nullptr, nullptr}, false, false);
+    // What the basis leaves of a dictionary for which full coordinates are the alternative,
+    // R = A - (A Qm) Qm^T: directions below the rank cut, of which A A^T knows nothing.
+    // They are the range of R, whose own Gram matrix resolves them as A A^T did the larger
+    // ones (three stages reach from 1 to the rounding of the largest column).
+    for (int stage = 0; p.ext && orth; ++stage) {
+        LRR_HIP(hipMemsetAsync(b.stat, 0, 4 * sizeof(unsigned long long), s));
+        lrr::launch_copy_cols(pr.A, pr.lda, b.Ares, m, m, n, s);
+        lrr::launch_colnorm_max(b.Ares, m, m, n, b.stat + 1, s);
+        gemm(4, GemmDesc{b.Mr, b.Qm, b.Ares, m, n, r, m, n, m, -1.0, 1.0, nullptr, nullptr}, false, true);
+        lrr::launch_colnorm_max(b.Ares, m, m, n, b.stat, s);
+        read_stat(2);
+        const double left = st[0], all = st[1];
+        if (left <= kSvdOut * all) break;
+        if (m < kStageRows || r == m || stage == kStages) return;   // full coordinates
+        LRR_HIP(hipMemsetAsync(b.Gb, 0, sizeof(double) * (size_t)p.Lm * p.Lm, s));
+        gemm(5, GemmDesc{b.Ares, b.Ares, b.Gb, m, m, n, m, m, p.Lm, 1.0, 0.0, nullptr, nullptr}, false, true);
+        basis_eig(p, b, m, s);
+        std::vector<double> lam(m);
+        LRR_HIP(hipMemcpyAsync(lam.data(), b.lamq, sizeof(double) * m, hipMemcpyDeviceToHost, s));
+        LRR_HIP(hipStreamSynchronize(s));
+        const double lmax = *std::max_element(lam.begin(), lam.end()), least = kStageLeast * all;
+        const int r2 = pick_eig(b, lam, std::max(kStageCut * lmax, least * least), m - r, s);
+        double* Q2 = b.Qm + (size_t)n * r;
+        lrr::launch_gather_cols(b.Wq, p.Lm, b.Um, m, m, r2, b.idxq, s);
+        gemm(6, GemmDesc{b.Um, b.Ares, b.Cr, r2, n, m, m, m, r2, 1.0, 0.0, nullptr, nullptr}, true, false);
+        gemm(7, GemmDesc{b.Cr, b.Cr, b.Gq, r2, r2, n, r2, r2, r2, 1.0, 0.0, nullptr, nullptr}, false, true);
+        lrr::launch_rows_factor(b.Gq, b.Tq, r2, s);
+        gemm(8, GemmDesc{b.Cr, b.Tq, Q2, n, r2, r2, r2, r2, n, 1.0, 0.0, nullptr, nullptr}, true, false);
+        // R is orthogonal to Qm up to the rounding of A, which the smallest directions see
+        gemm(9, GemmDesc{b.Qm, Q2, b.Gq, r, r2, n, n, n, r, 1.0, 0.0, nullptr, nullptr}, true, false);
+        gemm(5, GemmDesc{b.Qm, b.Gq, Q2, n, r2, r, n, r, n, -1.0, 1.0, nullptr, nullptr}, false, false);
+        r += r2;
+        orth = orthonormal(b.Qm, b.Qtmp, n);
+        gemm(3, GemmDesc{pr.A, b.Qm, b.Mr, m, r, n, (int)pr.lda, n, m, 1.0, 0.0, nullptr, nullptr}, false, false);
+    }
+    p.nr = r;
+    const int Lr = round_up(r, 2 * p.bq);
     std::vector<int> lo(Lr);
     for (int i = 0; i < Lr; ++i) lo[i] = i >= r ? 1 : 0;
     const EigDesc ed{b.Gb, b.Wq, b.Rq, b.lamq, Lr, r, b.runq, b.stq, b.scaleq, b.protq, b.loq, nullptr, nullptr, nullptr,
@@ -772,6 +867,9 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
         gemm(7, GemmDesc{b.Mr, b.Mr, b.Gq, r, r, m, m, m, r, 1.0, 0.0, nullptr, nullptr}, true, false);
         lrr::launch_rows_factor(b.Gq, b.Tq, r, s);
         gemm(8, GemmDesc{b.Mr, b.Tq, b.Um, m, r, r, m, r, m, 1.0, 0.0, nullptr, nullptr}, false, false);
+        // column norms and both residual bounds rest on U^T U = I, which small singular
+        // values reach in more than the one step
+        if (!orthonormal(b.Um, b.Ut, m)) break;
         gemm(9, GemmDesc{b.Um, b.Mr, b.Gq, r, r, m, m, m, r, 1.0, 0.0, nullptr, nullptr}, true, false);
         LRR_HIP(hipMemsetAsync(b.stat, 0, 4 * sizeof(unsigned long long), s));
         lrr::launch_take_diag(b.Gq, r, r, b.dsig, b.dinv, b.stat, s);
@@ -841,16 +939,8 @@ void pick_basis(const Problem& pr, Plan& p, Buffers& b, const double* dlam, hipS
     std::vector<double> lam(side);
     LRR_HIP(hipMemcpyAsync(lam.data(), dlam, sizeof(double) * side, hipMemcpyDeviceToHost, s));
     LRR_HIP(hipStreamSynchronize(s));
-    double lmax = 0.0;
-    for (int i = 0; i < side; ++i) lmax = std::max(lmax, lam[i]);
-    std::vector<int> idx;
-    for (int i = 0; i < side; ++i)
-        if (lam[i] > kRankCut * lmax) idx.push_back(i);
-    std::stable_sort(idx.begin(), idx.end(), [&](int x, int y) { return lam[x] > lam[y]; });
-    if (idx.empty()) idx.push_back(0);     // M = 0: a single zero column (scaled by 0 below)
-    const int r = (int)idx.size();
-    p.nr = r;
-    LRR_HIP(hipMemcpyAsync(b.idxq, idx.data(), sizeof(int) * r, hipMemcpyHostToDevice, s));
+    const double lmax = std::max(0.0, *std::max_element(lam.begin(), lam.end()));
+    p.nr = pick_eig(b, lam, kRankCut * lmax, side, s);
     finish_basis(pr, p, b, s);
 }
 
@@ -860,35 +950,9 @@ void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     // the smaller of M M^T and M^T M (padded to Lm), eigen-decomposition by block Jacobi from the identity
     LRR_HIP(hipMemsetAsync(b.Gb, 0, sizeof(double) * (size_t)Lm * Lm, s));
     GemmDesc gG{pr.A, pr.A, b.Gb, side, side, tall ? p.m : p.n, (int)pr.lda, (int)pr.lda, Lm, 1.0, 0.0, nullptr, nullptr};
-    std::vector<int> lo(Lm);
-    for (int i = 0; i < Lm; ++i) lo[i] = i >= side ? 1 : 0;
-    const int one = 1;
     LRR_HIP(hipMemcpyAsync(b.g_red, &gG, sizeof(GemmDesc), hipMemcpyHostToDevice, s));
-    LRR_HIP(hipMemcpyAsync(b.loq, lo.data(), sizeof(int) * Lm, hipMemcpyHostToDevice, s));
-    LRR_HIP(hipMemcpyAsync(b.runq, &one, sizeof(int), hipMemcpyHostToDevice, s));
-    EigDesc ed{b.Gb, b.Wq, b.Rq, b.lamq, Lm, side, b.runq, b.stq, b.scaleq, b.protq, b.loq, nullptr, nullptr, nullptr,
-                     nullptr, nullptr, b.B2q};
-    LRR_HIP(hipMemcpyAsync(b.eq, &ed, sizeof(EigDesc), hipMemcpyHostToDevice, s));
     lrr::launch_dgemm(b.g_red, 1, side, side, tall, !tall, s);
-    const bool small = side <= lrr::kSmallEig;
-    if (small) {
-        lrr::small_eig_prepare();
-        lrr::launch_small_syev(b.Gb, b.Wq, b.lamq, side, Lm, 80, true, s);
-    } else {
-        lrr::launch_set_identity(b.Wq, Lm, s);
-        lrr::launch_jacobi_init(b.eq, 1, s);
-    }
-    int* any = b.idxq;     // scratch flag until the index list is written
-    int h_any = 1;
-    for (int sw = 0; sw < 80 && !small; ++sw) {
-        LRR_HIP(hipMemsetAsync(any, 0, sizeof(int), s));
-        lrr::launch_jacobi_check(b.eq, 1, Lm, any, s);
-        LRR_HIP(hipMemcpyAsync(&h_any, any, sizeof(int), hipMemcpyDeviceToHost, s));
-        LRR_HIP(hipStreamSynchronize(s));
-        if (h_any == 0) break;
-        lrr::launch_jacobi_rounds(b.eq, 1, Lm, bq, Lm / bq - 1, s);
-    }
-    if (!small) lrr::launch_jacobi_eigvals(b.eq, 1, s);
+    basis_eig(p, b, side, s);
     pick_basis(pr, p, b, b.lamq, s);
 }
 

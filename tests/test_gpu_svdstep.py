@@ -343,3 +343,35 @@ def test_short_solves_do_without_a_basis(kw, reduced):
     assert bool((auto[0] == full[0]).all()) != reduced
     # (the two forms stop in the same iteration, or a fixed one)
     assert auto[2].iters.tolist() == full[2].iters.tolist()
+
+
+@pytest.mark.parametrize("m,kind,reduced", [(999, "rounded", False), (1000, "rounded", True), (1000, "decades", True),
+                                            (1000, "exact rank", True), (999, "exact rank", True)])
+def test_directions_below_the_rank_cut_are_kept(m, kind, reduced):
+    """m < n < 2m from 1000 rows on: what the first basis leaves of the dictionary (the
+    rounding of float32 data; singular values over 12 decades) gets a basis of its own;
+    below, such a solve runs in full coordinates, bit for bit."""
+    from paper_1304_5583_amd import binding as B
+    need_gpu()
+    rng = np.random.default_rng(m)
+    n = m + 56
+    if kind == "decades":
+        U = np.linalg.qr(rng.standard_normal((m, 200)))[0]
+        V = np.linalg.qr(rng.standard_normal((n, 200)))[0]
+        M = 20.0 * (U * np.logspace(0.0, -12.0, 200)) @ V.T
+    else:
+        M = rng.standard_normal((m, 30)) @ rng.standard_normal((30, n))
+        M /= np.linalg.norm(M, axis=0)
+        if kind == "rounded":
+            M = M.astype(np.float32).astype(np.float64)
+    offs = np.array([0, n // 4, n // 2, n // 2 + 100, n], dtype=np.int32)
+    perm = rng.permutation(n).astype(np.int32)
+    Mt = B.to_device_colmajor(M)
+    (Z, S, a), (Zf, Sf, f) = (B.dfc_lrr_solve(Mt, 0.3, perm, offs, opts=B.lrr_opts_default(coords=c))
+                              for c in (B.LRR_COORDS_AUTO, B.LRR_COORDS_FULL))
+    assert bool((Z == Zf).all()) != reduced
+    Z, S, Zf, Sf = (B.from_device_colmajor(x) for x in (Z, S, Zf, Sf))
+    say(f"[stages] m={m} {kind} relZ={rel(Z, Zf):.2e} |Z|={np.linalg.norm(Zf):.2e}")
+    assert np.linalg.norm(Zf) > 1.0
+    assert a.rank.tolist() == f.rank.tolist() and a.iters.tolist() == f.iters.tolist()
+    assert rel(Z, Zf) <= 1e-6 and np.linalg.norm(S - Sf) <= 1e-6 * max(np.linalg.norm(Sf), 1.0)
