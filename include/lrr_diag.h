@@ -81,6 +81,12 @@ lrr_status lrr_diag_small_svt(lrr_ctx *ctx, int e, int nr, int l, int left, cons
                               const double *G, const double *X0, double tau, int max_sweeps,
                               double *J, double *P, double *lam, double *X, int *rank, void *stream);
 
+/* on != 0: solves on this context take every basis in the dense form (Mr = A Qm, products
+ * as in full coordinates), which otherwise runs only where the bases miss the accuracy of
+ * singular coordinates.  Where full coordinates are the alternative (AUTO with m < n < 2m,
+ * a dictionary per block), they run. */
+lrr_status lrr_diag_dense_basis(lrr_ctx *ctx, int on);
+
 /* How recorded solves (save_for_backward) on this context keep their record.  bytes: up
  * to this size of a record of every iteration the forward resolves every eigenpair and,
  * if the record also takes at most `room`, keeps it; beyond, checkpoints are kept and the

@@ -118,6 +118,8 @@ def load_library(path: str = LIB_PATH):
     lib.lrr_diag_syevj.restype = i
     lib.lrr_diag_small_svt.argtypes = [vp, i, i, i, i, vp, vp, vp, d, i, vp, vp, vp, vp, ip, vp]
     lib.lrr_diag_small_svt.restype = i
+    lib.lrr_diag_dense_basis.argtypes = [vp, i]
+    lib.lrr_diag_dense_basis.restype = i
     lib.lrr_diag_record_limits.argtypes = [vp, C.c_size_t, C.c_size_t]
     lib.lrr_diag_record_limits.restype = i
     lib.lrr_diag_plan_rounds.argtypes = [ip, i, i, ip, ip]
@@ -426,6 +428,12 @@ def lrr_diag_syevj(Bs, ls, eig_block: int = 16, ctx: Context | None = None):
                                        _stream(torch, Bs.device))
     _check(st, ctx, allow_nc=False)
     return lam, W, sw.value
+
+
+def lrr_diag_dense_basis(on: bool, ctx: Context | None = None):
+    """Bases of this context's solves in the dense form (include/lrr_diag.h)."""
+    ctx = ctx or get_context(0)
+    _check(load_library().lrr_diag_dense_basis(ctx.handle, int(on)), ctx, allow_nc=False)
 
 
 def lrr_diag_record_limits(bytes: int = 0, room: int = 0, ctx: Context | None = None):

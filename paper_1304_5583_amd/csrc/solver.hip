@@ -126,6 +126,7 @@ struct lrr_ctx {
     unsigned long long* dwork = nullptr;   // operation counters of the Jacobi kernels
     Tape* tape = nullptr;
     size_t record_limit = 0, record_room = 0;   // lrr_diag_record_limits (0: the defaults)
+    bool dense_basis = false;                   // lrr_diag_dense_basis
     hipStream_t capture = nullptr;         // private stream for graph capture
     void* seg_ws = nullptr;                // workspace of lrr_segment (kept apart from the solver's)
     void* io_ws = nullptr;                 // FP64 copies of FP32 arguments (opts.io_type)
@@ -557,6 +558,7 @@ struct Problem {
     double lam;
     lrr_opts o;
     int local = 0;                // 1: block b uses its own observations as dictionary
+    int dense = 0;                // 1: bases are used in the dense form (lrr_diag_dense_basis)
     int record_all = 0;           // 1: a recorded forward resolves every eigenpair (tape_begin)
 };
 
@@ -876,7 +878,7 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
         read_stat(2);
         diagonal = st[1] > 0.0 && st[0] <= kSvdOff * st[1];
     }
-    if (!diagonal) return;
+    if (!diagonal || pr.dense) return;
     // observations in the left basis, and what lies outside it
     if (pr.perm) lrr::launch_gather_cols(pr.A, pr.lda, b.T, m, m, c, b.perm, s);
     else lrr::launch_copy_cols(pr.X, pr.ldx, b.T, m, m, c, s);
@@ -1008,7 +1010,7 @@ bool build_local_bases(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
         const int l = p.boff[bb + 1] - p.boff[bb];
         const size_t om = (size_t)p.boff[bb] * m;
         const int offs[2] = {0, l};
-        Problem one{m, l, l, 1, b.V + om, m, b.V + om, m, nullptr, offs, pr.lam, pr.o};
+        Problem one{m, l, l, 1, b.V + om, m, b.V + om, m, nullptr, offs, pr.lam, pr.o, 0, pr.dense};
         Plan po;
         po.m = m; po.n = l; po.ncols = l; po.t = 1; po.bq = p.bq;
         po.Lm = round_up(std::min(m, l), 2 * p.bq);
@@ -2500,9 +2502,6 @@ static double tape_backward(lrr_ctx* ctx, Tape& tp, const double* dZ, long lddz,
     return dl;
 }
 
-namespace {
-}  // namespace
-
 namespace lrr {
 lrr_status ctx_fail(lrr_ctx* ctx, lrr_status st, const std::string& msg) { return fail(ctx, st, msg); }
 int ctx_device(const lrr_ctx* ctx) { return ctx ? ctx->device : 0; }
@@ -2574,6 +2573,12 @@ lrr_status lrr_tune_load(lrr_ctx* ctx, const char* path) {
     std::string why;
     if (!lrr::host::parse_tune(path, t, why)) return fail(ctx, LRR_EINVAL, why);
     ctx->tune = std::move(t);
+    return LRR_OK;
+}
+
+lrr_status lrr_diag_dense_basis(lrr_ctx* ctx, int on) {
+    if (!ctx) return fail(nullptr, LRR_EINVAL, "ctx must not be NULL");
+    ctx->dense_basis = on != 0;
     return LRR_OK;
 }
 
@@ -2655,6 +2660,7 @@ static lrr_status lrr_solve_f64(lrr_ctx* ctx, int m, int n, int l, const void* A
         apply_tune(ctx, o, m, n, 1, l);
         Problem pr{m, n, l, 1, static_cast<const double*>(A), lda, static_cast<const double*>(X), ldx,
                    nullptr, offs, lambda, o};
+        pr.dense = ctx->dense_basis ? 1 : 0;
         Plan p = make_plan(pr);
         Buffers b{};
         Result r = run_alm(ctx, pr, p, b, s, false);
@@ -2715,6 +2721,7 @@ static lrr_status dfc_lrr_solve_f64(lrr_ctx* ctx, int m, int n, const void* M, i
         for (int b = 0; b < t; ++b) maxl = std::max(maxl, offsets[b + 1] - offsets[b]);
         apply_tune(ctx, o, m, n, t, maxl);
         Problem pr{m, n, n, t, static_cast<const double*>(M), ldm, nullptr, 0, perm, offsets, lambda, o};
+        pr.dense = ctx->dense_basis ? 1 : 0;
         Plan p = make_plan(pr);
         Buffers b{};
         IterHooks hooks;
@@ -2821,6 +2828,7 @@ static lrr_status dfc_lrr_solve_local_f64(lrr_ctx* ctx, int m, int n, const void
         apply_tune(ctx, o, m, n, t, maxl);
         o.coords = coords;
         Problem pr{m, n, n, t, static_cast<const double*>(M), ldm, nullptr, 0, perm, offsets, lambda, o, 1};
+        pr.dense = ctx->dense_basis ? 1 : 0;
         Plan p = make_plan(pr);
         Buffers b{};
         Result r = run_alm(ctx, pr, p, b, s, false, nullptr);

@@ -209,3 +209,35 @@ def test_fp32_io_rejections():
         B.dfc_lrr_solve(M64.float(), p.lam, p.perm, p.offsets,
                         opts=B.lrr_opts_default(save_for_backward=1, fixed_iters=5))
     assert e.value.status == B.LRR_EINVAL
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("seed,m,ns,t,uneven,normalize", [
+    (11, 60, 40, 3, (35, 45), False),
+    (12, 96, 64, 5, (30, 48), True),
+])
+def test_dense_reduced_form_small_vs_oracle(prec, seed, m, ns, t, uneven, normalize):
+    """Reduced coordinates without a diagonal dictionary (what runs where the bases miss
+    their accuracy), whose Z-step holds the products of the reduced-precision forms: the
+    bounds of those forms, 1e-6 in FP64."""
+    import oracle
+    from paper_1304_5583_amd import binding as B
+    from paper_1304_5583_amd.datagen import small_problem
+    need_gpu()
+    p = small_problem(seed, m=m, k=3, r=4, ns=ns, n_replace=8, t=t, lam=0.3, uneven=uneven, normalize=normalize)
+    ctx = B.Context(0)
+    B.lrr_diag_dense_basis(True, ctx=ctx)
+    Mt = B.to_device_colmajor(p.M)
+    opts = B.lrr_opts_default(precision=prec, coords=B.LRR_COORDS_REDUCED)
+    Zt, _, info = B.dfc_lrr_solve(Mt, p.lam, p.perm, p.offsets, opts=opts, ctx=ctx)
+    diag, _, _ = B.dfc_lrr_solve(Mt, p.lam, p.perm, p.offsets, opts=opts)
+    assert not (Zt == diag).all()      # another form
+    with one_thread():
+        ref = oracle.dfc_lrr(p.M, p.lam, p.perm, p.offsets)
+    ez = rel(B.from_device_colmajor(Zt), ref.Z)
+    it_o = np.array([b.iters for b in ref.blocks])
+    say(f"[dense reduced {NAMES.get(prec, 'FP64')}] relZ={ez:.2e} iters gpu={info.iters.tolist()} oracle={it_o.tolist()}")
+    assert info.status == 0
+    assert ez <= (TOL[prec] if prec else 1e-6)
+    assert np.all(info.iters >= it_o - 3) and np.all(info.iters <= 1.4 * it_o + 3)
+    assert info.rank.tolist() == [b.rank for b in ref.blocks]
