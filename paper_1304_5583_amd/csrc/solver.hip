@@ -700,17 +700,17 @@ constexpr double kSvdOff = 1e-13, kSvdOut = 1e-13, kSvdOrth = 1e-13;
 // kept of a stage's largest, the smallest singular value kept (of the dictionary's largest
 // column), stages after the first, and the rows from which one earns its eigenproblem
 // back.  Milliseconds in full coordinates, and with a second stage: image-like data with
-// a tail across the rank cut, m = 700 576 / 576, 1000 467 / 439, 1400 559 / 464, 2016 (n =
-// 2432) 748 / 608; singular values over 13 decades (three stages), 700 130 / 166, 1000 336
-// / 326, 2016 852 / 769.
+// a tail across the rank cut, m = 700 576 / 576, 1000 470 / 425, 1400 563 / 445, 2016 (n =
+// 2432) 805 / 544; singular values over 13 decades (three stages), 520 102 / 128, 1000 338
+// / 206, 2016 854 / 661.
 constexpr double kStageCut = 1e-12, kStageLeast = 1e-14;
 constexpr int kStages = 3;
 constexpr int kStageRows = 1000;
 
-// Eigen-decomposition of the symmetric matrix of order `side` in b.Gb (ld p.Lm, zero
+// Eigen-decomposition of the symmetric matrix of order `side` in b.Gb (ld Lm <= p.Lm, zero
 // beyond): eigenvectors in b.Wq, eigenvalues in b.lamq; block Jacobi from the identity.
-void basis_eig(const Plan& p, Buffers& b, int side, hipStream_t s) {
-    const int Lm = p.Lm, bq = p.bq;
+void basis_eig(const Plan& p, Buffers& b, int side, int Lm, hipStream_t s) {
+    const int bq = p.bq;
     if (side <= lrr::kSmallEig) {
         lrr::small_eig_prepare();
         lrr::launch_small_syev(b.Gb, b.Wq, b.lamq, side, Lm, 80, true, s);
@@ -738,17 +738,31 @@ void basis_eig(const Plan& p, Buffers& b, int side, hipStream_t s) {
     lrr::launch_jacobi_eigvals(b.eq, 1, s);
 }
 
-// Indices of the eigenvalues above `cut`, by decreasing eigenvalue, at most `most` of
-// them, into b.idxq; returns their number.
-int pick_eig(Buffers& b, const std::vector<double>& lam, double cut, int most, hipStream_t s) {
-    std::vector<int> idx;
-    for (int i = 0; i < (int)lam.size(); ++i)
-        if (lam[i] > cut) idx.push_back(i);
-    std::stable_sort(idx.begin(), idx.end(), [&](int x, int y) { return lam[x] > lam[y]; });
-    if (idx.empty()) idx.push_back(0);     // a zero matrix: a single zero column (scaled by 0 below)
-    if ((int)idx.size() > most) idx.resize(most);
+// Indices of the eigenvalues above `cut`, by decreasing eigenvalue (never none), and those
+// of the others.
+struct EigPick {
+    std::vector<int> kept, rest;
+};
+EigPick pick_eig(const double* dlam, int side, double cut_rel, double cut_abs, hipStream_t s) {
+    std::vector<double> lam(side);
+    LRR_HIP(hipMemcpyAsync(lam.data(), dlam, sizeof(double) * side, hipMemcpyDeviceToHost, s));
+    LRR_HIP(hipStreamSynchronize(s));
+    double lmax = 0.0;
+    for (double x : lam) lmax = std::max(lmax, x);
+    EigPick x;
+    for (int i = 0; i < side; ++i) (lam[i] > cut_rel * lmax && lam[i] > cut_abs ? x.kept : x.rest).push_back(i);
+    std::stable_sort(x.kept.begin(), x.kept.end(), [&](int i, int j) { return lam[i] > lam[j]; });
+    if (x.kept.empty()) {     // a zero matrix: a single zero column (scaled by 0 below)
+        x.kept.push_back(0);
+        x.rest.erase(x.rest.begin());
+    }
+    return x;
+}
+// out (rows x idx.size()) = those columns of b.Wq (ld Lm)
+void gather_eig(Buffers& b, const std::vector<int>& idx, int rows, int Lm, double* out, hipStream_t s) {
+    if (idx.empty()) return;
     LRR_HIP(hipMemcpyAsync(b.idxq, idx.data(), sizeof(int) * idx.size(), hipMemcpyHostToDevice, s));
-    return (int)idx.size();
+    lrr::launch_gather_cols(b.Wq, Lm, out, rows, rows, (int)idx.size(), b.idxq, s);
 }
 
 // Bases of range(A^T) and range(A) from the eigen-decomposition A A^T = W
@@ -762,9 +776,10 @@ int pick_eig(Buffers& b, const std::vector<double>& lam, double cut, int most, h
 //   a Newton-Schulz step, d = diag(U^T Mr).
 // The observations U^T X go to b.X.  p.svd tells whether the accuracy above was
 // reached; Qm and Mr serve the dense form otherwise.
-void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
+void finish_basis(const Problem& pr, Plan& p, Buffers& b, const double* dlam, hipStream_t s) {
     const int m = p.m, n = p.n, c = p.ncols;
-    int r = p.nr;
+    const EigPick first = pick_eig(dlam, std::min(m, n), kRankCut, 0.0, s);
+    int r = (int)first.kept.size();
     auto gemm = [&](int slot, const GemmDesc& g, bool ta, bool tb) {
         // pageable host source: staged before the call returns
         LRR_HIP(hipMemcpyAsync(b.g_sv + slot, &g, sizeof(g), hipMemcpyHostToDevice, s));
@@ -776,10 +791,11 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
         LRR_HIP(hipStreamSynchronize(s));
     };
     if (n < m) {
-        lrr::launch_gather_cols(b.Wq, p.Lm, b.Qtmp, n, n, r, b.idxq, s);
+        gather_eig(b, first.kept, n, p.Lm, b.Qtmp, s);
         gemm(0, GemmDesc{pr.A, b.Qtmp, b.Um, m, r, n, (int)pr.lda, n, m, 1.0, 0.0, nullptr, nullptr}, false, false);
     } else {
-        lrr::launch_gather_cols(b.Wq, p.Lm, b.Um, m, m, r, b.idxq, s);
+        if (p.ext) gather_eig(b, first.rest, m, p.Lm, b.Ut, s);   // the complement, for the stages below
+        gather_eig(b, first.kept, m, p.Lm, b.Um, s);
     }
     gemm(0, GemmDesc{b.Um, pr.A, b.Cr, r, n, m, m, (int)pr.lda, r, 1.0, 0.0, nullptr, nullptr}, true, false);
     gemm(1, GemmDesc{b.Cr, b.Cr, b.Gq, r, r, n, r, r, r, 1.0, 0.0, nullptr, nullptr}, false, true);
@@ -816,22 +832,29 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
         const double left = st[0], all = st[1];
         if (left <= kSvdOut * all) break;
         if (m < kStageRows || r == m || stage == kStages) return;   // full coordinates
-        LRR_HIP(hipMemsetAsync(b.Gb, 0, sizeof(double) * (size_t)p.Lm * p.Lm, s));
-        gemm(5, GemmDesc{b.Ares, b.Ares, b.Gb, m, m, n, m, m, p.Lm, 1.0, 0.0, nullptr, nullptr}, false, true);
-        basis_eig(p, b, m, s);
-        std::vector<double> lam(m);
-        LRR_HIP(hipMemcpyAsync(lam.data(), b.lamq, sizeof(double) * m, hipMemcpyDeviceToHost, s));
-        LRR_HIP(hipStreamSynchronize(s));
-        const double lmax = *std::max_element(lam.begin(), lam.end()), least = kStageLeast * all;
-        const int r2 = pick_eig(b, lam, std::max(kStageCut * lmax, least * least), m - r, s);
+        // C = Wc^T R (mc x n) on the mc = m - r left directions not used yet (b.Ut): its rows
+        // span those of R
+        const int mc = m - r, L = round_up(mc, 2 * p.bq);
+        gemm(5, GemmDesc{b.Ut, b.Ares, b.Cr, mc, n, m, m, m, mc, 1.0, 0.0, nullptr, nullptr}, true, false);
+        LRR_HIP(hipMemsetAsync(b.Gb, 0, sizeof(double) * (size_t)L * L, s));
+        gemm(6, GemmDesc{b.Cr, b.Cr, b.Gb, mc, mc, n, mc, mc, L, 1.0, 0.0, nullptr, nullptr}, false, true);
+        basis_eig(p, b, mc, L, s);
+        const double least = kStageLeast * all;
+        const EigPick x = pick_eig(b.lamq, mc, kStageCut, least * least, s);
+        const int r2 = (int)x.kept.size();
         double* Q2 = b.Qm + (size_t)n * r;
-        lrr::launch_gather_cols(b.Wq, p.Lm, b.Um, m, m, r2, b.idxq, s);
-        gemm(6, GemmDesc{b.Um, b.Ares, b.Cr, r2, n, m, m, m, r2, 1.0, 0.0, nullptr, nullptr}, true, false);
-        gemm(7, GemmDesc{b.Cr, b.Cr, b.Gq, r2, r2, n, r2, r2, r2, 1.0, 0.0, nullptr, nullptr}, false, true);
+        gather_eig(b, x.kept, mc, L, b.Um, s);
+        gemm(7, GemmDesc{b.Um, b.Cr, b.Qtmp, r2, n, mc, mc, mc, r2, 1.0, 0.0, nullptr, nullptr}, true, false);
+        gemm(8, GemmDesc{b.Qtmp, b.Qtmp, b.Gq, r2, r2, n, r2, r2, r2, 1.0, 0.0, nullptr, nullptr}, false, true);
         lrr::launch_rows_factor(b.Gq, b.Tq, r2, s);
-        gemm(8, GemmDesc{b.Cr, b.Tq, Q2, n, r2, r2, r2, r2, n, 1.0, 0.0, nullptr, nullptr}, true, false);
+        gemm(9, GemmDesc{b.Qtmp, b.Tq, Q2, n, r2, r2, r2, r2, n, 1.0, 0.0, nullptr, nullptr}, true, false);
+        if (!x.rest.empty()) {
+            gather_eig(b, x.rest, mc, L, b.Um, s);
+            gemm(4, GemmDesc{b.Ut, b.Um, b.Mr, m, mc - r2, mc, m, mc, m, 1.0, 0.0, nullptr, nullptr}, false, false);
+            std::swap(b.Ut, b.Mr);
+        }
         // R is orthogonal to Qm up to the rounding of A, which the smallest directions see
-        gemm(9, GemmDesc{b.Qm, Q2, b.Gq, r, r2, n, n, n, r, 1.0, 0.0, nullptr, nullptr}, true, false);
+        gemm(6, GemmDesc{b.Qm, Q2, b.Gq, r, r2, n, n, n, r, 1.0, 0.0, nullptr, nullptr}, true, false);
         gemm(5, GemmDesc{b.Qm, b.Gq, Q2, n, r2, r, n, r, n, -1.0, 1.0, nullptr, nullptr}, false, false);
         r += r2;
         orth = orthonormal(b.Qm, b.Qtmp, n);
@@ -934,28 +957,16 @@ void finish_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
     LRR_HIP(hipStreamSynchronize(s));   // host value goes out of scope
 }
 
-// Kept eigenpairs of the smaller Gram matrix (eigenvalues dlam, eigenvectors in b.Wq with
-// leading dimension p.Lm), then the bases.
-void pick_basis(const Problem& pr, Plan& p, Buffers& b, const double* dlam, hipStream_t s) {
-    const int side = std::min(p.m, p.n);
-    std::vector<double> lam(side);
-    LRR_HIP(hipMemcpyAsync(lam.data(), dlam, sizeof(double) * side, hipMemcpyDeviceToHost, s));
-    LRR_HIP(hipStreamSynchronize(s));
-    const double lmax = std::max(0.0, *std::max_element(lam.begin(), lam.end()));
-    p.nr = pick_eig(b, lam, kRankCut * lmax, side, s);
-    finish_basis(pr, p, b, s);
-}
-
 void build_basis(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
-    const int Lm = p.Lm, bq = p.bq, side = std::min(p.m, p.n);
+    const int Lm = p.Lm, side = std::min(p.m, p.n);
     const bool tall = p.n < p.m;
     // the smaller of M M^T and M^T M (padded to Lm), eigen-decomposition by block Jacobi from the identity
     LRR_HIP(hipMemsetAsync(b.Gb, 0, sizeof(double) * (size_t)Lm * Lm, s));
     GemmDesc gG{pr.A, pr.A, b.Gb, side, side, tall ? p.m : p.n, (int)pr.lda, (int)pr.lda, Lm, 1.0, 0.0, nullptr, nullptr};
     LRR_HIP(hipMemcpyAsync(b.g_red, &gG, sizeof(GemmDesc), hipMemcpyHostToDevice, s));
     lrr::launch_dgemm(b.g_red, 1, side, side, tall, !tall, s);
-    basis_eig(p, b, side, s);
-    pick_basis(pr, p, b, b.lamq, s);
+    basis_eig(p, b, side, Lm, s);
+    finish_basis(pr, p, b, b.lamq, s);
 }
 
 // Bases of every block's own dictionary C_b (m x l_b, also its observations), kept in
@@ -1020,7 +1031,7 @@ bool build_local_bases(const Problem& pr, Plan& p, Buffers& b, hipStream_t s) {
         if (batch) {
             bo.Wq = b.Wm[bb];   // then scratch of an order <= l_b
             po.Lm = p.L[bb];
-            pick_basis(one, po, bo, b.lam[bb], s);
+            finish_basis(one, po, bo, b.lam[bb], s);
         } else {
             build_basis(one, po, bo, s);
         }
