@@ -64,8 +64,11 @@ struct Found {
     int above;      // some entry exceeds the tolerance
     int steep;      // some such entry exceeds kLinear of its two eigenvalues' distance
     double sum;     // sum of the squared first-order corrections
+    double most;    // largest of them
 };
 constexpr double kLinear = 0.1;     // largest correction the refinement takes
+constexpr double kDone = 1e-13;     // corrections up to which the eigenvectors are final
+constexpr double kRounding = 1e-14; // couplings below this part of an eigenvalue don't change it or its vector
 constexpr double kSumMax = 0.02;    // and largest sum of their squares
 constexpr double kWarmMax = 1e-6;   // |X^T X - I| up to which earlier eigenvectors are used
 constexpr double kStepMax = 0.1;    // and above which a correction is given up
@@ -73,7 +76,7 @@ constexpr double kStepMax = 0.1;    // and above which a correction is given up
 // LDS of a small solve: B, X, then these
 template <int NT>
 struct SmallLds {
-    double *B, *X, *cs, *sn;
+    double *B, *X, *cs, *sn, *lam;
     int* pr;
     Found* f;
     double* red;
@@ -82,12 +85,13 @@ struct SmallLds {
         X = B + E * (E + 1);
         cs = X + E * (E + 1);
         sn = cs + 48;
-        red = sn + 48;
-        f = reinterpret_cast<Found*>(red + 16);
+        lam = sn + 48;
+        red = lam + 96;
+        f = reinterpret_cast<Found*>(red + 32);
         pr = reinterpret_cast<int*>(f + 1);
     }
 };
-constexpr int kSmallTail = 96 + 16 + 4 + 24;   // doubles beyond B and X
+constexpr int kSmallTail = 96 + 96 + 32 + 4 + 24;   // doubles beyond B and X
 
 template <int NT>
 __device__ double diag_max(const SmallLds<NT>& m, int e, int ES) {
@@ -101,10 +105,28 @@ __device__ double diag_max(const SmallLds<NT>& m, int e, int ES) {
     return mx;
 }
 
+// Whether entry b of B couples two indices with diagonal entries di and dj above the
+// tolerance of a rotation, and the first-order correction v = b / (dj - di) it asks for, 0
+// where that does not apply.  Corrections don't stop at the rotations' absolute floor: for an
+// eigenvalue of 1e-8 of the largest a coupling of 1e-14 is an angle of 1e-6 (m = 72, n =
+// 224, replaced columns: Z off by 9e-4 instead of 1e-6).  Below it a coupling matters if the
+// larger of its eigenvalues is not far below the squared threshold, and if it is more than
+// rounding of that eigenvalue or stands between a kept and a dropped one.
+__device__ __forceinline__ bool coupling(double b, double di, double dj, double floor_abs, double tau2, bool& steep,
+                                         double& v) {
+    const double s = fabs(b), gap = dj - di, big = fmax(di, dj);
+    const bool above = s > fmax(kRelTol * sqrt(fabs(di * dj)), floor_abs);
+    const bool lin = s <= kLinear * fabs(gap) && gap != 0.0;
+    const bool small = big > 0.25 * tau2 && (s > kRounding * big || (di > tau2) != (dj > tau2));
+    steep = above && !lin;
+    v = lin && (above || small) ? b / gap : 0.0;
+    return above;
+}
+
 // entries above the tolerance (relative to the two diagonal entries, and floor_abs),
-// and whether first-order corrections would resolve them
+// and whether first-order corrections would resolve what is left
 template <int NT>
-__device__ Found check(const SmallLds<NT>& m, int e, int ES, double floor_abs) {
+__device__ Found check(const SmallLds<NT>& m, int e, int ES, double floor_abs, double tau2) {
     const int tid = threadIdx.x;
     __syncthreads();
     if (tid == 0) {
@@ -113,26 +135,32 @@ __device__ Found check(const SmallLds<NT>& m, int e, int ES, double floor_abs) {
     }
     __syncthreads();
     int above = 0, steep = 0;
-    double sum = 0.0;
+    double sum = 0.0, most = 0.0;
     for (int idx = tid; idx < e * e; idx += NT) {
         const int i = idx / e, j = idx - i * e;
         if (i >= j) continue;
-        const double s = fabs(m.B[i * ES + j]), di = m.B[i * ES + i], dj = m.B[j * ES + j];
-        const double gap = fabs(dj - di);
-        if (s > fmax(kRelTol * sqrt(fabs(di * dj)), floor_abs)) {
-            above = 1;
-            if (s > kLinear * gap) steep = 1;
-            else sum += 2.0 * (s / gap) * (s / gap);
-        }
+        bool st;
+        double v;
+        above |= coupling(m.B[i * ES + j], m.B[i * ES + i], m.B[j * ES + j], floor_abs, tau2, st, v);
+        steep |= st;
+        sum += 2.0 * v * v;
+        most = fmax(most, fabs(v));
     }
     if (above) m.f->above = 1;   // every writer stores 1
     if (steep) m.f->steep = 1;
     sum = wave_sum(sum);
-    if ((tid & 63) == 0) m.red[tid >> 6] = sum;
+    most = wave_max(most);
+    if ((tid & 63) == 0) {
+        m.red[tid >> 6] = sum;
+        m.red[16 + (tid >> 6)] = most;
+    }
     __syncthreads();
     Found f = *m.f;
-    f.sum = 0.0;
-    for (int w = 0; w < NT / 64; ++w) f.sum += m.red[w];
+    f.sum = f.most = 0.0;
+    for (int w = 0; w < NT / 64; ++w) {
+        f.sum += m.red[w];
+        f.most = fmax(f.most, m.red[16 + w]);
+    }
     __syncthreads();
     return f;
 }
@@ -244,13 +272,12 @@ __device__ void transform(const SmallLds<NT>& m, int E, int ES) {
 }
 
 // First-order correction of the eigenvectors (X orthonormal to rounding, B = X^T G X):
-// X <- X (I + E), E_ij = -E_ji = b_ij / (b_jj - b_ii), i < j, where b_ij exceeds the
-// tolerance (Ogita and Aishima 2018 with X^T X = I; the caller's check of the same
-// entries found |E_ij| <= kLinear),
-// orthonormalised.  B is left as scratch.  False if X was not orthonormal after all.
+// X <- X (I + E), E_ij = -E_ji = b_ij / (b_jj - b_ii), i < j, for the couplings that the
+// caller's check counted (Ogita and Aishima 2018 with X^T X = I), orthonormalised.  B is
+// left as scratch, its diagonal in m.lam.  False if X was not orthonormal after all.
 template <int NT, int MT>
-__device__ bool refine(const SmallLds<NT>& m, int e, int E, int ES, double floor_abs, double sum) {
-    double* const d = m.cs;   // cs and sn: 96 diagonal entries
+__device__ bool refine(const SmallLds<NT>& m, int E, int ES, double floor_abs, double tau2, double sum) {
+    double* const d = m.lam;
     for (int i = threadIdx.x; i < E; i += NT) d[i] = m.B[i * ES + i];
     __syncthreads();
     // One decision a pair, the check's (upper half): the halves of B differ in the last
@@ -259,10 +286,9 @@ __device__ bool refine(const SmallLds<NT>& m, int e, int E, int ES, double floor
     for (int idx = threadIdx.x; idx < E * E; idx += NT) {
         const int i = idx / E, j = idx - i * E;
         if (i > j) continue;
-        const double s = m.B[i * ES + j], gap = d[j] - d[i];
-        // below the tolerance an entry is rounding, and so may the distance be
-        const bool on = i != j && fabs(s) > fmax(kRelTol * sqrt(fabs(d[i] * d[j])), floor_abs);
-        const double v = on ? s / gap : 0.0;
+        bool steep;
+        double v = 0.0;
+        if (i != j) coupling(m.B[i * ES + j], d[i], d[j], floor_abs, tau2, steep, v);
         m.B[i * ES + j] = v;
         if (i != j) m.B[j * ES + i] = -v;
     }
@@ -401,30 +427,47 @@ __global__ __launch_bounds__(NT) void k_small_svt(const SmallEig* __restrict__ d
     if (warm) transform<NT, MT>(m, E, ES);
     // Corrections where they resolve everything that is left (6 products, about a
     // quarter of a sweep's time at order 45), a Jacobi sweep otherwise
-    const double floor_abs = kAbsFloor * diag_max(m, e, ES);
+    const double floor_abs = kAbsFloor * diag_max(m, e, ES), tau = it->tau, tau2 = tau * tau;
     int left = max_sweeps;
-    bool linear = true;   // corrections are still tried
+    bool linear = true;       // corrections are still tried
+    bool fresh = true;        // B is X^T G X, not the sweeps' own update of it
+    bool lam_saved = false;   // the eigenvalues are in m.lam, no longer in B
     for (int step = 0; step < 4 * max_sweeps && left > 0; ++step) {
-        const Found f = check(m, e, ES, floor_abs);
-        if (!f.above) break;
-        if (linear && !f.steep && f.sum <= kSumMax && step < 2 * max_sweeps) {
-            linear = refine<NT, MT>(m, e, E, ES, floor_abs, f.sum);
+        const Found f = check(m, e, ES, floor_abs, tau2);
+        const bool below = !f.above;  // only couplings below the floor are left: one correction of
+                                      // them is the last step (the next would meet rounding)
+        if (below && (f.most <= kDone || !linear || f.sum > kSumMax)) break;
+        if (below && !fresh) {
+            load_gram();
+            transform<NT, MT>(m, E, ES);
+            fresh = true;
+        } else if (linear && !f.steep && f.sum <= kSumMax && step < 2 * max_sweeps) {
+            linear = refine<NT, MT>(m, E, ES, floor_abs, tau2, f.sum);
+            if (linear && below) {
+                lam_saved = true;
+                break;
+            }
             if (!linear) identity();
             load_gram();
             if (linear) transform<NT, MT>(m, E, ES);
-        } else {
+            fresh = true;
+        } else if (f.above) {
             sweep(m, e, ES, floor_abs);
             --left;
+            fresh = false;
+        } else {
+            break;
         }
     }
     // weights g = (1 - tau / sigma)_+, eigenvectors back, then B = X diag(g)
-    const double tau = it->tau;
     int* const flag = m.pr;
     if (tid == 0) *flag = 0;
+    if (!lam_saved)
+        for (int i = tid; i < E; i += NT) m.lam[i] = i < e ? B[i * ES + i] : 0.0;
     __syncthreads();
     int kept = 0;
     for (int i = tid; i < L; i += NT) {
-        const double lam = i < e ? B[i * ES + i] : 0.0, sig = sqrt(fmax(lam, 0.0));
+        const double lam = i < e ? m.lam[i] : 0.0, sig = sqrt(fmax(lam, 0.0));
         const bool keep = sig > tau;
         d.lam[i] = lam;
         d.h[i] = keep ? 1.0 / sig : 0.0;
@@ -437,7 +480,7 @@ __global__ __launch_bounds__(NT) void k_small_svt(const SmallEig* __restrict__ d
     }
     double* g = m.cs;   // cs and sn are free now: E <= 96 weights
     for (int j = tid; j < E; j += NT) {
-        const double sig = j < e ? sqrt(fmax(B[j * ES + j], 0.0)) : 0.0;
+        const double sig = j < e ? sqrt(fmax(m.lam[j], 0.0)) : 0.0;
         g[j] = sig > tau ? 1.0 - tau / sig : 0.0;
     }
     __syncthreads();
@@ -481,7 +524,7 @@ __global__ __launch_bounds__(NT) void k_small_syev(const double* __restrict__ A,
     }
     __syncthreads();
     const double floor_abs = floor_rel * diag_max(m, e, ES);
-    for (int sw = 0; sw < max_sweeps && check(m, e, ES, floor_abs).above; ++sw) sweep(m, e, ES, floor_abs);
+    for (int sw = 0; sw < max_sweeps && check(m, e, ES, floor_abs, INFINITY).above; ++sw) sweep(m, e, ES, floor_abs);
     __syncthreads();
     for (int i = tid; i < L; i += NT) lam[i] = i < e ? B[i * ES + i] : 0.0;
     for (long idx = tid; idx < (long)L * L; idx += NT) {

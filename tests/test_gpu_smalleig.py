@@ -117,3 +117,31 @@ def test_eigenvectors_of_an_earlier_step_that_are_not_orthonormal(e, kind):
     assert rank == int((np.sqrt(np.maximum(w, 0.0)) > tau).sum())
     assert np.abs(Pt.cpu().numpy() - ref).max() <= 1e-11
     assert np.abs(X.T @ X - np.eye(e)).max() <= 1e-12
+
+
+@pytest.mark.parametrize("e", [10, 48, 96])
+@pytest.mark.parametrize("warm", [False, True])
+def test_couplings_below_the_absolute_floor(e, warm):
+    """Kept eigenvalues of 1e-7 and 1e-8 of the largest, coupled by 5e-15 of it: less
+    than the floor of the Jacobi rotations, but an angle of 5e-8.  The Gram matrix
+    consists of 2 x 2 blocks, whose P has a closed form; what a first-order correction
+    leaves is the angle's square, and rounding: 1e-12."""
+    torch = need_gpu()
+    from paper_1304_5583_amd import binding as B
+    import math
+    tau = math.sqrt(5e-9)
+    G, ref, kept = np.zeros((e, e)), np.zeros((e, e)), 0
+    for i in range(0, e, 2):
+        a, b, s = (1.0, 0.5, 0.0) if i == 0 else (1e-7 * (1.0 + i / e), 1e-8 * (1.0 + i / e), 5e-15)
+        G[i:i + 2, i:i + 2] = [[a, s], [s, b]]
+        t = 2.0 * s / ((a - b) + math.hypot(a - b, 2.0 * s))      # tan of the angle
+        c = 1.0 / math.sqrt(1.0 + t * t)
+        V = np.array([[c, -c * t], [c * t, c]])
+        g = [max(1.0 - tau / math.sqrt(x), 0.0) for x in (a + s * t, b - s * t)]
+        ref[i:i + 2, i:i + 2] = (V * g) @ V.T
+        kept += sum(x > 0.0 for x in g)
+    X0 = torch.eye(e, dtype=torch.float64, device="cuda") if warm else None
+    Pt, lam, Xt, rank = B.lrr_diag_small_svt(e, tau, Gt=B.to_device_colmajor(G), X0t=X0)
+    say(f"[small svt] e={e} below the floor: {np.abs(Pt.cpu().numpy() - ref).max():.2e}")
+    assert rank == kept
+    assert np.abs(Pt.cpu().numpy() - ref).max() <= 1e-12
