@@ -4,7 +4,7 @@ For a problem shape it times the schedule choices the library exposes -- the
 Jacobi block width of the eigensolver (16 or 32 indices: the tile shape of its
 pair and apply kernels), replaying each iteration's Z- and E-step launches from
 a HIP graph or launching them one by one, the spacing of the host's
-convergence checks, and full versus reduced coordinates -- and keeps the
+convergence checks, and automatic, full or reduced coordinates -- and keeps the
 fastest candidate that reproduces the default schedule's iterates (identical
 per-block iteration counts, relative difference of Z at most 1e-8).  The
 result is a table the C library reads (lrr_tune_load; solves with opts.tune =
@@ -30,7 +30,8 @@ HEADER = "# m n t maxl precision eig_block use_graph check_every coords\n"
 
 
 def candidates(n: int, m: int):
-    coords = (B.LRR_COORDS_FULL, B.LRR_COORDS_REDUCED) if n >= m else (B.LRR_COORDS_FULL,)
+    # AUTO first: for m < n < 2m it is a form of its own (reduced coordinates that drop nothing)
+    coords = (B.LRR_COORDS_AUTO, B.LRR_COORDS_FULL, B.LRR_COORDS_REDUCED) if n >= m else (B.LRR_COORDS_FULL,)
     for eb, g, ce, co in itertools.product((16, 32), (1, 0), (1, 4), coords):
         yield dict(eig_block=eb, use_graph=g, check_every=ce, coords=co)
 

@@ -53,3 +53,14 @@ def test_traffic_from_counter_runs(tmp_path):
     assert t["k_dgemm<false, false>"] == round((2000.0 * 2 + 200.0) * 1024)
     assert t["k_estep"] == round((500.0 * 2 + 800.0) * 1024)
     assert "__amd_rocclr_copyBuffer" not in t
+
+
+def test_autotuner_candidates_hold_the_default_form():
+    """A candidate has to reproduce the default schedule's iterates, so the default's own
+    coordinates are among them: for m < n < 2m they are neither FULL nor REDUCED."""
+    from paper_1304_5583_amd import autotune
+    from paper_1304_5583_amd import binding as B
+    for n, m in ((2000, 500), (2432, 2016), (300, 400)):
+        cands = list(autotune.candidates(n, m))
+        assert dict(eig_block=16, use_graph=1, check_every=1, coords=B.LRR_COORDS_AUTO) in cands or n < m
+        assert len({tuple(c.items()) for c in cands}) == len(cands)
