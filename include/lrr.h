@@ -169,7 +169,9 @@ typedef struct {
     int *iters;              /* iterations run by each block                        */
     int *rank;               /* rank of each block estimate J_i                     */
     double *res_primal;      /* ||X_i - A Z_i - E_i||_max at the last iteration     */
-    double *res_coupling;    /* ||Z_i - J_i||_max at the last iteration             */
+    double *res_coupling;    /* ||Z_i - J_i||_max at the last iteration; in reduced */
+                             /* and singular coordinates the column-norm bound      */
+                             /* where that decided the stop test                    */
     int batch_iters;         /* (out) iterations of the batched loop                */
     int combine_rank;        /* (out) rank r_1 of the combine basis                 */
 } lrr_info;

@@ -2,10 +2,10 @@
 
 ``dfc_lrr(Mt, lam, perm, offsets, opts)`` returns ``Zt`` (an (n, n) tensor
 holding the column-major Z, as ``binding.dfc_lrr_solve``) and records the
-unrolled forward (``opts.fixed_iters`` iterations, checkpoints every
-``opts.checkpoint_every``) on the context, so that ``Zt.backward(...)`` or
+unrolled forward (``opts.fixed_iters`` iterations, every one of them or checkpoints
+every ``opts.checkpoint_every``) on the context, so that ``Zt.backward(...)`` or
 ``torch.autograd.grad`` returns gradients with respect to ``Mt`` and to
-``lam`` (a 0-d float64 tensor).  The reverse sweep replays the checkpointed
+``lam`` (a 0-d float64 tensor).  The reverse sweep replays checkpointed
 segments; it consumes the record, so one forward supports one backward, and any
 other solve on the same context in between invalidates it (LRR_ENOTAPE).
 """
