@@ -699,10 +699,10 @@ constexpr double kSvdOff = 1e-13, kSvdOut = 1e-13, kSvdOrth = 1e-13;
 // Further stages for what a basis leaves of the dictionary (finish_basis): eigenvalues
 // kept of a stage's largest, the smallest singular value kept (of the dictionary's largest
 // column), stages after the first, and the rows from which one earns its eigenproblem
-// back.  Milliseconds in full coordinates, and with a second stage: image-like data with
-// a tail across the rank cut, m = 700 576 / 576, 1000 470 / 425, 1400 563 / 445, 2016 (n =
-// 2432) 805 / 544; singular values over 13 decades (three stages), 520 102 / 128, 1000 338
-// / 206, 2016 854 / 661.
+// back.  Milliseconds in full coordinates, and with further stages: image-like data with
+// a tail across the rank cut, m = 700 575 / 562, 850 422 / 398, 1000 469 / 424, 2016 (n =
+// 2432) 807 / 541; singular values over 13 decades (three stages), 700 131 / 153, 850 147
+// / 171, 1000 336 / 205, 2016 858 / 657.
 constexpr double kStageCut = 1e-12, kStageLeast = 1e-14;
 constexpr int kStages = 3;
 constexpr int kStageRows = 1000;
