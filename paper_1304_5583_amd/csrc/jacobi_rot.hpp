@@ -8,7 +8,9 @@ namespace lrr {
 // Rotation [c s; -s c] with [c s; -s c]^T [app apq; apq aqq] [c s; -s c] nearly
 // diagonal.  t = tan of the angle comes from the hardware's approximate square
 // root and reciprocal (about 2^-23): an inexact angle only leaves about 1e-7 of
-// the rotated coupling behind, which the following sweep removes.  What has to
+// the rotated coupling behind, which the following sweep removes unless it is below the
+// absolute floor, like couplings that were never rotated (one Newton step on t changed no
+// error of Z measured at orders of 130, 1e-6 on replaced columns).  What has to
 // hold to full precision is c^2 + s^2 = 1: c = 1 / sqrt(1 + t^2) takes one
 // third-order step from the approximate value.  d and f are scaled by a power of
 // two first, so that their squares neither overflow nor vanish.  The chain of a
